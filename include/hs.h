@@ -282,6 +282,21 @@ HS_API int hs_prefill_attn_at(const hs_shape* shape, int32_t Lq, int32_t q_start
                        const void* Q, const hs_kv* kv, void* O, float* LSE,
                        void* workspace, void* stream);
 
+/* hs_prefill_attn_at for callers that hand over scratch memory.  A call with few queries on a long context (a
+ * chat turn, a small chunk) has too few query blocks to fill the GPU; with a workspace of
+ * hs_prefill_workspace_bytes the tiles are cut into ranges that run side by side, and their partial
+ * results are merged (the split of decode, Sec. IV-C).  workspace: device, 16-byte aligned, no
+ * initial content needed, not shared between two calls in flight.  With fewer bytes (or NULL)
+ * fewer ranges (or one) are used: any size is accepted. */
+HS_API int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start, float scale, int causal,
+                       const void* Q, const hs_kv* kv, void* O, float* LSE,
+                       void* workspace, size_t workspace_bytes, void* stream);
+
+/* Workspace bytes with which hs_prefill_attn_ws uses as many ranges as serve the call best; 0 where
+ * one is best.  Of kv only the capacities are read.  [host, pure] */
+HS_API int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv,
+                               size_t* bytes);
+
 /* Decode attention (split-KV kernel + merge, Sec. IV-C): one query token per
  * (b, query head) against all L cached tokens.  Q, O: bf16 [B, Hq, D];
  * LSE: fp32 [B, Hq] or NULL.  n_splits == 0 picks hs_decode_auto_splits.

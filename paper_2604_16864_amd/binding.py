@@ -65,6 +65,10 @@ EXPORTS = {
                                   C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     "hs_prefill_attn_at": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_float, C.c_int, C.c_void_p,
                                      C.POINTER(HsKV), C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "hs_prefill_attn_ws": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_float, C.c_int, C.c_void_p, C.POINTER(HsKV),
+                                     C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "hs_prefill_workspace_bytes": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_int, C.POINTER(HsKV),
+                                             C.POINTER(C.c_size_t)]),
     "hs_decode_attn": (C.c_int, [C.POINTER(HsShape), C.c_float, C.c_int32, C.c_void_p, C.POINTER(HsKV), C.c_void_p,
                                  C.c_void_p, C.c_void_p, C.c_void_p]),
     "hs_decode_attn_static": (C.c_int, [C.POINTER(HsShape), C.c_float, C.c_int32, C.c_void_p, C.POINTER(HsKV), C.c_void_p,
@@ -346,6 +350,13 @@ def unpack_kv(shape, kv):
     return K, V
 
 
+def prefill_workspace_bytes(shape, Lq, q_start, kv, causal=True):
+    """kv: PackedKV."""
+    out = C.c_size_t(0)
+    _check(lib().hs_prefill_workspace_bytes(C.byref(shape), Lq, q_start, int(bool(causal)), C.byref(kv.struct()), C.byref(out)))
+    return out.value
+
+
 def prefill_attn(shape, Q, kv, causal=True, scale=0.0, want_lse=True, out=None, lse=None, q_start=None):
     """Q: bf16 [B, Hq, Lq, D] contiguous.  Returns (O bf16 [B, Hq, Lq, D], LSE fp32 [B, Hq, Lq] or None).
     q_start: position in the cache of the first query (default: the queries are the last Lq tokens)."""
@@ -355,12 +366,17 @@ def prefill_attn(shape, Q, kv, causal=True, scale=0.0, want_lse=True, out=None, 
     if lse is None and want_lse:
         lse = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
     kvs = kv.struct()
-    if q_start is None:
-        _check(lib().hs_prefill_attn(C.byref(shape), Lq, float(scale), int(bool(causal)), _ptr(Q), C.byref(kvs), _ptr(O),
-                                     _ptr(lse), None, _stream()))
-    else:
-        _check(lib().hs_prefill_attn_at(C.byref(shape), Lq, int(q_start), float(scale), int(bool(causal)), _ptr(Q),
-                                        C.byref(kvs), _ptr(O), _ptr(lse), None, _stream()))
+    at = shape.L - Lq if q_start is None else int(q_start)
+    need = C.c_size_t(0)
+    _check(lib().hs_prefill_workspace_bytes(C.byref(shape), Lq, at, int(bool(causal)), C.byref(kvs), C.byref(need)))
+    need, ws = need.value, None
+    if need:
+        try:
+            ws = _workspace(need, Q.device)
+        except torch.OutOfMemoryError:      # the call also works without: fewer workgroups, no scratch
+            need = 0
+    _check(lib().hs_prefill_attn_ws(C.byref(shape), Lq, at, float(scale), int(bool(causal)), _ptr(Q), C.byref(kvs), _ptr(O),
+                                    _ptr(lse), _ptr(ws), need, _stream()))
     return O, lse
 
 

@@ -80,6 +80,16 @@ int append_common(const hs_shape* shape, int32_t tile, int32_t n_tiles, const in
 
 constexpr int kSelectMaxTiles = 65536;  // one workgroup per row walks its tiles: 4M tokens per row
 
+// split partials of prefill: one fp32 output row and one log-sum-exp per query and split
+size_t prefill_split_bytes(const hs_shape* s, int32_t Lq) {
+  return (size_t)s->B * s->Hq * (size_t)Lq * (HS_D + 1) * sizeof(float);
+}
+
+int prefill_splits(const hs_shape* s, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv) {
+  return hs_prefill_auto_splits(s->B, s->Hq, s->Hkv, s->L / HS_BT, Lq, q_start, causal != 0,
+                                (int64_t)kv->cap_dense_k + kv->cap_sparse_k);
+}
+
 // shared body of the decode entry points; tail_len < 0: no dense tail
 int decode_common(const hs_shape* shape, float scale, int32_t n_splits, const void* Q, const hs_kv* kv,
                   const void* tail_k, const void* tail_v, int tail_len, const int32_t* tail_lens, void* O, float* LSE,
@@ -393,12 +403,28 @@ int hs_prefill_attn(const hs_shape* shape, int32_t Lq, float scale, int causal, 
 
 int hs_prefill_attn_at(const hs_shape* shape, int32_t Lq, int32_t q_start, float scale, int causal, const void* Q,
                        const hs_kv* kv, void* O, float* LSE, void* workspace, void* stream) {
-  (void)workspace;
+  (void)workspace;  // no size comes with it: this call never writes to it
+  return hs_prefill_attn_ws(shape, Lq, q_start, scale, causal, Q, kv, O, LSE, nullptr, 0, stream);
+}
+
+int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv,
+                               size_t* bytes) {
+  const int rc = check_shape(shape);
+  if (rc != HS_OK) return rc;
+  if (bytes == nullptr || kv == nullptr || Lq <= 0 || Lq > shape->L || q_start < 0 || q_start > shape->L - Lq) return HS_EINVAL;
+  if (Lq % HS_BT != 0) return HS_EUNSUPPORTED;
+  const int n = prefill_splits(shape, Lq, q_start, causal, kv);
+  *bytes = n > 1 ? (size_t)n * prefill_split_bytes(shape, Lq) : 0;
+  return HS_OK;
+}
+
+int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start, float scale, int causal, const void* Q,
+                       const hs_kv* kv, void* O, float* LSE, void* workspace, size_t workspace_bytes, void* stream) {
   int rc = check_shape(shape);
   if (rc != HS_OK) return rc;
   rc = check_kv(shape, kv);
   if (rc != HS_OK) return rc;
-  if (Q == nullptr || O == nullptr || (((uintptr_t)Q | (uintptr_t)O) & 15u)) return HS_EINVAL;
+  if (Q == nullptr || O == nullptr || (((uintptr_t)Q | (uintptr_t)O | (uintptr_t)workspace) & 15u)) return HS_EINVAL;
   if (Lq <= 0 || Lq > shape->L) return HS_EINVAL;
   if (q_start < 0 || q_start > shape->L - Lq) return HS_EINVAL;
   if (Lq % HS_BT != 0) return HS_EUNSUPPORTED;
@@ -410,9 +436,16 @@ int hs_prefill_attn_at(const hs_shape* shape, int32_t Lq, int32_t q_start, float
     return HS_EUNSUPPORTED;
   if (!(scale >= 0.f)) return HS_EINVAL;
   if (scale == 0.f) scale = 1.0f / sqrtf((float)HS_D);
+  // as many tile ranges as fill the chip, or as the workspace has room for
+  int n_splits = 1;
+  if (workspace != nullptr) {
+    n_splits = prefill_splits(shape, Lq, q_start, causal, kv);
+    const size_t fit = workspace_bytes / prefill_split_bytes(shape, Lq);
+    if ((size_t)n_splits > fit) n_splits = fit > 1 ? (int)fit : 1;
+  }
   const hipError_t e = hs_launch_prefill(shape->B, shape->Hq, shape->Hkv, shape->L / HS_BT, Lq / HS_BT, q_start, scale,
                                          causal != 0, (const uint16_t*)Q, hs_make_kv_dev(kv), (uint16_t*)O, LSE,
-                                         (hipStream_t)stream, shape->dtype);
+                                         (hipStream_t)stream, shape->dtype, n_splits, (float*)workspace);
   if (e != hipSuccess) return hip_fail(e);
   return HS_OK;
 }

@@ -168,6 +168,13 @@ hipError_t hs_launch_mfma_rate(int kind, int iters, int n_workgroups, long long*
 // load-only kernel with the decode kernel's access pattern over n_tiles tiles laid out as four pool regions in buf
 hipError_t hs_launch_stream_read(const uint8_t* buf, int n_tiles, int n_workgroups, int with_epilogue, float* sink,
                                  hipStream_t st);
+// merge of split partials: rows x n_splits partial outputs (ws_o [row][split][128], normalised, fp32) and natural-log
+// log-sum-exps (ws_l [row][split]) -> O [row][128] (16 bit), LSE [row] (or NULL)
+hipError_t hs_launch_merge(int64_t rows, int n_splits, const float* ws_o, const float* ws_l, uint16_t* O, float* LSE,
+                           hipStream_t st, int dtype);
 // q_start: position in the cache of the first query (query i sees tokens <= q_start + i when causal)
+// n_splits > 1: the tiles of a workgroup are cut into so many ranges; ws = B * Hq * 64 Tq * n_splits * 129 floats
 hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start, float scale, int causal, const uint16_t* Q,
-                             hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype);
+                             hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype, int n_splits, float* ws);
+// number of ranges that serve this shape best (1: do not split); cap_tiles: tiles a row's K pools can hold
+int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, int64_t cap_tiles);

@@ -497,24 +497,26 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int Hq, i
 
 // Merge of the split partials (Sec. IV-C "lightweight post-processing kernel"):
 // O = sum_s e^{LSE_s - M} O_s / sum_s e^{LSE_s - M}, M = max_s LSE_s, done in one pass with a
-// running reference per thread.  One workgroup of 256 threads per (b, query head):
-// thread = (split lane tid/32 of 8, 4 channels); the 8 split lanes are combined in LDS.
+// running reference per thread.  A row (one query of one head) is merged by SL split lanes of 32
+// threads (4 channels each), which are combined in LDS; a workgroup takes R rows.
 // A separate launch on purpose: folding it into the split kernel ("last workgroup to arrive
 // merges") needs device-scope visibility between workgroups on different XCDs, and both ways
 // of getting it (a device-wide fence per workgroup, or write-through stores and L2-bypassing
 // loads) measured slower than this launch.
-template <bool F16>
-__global__ __launch_bounds__(256) void decode_merge_kernel(int n_splits, const float* __restrict__ ws_o,
-                                                           const float* __restrict__ ws_l, uint16_t* __restrict__ O,
-                                                           float* __restrict__ LSE) {
-  __shared__ float sm_acc[8][HS_D];
-  __shared__ float sm_ml[8][2];
-  const int hq = blockIdx.x, tid = threadIdx.x, sl = tid >> 5, ch = (tid & 31) * 4;
-  const float* po = ws_o + (int64_t)hq * n_splits * HS_D + ch;
-  const float* pl = ws_l + (int64_t)hq * n_splits;
+template <bool F16, int SL, int R>
+__global__ __launch_bounds__(32 * SL * R) void merge_kernel(int64_t rows, int n_splits, const float* __restrict__ ws_o,
+                                                            const float* __restrict__ ws_l, uint16_t* __restrict__ O,
+                                                            float* __restrict__ LSE) {
+  __shared__ __attribute__((aligned(16))) float sm_acc[R][SL][HS_D];
+  __shared__ float sm_ml[R][SL][2];
+  const int tid = threadIdx.x, r = tid / (32 * SL), sl = tid / 32 % SL, ch = (tid & 31) * 4;
+  const int64_t row = (int64_t)blockIdx.x * R + r;
+  const bool valid = R == 1 || row < rows;
+  const float* po = ws_o + (valid ? row : 0) * n_splits * HS_D + ch;
+  const float* pl = ws_l + (valid ? row : 0) * n_splits;
   float M = -INFINITY, den = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-  for (int s = sl; s < n_splits; s += 8) {
+  for (int s = sl; s < n_splits; s += SL) {
     const float lse = pl[s];
     const float4 v = *reinterpret_cast<const float4*>(po + (int64_t)s * HS_D);
     if (lse > -INFINITY) {
@@ -526,27 +528,33 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(int n_splits, const f
       M = Mn;
     }
   }
-  if ((tid & 31) == 0) { sm_ml[sl][0] = M; sm_ml[sl][1] = den; }
-#pragma unroll
-  for (int i = 0; i < 4; i++) sm_acc[sl][ch + i] = acc[i];
-  __syncthreads();
-  if (tid < HS_D) {
+  if (SL > 1) {
+    if ((tid & 31) == 0) { sm_ml[r][sl][0] = M; sm_ml[r][sl][1] = den; }
+    *reinterpret_cast<float4*>(&sm_acc[r][sl][ch]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    __syncthreads();
+    if (sl != 0) return;
     float Mt = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < 8; k++) Mt = fmaxf(Mt, sm_ml[k][0]);
-    float num = 0.f, d = 0.f;
+    for (int k = 0; k < SL; k++) Mt = fmaxf(Mt, sm_ml[r][k][0]);
+    den = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; i++) acc[i] = 0.f;
     if (Mt > -INFINITY) {
 #pragma unroll
-      for (int k = 0; k < 8; k++) {
-        const float f = __expf(sm_ml[k][0] - Mt);  // 0 for a split lane that saw nothing
-        num += f * sm_acc[k][tid];
-        d += f * sm_ml[k][1];
+      for (int k = 0; k < SL; k++) {
+        const float f = __expf(sm_ml[r][k][0] - Mt);  // 0 for a split lane that saw nothing
+        const float4 v = *reinterpret_cast<const float4*>(&sm_acc[r][k][ch]);
+        den += f * sm_ml[r][k][1];
+        acc[0] += f * v.x; acc[1] += f * v.y; acc[2] += f * v.z; acc[3] += f * v.w;
       }
     }
-    const float out = d > 0.f ? num / d : 0.f;
-    O[(int64_t)hq * HS_D + tid] = (uint16_t)(hs_elem<F16>::pack2(out, 0.f) & 0xffffu);
-    if (LSE != nullptr && tid == 0) LSE[hq] = d > 0.f ? Mt + __logf(d) : -INFINITY;
+    M = Mt;
   }
+  if (!valid) return;
+#pragma unroll
+  for (int i = 0; i < 4; i++) acc[i] = den > 0.f ? acc[i] / den : 0.f;
+  *reinterpret_cast<uint2*>(O + row * HS_D + ch) = make_uint2(hs_elem<F16>::pack2(acc[0], acc[1]), hs_elem<F16>::pack2(acc[2], acc[3]));
+  if (LSE != nullptr && (tid & 31) == 0) LSE[row] = den > 0.f ? M + __logf(den) : -INFINITY;
 }
 
 
@@ -710,9 +718,19 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
     e = hipGetLastError();
   }
   if (e != hipSuccess || !(phases & 2)) return e;
-  if (f16)
-    hipLaunchKernelGGL(decode_merge_kernel<true>, dim3(B * Hq), dim3(256), 0, st, n_splits, wo, wl, O, LSE);
-  else
-    hipLaunchKernelGGL(decode_merge_kernel<false>, dim3(B * Hq), dim3(256), 0, st, n_splits, wo, wl, O, LSE);
+  return hs_launch_merge((int64_t)B * Hq, n_splits, wo, wl, O, LSE, st, dtype);
+}
+
+hipError_t hs_launch_merge(int64_t rows, int n_splits, const float* ws_o, const float* ws_l, uint16_t* O, float* LSE,
+                           hipStream_t st, int dtype) {
+#define HS_MERGE(SL_, R_)                                                                                                  \
+  do {                                                                                                                     \
+    const dim3 grid((unsigned)((rows + R_ - 1) / R_)), block(32 * SL_ * R_);                                               \
+    if (dtype == HS_FP16) hipLaunchKernelGGL((merge_kernel<true, SL_, R_>), grid, block, 0, st, rows, n_splits, ws_o, ws_l, O, LSE); \
+    else hipLaunchKernelGGL((merge_kernel<false, SL_, R_>), grid, block, 0, st, rows, n_splits, ws_o, ws_l, O, LSE);       \
+  } while (0)
+  if (n_splits >= 8 || rows < 4096) HS_MERGE(8, 1);
+  else HS_MERGE(1, 8);
+#undef HS_MERGE
   return hipGetLastError();
 }

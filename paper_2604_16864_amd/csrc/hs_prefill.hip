@@ -212,12 +212,16 @@ union B16 {  // one B operand of the 16x16x64 sparse instruction = two of the de
 // GEMM2 as one fp16 term; against bf16 V they enter as two bf16 terms.  The reference is kept
 // kShift binades under the running maximum and renewed before a numerator can reach the fp16
 // maximum (constants below).
-template <int KM, int VM, int NB, bool F16>
+// SPLIT: the tiles a workgroup may look at are cut into gridDim.y ranges, one workgroup per range; each
+// writes a normalised fp32 partial output and its log-sum-exp (ws_o [row][split][128], ws_l
+// [row][split], row = (b, query head, query)) for the merge kernel instead of O and LSE.
+template <int KM, int VM, int NB, bool F16, bool SPLIT>
 __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, int Hkv, int T, int Lq, int off,
                                                                       float scale_log2, int causal,
                                                                       const uint16_t* __restrict__ Q, hs_kv_dev kv,
                                                                       uint16_t* __restrict__ O,
-                                                                      float* __restrict__ LSE) {
+                                                                      float* __restrict__ LSE, float* __restrict__ ws_o,
+                                                                      float* __restrict__ ws_l) {
   typedef hs_elem<F16> E;
   typedef hs_elem<true> E16;
   // Reference = running maximum - kShift at the time it was last renewed; it is renewed when a lane's
@@ -261,6 +265,10 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
   const int jmax_w = causal ? (qpos + QS - 1 + off) / HS_BT : T - 1;
   const int last_slab = min(4 * grp + 3, n_slabs - 1);
   const int jmax_wg = causal ? min(T - 1, ((last_slab / G) * QS + QS - 1 + off) / HS_BT) : T - 1;
+  // tiles [t_lo, t_hi) are this workgroup's: all it may look at, or its share of them
+  const int n_splits = SPLIT ? (int)gridDim.y : 1, split = SPLIT ? (int)blockIdx.y : 0;
+  const int t_lo = SPLIT ? (int)((int64_t)(jmax_wg + 1) * split / n_splits) : 0;
+  const int t_hi = SPLIT ? (int)((int64_t)(jmax_wg + 1) * (split + 1) / n_splits) : jmax_wg + 1;
 
   // Q^T (B operand): column block nb, 64-channel block kb: query qpos+16nb+c, channels
   // 64kb + 32h + 8a + e for element 8h+e
@@ -311,33 +319,33 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
   uint64_t wrem = 0;  // tiles of the window still to hand out
   auto window_load = [&](int base) {
     const int t = base + l;
-    wk = t <= jmax_wg ? km[t] : 0;
-    wv = t <= jmax_wg ? vm[t] : 0;
+    wk = t < t_hi ? km[t] : 0;
+    wv = t < t_hi ? vm[t] : 0;
     const bool g2 = !F16 && !hs_map_f16(wv);
     const bool g1 = !g2 && VM == 2 && wv > 0;
     const int grp = g2 ? 2 : (g1 ? 1 : 0);
     wrem = __ballot(wk != 0 && grp == wgroup);
     wbase = base;
   };
-  auto next_tile = [&]() -> int {  // next tile (<= jmax_wg, not skipped) in the order above, or -1
+  auto next_tile = [&]() -> int {  // next tile (< t_hi, not skipped) in the order above, or -1
     for (;;) {
       if (wrem != 0) {
         const int t = __builtin_ctzll(wrem);
         wrem &= wrem - 1;
         return wbase + t;
       }
-      if (wbase + 64 <= jmax_wg) {
+      if (wbase + 64 < t_hi) {
         window_load(wbase + 64);
         continue;
       }
       do wgroup++;
       while ((wgroup == 1 && VM != 2) || (wgroup == 2 && F16));  // groups this kernel cannot meet
       if (wgroup > 2) return -1;
-      window_load(0);
+      window_load(t_lo);
     }
   };
   int st = 0;
-  window_load(0);
+  window_load(t_lo);
 #pragma unroll
   for (int i = 0; i < D; i++) {
     tj[i] = i == 0 || tj[i - 1] >= 0 ? next_tile() : -1;
@@ -622,9 +630,9 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
     // bf16 cache: are all V tiles this workgroup can meet in fp16 encoding?  (every wave scans the
     // same entries, so the workgroup agrees; the answer is scalar)
     bool all16 = true;
-    for (int base = 0; base <= jmax_wg; base += 64) {
+    for (int base = t_lo; base < t_hi; base += 64) {
       const int t = base + l;
-      const int32_t m = t <= jmax_wg ? vm[t] : 0;
+      const int32_t m = t < t_hi ? vm[t] : 0;
       all16 = all16 && !__any(m != 0 && !hs_map_f16(m));
     }
     if (all16) main_loop(std::integral_constant<bool, MID_OK>{}, std::true_type{});
@@ -642,6 +650,16 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
     lt += __shfl_xor(lt, 32);
     const float inv = lt > 0.f ? 1.f / lt : 0.f;
     const int64_t qrow = ((int64_t)b * Hq + hq) * Lq + qpos + 16 * nb + c;
+    if constexpr (SPLIT) {
+      float* op = ws_o + (qrow * n_splits + split) * HS_D + 4 * a;
+#pragma unroll
+      for (int mb = 0; mb < 8; mb++)
+        *reinterpret_cast<float4*>(op + 16 * mb) =
+            make_float4(o[mb][nb][0] * inv, o[mb][nb][1] * inv, o[mb][nb][2] * inv, o[mb][nb][3] * inv);
+      if (a == 0)
+        ws_l[qrow * n_splits + split] = lt > 0.f ? (m_run[nb] + __builtin_amdgcn_logf(lt)) * kLn2 : -INFINITY;
+      continue;
+    }
     uint16_t* op = O + qrow * HS_D + 4 * a;
 #pragma unroll
     for (int mb = 0; mb < 8; mb++) {
@@ -658,26 +676,63 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
 
 template <int KM, int VM, int NB>
 static hipError_t launch_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, float sl2, int causal, const uint16_t* Q,
-                                 const hs_kv_dev& kv, uint16_t* O, float* LSE, hipStream_t st, bool f16) {
+                                 const hs_kv_dev& kv, uint16_t* O, float* LSE, hipStream_t st, bool f16, int n_splits, float* ws_o,
+                                 float* ws_l) {
   const int G = Hq / Hkv;
   const int n_groups = ((Lq / (16 * NB)) * G + 3) / 4;
-  if (f16)
-    hipLaunchKernelGGL((prefill_kernel<KM, VM, NB, true>), dim3(n_groups * Hkv, 1, B), dim3(256), 0, st, Hq, Hkv, T, Lq,
-                       q_start, sl2, causal, Q, kv, O, LSE);
-  else
-    hipLaunchKernelGGL((prefill_kernel<KM, VM, NB, false>), dim3(n_groups * Hkv, 1, B), dim3(256), 0, st, Hq, Hkv, T, Lq,
-                       q_start, sl2, causal, Q, kv, O, LSE);
+  const dim3 grid(n_groups * Hkv, n_splits, B);
+#define HS_LAUNCH(F16_, SPLIT_)                                                                                            \
+  hipLaunchKernelGGL((prefill_kernel<KM, VM, NB, F16_, SPLIT_>), grid, dim3(256), 0, st, Hq, Hkv, T, Lq, q_start, sl2, causal, \
+                     Q, kv, O, LSE, ws_o, ws_l)
+  if (n_splits > 1) {
+    if (f16) HS_LAUNCH(true, true); else HS_LAUNCH(false, true);
+  } else {
+    if (f16) HS_LAUNCH(true, false); else HS_LAUNCH(false, false);
+  }
+#undef HS_LAUNCH
   return hipGetLastError();
 }
 
+// Ranges to cut a workgroup's tiles into, from what was measured on 2:4 tensors (32/8 heads): a tile takes a workgroup
+// 1.0 us alone on its compute unit and 1.2 us beside a second one, so 512 workgroups at a time are two on every unit;
+// splitting costs 5 us for the merge launch and 0.028 us per workgroup for writing and reading its 66 KB of partials.
+// The number of ranges that makes this sum smallest is taken.  Measured, one range / the chosen number: 64 queries on
+// 32768 tokens 501 / 41.5 us (32 ranges), on 2048 tokens 37 / 18.8 us (8); 256 queries on 32768 tokens 504 / 101 us (8);
+// 1024 queries on 32768 tokens 510 / 347 us (2); whole prompts of 256 to 2048 tokens are fastest unsplit (2048: 46 us, two
+// ranges 56 us), and there the sum says one range too.  Beyond 512 workgroups one range is only
+// worse where a last, nearly empty round of equally long workgroups follows: queries at the end of a long context (2304
+// queries on 32768 tokens, 576 workgroups: 1116 / 828 us).  Skipped tiles cost nothing, so the tiles are counted by what
+// the pools can hold (75 % skipped, 1024 queries on 2048 tokens: 14 us unsplit, 18 us with the ranges that all tiles would ask for).
+int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, int64_t cap_tiles) {
+  const int64_t n_wg = (int64_t)(((Lq / 32) * (Hq / Hkv) + 3) / 4) * Hkv * B;
+  int n_tiles = causal ? (q_start + Lq + HS_BT - 1) / HS_BT : T;  // of the last query
+  if (cap_tiles < n_tiles) n_tiles = (int)cap_tiles;
+  if (n_wg > 2048 || (n_wg > 512 && causal && q_start < 3 * (int64_t)Lq)) return 1;
+  int best = 1;
+  double best_us = 0.0;
+  for (int n = 1; n <= 128 && (n == 1 || (2 * n <= n_tiles && n_wg * n <= 4096)); n++) {
+    const int64_t wgs = n_wg * n, full = wgs / 512, rest = wgs % 512;
+    const int per = (n_tiles + n - 1) / n;
+    const double us = per * (1.2 * full + (rest == 0 ? 0.0 : (rest <= 256 ? 1.0 : 1.2))) + (n > 1 ? 5.0 + 0.028 * wgs : 0.0);
+    if (n == 1 || us < best_us) { best = n; best_us = us; }
+  }
+  return best;
+}
+
 hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start, float scale, int causal, const uint16_t* Q,
-                             hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype) {
+                             hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype, int n_splits, float* ws) {
   const bool f16 = dtype == HS_FP16;
   const float sl2 = scale * kLog2e;
   const int Lq = Tq * HS_BT;
   const int km = kv.cap_dense_k == 0 ? 0 : (kv.cap_sparse_k == 0 ? 1 : 2);
   const int vm = kv.cap_dense_v == 0 ? 0 : (kv.cap_sparse_v == 0 ? 1 : 2);
-#define HS_GO(KM_, VM_) return launch_prefill<KM_, VM_, 2>(B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16)
+  const int64_t rows = (int64_t)B * Hq * Lq;
+  float* ws_o = ws;
+  float* ws_l = n_splits > 1 ? ws + rows * n_splits * HS_D : nullptr;
+  hipError_t e = hipSuccess;
+#define HS_GO(KM_, VM_)                                                                                                  \
+  e = launch_prefill<KM_, VM_, 2>(B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l); \
+  break
   switch (km * 3 + vm) {
     case 0: HS_GO(0, 0);
     case 1: HS_GO(0, 1);
@@ -690,4 +745,6 @@ hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start,
     default: HS_GO(2, 2);
   }
 #undef HS_GO
+  if (e != hipSuccess || n_splits <= 1) return e;
+  return hs_launch_merge(rows, n_splits, ws_o, ws_l, O, LSE, st, dtype);
 }

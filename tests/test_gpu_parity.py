@@ -433,6 +433,47 @@ def test_prefill_queries_placed_inside_a_capacity_cache(q_start, Lq):
                 hb.prefill_attn(sh, _dev(Q), kv, q_start=bad)
 
 
+@pytest.mark.parametrize("n_ranges", [2, 5, 0])                   # 0: as many as the library picks
+@pytest.mark.parametrize("B,G,T,Lq,q_start,causal,dtype,pol", [
+    (1, 4, 40, 64, None, True, "bf16", dict()),                            # a short turn at the end of a context
+    (2, 3, 33, 128, 64 * 20 + 17, True, "fp16", dict(sparse_frac_k=0.0)),  # off the tile grid, a group with idle waves
+    (1, 1, 70, 64, 0, False, "bf16", dict(sparse_frac_k=0.5, sparse_frac_v=0.5)),
+    (1, 8, 48, 192, None, True, "bf16", "states"),                         # ranges without a kept tile, queries that see nothing
+])
+def test_prefill_tiles_cut_into_ranges(n_ranges, B, G, T, Lq, q_start, causal, dtype, pol):
+    import ctypes as C
+    Hkv, L = 2, 64 * T
+    Q, K, V = wl.make_qkv(B, G * Hkv, Hkv, L, 128, Lq, seed=900 + T, dtype=dtype)
+    if pol == "states":
+        sk, sv = _mixed_states(B, Hkv, T, seed=901)
+        sk[:, 0, :T - 3] = sv[:, 0, :T - 3] = 0
+        sk[:, 1, 5:15] = sv[:, 1, 5:15] = 0
+        sk[:, 0, T - 3] = sv[:, 0, T - 3] = 0
+        V[:, :, ::67, 5] = 0x0001                     # bf16 values that fp16 does not hold: both encodings
+        pol = dict(state_k=sk, state_v=sv)
+    sh, kv, pk, pv, _ = compress_both(B, G * Hkv, Hkv, L, K, V, dtype=dtype, **pol)
+    Qd, at = _dev(Q, dtype), L - Lq if q_start is None else q_start
+    need = hb.prefill_workspace_bytes(sh, Lq, at, kv, causal)
+    one = B * G * Hkv * Lq * 129 * 4
+    assert need >= 2 * one                            # the library does cut these shapes
+    n = n_ranges or need // one
+    ws = torch.full((n * one + 64,), 255, dtype=torch.uint8, device="cuda")
+    O, LSE = torch.full_like(Qd, float("nan")), torch.full(Qd.shape[:3], float("nan"), device="cuda")
+    kvs = kv.struct()
+    hb._check(hb.lib().hs_prefill_attn_ws(C.byref(sh), Lq, at, 0.0, int(causal), hb._ptr(Qd), C.byref(kvs), hb._ptr(O), hb._ptr(LSE),
+                                          hb._ptr(ws), n * one, hb._stream()))
+    torch.cuda.synchronize()
+    assert (ws[n * one:] == 255).all()                # nothing past the bytes it was given
+    rows = [(b, h, i) for b in range(B) for h in range(G * Hkv) for i in range(0, Lq, 3)]
+    idx = tuple(np.array(rows).T)
+    Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=causal, **({} if q_start is None else {"q_offset": q_start}))
+    assert_close(_f32(O)[idx], Or, f"prefill in {n} ranges")
+    assert_lse_close(LSE.cpu().numpy()[idx], Lr, f"prefill in {n} ranges lse")
+    if n_ranges == 0:                                 # the binding's own call takes the same way
+        O2, LSE2 = hb.prefill_attn(sh, Qd, kv, causal=causal, q_start=q_start)
+        assert torch.equal(O2.view(torch.int16), O.view(torch.int16)) and torch.equal(LSE2, LSE)
+
+
 def test_decode_equals_last_prefill_row():
     B, Hq, Hkv, L = 1, 8, 2, 64 * 6
     Q, K, V = wl.make_qkv(B, Hq, Hkv, L, 128, L, seed=120)

@@ -115,3 +115,26 @@ def test_argument_errors(L):
     assert L.hs_tile_counts(C.byref(ok), C.byref(pol_s), c) == -2
     assert hb.workspace_bytes(ok, 2, 4) == 1 * 4 * 4 * 129 * 4
     assert hb.decode_auto_splits(ok) == 4
+
+
+def test_prefill_workspace_rule(L):
+    """Few queries on a long context ask for scratch, whole prompts and nearly empty caches do not."""
+    def ranges(B, Hq, Hkv, L_, Lq, cap=None, causal=1, q_start=None):
+        sh, kv, n = hb.make_shape(B, Hq, Hkv, L_), hb.HsKV(), C.c_size_t(0)
+        kv.cap_sparse_k = L_ // 64 if cap is None else cap
+        assert L.hs_prefill_workspace_bytes(C.byref(sh), Lq, L_ - Lq if q_start is None else q_start, causal, C.byref(kv), C.byref(n)) == 0
+        assert n.value % (B * Hq * Lq * 129 * 4) == 0
+        return n.value // (B * Hq * Lq * 129 * 4)
+    assert ranges(1, 32, 8, 32768, 64) == 32 and ranges(1, 32, 8, 32768, 1024) == 2
+    for L_ in (64, 256, 1024, 2048, 16384):
+        assert ranges(1, 32, 8, L_, L_) == 0
+    assert ranges(1, 32, 8, 32768, 64, cap=4) == 0 and ranges(1, 32, 8, 64, 64) == 0
+    for B in (1, 3, 16):                              # bounded: at most 4096 workgroups of 66 KB
+        for Lq in (64, 192, 2304, 4608, 32704):
+            assert ranges(B, 32, 8, 65536, Lq) * B * 8 * (Lq // 32) <= 4096
+    sh, n = hb.make_shape(1, 32, 8, 1024), C.c_size_t(0)
+    kv = hb.HsKV()
+    assert L.hs_prefill_workspace_bytes(C.byref(sh), 64, 1024, 1, C.byref(kv), C.byref(n)) == -1
+    assert L.hs_prefill_workspace_bytes(C.byref(sh), 100, 0, 1, C.byref(kv), C.byref(n)) == -2
+    assert L.hs_prefill_workspace_bytes(C.byref(sh), 64, 0, 1, None, C.byref(n)) == -1
+    assert hb.workspace_bytes(sh, 1, 64) == 0         # the call without scratch needs none, as ever
