@@ -203,7 +203,111 @@ __device__ __forceinline__ void static_for_forms(Fn&& fn) {
   }
 }
 
-// Split-KV kernel.  grid = (n_splits, Hkv, B); workgroup = 4 waves; split s owns tiles
+// The dense tail (at most one tile of not yet compressed tokens) as seen by the split kernel: `len` < 0 = the call has
+// none; `lens` (device, [B], or NULL) replaces `len` per batch row, kept inside the tail buffer.
+struct TailArgs {
+  const uint16_t* k;
+  const uint16_t* v;
+  const int32_t* lens;
+  int len;
+};
+
+// Partial of the dense tail of one (batch, kv head) row, written as split `slot`: plain fp32 attention of its G query
+// heads over tail_len tokens.  One workgroup of 256 threads, latency-bound (32 KB of input, 3 barriers), so everything
+// it reads from memory is requested at once, in 16-byte (K) and coalesced 4-byte (V) loads, before the first barrier.
+// It runs as one more workgroup per row of the split kernel, beside the others, instead of as a launch of its own in
+// front of the merge (7.9 us at 16 rows x 8 heads, 6.2 us at 4 x 8): calls of 74.6 -> 66.1 us and 65.5 -> 59.6 us there.
+//   scores   thread = (token tid / 4, quarter of the channels tid % 4), quarters summed across lanes
+//   softmax  wave w = heads w and w + 4, lane = token
+//   output   thread = (tokens 16 (tid / 64) .. +15, channels 2 (tid % 64), +1), the four token quarters summed in LDS
+template <bool F16>
+__device__ __forceinline__ void tail_partial(const TailArgs& tail, int tail_len, int G, int64_t row, int64_t hq0, float scale_log2,
+                                             const uint16_t* __restrict__ Q, float (&sm_o)[4][8][HS_D], int n_splits, int slot,
+                                             float* __restrict__ ws_o, float* __restrict__ ws_l) {
+  typedef hs_elem<F16> E;
+  constexpr int kQRow = 4 * 36;  // a head's 128 channels in LDS: quarters 36 floats apart, so that the four lanes of a token
+                                 // read from different banks
+  __shared__ __attribute__((aligned(16))) float sq[8][kQRow];
+  __shared__ float sp[8][HS_BT];
+  __shared__ float sl[8];
+  const int tid = threadIdx.x, w = tid >> 6;
+  const int tok = tid >> 2, qd = tid & 3;
+  const uint16_t* tk = tail.k + row * HS_BT * HS_D + tok * HS_D + 32 * qd;
+  const uint16_t* tv = tail.v + row * HS_BT * HS_D + 2 * (tid & 63);
+  uint4 kk[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) kk[i] = tok < tail_len ? *reinterpret_cast<const uint4*>(tk + 8 * i) : make_uint4(0, 0, 0, 0);
+  uint32_t vv[16];
+#pragma unroll
+  for (int i = 0; i < 16; i++)
+    vv[i] = 16 * w + i < tail_len ? *reinterpret_cast<const uint32_t*>(tv + (16 * w + i) * HS_D) : 0u;
+  for (int i = tid; i < G * (HS_D / 2); i += 256) {
+    const uint32_t pair = *reinterpret_cast<const uint32_t*>(Q + hq0 * HS_D + 2 * i);
+    const int g = i / (HS_D / 2), c = 2 * (i % (HS_D / 2));
+    float* d = &sq[g][(c >> 5) * 36 + (c & 31)];
+    d[0] = E::lo_f32(pair);
+    d[1] = E::hi_f32(pair);
+  }
+  __syncthreads();
+  for (int g = 0; g < G; g++) {
+    float acc = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const float4 q0 = *reinterpret_cast<const float4*>(&sq[g][36 * qd + 8 * i]);
+      const float4 q1 = *reinterpret_cast<const float4*>(&sq[g][36 * qd + 8 * i + 4]);
+      acc = fmaf(E::lo_f32(kk[i].x), q0.x, acc); acc = fmaf(E::hi_f32(kk[i].x), q0.y, acc);
+      acc = fmaf(E::lo_f32(kk[i].y), q0.z, acc); acc = fmaf(E::hi_f32(kk[i].y), q0.w, acc);
+      acc = fmaf(E::lo_f32(kk[i].z), q1.x, acc); acc = fmaf(E::hi_f32(kk[i].z), q1.y, acc);
+      acc = fmaf(E::lo_f32(kk[i].w), q1.z, acc); acc = fmaf(E::hi_f32(kk[i].w), q1.w, acc);
+    }
+    acc += __shfl_xor(acc, 1);
+    acc += __shfl_xor(acc, 2);
+    if (qd == 0) sp[g][tok] = tok < tail_len ? acc * scale_log2 : -INFINITY;
+  }
+  __syncthreads();
+  for (int g = w; g < G; g += 4) {
+    const int t = tid & 63;
+    const float sc = sp[g][t];
+    float mx = sc;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    const float p = t < tail_len ? __builtin_amdgcn_exp2f(sc - mx) : 0.f;
+    float l = p;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+    sp[g][t] = p;
+    if (t == 0) {
+      sl[g] = l;
+      ws_l[(hq0 + g) * n_splits + slot] = l > 0.f ? (mx + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+    }
+  }
+  __syncthreads();
+  for (int g = 0; g < G; g++) {
+    float a0 = 0.f, a1 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      const float p = sp[g][16 * w + i];
+      a0 = fmaf(p, E::lo_f32(vv[i]), a0);
+      a1 = fmaf(p, E::hi_f32(vv[i]), a1);
+    }
+    *reinterpret_cast<float2*>(&sm_o[w][g][2 * (tid & 63)]) = make_float2(a0, a1);
+  }
+  __syncthreads();
+  const int g = tid >> 5, ch = (tid & 31) * 4;
+  if (g < G) {
+    float acc[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) acc[i] = (sm_o[0][g][ch + i] + sm_o[1][g][ch + i]) + (sm_o[2][g][ch + i] + sm_o[3][g][ch + i]);
+    const float l = sl[g];
+    float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (l > 0.f) out = make_float4(acc[0] / l, acc[1] / l, acc[2] / l, acc[3] / l);
+    *reinterpret_cast<float4*>(ws_o + ((hq0 + g) * n_splits + slot) * HS_D + ch) = out;
+  }
+}
+
+// Split-KV kernel.  grid = (n_work, Hkv, B); with a dense tail the B * Hkv tail workgroups follow as further
+// planes of the grid, behind all others: as one more workgroup of every row they pushed whole splits onto compute
+// units that already had one (16 rows x 8 heads, 2 splits: 99 instead of 66 us).  workgroup = 4 waves; split s owns tiles
 // [s*per, (s+1)*per); wave w takes every 4th tile of them.  Each wave preloads the map
 // entries of its tiles with one vector load, drops the skipped ones, and streams the rest
 // with a two-deep register pipeline (the loads of tile i+1 are in flight while tile i is
@@ -224,15 +328,27 @@ constexpr int kListCap = 2048;  // tiles listed in LDS at a time (kByCount); lon
 constexpr int kScanBatch = 2048;  // tiles of the row looked at per scan step: 8 per thread
 
 template <int KM, int VM, int MODE, bool F16>
-__global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int Hq, int Hkv, int T, float scale_log2,
+__global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, int Hq, int Hkv, int T, float scale_log2,
                                                                              int n_splits, int per,
                                                                              const uint16_t* __restrict__ Q,
-                                                                             hs_kv_dev kv, float* __restrict__ ws_o,
+                                                                             hs_kv_dev kv, TailArgs tail,
+                                                                             float* __restrict__ ws_o,
                                                                              float* __restrict__ ws_l) {
   const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, l = tid & 63, a = l >> 4, c = l & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, scalar: branches on it stay scalar
   const int G = Hq / Hkv;
+  __shared__ __attribute__((aligned(16))) float sm_o[4][8][HS_D];
+  const int n_work = gridDim.x;  // partial slots of the cache's tiles; the tail's is the next one
+  if (b >= B) {  // the whole workgroup
+    const int64_t t_row = ((int64_t)(b - B) * Hkv + hkv) * n_work + split;
+    if (t_row >= (int64_t)B * Hkv) return;
+    const int tb = (int)(t_row / Hkv);
+    const int len = tail.lens != nullptr ? min(max(tail.lens[tb], 0), HS_BT) : tail.len;
+    tail_partial<F16>(tail, len, G, t_row, (int64_t)tb * Hq + (t_row - (int64_t)tb * Hkv) * G, scale_log2, Q, sm_o, n_splits, n_work,
+                      ws_o, ws_l);
+    return;
+  }
   const int64_t row = (int64_t)b * Hkv + hkv;
   const int t_begin = split * per, t_end = min(T, t_begin + per);
 
@@ -400,7 +516,6 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int Hq, i
     if (l == 0) sm_cnt[w] = mine_cnt;
     __syncthreads();
     const int n_kept = sm_cnt[0] + sm_cnt[1] + sm_cnt[2] + sm_cnt[3];
-    const int n_work = gridDim.x;
     const int lo = (int)((int64_t)n_kept * split / n_work), hi = (int)((int64_t)n_kept * (split + 1) / n_work);
     if (n_kept == T) {  // nothing skipped: a tile's number is its index, no list needed
       all_sweeps(lo, hi, from_map);
@@ -464,7 +579,6 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int Hq, i
     }
 
   __shared__ float sm_m[4][8], sm_l[4][8];
-  __shared__ __attribute__((aligned(16))) float sm_o[4][8][HS_D];
   if (c < 8) {
     if (a == 0) { sm_m[w][c] = m_run; sm_l[w][c] = l_run; }
 #pragma unroll
@@ -558,71 +672,6 @@ __global__ __launch_bounds__(32 * SL * R) void merge_kernel(int64_t rows, int n_
 }
 
 
-// Partial for the dense tail (at most one tile of not yet compressed tokens): plain fp32
-// attention of the G query heads of one kv head over tail_len tokens, written as split `slot`.
-// One workgroup per (kv head, b); thread t: phase 1 token t%64 for heads t/64 and t/64 + 4,
-// phase 3 channel t%128 for heads t/128, t/128 + 2, ...
-template <bool F16>
-__global__ __launch_bounds__(256) void decode_tail_kernel(int Hq, int Hkv, float scale_log2, int n_slots, int slot,
-                                                          int tail_len, const int32_t* __restrict__ tail_lens,
-                                                          const uint16_t* __restrict__ Q,
-                                                          const uint16_t* __restrict__ TK,
-                                                          const uint16_t* __restrict__ TV, float* __restrict__ ws_o,
-                                                          float* __restrict__ ws_l) {
-  __shared__ float sq[8][HS_D];
-  __shared__ float sp[8][HS_BT];
-  __shared__ float sl_[8];
-  const int tid = threadIdx.x, hkv = blockIdx.x, b = blockIdx.y;
-  const int G = Hq / Hkv;
-  if (tail_lens != nullptr) tail_len = min(max(tail_lens[b], 0), HS_BT);  // one per batch row, kept inside the tail buffer
-  const int64_t hq0 = (int64_t)b * Hq + (int64_t)hkv * G;
-  const uint16_t* tk = TK + ((int64_t)b * Hkv + hkv) * HS_BT * HS_D;
-  const uint16_t* tv = TV + ((int64_t)b * Hkv + hkv) * HS_BT * HS_D;
-  for (int i = tid; i < G * HS_D; i += 256) sq[i / HS_D][i % HS_D] = hs_elem<F16>::to_f32(Q[hq0 * HS_D + i]);
-  __syncthreads();
-  {  // scores (log2 units) and softmax numerators: wave w serves heads w and w + 4, lane = token
-    const int tok = tid & 63, w = tid >> 6;
-    for (int g = w; g < G; g += 4) {
-      float sc = -INFINITY;
-      if (tok < tail_len) {
-        float acc = 0.f;
-        for (int c = 0; c < HS_D; c += 8) {
-          const uint4 kk = *reinterpret_cast<const uint4*>(tk + (int64_t)tok * HS_D + c);
-          const uint32_t wds[4] = {kk.x, kk.y, kk.z, kk.w};
-#pragma unroll
-          for (int e = 0; e < 4; e++) {
-            acc = fmaf(hs_elem<F16>::lo_f32(wds[e]), sq[g][c + 2 * e], acc);
-            acc = fmaf(hs_elem<F16>::hi_f32(wds[e]), sq[g][c + 2 * e + 1], acc);
-          }
-        }
-        sc = acc * scale_log2;
-      }
-      float mx = sc;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-      const float p = tok < tail_len ? __builtin_amdgcn_exp2f(sc - mx) : 0.f;
-      float l = p;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
-      sp[g][tok] = p;
-      if (tok == 0) {
-        sl_[g] = l;
-        ws_l[(hq0 + g) * n_slots + slot] = l > 0.f ? (mx + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
-      }
-    }
-  }
-  __syncthreads();
-  {
-    const int ch = tid & 127;
-    for (int g = tid >> 7; g < G; g += 2) {
-      float acc = 0.f;
-      for (int t = 0; t < tail_len; t++) acc = fmaf(sp[g][t], hs_elem<F16>::to_f32(tv[(int64_t)t * HS_D + ch]), acc);
-      const float l = sl_[g];
-      ws_o[((hq0 + g) * n_slots + slot) * HS_D + ch] = l > 0.f ? acc / l : 0.f;
-    }
-  }
-}
-
 }  // namespace
 
 // Split partials of hs_decode_attn_static: a fixed array in device memory, one copy per GPU the
@@ -653,21 +702,22 @@ hipError_t hs_static_scratch(void** ptr, size_t* bytes) {
 
 // Workspace: [partial O (normalised) [B*Hq][n_splits][128] fp32][partial LSE [B*Hq][n_splits] fp32].
 template <int KM, int VM, int MODE>
-static hipError_t launch_split(dim3 grid, hipStream_t st, int Hq, int Hkv, int T, float sl2, int n_splits, int per,
-                               const uint16_t* Q, const hs_kv_dev& kv, float* wo, float* wl, bool f16) {
+static hipError_t launch_split(dim3 grid, hipStream_t st, int B, int Hq, int Hkv, int T, float sl2, int n_splits, int per,
+                               const uint16_t* Q, const hs_kv_dev& kv, const TailArgs& tail, float* wo, float* wl, bool f16) {
   if (f16)
-    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, true>), grid, dim3(256), 0, st, Hq, Hkv, T, sl2, n_splits,
-                       per, Q, kv, wo, wl);
+    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, true>), grid, dim3(256), 0, st, B, Hq, Hkv, T, sl2, n_splits,
+                       per, Q, kv, tail, wo, wl);
   else
-    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, false>), grid, dim3(256), 0, st, Hq, Hkv, T, sl2, n_splits,
-                       per, Q, kv, wo, wl);
+    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, false>), grid, dim3(256), 0, st, B, Hq, Hkv, T, sl2, n_splits,
+                       per, Q, kv, tail, wo, wl);
   return hipGetLastError();
 }
 
 hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_work, const uint16_t* Q, hs_kv_dev kv,
                             const uint16_t* tail_k, const uint16_t* tail_v, int tail_len, const int32_t* tail_lens,
                             uint16_t* O, float* LSE, float* ws, hipStream_t st, int phases, int dtype) {
-  const dim3 grid(n_work, Hkv, B);
+  const TailArgs tail{tail_k, tail_v, tail_lens, tail_len};
+  const dim3 grid(n_work, Hkv, B + (tail_len >= 0 ? (B + n_work - 1) / n_work : 0));
   const bool f16 = dtype == HS_FP16;
   const float sl2 = scale * kLog2e;
   const int per = (T + n_work - 1) / n_work;
@@ -685,12 +735,12 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   // all-2:4 tensors and from 256 for the other kernels (measured)
   const bool by_count = per >= (km == 0 && vm == 0 ? HS_DEC_BYCOUNT_MIN_PER : 2 * HS_DEC_BYCOUNT_MIN_PER);
 #define HS_GO_DYN(KM_, VM_)                                                                                            \
-  e = by_count ? launch_split<KM_, VM_, kByCount>(grid, st, Hq, Hkv, T, sl2, n_splits, per, Q, kv, wo, wl, f16)       \
-               : launch_split<KM_, VM_, kByRange>(grid, st, Hq, Hkv, T, sl2, n_splits, per, Q, kv, wo, wl, f16);      \
+  e = by_count ? launch_split<KM_, VM_, kByCount>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16)       \
+               : launch_split<KM_, VM_, kByRange>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16);      \
   break
 #define HS_GO(KM_, VM_)                                                                                       \
   if (kv.uniform) {                                                                                           \
-    e = launch_split<KM_, VM_, kUniform>(grid, st, Hq, Hkv, T, sl2, n_splits, per, Q, kv, wo, wl, f16);       \
+    e = launch_split<KM_, VM_, kUniform>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16);       \
     break;                                                                                                    \
   }                                                                                                           \
   HS_GO_DYN(KM_, VM_)
@@ -707,15 +757,6 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   }
 #undef HS_GO
 #undef HS_GO_DYN
-  }
-  if (e == hipSuccess && (phases & 1) && tail_len >= 0) {
-    if (f16)
-      hipLaunchKernelGGL(decode_tail_kernel<true>, dim3(Hkv, B), dim3(256), 0, st, Hq, Hkv, sl2, n_splits, n_work,
-                         tail_len, tail_lens, Q, tail_k, tail_v, wo, wl);
-    else
-      hipLaunchKernelGGL(decode_tail_kernel<false>, dim3(Hkv, B), dim3(256), 0, st, Hq, Hkv, sl2, n_splits, n_work,
-                         tail_len, tail_lens, Q, tail_k, tail_v, wo, wl);
-    e = hipGetLastError();
   }
   if (e != hipSuccess || !(phases & 2)) return e;
   return hs_launch_merge((int64_t)B * Hq, n_splits, wo, wl, O, LSE, st, dtype);

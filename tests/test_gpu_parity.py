@@ -747,6 +747,28 @@ def test_decode_with_dense_tail():
                                         hb._ptr(qd), None) == -1
 
 
+@pytest.mark.parametrize("B,Hkv,G,T,n_splits,dtype", [(3, 2, 1, 1, 1, "bf16"), (5, 1, 3, 4, 2, "fp16"), (2, 3, 8, 6, 4, "bf16"),
+                                                       (7, 2, 5, 3, 1, "fp16")])
+def test_decode_tail_workgroups_of_every_row(B, Hkv, G, T, n_splits, dtype):
+    """Tail lengths of every kind side by side (none, one token, both sides of a 16-token block, all 64) and
+    numbers of rows that do and do not fill the last plane of tail workgroups."""
+    lens = [0, 1, 15, 16, 17, 63, 64][:B]
+    L = 64 * T
+    Q, K, V = wl.make_qkv(B, G * Hkv, Hkv, L + 64, 128, 1, seed=950 + B, dtype=dtype)
+    q, Kc, Vc, Kt, Vt = Q[:, :, 0].copy(), K[:, :, :L].copy(), V[:, :, :L].copy(), K[:, :, L:].copy(), V[:, :, L:].copy()
+    sh, kv, pk, pv, _ = compress_both(B, G * Hkv, Hkv, L, Kc, Vc, dtype=dtype)
+    tk, tv = _dev(Kt, dtype), _dev(Vt, dtype)
+    for b, n in enumerate(lens):                      # tokens past a row's tail must not be looked at
+        tk[b, :, n:], tv[b, :, n:] = float("nan"), float("nan")
+    rows = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    O, LSE = hb.decode_attn(sh, _dev(q, dtype), kv, n_splits=n_splits, tail_k=tk, tail_v=tv, tail_len=rows)
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        Or, Lr = orc.attention_decode(q, pk, pv, tail_k=Kt, tail_v=Vt, tail_len=n)
+        assert_close(_f32(O)[b], Or[b], f"decode tail of {n} in row {b}")
+        assert_lse_close(LSE.cpu().numpy()[b], Lr[b], f"decode tail of {n} in row {b} lse")
+
+
 def test_append_tiles_during_decode():
     """A cache allocated for 9 tiles, compressed with 4, then grown tile by tile (mixed tile kinds, the last
     one from a strided buffer); after every append decode equals the oracle's, and at the end pools and maps
