@@ -612,12 +612,14 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, in
 // Merge of the split partials (Sec. IV-C "lightweight post-processing kernel"):
 // O = sum_s e^{LSE_s - M} O_s / sum_s e^{LSE_s - M}, M = max_s LSE_s, done in one pass with a
 // running reference per thread.  A row (one query of one head) is merged by SL split lanes of 32
-// threads (4 channels each), which are combined in LDS; a workgroup takes R rows.
+// threads (4 channels each), which are combined in LDS; a workgroup takes R rows.  A thread requests U partials before
+// it looks at the first (a test per partial in front of its use made them wait for each other: 4.0 -> 3.2 us at 32 rows
+// x 32 splits, 16 -> 4.2 us at 256 splits).
 // A separate launch on purpose: folding it into the split kernel ("last workgroup to arrive
 // merges") needs device-scope visibility between workgroups on different XCDs, and both ways
 // of getting it (a device-wide fence per workgroup, or write-through stores and L2-bypassing
 // loads) measured slower than this launch.
-template <bool F16, int SL, int R>
+template <bool F16, int SL, int R, int U>
 __global__ __launch_bounds__(32 * SL * R) void merge_kernel(int64_t rows, int n_splits, const float* __restrict__ ws_o,
                                                             const float* __restrict__ ws_l, uint16_t* __restrict__ O,
                                                             float* __restrict__ LSE) {
@@ -629,16 +631,29 @@ __global__ __launch_bounds__(32 * SL * R) void merge_kernel(int64_t rows, int n_
   const float* po = ws_o + (valid ? row : 0) * n_splits * HS_D + ch;
   const float* pl = ws_l + (valid ? row : 0) * n_splits;
   float M = -INFINITY, den = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-  for (int s = sl; s < n_splits; s += SL) {
-    const float lse = pl[s];
-    const float4 v = *reinterpret_cast<const float4*>(po + (int64_t)s * HS_D);
-    if (lse > -INFINITY) {
-      const float Mn = fmaxf(M, lse);
-      const float fo = __expf(M - Mn), fn = __expf(lse - Mn);  // fo = 0 while M is still -inf
-      den = den * fo + fn;
-      acc[0] = acc[0] * fo + fn * v.x; acc[1] = acc[1] * fo + fn * v.y;
-      acc[2] = acc[2] * fo + fn * v.z; acc[3] = acc[3] * fo + fn * v.w;
+  for (int s0 = sl; s0 < n_splits; s0 += SL * U) {  // U partials requested at once
+    float lse[U];
+    float4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int s = s0 + SL * u;
+      lse[u] = s < n_splits ? pl[s] : -INFINITY;
+      v[u] = s < n_splits ? *reinterpret_cast<const float4*>(po + (int64_t)s * HS_D) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    float Mn = M;
+#pragma unroll
+    for (int u = 0; u < U; u++) Mn = fmaxf(Mn, lse[u]);
+    if (Mn > -INFINITY) {
+      const float fo = __expf(M - Mn);  // 0 while M is still -inf
+      den *= fo;
+#pragma unroll
+      for (int i = 0; i < 4; i++) acc[i] *= fo;
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        const float fn = __expf(lse[u] - Mn);  // 0 for a split that saw nothing
+        den += fn;
+        acc[0] += fn * v[u].x; acc[1] += fn * v[u].y; acc[2] += fn * v[u].z; acc[3] += fn * v[u].w;
+      }
       M = Mn;
     }
   }
@@ -764,14 +779,18 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
 
 hipError_t hs_launch_merge(int64_t rows, int n_splits, const float* ws_o, const float* ws_l, uint16_t* O, float* LSE,
                            hipStream_t st, int dtype) {
-#define HS_MERGE(SL_, R_)                                                                                                  \
+#define HS_MERGE(SL_, R_, U_)                                                                                              \
   do {                                                                                                                     \
     const dim3 grid((unsigned)((rows + R_ - 1) / R_)), block(32 * SL_ * R_);                                               \
-    if (dtype == HS_FP16) hipLaunchKernelGGL((merge_kernel<true, SL_, R_>), grid, block, 0, st, rows, n_splits, ws_o, ws_l, O, LSE); \
-    else hipLaunchKernelGGL((merge_kernel<false, SL_, R_>), grid, block, 0, st, rows, n_splits, ws_o, ws_l, O, LSE);       \
+    if (dtype == HS_FP16) hipLaunchKernelGGL((merge_kernel<true, SL_, R_, U_>), grid, block, 0, st, rows, n_splits, ws_o, ws_l, O, LSE); \
+    else hipLaunchKernelGGL((merge_kernel<false, SL_, R_, U_>), grid, block, 0, st, rows, n_splits, ws_o, ws_l, O, LSE);   \
   } while (0)
-  if (n_splits >= 8 || rows < 4096) HS_MERGE(8, 1);
-  else HS_MERGE(1, 8);
+  // Latency decides: few splits want no exchange between lanes, many want them requested side by side.  Kernel times in us
+  // of <1, 8, 4> / <8, 1, 4> / <16, 1, 4>: 32 rows x 8 splits 2.7 / 3.0 / 3.3, 8192 x 8 4.4 / 9.4 / 12.1, 32768 x 2 7.8 /
+  // 19.7 / 34; 32 x 32 4.7 / 3.2 / 3.4, 2048 x 32 7.2 / 4.8 / 6.3; 32 x 128 13.3 / 4.3 / 4.0, 4 x 256 23.7 / 5.4 / 4.2.
+  if (n_splits <= 8) HS_MERGE(1, 8, 4);
+  else if (n_splits <= 64) HS_MERGE(8, 1, 4);
+  else HS_MERGE(16, 1, 4);
 #undef HS_MERGE
   return hipGetLastError();
 }
