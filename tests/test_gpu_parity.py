@@ -1409,6 +1409,36 @@ def test_recompress_ranked_targets_from_kept_tile_scores():
     assert_lse_close(LSE.cpu().numpy(), Lr, "decode after ranked recompress lse")
 
 
+@pytest.mark.parametrize("T,first,last", [(1, 0, 0), (3, 1, 1), (64, 0, 0), (65, 0, 0), (130, 1, 4), (257, 0, 0), (1024, 2, 3), (2048, 0, 0), (2049, 1, 0)])
+def test_selection_of_given_scores(T, first, last):
+    """The n lowest (score, tile index), for scores of every kind: all equal, more and fewer equal ones than one wave
+    ranks at once, differing only in the lowest or only in the highest bits, zeros, infinities."""
+    rng = np.random.default_rng(T)
+    kinds = [np.full(T, 3.25), rng.integers(0, 2, T) * 1.0, rng.integers(0, 7, T) * 0.5, 1.0 + rng.integers(0, 9, T) * 2.0 ** -52,
+             rng.random(T), 10.0 ** rng.uniform(-300, 300, T), 8192 + rng.standard_normal(T), np.where(rng.random(T) < 0.4, np.inf, rng.random(T))]
+    Hkv = len(kinds)
+    sh = hb.make_shape(1, Hkv, Hkv, 64 * T)
+    scores = np.stack([np.stack(kinds), np.stack(kinds[1:] + kinds[:1]), np.stack(kinds[3:] + kinds[:3])])[:, None]
+    x = torch.ones(1, Hkv, 64 * T, 128, device="cuda", dtype=torch.bfloat16)
+    kv = hb.compress_kv(sh, hb.make_policy(sparse_frac_k=0.0, sparse_frac_v=0.0), x, x)
+    del x
+    for skip, fk, fv in ((0.25, 0.5, 0.3), (0.5, 1.0, 0.99), (0.0, 0.01, 1.0), (0.97, 0.5, 0.5)):
+        pol = hb.make_policy(skip_frac=skip, sparse_frac_k=fk, sparse_frac_v=fv, dense_first_tiles=first, dense_last_tiles=last,
+                             tile_scores=torch.from_numpy(scores).cuda())
+        out = hb.recompress_kv(sh, kv, pol, counts=[0, T, T, T, T])
+        km, vm = lib_maps(out.k_map, out.v_map)[:2]
+        for h in range(Hkv):
+            mid = np.arange(first, T - last)
+            order = mid[np.lexsort((mid, scores[0, 0, h, mid]))]
+            n_skip = int(np.floor(skip * len(mid)))
+            kept = np.sort(order[n_skip:])
+            want = np.ones((2, T), dtype=np.int64)
+            want[:, order[:n_skip]] = 0
+            for x_, f in ((0, fk), (1, fv)):
+                want[x_, kept[np.lexsort((kept, scores[1 + x_, 0, h, kept]))][:int(np.floor(f * len(kept)))]] = -1
+            assert (np.sign(np.asarray(km)[0, h]) == want[0]).all() and (np.sign(np.asarray(vm)[0, h]) == want[1]).all(), (h, skip, fk, fv)
+
+
 def test_recompress_capacity_overflow_and_argument_errors():
     B, Hq, Hkv, L = 1, 4, 1, 64 * 8
     T = L // 64
