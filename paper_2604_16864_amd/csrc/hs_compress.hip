@@ -77,18 +77,18 @@ __device__ __forceinline__ void stage_v_tile(const uint16_t* vt, int64_t tok_str
 // plane that is not asked for is written as zeros (the selection then falls back to tile order
 // there, which is all it needs when a count is 0 or everything).
 // ----------------------------------------------------------------------------------
-template <bool F16> __device__ __forceinline__ double sum_sq8(uint4 d) {  // sum of squares of 8 elements
+template <bool F16> __device__ __forceinline__ double add_sq8(double e, uint4 d) {  // e + the squares of 8 elements
   const uint32_t w[4] = {d.x, d.y, d.z, d.w};
-  double e = 0.0;
 #pragma unroll
   for (int i = 0; i < 4; i++) {
-    const double f0 = elem_val<F16>(w[i] & 0xffffu), f1 = elem_val<F16>(w[i] >> 16);
-    e += f0 * f0 + f1 * f1;
+    const double f0 = (double)hs_elem<F16>::lo_f32(w[i]), f1 = (double)hs_elem<F16>::hi_f32(w[i]);
+    e = fma(f0, f0, e);
+    e = fma(f1, f1, e);
   }
   return e;
 }
 
-// sum of the magnitudes of the two elements of a group that the 2:4 mask drops
+// sum of the magnitudes of the two elements of a group that the 2:4 mask drops, any rule
 template <bool F16>
 __device__ __forceinline__ double dropped_l1(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, int rule) {
   const uint32_t drop = ~top2_mask(x0, x1, x2, x3, rule) & 15u;
@@ -97,73 +97,105 @@ __device__ __forceinline__ double dropped_l1(uint32_t x0, uint32_t x1, uint32_t 
   return fabs(elem_val<F16>(pair & 0xffffu)) + fabs(elem_val<F16>(pair >> 16));
 }
 
-// NT: non-temporal reads in the energy-only form.  They pay when K and V exceed the last-level
-// cache (B 8 x L 131072: 1.32 -> 1.26 ms for score + select + pack) and cost when they fit, because
-// the pack kernel's second read of the kept tiles then no longer hits that cache (L 32768: 56 -> 60 us).
+// The same by magnitude needs no mask: the sum of the two smallest of four magnitudes (which of several equal
+// ones is dropped does not matter to the sum).  Bit patterns without the sign order like the magnitudes, so a network
+// of packed 16-bit minima and maxima finds them, two groups at a time.
+typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
+}
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
+}
+// a group = four channels in two words: (x0, x1), (x2, x3)
+template <bool F16> __device__ __forceinline__ double add_dropped_row(double s, uint32_t x01, uint32_t x23, int rule) {
+  if (rule != 0) return s + dropped_l1<F16>(x01 & 0xffffu, x01 >> 16, x23 & 0xffffu, x23 >> 16, rule);
+  const uint32_t a = x01 & 0x7fff7fffu, b = x23 & 0x7fff7fffu;
+  const uint32_t lo = pk_min(a, b), hi = pk_max(a, b);
+  const uint32_t lo_r = __builtin_amdgcn_alignbit(lo, lo, 16), hi_r = __builtin_amdgcn_alignbit(hi, hi, 16);
+  const uint32_t s1 = pk_min(lo, lo_r), s2 = pk_min(pk_max(lo, lo_r), pk_min(hi, hi_r));
+  return s + ((double)hs_elem<F16>::lo_f32(s1) + (double)hs_elem<F16>::lo_f32(s2));
+}
+// two groups = two channels of four tokens, a word per token
+template <bool F16>
+__device__ __forceinline__ double add_dropped_col(double s, uint32_t r0, uint32_t r1, uint32_t r2, uint32_t r3, int rule) {
+  if (rule != 0)
+    return s + (dropped_l1<F16>(r0 & 0xffffu, r1 & 0xffffu, r2 & 0xffffu, r3 & 0xffffu, rule) +
+                dropped_l1<F16>(r0 >> 16, r1 >> 16, r2 >> 16, r3 >> 16, rule));
+  const uint32_t m0 = r0 & 0x7fff7fffu, m1 = r1 & 0x7fff7fffu, m2 = r2 & 0x7fff7fffu, m3 = r3 & 0x7fff7fffu;
+  const uint32_t lo0 = pk_min(m0, m1), hi0 = pk_max(m0, m1), lo1 = pk_min(m2, m3), hi1 = pk_max(m2, m3);
+  const uint32_t s1 = pk_min(lo0, lo1), s2 = pk_min(pk_max(lo0, lo1), pk_min(hi0, hi1));
+  return s + (((double)hs_elem<F16>::lo_f32(s1) + (double)hs_elem<F16>::lo_f32(s2)) +
+              ((double)hs_elem<F16>::hi_f32(s1) + (double)hs_elem<F16>::hi_f32(s2)));
+}
+
+// Data-parallel-primitive moves (a few cycles against the ~100 of a lane shuffle through LDS): lanes without a source
+// read `id`.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_mov(int v, int id) { return __builtin_amdgcn_update_dpp(id, v, CTRL, ROW_MASK, 0xf, false); }
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ double dpp_add(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)dpp_mov<CTRL, ROW_MASK>((int)b, 0), hi = (unsigned)dpp_mov<CTRL, ROW_MASK>((int)(b >> 32), 0);
+  return v + __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+__device__ __forceinline__ double wave_sum_last(double v) {  // lane 63: the sum of the wave, fixed order
+  v = dpp_add<0x111, 0xf>(v);  // row_shr:1
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+}
+
+// One workgroup per tile.  Bound by the read of K and V; what could keep it from that is arithmetic, so: no LDS staging
+// (a thread reads the same 8 channels of a whole token group of V), no element masks (above), one fma per square.
+// All three planes at 8 rows of 512 tiles (134 MB): 44.8 -> 29.0 us = 4.6 TB/s (a large copy reaches 5.1 here).
+// NT: non-temporal reads.  They pay when K and V exceed the last-level cache (energy alone, B 8 x L 131072: 1.32 -> 1.26 ms
+// for score + select + pack) and cost when they fit, because the pack kernel's second read of the kept tiles then no
+// longer hits that cache (L 32768: 56 -> 60 us).
 template <bool F16, int WHAT, bool NT>
 __global__ __launch_bounds__(256) void score_kernel(const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                                                     int64_t sb, int64_t sh, int64_t st, int Hkv, int T, int rule,
                                                     double* __restrict__ scores) {
   constexpr bool ENERGY = (WHAT & 1) != 0, LOSS = (WHAT & 2) != 0;
-  __shared__ uint16_t vl[LOSS ? HS_BT * kVStride : 8];
   __shared__ double red[3][4];
   const int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, a = l >> 4, r = l & 15;
-  const uint16_t* kt = K + b * sb + h * sh + (int64_t)t * HS_BT * st;
-  const uint16_t* vt = V + b * sb + h * sh + (int64_t)t * HS_BT * st;
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const uint16_t* kt = K + b * sb + h * sh + (int64_t)t * HS_BT * st + 8 * (tid & 15);
+  const uint16_t* vt = V + b * sb + h * sh + (int64_t)t * HS_BT * st + 8 * (tid & 15);
+  uint4 kd[4], vd[4];  // K: tokens tid / 16 + 16 i; V: tokens 4 (tid / 16) + i; channels 8 (tid % 16) .. +7
+#pragma unroll
+  for (int i = 0; i < 4; i++) kd[i] = ld16<NT>(kt + ((tid >> 4) + 16 * i) * st);
+#pragma unroll
+  for (int i = 0; i < 4; i++) vd[i] = ld16<NT>(vt + (4 * (tid >> 4) + i) * st);
   double e = 0.0, lk = 0.0, lv = 0.0;
-  if (!LOSS) {
-    // energy alone does not care which thread sees which element: coalesced 16-byte reads
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int q = tid + 256 * i, tok = q >> 4, c8 = q & 15;
-      e += sum_sq8<F16>(ld16<NT>(kt + tok * st + 8 * c8));
-      e += sum_sq8<F16>(ld16<NT>(vt + tok * st + 8 * c8));
-    }
-  } else {
-    stage_v_tile(vt, st, vl);
-    {  // K: this thread owns token 16w+r, channels 64kb+16a .. +15
-      const uint16_t* row = kt + (int64_t)(16 * w + r) * st;
-#pragma unroll
-      for (int kb = 0; kb < 2; kb++) {
-        const uint4 d0 = *reinterpret_cast<const uint4*>(row + 64 * kb + 16 * a);
-        const uint4 d1 = *reinterpret_cast<const uint4*>(row + 64 * kb + 16 * a + 8);
-        if (ENERGY) e += sum_sq8<F16>(d0) + sum_sq8<F16>(d1);
-        const uint32_t wds[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-#pragma unroll
-        for (int q = 0; q < 4; q++)
-          lk += dropped_l1<F16>(wds[2 * q] & 0xffffu, wds[2 * q] >> 16, wds[2 * q + 1] & 0xffffu, wds[2 * q + 1] >> 16, rule);
-      }
-    }
-    __syncthreads();
-    {  // V: channel 16mb+r for mb = 2w, 2w+1; token groups of lane group a
-#pragma unroll
-      for (int j = 0; j < 2; j++) {
-        const int c = 16 * (2 * w + j) + r;
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          const int g = hs_v_group(a, q);
-          const uint32_t x0 = vl[(4 * g + 0) * kVStride + c], x1 = vl[(4 * g + 1) * kVStride + c];
-          const uint32_t x2 = vl[(4 * g + 2) * kVStride + c], x3 = vl[(4 * g + 3) * kVStride + c];
-          if (ENERGY) {
-            const double f0 = elem_val<F16>(x0), f1 = elem_val<F16>(x1), f2 = elem_val<F16>(x2), f3 = elem_val<F16>(x3);
-            e += f0 * f0 + f1 * f1 + f2 * f2 + f3 * f3;
-          }
-          lv += dropped_l1<F16>(x0, x1, x2, x3, rule);
-        }
-      }
-    }
-  }
-  // wave reduction (fixed butterfly), then 4 partials in LDS
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    e += __shfl_xor(e, off);
+  for (int i = 0; i < 4; i++) {
+    if (ENERGY) e = add_sq8<F16>(e, kd[i]);
     if (LOSS) {
-      lk += __shfl_xor(lk, off);
-      lv += __shfl_xor(lv, off);
+      lk = add_dropped_row<F16>(lk, kd[i].x, kd[i].y, rule);
+      lk = add_dropped_row<F16>(lk, kd[i].z, kd[i].w, rule);
     }
   }
-  if (l == 0) { red[0][w] = e; red[1][w] = lk; red[2][w] = lv; }
+  if (ENERGY) {
+    double ev = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) ev = add_sq8<F16>(ev, vd[i]);
+    e += ev;
+  }
+  if (LOSS) {
+    lv = add_dropped_col<F16>(lv, vd[0].x, vd[1].x, vd[2].x, vd[3].x, rule);
+    lv = add_dropped_col<F16>(lv, vd[0].y, vd[1].y, vd[2].y, vd[3].y, rule);
+    lv = add_dropped_col<F16>(lv, vd[0].z, vd[1].z, vd[2].z, vd[3].z, rule);
+    lv = add_dropped_col<F16>(lv, vd[0].w, vd[1].w, vd[2].w, vd[3].w, rule);
+  }
+  // wave sums, then 4 partials in LDS
+  if (ENERGY) e = wave_sum_last(e);
+  if (LOSS) {
+    lk = wave_sum_last(lk);
+    lv = wave_sum_last(lv);
+  }
+  if (l == 63) { red[0][w] = e; red[1][w] = lk; red[2][w] = lv; }
   __syncthreads();
   if (tid < 3) {
     const int64_t rows = (int64_t)gridDim.z * Hkv;
@@ -185,10 +217,7 @@ __global__ __launch_bounds__(256) void score_kernel(const uint16_t* __restrict__
 // Every thread owns a contiguous run of tiles, so "ascending tile index" is thread order, and a thread only
 // re-reads map entries it wrote itself.
 // ----------------------------------------------------------------------------------
-// Data-parallel-primitive moves (a few cycles against the ~100 of a lane shuffle through LDS): lanes without a source
-// read `id`.  wave_scan: inclusive sums over the 64 lanes; wave_last: what lane 63 holds, as a scalar.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int dpp_mov(int v, int id) { return __builtin_amdgcn_update_dpp(id, v, CTRL, ROW_MASK, 0xf, false); }
+// inclusive scan over the 64 lanes; `id` is the operation's neutral element
 template <class Op>
 __device__ __forceinline__ int wave_scan(int v, int id, Op op) {
   v = op(v, dpp_mov<0x111, 0xf>(v, id));  // row_shr:1
@@ -997,7 +1026,7 @@ hipError_t hs_launch_score(const uint16_t* K, const uint16_t* V, int64_t sb, int
                            int T, int rule, int dtype, int what, double* scores, hipStream_t st) {
   const dim3 grid(T, Hkv, B), block(256);
   // non-temporal reads once K and V together are larger than the 256 MB last-level cache
-  const bool nt = what == 1 && 2.0 * B * Hkv * T * HS_BT * HS_D * 2.0 > 256e6;
+  const bool nt = 2.0 * B * Hkv * T * HS_BT * HS_D * 2.0 > 256e6;
 #define HS_SCORE(F16_, WHAT_)                                                                                              \
   do {                                                                                                                     \
     if (nt) hipLaunchKernelGGL((score_kernel<F16_, WHAT_, true>), grid, block, 0, st, K, V, sb, sh, st_, Hkv, T, rule, scores); \
