@@ -556,17 +556,10 @@ __global__ __launch_bounds__(256) void states_to_maps_kernel(const int8_t* __res
 // next slots of the pool their state names, counted from how many tiles of that kind the row
 // holds; tiles for which a pool has no slot left stay skipped and raise *overflow.  One workgroup
 // per row.
-// tile_rows (or NULL): one tile index per batch row instead of `tile` (then n_tiles = 1); a batch
-// row whose entry is not a tile index is left as it is.
-__global__ __launch_bounds__(256) void append_slots_kernel(int Hkv, int T, int tile, int n_tiles,
-                                                           const int32_t* __restrict__ tile_rows, int state_k,
-                                                           int state_v, hs_kv_dev kv, int32_t* overflow) {
+__global__ __launch_bounds__(256) void append_slots_kernel(int T, int tile, int n_tiles, int state_k, int state_v,
+                                                           hs_kv_dev kv, int32_t* overflow) {
   __shared__ int part[4][4];
   const int row = blockIdx.x, tid = threadIdx.x;
-  if (tile_rows != nullptr) {
-    tile = tile_rows[row / Hkv];
-    if (tile < 0 || tile >= T) return;  // the whole workgroup
-  }
   int32_t* km = const_cast<int32_t*>(kv.k_map) + (int64_t)row * T;
   int32_t* vm = const_cast<int32_t*>(kv.v_map) + (int64_t)row * T;
   int n[4] = {0, 0, 0, 0};  // dense K, 2:4 K, dense V, 2:4 V
@@ -738,11 +731,14 @@ __device__ __forceinline__ void v_dense_to_lds(const uint8_t* src, bool is_f16, 
 // NTL: the inputs of tiles that become 2:4 are read non-temporally.  That pays when K and V exceed the
 // last-level cache (B 8 x L 131072: 1.20 -> 1.08 ms) and costs a little when they fit (L 32768: 38.7 -> 40.3 us;
 // the two 16-byte reads a lane makes of one K line then both go to L2), so the launcher decides by size.
-template <bool NTL>
+// APPEND: the tile is new in its row, in states uni_k / uni_v: this kernel counts the row's tiles of these kinds itself
+// (next slot of each pool, Sec. III-B) while the tile's first loads are under way, writes the entries, and raises
+// *overflow where a pool has no slot left.  Counting in every workgroup saves the launch of append_slots_kernel.
+template <bool NTL, bool APPEND>
 __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                                                    int64_t sb, int64_t sh, int64_t st, int Hkv, int T, hs_kv_dev kv,
                                                    int uni_k, int uni_v, int rule, int t0, int v_f16,
-                                                   const int32_t* __restrict__ t0_rows) {
+                                                   const int32_t* __restrict__ t0_rows, int32_t* overflow) {
   __shared__ uint16_t vl[HS_BT * kVStride];
   // source tile blockIdx.x of K, V goes to tile t of the cache (t0 = 0 except when appending;
   // t0_rows: one t0 per batch row, entries that are not a tile index leave the row out)
@@ -754,8 +750,38 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
   const int t = ts + t0;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, a = l >> 4, r = l & 15;
   const int64_t row = (int64_t)b * Hkv + h;
+  const uint16_t* kt = K + b * sb + h * sh + (int64_t)ts * HS_BT * st;
+  const uint16_t* vt = V + b * sb + h * sh + (int64_t)ts * HS_BT * st;
   int mk, mv;
-  if (uni_k != 0) {
+  if constexpr (APPEND) {
+    __shared__ int part[2][4];
+    int32_t* km = const_cast<int32_t*>(kv.k_map) + row * T;
+    int32_t* vm = const_cast<int32_t*>(kv.v_map) + row * T;
+    if (uni_v == HS_SPARSE24) stage_v_tile<NTL>(vt, st, vl);
+    else stage_v_tile<false>(vt, st, vl);
+    int nk = 0, nv = 0;  // entries [t0, t0 + gridDim.x) are being written by this launch and do not count
+#pragma unroll 4
+    for (int i = tid; i < T; i += 256) {
+      const bool old = i < t0 || i >= t0 + (int)gridDim.x;
+      const int a_ = old ? km[i] : 0, c_ = old ? vm[i] : 0;
+      nk += uni_k == HS_DENSE ? a_ > 0 : a_ < 0;
+      nv += uni_v == HS_DENSE ? c_ > 0 : c_ < 0;
+    }
+    nk = wave_scan_sum(nk);
+    nv = wave_scan_sum(nv);
+    if (l == 63) { part[0][w] = nk; part[1][w] = nv; }
+    __syncthreads();
+    const int sk = part[0][0] + part[0][1] + part[0][2] + part[0][3] + ts, sv = part[1][0] + part[1][1] + part[1][2] + part[1][3] + ts;
+    const bool fits = sk < (uni_k == HS_DENSE ? kv.cap_dense_k : kv.cap_sparse_k) && sv < (uni_v == HS_DENSE ? kv.cap_dense_v : kv.cap_sparse_v);
+    mk = !fits ? 0 : (uni_k == HS_DENSE ? sk + 1 : -(sk + 1));
+    mv = !fits ? 0 : (uni_v == HS_DENSE ? sv + 1 : -(sv + 1));
+    if (tid == 0) {
+      km[t] = mk;
+      vm[t] = mv;
+      if (!fits && overflow != nullptr) *overflow = 1;
+    }
+    if (!fits) return;  // the whole workgroup
+  } else if (uni_k != 0) {
     mk = uni_k == HS_DENSE ? t + 1 : -(t + 1);
     mv = uni_v == HS_DENSE ? t + 1 : -(t + 1);
     if (tid == 0) {
@@ -766,10 +792,10 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
     mk = kv.k_map[row * T + t];
     mv = kv.v_map[row * T + t];
   }
-  const uint16_t* kt = K + b * sb + h * sh + (int64_t)ts * HS_BT * st;
-  const uint16_t* vt = V + b * sb + h * sh + (int64_t)ts * HS_BT * st;
-  if (mv < 0) stage_v_tile<NTL>(vt, st, vl);
-  else if (mv > 0) stage_v_tile<false>(vt, st, vl);
+  if (!APPEND) {
+    if (mv < 0) stage_v_tile<NTL>(vt, st, vl);
+    else if (mv > 0) stage_v_tile<false>(vt, st, vl);
+  }
 
   // ---- K ----
   if (mk > 0) {  // dense: permuted copy into operand order
@@ -1056,27 +1082,39 @@ hipError_t hs_launch_select(const double* scores, int rows, int T, int n_skip, i
 hipError_t hs_launch_pack(const uint16_t* K, const uint16_t* V, int64_t sb, int64_t sh, int64_t st_, int B, int Hkv,
                           int T, hs_kv_dev kv, int uni_k, int uni_v, int rule, int v_f16, hipStream_t st) {
   if (2.0 * B * Hkv * T * HS_BT * HS_D * 2.0 > 256e6)  // K and V together beyond the 256 MB last-level cache
-    hipLaunchKernelGGL(pack_kernel<true>, dim3(T, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, uni_k, uni_v, rule, 0,
-                       v_f16, (const int32_t*)nullptr);
+    hipLaunchKernelGGL((pack_kernel<true, false>), dim3(T, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, uni_k, uni_v, rule, 0,
+                       v_f16, (const int32_t*)nullptr, (int32_t*)nullptr);
   else
-    hipLaunchKernelGGL(pack_kernel<false>, dim3(T, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, uni_k, uni_v, rule, 0,
-                       v_f16, (const int32_t*)nullptr);
+    hipLaunchKernelGGL((pack_kernel<false, false>), dim3(T, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, uni_k, uni_v, rule, 0,
+                       v_f16, (const int32_t*)nullptr, (int32_t*)nullptr);
   return hipGetLastError();
 }
 
 hipError_t hs_launch_append(const uint16_t* K, const uint16_t* V, int64_t sb, int64_t sh, int64_t st_, int B, int Hkv,
                             int T, int tile, int n_tiles, const int32_t* tile_rows, int state_k, int state_v,
                             hs_kv_dev kv, int rule, int v_f16, int32_t* overflow, hipStream_t st) {
-  hipLaunchKernelGGL(append_slots_kernel, dim3(B * Hkv), dim3(256), 0, st, Hkv, T, tile, n_tiles, tile_rows, state_k, state_v,
-                     kv, overflow);
+  const bool nt = 2.0 * B * Hkv * n_tiles * HS_BT * HS_D * 2.0 > 256e6;
+  // One launch while the map entries that all workgroups read to count are few (32 MB): 1 x 8 rows of 512 tiles, one tile
+  // 8.1 -> 6.1 us, 64 tiles 10.7 -> 8.1 us; 1 x 8 rows of 2048, 256 tiles 26.6 -> 23.3 us, 1024 tiles 76.5 us either way;
+  // 16 x 8 rows of 512, 128 tiles 137 -> 140 us.  Per-row places come one tile at a time and always take it.
+  if (tile_rows != nullptr || (double)n_tiles * B * Hkv * T <= (double)(4 << 20)) {
+    if (nt)
+      hipLaunchKernelGGL((pack_kernel<true, true>), dim3(n_tiles, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, state_k,
+                         state_v, rule, tile, v_f16, tile_rows, overflow);
+    else
+      hipLaunchKernelGGL((pack_kernel<false, true>), dim3(n_tiles, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, state_k,
+                         state_v, rule, tile, v_f16, tile_rows, overflow);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(append_slots_kernel, dim3(B * Hkv), dim3(256), 0, st, T, tile, n_tiles, state_k, state_v, kv, overflow);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (2.0 * B * Hkv * n_tiles * HS_BT * HS_D * 2.0 > 256e6)
-    hipLaunchKernelGGL(pack_kernel<true>, dim3(n_tiles, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, 0, 0, rule, tile,
-                       v_f16, tile_rows);
+  if (nt)
+    hipLaunchKernelGGL((pack_kernel<true, false>), dim3(n_tiles, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, 0, 0, rule, tile,
+                       v_f16, (const int32_t*)nullptr, (int32_t*)nullptr);
   else
-    hipLaunchKernelGGL(pack_kernel<false>, dim3(n_tiles, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, 0, 0, rule, tile,
-                       v_f16, tile_rows);
+    hipLaunchKernelGGL((pack_kernel<false, false>), dim3(n_tiles, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, 0, 0, rule, tile,
+                       v_f16, (const int32_t*)nullptr, (int32_t*)nullptr);
   return hipGetLastError();
 }
 

@@ -822,6 +822,52 @@ def test_append_tiles_during_decode():
     assert hb.lib().hs_append_tile(C.byref(sh), 5, 2, 2, 7, *args) == -1          # unknown element rule
 
 
+@pytest.mark.parametrize("T,n,rows", [(5, 2, 2), (300, 64, 2), (300, 63, 3), (2100, 1000, 2), (1100, 500, 8)])   # both ways of counting
+@pytest.mark.parametrize("state_k,state_v", [(2, 2), (1, 2)])
+def test_append_counts_what_the_row_holds(T, n, rows, state_k, state_v):
+    """New tiles take the slots after those their row holds, wherever they stand and whatever their old entries are;
+    tiles that find a pool full stay SKIP and raise the flag."""
+    rng = np.random.default_rng(T + n)
+    at = T // 3
+    sk, sv = rng.integers(1, 3, (1, rows, T)).astype(np.int8), rng.integers(1, 3, (1, rows, T)).astype(np.int8)
+    hole = rng.random((1, rows, T)) < 0.3
+    sk[hole], sv[hole] = 0, 0
+    sk[:, :, at:at + n], sv[:, :, at:at + n] = 0, 0
+    held = [int(((s == k).sum(-1)).max()) for s, k in ((sk, 1), (sk, 2), (sv, 1), (sv, 2))]
+    room = n - 1                                      # one tile too few in the fullest row's pools
+    caps = [0, held[0] + room * (state_k == 1), held[1] + room * (state_k == 2), held[2] + room * (state_v == 1), held[3] + room * (state_v == 2)]
+    sh = hb.make_shape(1, rows, rows, 64 * T)
+    kv = hb.PackedKV(sh, caps)
+    kv.uniform = 0
+    maps = [np.zeros((1, rows, T), dtype=np.int32) for _ in range(2)]
+    for m, s in zip(maps, (sk, sv)):
+        for r in range(rows):
+            for state, sign in ((1, 1), (2, -1)):
+                idx = np.flatnonzero(s[0, r] == state)
+                m[0, r, idx] = sign * (np.arange(len(idx)) + 1)
+    kv.k_map.copy_(torch.from_numpy(maps[0]))
+    kv.v_map.copy_(torch.from_numpy(maps[1]))
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K = torch.randn((1, rows, 64 * n, 128), device="cuda", generator=g).bfloat16()
+    V = torch.randn((1, rows, 64 * n, 128), device="cuda", generator=g).bfloat16()
+    for _ in range(2):                                # a second call over the same place gives the same again
+        over = torch.zeros(1, dtype=torch.int32, device="cuda")
+        hb.append_tile(sh, kv, at, K, V, state_k=state_k, state_v=state_v, overflow=over)
+        km, vm = lib_maps(kv.k_map, kv.v_map)[:2]
+        want = [m.copy() for m in maps]
+        full = False
+        for r in range(rows):
+            ck, cv = int((sk[0, r] == state_k).sum()), int((sv[0, r] == state_v).sum())
+            for i in range(n):
+                if ck + i < caps[state_k] and cv + i < caps[2 + state_v]:
+                    want[0][0, r, at + i] = (ck + i + 1) * (1 if state_k == 1 else -1)
+                    want[1][0, r, at + i] = (cv + i + 1) * (1 if state_v == 1 else -1)
+                else:
+                    full = True
+        assert (km == want[0]).all() and (vm == want[1]).all()
+        assert int(over.item()) == int(full)
+
+
 def test_batch_rows_of_different_length_decode_and_append():
     """A batch whose sequences hold 3, 9 and 6 tiles and 17, 0 and 64 tail tokens: decode with one tail
     length per batch row; the row with the full tail (and only that one) appends it at its own position;
