@@ -219,7 +219,7 @@ int hs_compress_kv(const hs_shape* shape, const hs_policy* policy, const void* K
   hipStream_t s = (hipStream_t)stream;
   int32_t c[5];
   hipError_t e;
-  int uni_k = 0, uni_v = 0;
+  int uni_k = 0, uni_v = 0, n_first = 0, n_last = 0;
   if (policy->state_k != nullptr) {
     // states -> maps on the device (prefix counts = the sequential counters of Sec. III-B); what the host
     // cannot see (a state pair that is not valid, a row that needs more slots than a pool has) is reported
@@ -231,20 +231,15 @@ int hs_compress_kv(const hs_shape* shape, const hs_policy* policy, const void* K
     policy_counts(T, policy, c);
     if (c[1] > out->cap_dense_k || c[2] > out->cap_sparse_k || c[3] > out->cap_dense_v || c[4] > out->cap_sparse_v)
       return HS_EINVAL;
-    int n_first, n_last;
     protected_tiles(T, policy, &n_first, &n_last);
     const int n_keep = T - n_first - n_last - c[0];
     const bool uniform_k = c[1] == 0 || c[2] == 0, uniform_v = c[3] == 0 || c[4] == 0;
-    if (c[0] == 0 && uniform_k && uniform_v) {
-      // no ranking needed: every tile in one state; the pack kernel writes the maps itself
+    if (c[0] == 0 && (c[2] == 0 || c[2] == n_keep) && (c[4] == 0 || c[4] == n_keep)) {
+      // no ranking needed: protected end tiles dense, every tile in between in one state; the pack
+      // kernel writes the maps itself
+      if (!(uniform_k && uniform_v) && T > kSelectMaxTiles) return HS_EUNSUPPORTED;
       uni_k = c[2] ? HS_SPARSE24 : HS_DENSE;
       uni_v = c[4] ? HS_SPARSE24 : HS_DENSE;
-    } else if (c[0] == 0 && (c[2] == 0 || c[2] == n_keep) && (c[4] == 0 || c[4] == n_keep)) {
-      // no ranking needed either: protected end tiles dense, every tile in between in one state;
-      // the selection kernel never looks at the scores then
-      if (T > kSelectMaxTiles) return HS_EUNSUPPORTED;
-      e = hs_launch_select(nullptr, rows, T, 0, c[2], c[4], n_first, n_last, out->k_map, out->v_map, s);
-      if (e != hipSuccess) return hip_fail(e);
     } else {
       if (workspace == nullptr || ((uintptr_t)workspace & 7u)) return HS_EINVAL;
       if (T > kSelectMaxTiles) return HS_EUNSUPPORTED;
@@ -259,7 +254,7 @@ int hs_compress_kv(const hs_shape* shape, const hs_policy* policy, const void* K
     }
   }
   e = hs_launch_pack((const uint16_t*)K, (const uint16_t*)V, sb, sh, st, shape->B, shape->Hkv, T,
-                     hs_make_kv_dev(out), uni_k, uni_v, policy->element_rule, shape->dtype == HS_BF16, s);
+                     hs_make_kv_dev(out), uni_k, uni_v, n_first, n_last, policy->element_rule, shape->dtype == HS_BF16, s);
   if (e != hipSuccess) return hip_fail(e);
   return HS_OK;
 }

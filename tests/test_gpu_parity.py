@@ -182,6 +182,16 @@ def test_compress_protected_end_tiles(skip, sfk, sfv, first, last):
     assert_lse_close(LSE.cpu().numpy(), Lr, "decode protected tiles lse")
 
 
+@pytest.mark.parametrize("sfk,sfv", [(1.0, 1.0), (1.0, 0.0), (0.0, 1.0)])
+@pytest.mark.parametrize("T,first,last", [(6, 1, 4), (6, 0, 1), (6, 3, 0), (5, 1, 4), (4, 2, 9), (1, 0, 1), (7, 0, 0)])
+def test_compress_protected_end_tiles_without_ranking(T, first, last, sfk, sfv):
+    """Entries that follow from the tile's index: sinks and windows of every size, up to all of the row."""
+    Q, K, V = wl.make_qkv(2, 2, 2, 64 * T, 128, 1, seed=40 + T)
+    sh, kv, pk, pv, _ = compress_both(2, 2, 2, 64 * T, K, V, sparse_frac_k=sfk, sparse_frac_v=sfv, dense_first_tiles=first,
+                                      dense_last_tiles=last)
+    check_packed_bit_exact(sh, kv, pk, pv)
+
+
 def test_compress_nonzero_rule_premasked_input():
     """Generic compressor (Sec. IV-B): K, V arrive with an arbitrary 2:4 element mask applied
     (zeros at pruned places); under the non-zero rule the packed form decodes to the input."""
