@@ -178,7 +178,8 @@ HS_API int hs_kv_bytes(const hs_shape* shape, const int32_t counts[5], size_t by
  *   (op 1 needs none; op 3 only when the target ranks tiles: then 8 bytes per tile) */
 HS_API int hs_workspace_bytes(const hs_shape* shape, int op, int32_t arg, size_t* bytes);
 
-/* Number of KV splits hs_decode_attn uses when n_splits == 0. [host, pure] */
+/* Number of KV splits hs_decode_attn uses at most when n_splits == 0 (rows that one workgroup
+ * serves best are not split). [host, pure] */
 HS_API int hs_decode_auto_splits(const hs_shape* shape);
 
 /* Compress (Sec. III-A + III-B; fused top-2-of-4 compressor of Sec. IV-B).

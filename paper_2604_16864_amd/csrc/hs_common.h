@@ -158,7 +158,8 @@ hipError_t hs_launch_unpack(int B, int Hkv, int T, hs_kv_dev kv, uint16_t* K_out
 // tail_len < 0: no tail slot; tail_len >= 0: one extra partial per query head, computed from the
 // dense tail tokens (tail_k / tail_v, bf16 [B, Hkv, 64, D]); tail_lens (device, [B]) replaces
 // tail_len per batch row when not NULL
-hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_splits, const uint16_t* Q,
+// auto_splits: n_splits is the library's own choice (a row short enough is then done by one workgroup, without ws)
+hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_splits, int auto_splits, const uint16_t* Q,
                             hs_kv_dev kv, const uint16_t* tail_k, const uint16_t* tail_v, int tail_len, const int32_t* tail_lens,
                             uint16_t* O, float* LSE, float* ws, hipStream_t st, int phases, int dtype);
 // address (on the current device) and size of the library's static device array that hs_decode_attn_static

@@ -23,7 +23,7 @@
 #define HS_DEC_EARLY 1  /* uniform caches: the first round of a wave guesses its tiles' form and loads them at once */
 #endif
 #ifndef HS_DEC_OCC
-#define HS_DEC_OCC ((KM == 0 && VM == 0) || KM == 2 || VM == 2 ? 2 : 1)  /* a dense tensor at depth 2 needs > 256 registers */
+#define HS_DEC_OCC (NW == 8 || (KM == 0 && VM == 0) || KM == 2 || VM == 2 ? 2 : 1)  /* a dense tensor at depth 2 needs > 256 registers */
 #endif
 
 namespace {
@@ -39,6 +39,15 @@ __device__ __forceinline__ uint4 ld_stream(const uint4* p) {
 }
 
 
+
+// four consecutive 16-bit outputs; O is the caller's and need not be aligned to more than its elements
+__device__ __forceinline__ void store4(uint16_t* p, uint32_t lo, uint32_t hi, bool aligned8) {
+  if (aligned8) {
+    *reinterpret_cast<uint2*>(p) = make_uint2(lo, hi);
+  } else {
+    p[0] = (uint16_t)lo; p[1] = (uint16_t)(lo >> 16); p[2] = (uint16_t)hi; p[3] = (uint16_t)(hi >> 16);
+  }
+}
 
 // Operand registers of one tile (K and V), filled by tile_load and consumed by tile_compute.
 // KM / VM: kind of the K / V tile, 0 = 2:4, 1 = dense (the kernel sorts its tiles by kind first).
@@ -327,8 +336,10 @@ enum { kByRange = 0, kUniform = 1, kByCount = 2 };
 constexpr int kListCap = 2048;  // tiles listed in LDS at a time (kByCount); longer shares take several passes
 constexpr int kScanBatch = 2048;  // tiles of the row looked at per scan step: 8 per thread
 
-template <int KM, int VM, int MODE, bool F16>
-__global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, int Hq, int Hkv, int T, float scale_log2,
+// NW: waves per workgroup.  4: the partial of a split goes to ws_o / ws_l.  8: the workgroup has the whole row (one
+// split, no tail) and writes O and LSE itself (handed in as ws_o, ws_l): no merge launch.
+template <int KM, int VM, int MODE, bool F16, int NW>
+__global__ __launch_bounds__(64 * NW, HS_DEC_OCC) void decode_split_kernel(int B, int Hq, int Hkv, int T, float scale_log2,
                                                                              int n_splits, int per,
                                                                              const uint16_t* __restrict__ Q,
                                                                              hs_kv_dev kv, TailArgs tail,
@@ -338,16 +349,19 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, in
   const int tid = threadIdx.x, l = tid & 63, a = l >> 4, c = l & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, scalar: branches on it stay scalar
   const int G = Hq / Hkv;
-  __shared__ __attribute__((aligned(16))) float sm_o[4][8][HS_D];
+  constexpr bool DIRECT = NW == 8;
+  __shared__ __attribute__((aligned(16))) float sm_o[NW][8][HS_D];
   const int n_work = gridDim.x;  // partial slots of the cache's tiles; the tail's is the next one
-  if (b >= B) {  // the whole workgroup
-    const int64_t t_row = ((int64_t)(b - B) * Hkv + hkv) * n_work + split;
-    if (t_row >= (int64_t)B * Hkv) return;
-    const int tb = (int)(t_row / Hkv);
-    const int len = tail.lens != nullptr ? min(max(tail.lens[tb], 0), HS_BT) : tail.len;
-    tail_partial<F16>(tail, len, G, t_row, (int64_t)tb * Hq + (t_row - (int64_t)tb * Hkv) * G, scale_log2, Q, sm_o, n_splits, n_work,
-                      ws_o, ws_l);
-    return;
+  if constexpr (!DIRECT) {
+    if (b >= B) {  // the whole workgroup
+      const int64_t t_row = ((int64_t)(b - B) * Hkv + hkv) * n_work + split;
+      if (t_row >= (int64_t)B * Hkv) return;
+      const int tb = (int)(t_row / Hkv);
+      const int len = tail.lens != nullptr ? min(max(tail.lens[tb], 0), HS_BT) : tail.len;
+      tail_partial<F16>(tail, len, G, t_row, (int64_t)tb * Hq + (t_row - (int64_t)tb * Hkv) * G, scale_log2, Q, sm_o, n_splits, n_work,
+                        ws_o, ws_l);
+      return;
+    }
   }
   const int64_t row = (int64_t)b * Hkv + hkv;
   const int t_begin = split * per, t_end = min(T, t_begin + per);
@@ -377,7 +391,7 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, in
   constexpr bool kMixed = KM == 2 || VM == 2;
   constexpr int kFirstForm = (KM == 1 ? 1 : 0) | (VM == 1 ? 2 : 0);  // swept first: it also notes which other forms occur
   // One sweep.  The tiles come as a sequence of map entry pairs numbered [first, last): `entry(i, mk, mv)` yields
-  // pair i; wave w takes every 4th pair starting at first + w.  Returns (COLLECT) the set of forms among them.
+  // pair i; wave w takes every NW-th pair starting at first + w.  Returns (COLLECT) the set of forms among them.
   // SPEC (uniform caches, first sweep): where the wave's first tiles sit is known without the maps (slot ==
   // tile), only their form is not (the encoding bit of the V map of a bf16 cache), so the first round is a
   // straight-line copy of its own that issues their loads at once, behind the map read instead of after it
@@ -395,7 +409,7 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, in
     // 1 wave per SIMD) all land within run-to-run noise, and even a variant with the arithmetic removed is only
     // ~10 % faster: the kernel is bound by the load stream.  A kernel for mixed tensors runs at 2 waves per
     // SIMD, where only two 2:4 tiles (or one tile with a dense operand) fit.
-    constexpr int DEPTH = kMixed ? ((KK == 0 && VK == 0) ? 2 : 1) : HS_DEC_DEPTH;
+    constexpr int DEPTH = kMixed || NW == 8 ? ((KK == 0 && VK == 0) ? 2 : 1) : HS_DEC_DEPTH;
     TileRegs<KK, VK> ring[DEPTH];
     unsigned seen = 0;
 // what the two copies of a round below share: the form ballots, and the loop that consumes the tiles in
@@ -427,14 +441,14 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, in
     int base = first + w;
     if constexpr (SPEC) {
       if (base < last) {  // first round, tiles guessed
-        const int i_mine = base + 4 * l;
+        const int i_mine = base + NW * l;
         int mk_v = 0, mv_v = 0;
         if (i_mine < last) entry(i_mine, mk_v, mv_v);
         bool have[DEPTH];
         unsigned long long guessed = 0ull;
 #pragma unroll
         for (int d = 0; d < DEPTH; d++) {
-          const int t = base + 4 * d;
+          const int t = base + NW * d;
           have[d] = t < last;
           if (have[d]) {
             guessed |= 1ull << d;
@@ -446,11 +460,11 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, in
           if ((act & ((1ull << DEPTH) - 1ull)) != guessed) return kGuessFailed;
         act &= ~guessed;
         HS_ROUND_CONSUME
-        base += 256;
+        base += 64 * NW;
       }
     }
-    for (; base < last; base += 256) {  // up to 64 tiles of this wave per round
-      const int i_mine = base + 4 * l;
+    for (; base < last; base += 64 * NW) {  // up to 64 tiles of this wave per round
+      const int i_mine = base + NW * l;
       int mk_v = 0, mv_v = 0;
       if (i_mine < last) entry(i_mine, mk_v, mv_v);
       // Tile kinds must reach the branches below as scalar (wave-uniform) values: matrix
@@ -578,7 +592,7 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, in
       o[i][j] += __int_as_float(other);
     }
 
-  __shared__ float sm_m[4][8], sm_l[4][8];
+  __shared__ float sm_m[NW][8], sm_l[NW][8];
   if (c < 8) {
     if (a == 0) { sm_m[w][c] = m_run; sm_l[w][c] = l_run; }
 #pragma unroll
@@ -590,11 +604,13 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, in
   const int g = tid >> 5, ch = (tid & 31) * 4;
   const int64_t hq = (int64_t)b * Hq + hkv * G + (g < G ? g : 0);
   if (g < G) {
-    float mstar = fmaxf(fmaxf(sm_m[0][g], sm_m[1][g]), fmaxf(sm_m[2][g], sm_m[3][g]));
+    float mstar = -INFINITY;
+#pragma unroll
+    for (int ww = 0; ww < NW; ww++) mstar = fmaxf(mstar, sm_m[ww][g]);
     float lsum = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
     if (mstar > -INFINITY) {
 #pragma unroll
-      for (int ww = 0; ww < 4; ww++) {
+      for (int ww = 0; ww < NW; ww++) {
         const float f = __builtin_amdgcn_exp2f(sm_m[ww][g] - mstar);
         lsum += f * sm_l[ww][g];
 #pragma unroll
@@ -602,10 +618,17 @@ __global__ __launch_bounds__(256, HS_DEC_OCC) void decode_split_kernel(int B, in
       }
     }
     const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-    float* po = ws_o + (hq * n_splits + split) * HS_D + ch;
-    *reinterpret_cast<float4*>(po) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
-    if ((tid & 31) == 0)
-      ws_l[hq * n_splits + split] = lsum > 0.f ? (mstar + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
+    const float lse = lsum > 0.f ? (mstar + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
+    if constexpr (DIRECT) {
+      typedef hs_elem<F16> E;
+      uint16_t* po = reinterpret_cast<uint16_t*>(ws_o) + hq * HS_D + ch;
+      store4(po, E::pack2(acc[0] * inv, acc[1] * inv), E::pack2(acc[2] * inv, acc[3] * inv), ((uintptr_t)ws_o & 7) == 0);
+      if (ws_l != nullptr && (tid & 31) == 0) ws_l[hq] = lse;
+    } else {
+      float* po = ws_o + (hq * n_splits + split) * HS_D + ch;
+      *reinterpret_cast<float4*>(po) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+      if ((tid & 31) == 0) ws_l[hq * n_splits + split] = lse;
+    }
   }
 }
 
@@ -682,7 +705,7 @@ __global__ __launch_bounds__(32 * SL * R) void merge_kernel(int64_t rows, int n_
   if (!valid) return;
 #pragma unroll
   for (int i = 0; i < 4; i++) acc[i] = den > 0.f ? acc[i] / den : 0.f;
-  *reinterpret_cast<uint2*>(O + row * HS_D + ch) = make_uint2(hs_elem<F16>::pack2(acc[0], acc[1]), hs_elem<F16>::pack2(acc[2], acc[3]));
+  store4(O + row * HS_D + ch, hs_elem<F16>::pack2(acc[0], acc[1]), hs_elem<F16>::pack2(acc[2], acc[3]), ((uintptr_t)O & 7) == 0);
   if (LSE != nullptr && (tid & 31) == 0) LSE[row] = den > 0.f ? M + __logf(den) : -INFINITY;
 }
 
@@ -716,21 +739,32 @@ hipError_t hs_static_scratch(void** ptr, size_t* bytes) {
 }
 
 // Workspace: [partial O (normalised) [B*Hq][n_splits][128] fp32][partial LSE [B*Hq][n_splits] fp32].
-template <int KM, int VM, int MODE>
+template <int KM, int VM, int MODE, int NW>
 static hipError_t launch_split(dim3 grid, hipStream_t st, int B, int Hq, int Hkv, int T, float sl2, int n_splits, int per,
                                const uint16_t* Q, const hs_kv_dev& kv, const TailArgs& tail, float* wo, float* wl, bool f16) {
   if (f16)
-    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, true>), grid, dim3(256), 0, st, B, Hq, Hkv, T, sl2, n_splits,
+    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, true, NW>), grid, dim3(64 * NW), 0, st, B, Hq, Hkv, T, sl2, n_splits,
                        per, Q, kv, tail, wo, wl);
   else
-    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, false>), grid, dim3(256), 0, st, B, Hq, Hkv, T, sl2, n_splits,
+    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, false, NW>), grid, dim3(64 * NW), 0, st, B, Hq, Hkv, T, sl2, n_splits,
                        per, Q, kv, tail, wo, wl);
   return hipGetLastError();
 }
 
-hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_work, const uint16_t* Q, hs_kv_dev kv,
+hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_work, int auto_splits, const uint16_t* Q, hs_kv_dev kv,
                             const uint16_t* tail_k, const uint16_t* tail_v, int tail_len, const int32_t* tail_lens,
                             uint16_t* O, float* LSE, float* ws, hipStream_t st, int phases, int dtype) {
+  const int km = kv.cap_dense_k == 0 ? 0 : (kv.cap_sparse_k == 0 ? 1 : 2);
+  const int vm = kv.cap_dense_v == 0 ? 0 : (kv.cap_sparse_v == 0 ? 1 : 2);
+  // One workgroup of 8 waves per row and no merge launch, where that is faster than split + merge: very short rows (one
+  // compute unit reads about 42 GB/s; us, split + merge / direct, 2:4: 1 row of 4 / 8 / 16 tiles 6.1 / 4.1, 6.0 / 5.4, 6.2 /
+  // 8.2; dense, 4 / 8 tiles 6.3 / 5.4, 6.8 / 7.6), and rows numerous enough to fill the chip (256 rows of 8 / 32 / 96 tiles
+  // 11.7 / 8.8, 27.5 / 25.4, 69.9 / 67.7; 128 rows of 16 / 32 tiles 11.6 / 10.2, 17.4 / 17.4).  Longer rows are split or
+  // handed out by count.
+  const int short_row = km == 0 && vm == 0 ? 8 : 4;
+  const bool direct = auto_splits && tail_len < 0 && phases == 3 &&
+                      (T <= short_row || (n_work == 1 && T < HS_DEC_BYCOUNT_MIN_PER) || ((int64_t)B * Hkv >= 128 && T <= 16));
+  if (direct) n_work = 1;
   const TailArgs tail{tail_k, tail_v, tail_lens, tail_len};
   const dim3 grid(n_work, Hkv, B + (tail_len >= 0 ? (B + n_work - 1) / n_work : 0));
   const bool f16 = dtype == HS_FP16;
@@ -739,23 +773,23 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   // partial slots per query head: the n_work cache splits, then one for the dense tail if there is
   // one (the kernels take the slot count as their stride)
   const int n_splits = n_work + (tail_len >= 0 ? 1 : 0);
-  float* wo = ws;
-  float* wl = wo + (size_t)B * Hq * n_splits * HS_D;
-  const int km = kv.cap_dense_k == 0 ? 0 : (kv.cap_sparse_k == 0 ? 1 : 2);
-  const int vm = kv.cap_dense_v == 0 ? 0 : (kv.cap_sparse_v == 0 ? 1 : 2);
+  float* wo = direct ? reinterpret_cast<float*>(O) : ws;
+  float* wl = direct ? LSE : wo + (size_t)B * Hq * n_splits * HS_D;
   hipError_t e = hipSuccess;
   if (phases & 1) {
   // tiles by count on long splits only: the two passes over the maps at kernel start cost about 3 us, which
   // the even shares win back (3-7 % of the kernel when tiles are skipped) from 128 tiles per split for
   // all-2:4 tensors and from 256 for the other kernels (measured)
   const bool by_count = per >= (km == 0 && vm == 0 ? HS_DEC_BYCOUNT_MIN_PER : 2 * HS_DEC_BYCOUNT_MIN_PER);
+#define HS_SPLIT(KM_, VM_, MODE_, NW_) \
+  launch_split<KM_, VM_, MODE_, NW_>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16)
 #define HS_GO_DYN(KM_, VM_)                                                                                            \
-  e = by_count ? launch_split<KM_, VM_, kByCount>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16)       \
-               : launch_split<KM_, VM_, kByRange>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16);      \
+  e = direct ? HS_SPLIT(KM_, VM_, kByRange, 8)                                                                         \
+             : (by_count ? HS_SPLIT(KM_, VM_, kByCount, 4) : HS_SPLIT(KM_, VM_, kByRange, 4));                         \
   break
 #define HS_GO(KM_, VM_)                                                                                       \
   if (kv.uniform) {                                                                                           \
-    e = launch_split<KM_, VM_, kUniform>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16);       \
+    e = direct ? HS_SPLIT(KM_, VM_, kUniform, 8) : HS_SPLIT(KM_, VM_, kUniform, 4);                           \
     break;                                                                                                    \
   }                                                                                                           \
   HS_GO_DYN(KM_, VM_)
@@ -772,8 +806,9 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   }
 #undef HS_GO
 #undef HS_GO_DYN
+#undef HS_SPLIT
   }
-  if (e != hipSuccess || !(phases & 2)) return e;
+  if (e != hipSuccess || direct || !(phases & 2)) return e;
   return hs_launch_merge((int64_t)B * Hq, n_splits, wo, wl, O, LSE, st, dtype);
 }
 

@@ -779,6 +779,36 @@ def test_decode_tail_workgroups_of_every_row(B, Hkv, G, T, n_splits, dtype):
         assert_lse_close(LSE.cpu().numpy()[b], Lr[b], f"decode tail of {n} in row {b} lse")
 
 
+@pytest.mark.parametrize("B,Hkv,T", [(1, 1, 1), (2, 1, 8), (1, 2, 9), (16, 8, 16), (64, 4, 5), (64, 4, 127)])
+@pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict()), ("bf16", dict(sparse_frac_k=0.0)), ("fp16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)),
+                                       ("bf16", dict(sparse_frac_k=0.5, sparse_frac_v=0.5)), ("fp16", dict(skip_frac=0.5)), ("bf16", "empty")])
+def test_decode_rows_served_by_one_workgroup(B, Hkv, T, dtype, pol):
+    """Short rows and rows numerous enough: O and LSE written without a merge, wherever O begins; against the
+    same call cut into three splits, which is checked against the oracle elsewhere."""
+    G = 3
+    sh = hb.make_shape(B, G * Hkv, Hkv, 64 * T, dtype=torch.float16 if dtype == "fp16" else torch.bfloat16)
+    dt = hb.torch_dtype(sh)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V = (torch.randn((B, Hkv, 64 * T, 128), device="cuda", generator=g).to(dt) for _ in range(2))
+    V[:, :, ::61, 3] = 1e-6                            # bf16: tiles of both encodings
+    V[:, :, :64] = V[:, :, :64].clamp(0.1, 1.0)
+    if pol == "empty":
+        s = np.zeros((B, Hkv, T), dtype=np.int8)
+        s[::2] = 2                                     # every other batch row holds nothing
+        pol = dict(state_k=s, state_v=s)
+    kv = hb.compress_kv(sh, hb.make_policy(**pol), K, V)
+    Q = torch.randn((B, G * Hkv, 128), device="cuda", generator=g).to(dt)
+    O3, L3 = hb.decode_attn(sh, Q, kv, n_splits=3)
+    out = torch.empty(Q.numel() + 1, device="cuda", dtype=dt)[1:].view_as(Q)      # 2-byte aligned
+    for o in (None, out):
+        O, LSE = hb.decode_attn(sh, Q, kv, out=o)
+        assert (torch.isneginf(LSE) == torch.isneginf(L3)).all()
+        seen = ~torch.isneginf(L3)
+        assert (LSE[seen] - L3[seen]).abs().max() < 1e-5 and (O[~seen] == 0).all()
+        # fp32 accumulation in another order, then one rounding to 16 bits
+        assert (O.float() - O3.float()).abs().max() <= (2 ** -8 if dt is torch.bfloat16 else 2 ** -11) * 1.01 * O3.float().abs().max()
+
+
 def test_append_tiles_during_decode():
     """A cache allocated for 9 tiles, compressed with 4, then grown tile by tile (mixed tile kinds, the last
     one from a strided buffer); after every append decode equals the oracle's, and at the end pools and maps
