@@ -751,6 +751,36 @@ static hipError_t launch_split(dim3 grid, hipStream_t st, int B, int Hq, int Hkv
   return hipGetLastError();
 }
 
+// Splits per row for n_splits == 0: at most `most` (what the workspace has room for).  Time relative to the best, against
+// the number of workgroups (1 per compute unit is 256), measured on caches of 0.3 to 2.4 GB: 100 1.30, 128 1.14, 160
+// 1.035, 192 to 224 1.00, 256 1.03 (all-2:4 caches 50.7 us at 256 and 48.7 us at 192, dense 86.7 and 83.8 us, 8 x 128K
+// tokens with half of the tiles skipped 185 and 178 us), and a second, partly filled round costs: 264 1.36 (24 rows of 512
+// tiles: 51.8 us with 11 splits, 38.3 us with 10), 320 1.21, 384 1.075, 512 1.05.  A split whose tiles do not divide among
+// its waves costs about a quarter of what it wastes.  Small caches (fewer than 8 tiles per wave) do not gain from fewer than
+// 256 workgroups unless all tiles are dense, and rows with skipped tiles that are split by range want as many as fit.
+static int pick_splits(int64_t rows, int T, int most, bool dense, bool skips, int bycount_per) {
+  static const struct { double wgs, g; } kCurve[] = {{100, 1.30}, {128, 1.14}, {160, 1.035}, {192, 1.0}, {224, 1.005}, {256, 1.03},
+                                                     {257, 1.36}, {320, 1.21}, {384, 1.075}, {512, 1.05}};
+  const bool prefer_fewer = dense || rows * T >= 8192;
+  int best = most;
+  double best_cost = 0.0;
+  for (int n = most; n >= 1 && rows * n >= 96; n--) {  // below 96 workgroups fewer is never better
+    const double w = (double)(rows * n);
+    if (w > 512) continue;
+    double g = 1.30;
+    for (int i = 0; i + 1 < 10; i++)
+      if (w >= kCurve[i].wgs && w <= kCurve[i + 1].wgs)
+        g = kCurve[i].g + (kCurve[i + 1].g - kCurve[i].g) * (w - kCurve[i].wgs) / (kCurve[i + 1].wgs - kCurve[i].wgs);
+    const int per = (T + n - 1) / n;
+    const bool by_count = per >= bycount_per;
+    if (w >= 192 && w <= 256 && (!prefer_fewer || (skips && !by_count))) g = 1.0 + (256 - w) * 1e-4;
+    const double waste = by_count ? 0.0 : (double)((per + 3) / 4) * 4 * n / T - 1.0;
+    const double cost = g * (1.0 + 0.25 * waste);
+    if (best_cost == 0.0 || cost < best_cost) { best = n; best_cost = cost; }
+  }
+  return best;
+}
+
 hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_work, int auto_splits, const uint16_t* Q, hs_kv_dev kv,
                             const uint16_t* tail_k, const uint16_t* tail_v, int tail_len, const int32_t* tail_lens,
                             uint16_t* O, float* LSE, float* ws, hipStream_t st, int phases, int dtype) {
@@ -761,6 +791,9 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   // 8.2; dense, 4 / 8 tiles 6.3 / 5.4, 6.8 / 7.6), and rows numerous enough to fill the chip (256 rows of 8 / 32 / 96 tiles
   // 11.7 / 8.8, 27.5 / 25.4, 69.9 / 67.7; 128 rows of 16 / 32 tiles 11.6 / 10.2, 17.4 / 17.4).  Longer rows are split or
   // handed out by count.
+  const int bycount_per = km == 0 && vm == 0 ? HS_DEC_BYCOUNT_MIN_PER : 2 * HS_DEC_BYCOUNT_MIN_PER;
+  if (auto_splits)
+    n_work = pick_splits((int64_t)B * Hkv, T, n_work, km == 1 && vm == 1, (int64_t)kv.cap_dense_k + kv.cap_sparse_k < T, bycount_per);
   const int short_row = km == 0 && vm == 0 ? 8 : 4;
   const bool direct = auto_splits && tail_len < 0 && phases == 3 &&
                       (T <= short_row || (n_work == 1 && T < HS_DEC_BYCOUNT_MIN_PER) || ((int64_t)B * Hkv >= 128 && T <= 16));
@@ -780,7 +813,7 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   // tiles by count on long splits only: the two passes over the maps at kernel start cost about 3 us, which
   // the even shares win back (3-7 % of the kernel when tiles are skipped) from 128 tiles per split for
   // all-2:4 tensors and from 256 for the other kernels (measured)
-  const bool by_count = per >= (km == 0 && vm == 0 ? HS_DEC_BYCOUNT_MIN_PER : 2 * HS_DEC_BYCOUNT_MIN_PER);
+  const bool by_count = per >= bycount_per;
 #define HS_SPLIT(KM_, VM_, MODE_, NW_) \
   launch_split<KM_, VM_, MODE_, NW_>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16)
 #define HS_GO_DYN(KM_, VM_)                                                                                            \

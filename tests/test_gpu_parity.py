@@ -809,6 +809,28 @@ def test_decode_rows_served_by_one_workgroup(B, Hkv, T, dtype, pol):
         assert (O.float() - O3.float()).abs().max() <= (2 ** -8 if dt is torch.bfloat16 else 2 ** -11) * 1.01 * O3.float().abs().max()
 
 
+@pytest.mark.parametrize("B,Hkv,T", [(3, 8, 72), (5, 8, 70), (33, 4, 40), (8, 8, 256), (1, 3, 301)])
+@pytest.mark.parametrize("pol", [dict(), dict(sparse_frac_k=0.0, sparse_frac_v=0.0), dict(skip_frac=0.5, sparse_frac_k=0.5)])
+def test_decode_number_of_splits_is_the_librarys_choice(B, Hkv, T, pol):
+    """Row counts that do not divide the compute units: the choice fits the workspace of hs_decode_auto_splits, its
+    two phases agree on it, and the result is that of an explicit count."""
+    sh = hb.make_shape(B, 2 * Hkv, Hkv, 64 * T)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V = (torch.randn((B, Hkv, 64 * T, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
+    kv = hb.compress_kv(sh, hb.make_policy(**pol), K, V)
+    Q = torch.randn((B, 2 * Hkv, 128), device="cuda", generator=g).bfloat16()
+    O2, L2 = hb.decode_attn(sh, Q, kv, n_splits=2)
+    n = hb.workspace_bytes(sh, 2, 0)
+    for phases in ((3,), (1, 2)):
+        ws = torch.full((n + 4096,), 255, dtype=torch.uint8, device="cuda")
+        O, LSE = torch.empty_like(Q), torch.empty(Q.shape[:2], device="cuda")
+        for ph in phases:
+            hb.decode_attn(sh, Q, kv, out=O, lse=LSE, workspace=ws, phases=ph)
+        assert (ws[n:] == 255).all()
+        assert (LSE - L2).abs().max() < 1e-5
+        assert (O.float() - O2.float()).abs().max() <= 2 ** -8 * 1.01 * O2.float().abs().max()
+
+
 def test_append_tiles_during_decode():
     """A cache allocated for 9 tiles, compressed with 4, then grown tile by tile (mixed tile kinds, the last
     one from a strided buffer); after every append decode equals the oracle's, and at the end pools and maps
