@@ -7,7 +7,7 @@
 // state and O^T (128 x 16 NB fp32) in registers for the whole kernel.  The 4 waves of a
 // workgroup take 4 consecutive slabs in (position-tile, head-in-group) order, so for a GQA
 // group of 4 they are the 4 query heads of one position tile and share every KV tile, which is
-// copied once per workgroup into an LDS ring by direct global->LDS loads issued up to 3 tiles
+// copied once per workgroup into an LDS ring by direct global->LDS loads issued up to 2 tiles
 // ahead.  Pools are stored in operand order, so LDS reads are conflict-free 16-byte-per-lane
 // reads and GEMM1's accumulators become GEMM2's B operand in place (no re-layout step).
 #include <type_traits>
@@ -59,12 +59,14 @@ __device__ __forceinline__ void split_hi_lo(float p0, float p1, const SplitConst
 
 // LDS staging ring.  One stage holds one tile: a K region then a V region, each 9 KiB (8 KiB of
 // values + 1 KiB of metadata) when every tile of that tensor is 2:4 and 16 KiB otherwise.  Two
-// workgroups share a compute unit's 160 KiB, so a ring may take 80 KiB: 4 stages when both tensors
-// are 2:4 (tiles are requested 3 iterations before use), 3 when one is, 2 otherwise.
+// workgroups share a compute unit's 160 KiB, so a ring may take 80 KiB: 3 stages when at least one
+// tensor is all 2:4 (tiles are requested 2 iterations before use), 2 otherwise.  4 would fit when both are: 1394 us
+// against 1378 us with 3 for a 16K prompt, 42.9 against 41.8 us for 2K (one tile less to wait for before the
+// first is worked on, less state per tile; two iterations cover the latency).
 template <int KM> constexpr int region_bytes() { return KM == 0 ? 9216 : 16384; }
 template <int KM, int VM> constexpr int stage_bytes() { return region_bytes<KM>() + region_bytes<VM>(); }
 #ifndef HS_MAX_STAGES
-#define HS_MAX_STAGES 4  // at most 2 tiles in flight behind the next one (see stage_wait)
+#define HS_MAX_STAGES 3  // at most 2 tiles in flight behind the next one (see stage_wait)
 #endif
 template <int KM, int VM> constexpr int n_stages() {
   constexpr int fit = 81920 / stage_bytes<KM, VM>();
