@@ -786,17 +786,22 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
                             uint16_t* O, float* LSE, float* ws, hipStream_t st, int phases, int dtype) {
   const int km = kv.cap_dense_k == 0 ? 0 : (kv.cap_sparse_k == 0 ? 1 : 2);
   const int vm = kv.cap_dense_v == 0 ? 0 : (kv.cap_sparse_v == 0 ? 1 : 2);
+  // Tiles by count on long splits only: the two passes over the maps at kernel start cost about 3 us, which the even
+  // shares win back (3-7 % of the kernel when tiles are skipped) from 128 tiles per split where the pools say
+  // that all-2:4 tensors have skipped tiles, and from 256 otherwise.  (Caches with room for every tile that are
+  // filled to different lengths, 2:4, 16 rows of up to 256 tiles: 72.6 us by count, 66.8 us by range; 64 rows of up to 128
+  // 138 / 133 us; 8 rows of up to 2048 261 / 266 us.)
+  const bool skips = (int64_t)kv.cap_dense_k + kv.cap_sparse_k < T;
+  const int bycount_per = km == 0 && vm == 0 && skips ? HS_DEC_BYCOUNT_MIN_PER : 2 * HS_DEC_BYCOUNT_MIN_PER;
+  if (auto_splits) n_work = pick_splits((int64_t)B * Hkv, T, n_work, km == 1 && vm == 1, skips, bycount_per);
   // One workgroup of 8 waves per row and no merge launch, where that is faster than split + merge: very short rows (one
   // compute unit reads about 42 GB/s; us, split + merge / direct, 2:4: 1 row of 4 / 8 / 16 tiles 6.1 / 4.1, 6.0 / 5.4, 6.2 /
   // 8.2; dense, 4 / 8 tiles 6.3 / 5.4, 6.8 / 7.6), and rows numerous enough to fill the chip (256 rows of 8 / 32 / 96 tiles
-  // 11.7 / 8.8, 27.5 / 25.4, 69.9 / 67.7; 128 rows of 16 / 32 tiles 11.6 / 10.2, 17.4 / 17.4).  Longer rows are split or
-  // handed out by count.
-  const int bycount_per = km == 0 && vm == 0 ? HS_DEC_BYCOUNT_MIN_PER : 2 * HS_DEC_BYCOUNT_MIN_PER;
-  if (auto_splits)
-    n_work = pick_splits((int64_t)B * Hkv, T, n_work, km == 1 && vm == 1, (int64_t)kv.cap_dense_k + kv.cap_sparse_k < T, bycount_per);
+  // 11.7 / 8.8, 27.5 / 25.4, 69.9 / 67.7; 200 rows of 192 tiles, half of them skipped, 60.2 by count / 58.6; 128 rows of
+  // 16 / 32 tiles 11.6 / 10.2, 17.4 / 17.4).  Longer rows are split or handed out by count.
   const int short_row = km == 0 && vm == 0 ? 8 : 4;
   const bool direct = auto_splits && tail_len < 0 && phases == 3 &&
-                      (T <= short_row || (n_work == 1 && T < HS_DEC_BYCOUNT_MIN_PER) || ((int64_t)B * Hkv >= 128 && T <= 16));
+                      (T <= short_row || (n_work == 1 && T < 2 * HS_DEC_BYCOUNT_MIN_PER) || ((int64_t)B * Hkv >= 128 && T <= 16));
   if (direct) n_work = 1;
   const TailArgs tail{tail_k, tail_v, tail_lens, tail_len};
   const dim3 grid(n_work, Hkv, B + (tail_len >= 0 ? (B + n_work - 1) / n_work : 0));
@@ -810,9 +815,6 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   float* wl = direct ? LSE : wo + (size_t)B * Hq * n_splits * HS_D;
   hipError_t e = hipSuccess;
   if (phases & 1) {
-  // tiles by count on long splits only: the two passes over the maps at kernel start cost about 3 us, which
-  // the even shares win back (3-7 % of the kernel when tiles are skipped) from 128 tiles per split for
-  // all-2:4 tensors and from 256 for the other kernels (measured)
   const bool by_count = per >= bycount_per;
 #define HS_SPLIT(KM_, VM_, MODE_, NW_) \
   launch_split<KM_, VM_, MODE_, NW_>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16)

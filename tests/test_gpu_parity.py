@@ -779,7 +779,7 @@ def test_decode_tail_workgroups_of_every_row(B, Hkv, G, T, n_splits, dtype):
         assert_lse_close(LSE.cpu().numpy()[b], Lr[b], f"decode tail of {n} in row {b} lse")
 
 
-@pytest.mark.parametrize("B,Hkv,T", [(1, 1, 1), (2, 1, 8), (1, 2, 9), (16, 8, 16), (64, 4, 5), (64, 4, 127)])
+@pytest.mark.parametrize("B,Hkv,T", [(1, 1, 1), (2, 1, 8), (1, 2, 9), (16, 8, 16), (64, 4, 5), (64, 4, 127), (50, 4, 160)])
 @pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict()), ("bf16", dict(sparse_frac_k=0.0)), ("fp16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)),
                                        ("bf16", dict(sparse_frac_k=0.5, sparse_frac_v=0.5)), ("fp16", dict(skip_frac=0.5)), ("bf16", "empty")])
 def test_decode_rows_served_by_one_workgroup(B, Hkv, T, dtype, pol):
