@@ -697,7 +697,8 @@ static hipError_t launch_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_st
 
 // Ranges to cut a workgroup's tiles into, from what was measured on 2:4 tensors (32/8 heads): a tile takes a workgroup
 // 1.0 us alone on its compute unit and 1.2 us beside a second one, so 512 workgroups at a time are two on every unit;
-// splitting costs 5 us for the merge launch and 0.028 us per workgroup for writing and reading its 66 KB of partials.
+// splitting costs 8 us for the merge launch and the caller's scratch (5 us on the GPU alone) and 0.028 us per workgroup
+// for writing and reading its 66 KB of partials.
 // The number of ranges that makes this sum smallest is taken.  Measured, one range / the chosen number: 64 queries on
 // 32768 tokens 501 / 41.5 us (32 ranges), on 2048 tokens 37 / 18.8 us (8); 256 queries on 32768 tokens 504 / 101 us (8);
 // 1024 queries on 32768 tokens 510 / 347 us (2); whole prompts of 256 to 2048 tokens are fastest unsplit (2048: 46 us, two
@@ -715,7 +716,7 @@ int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, i
   for (int n = 1; n <= 128 && (n == 1 || (2 * n <= n_tiles && n_wg * n <= 4096)); n++) {
     const int64_t wgs = n_wg * n, full = wgs / 512, rest = wgs % 512;
     const int per = (n_tiles + n - 1) / n;
-    const double us = per * (1.2 * full + (rest == 0 ? 0.0 : (rest <= 256 ? 1.0 : 1.2))) + (n > 1 ? 5.0 + 0.028 * wgs : 0.0);
+    const double us = per * (1.2 * full + (rest == 0 ? 0.0 : (rest <= 256 ? 1.0 : 1.2))) + (n > 1 ? 8.0 + 0.028 * wgs : 0.0);
     if (n == 1 || us < best_us) { best = n; best_us = us; }
   }
   return best;
