@@ -300,7 +300,7 @@ HS_API int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t
 
 /* Decode attention (split-KV kernel + merge, Sec. IV-C): one query token per
  * (b, query head) against all L cached tokens.  Q, O: bf16 [B, Hq, D];
- * LSE: fp32 [B, Hq] or NULL.  n_splits == 0 picks hs_decode_auto_splits.
+ * LSE: fp32 [B, Hq] or NULL.  n_splits == 0: the library picks (at most hs_decode_auto_splits).
  * workspace: hs_workspace_bytes(op 2, n_splits), 16-byte aligned (split partials;
  * no initial content needed).  Two calls in flight at once must not share one. */
 HS_API int hs_decode_attn(const hs_shape* shape, float scale, int32_t n_splits,

@@ -339,13 +339,13 @@ constexpr int kScanBatch = 2048;  // tiles of the row looked at per scan step: 8
 // NW: waves per workgroup.  4: the partial of a split goes to ws_o / ws_l.  8: the workgroup has the whole row (one
 // split, no tail) and writes O and LSE itself (handed in as ws_o, ws_l): no merge launch.
 template <int KM, int VM, int MODE, bool F16, int NW>
-__global__ __launch_bounds__(64 * NW, HS_DEC_OCC) void decode_split_kernel(int B, int Hq, int Hkv, int T, float scale_log2,
+__global__ __launch_bounds__(64 * NW, HS_DEC_OCC) void decode_split_kernel(int B, int z0, int Hq, int Hkv, int T, float scale_log2,
                                                                              int n_splits, int per,
                                                                              const uint16_t* __restrict__ Q,
                                                                              hs_kv_dev kv, TailArgs tail,
                                                                              float* __restrict__ ws_o,
                                                                              float* __restrict__ ws_l) {
-  const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
+  const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z + z0;
   const int tid = threadIdx.x, l = tid & 63, a = l >> 4, c = l & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, scalar: branches on it stay scalar
   const int G = Hq / Hkv;
@@ -742,12 +742,17 @@ hipError_t hs_static_scratch(void** ptr, size_t* bytes) {
 template <int KM, int VM, int MODE, int NW>
 static hipError_t launch_split(dim3 grid, hipStream_t st, int B, int Hq, int Hkv, int T, float sl2, int n_splits, int per,
                                const uint16_t* Q, const hs_kv_dev& kv, const TailArgs& tail, float* wo, float* wl, bool f16) {
-  if (f16)
-    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, true, NW>), grid, dim3(64 * NW), 0, st, B, Hq, Hkv, T, sl2, n_splits,
-                       per, Q, kv, tail, wo, wl);
-  else
-    hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, false, NW>), grid, dim3(64 * NW), 0, st, B, Hq, Hkv, T, sl2, n_splits,
-                       per, Q, kv, tail, wo, wl);
+  // planes B .. grid.z - 1 are the tail's; a grid has at most 65535, so batches of more than half of that take a second launch
+  const unsigned all = grid.z;
+  for (unsigned z0 = 0; z0 < all; z0 += grid.z) {
+    grid.z = all - z0 > 65535u ? (unsigned)B : all - z0;
+    if (f16)
+      hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, true, NW>), grid, dim3(64 * NW), 0, st, B, (int)z0, Hq, Hkv, T, sl2,
+                         n_splits, per, Q, kv, tail, wo, wl);
+    else
+      hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, false, NW>), grid, dim3(64 * NW), 0, st, B, (int)z0, Hq, Hkv, T, sl2,
+                         n_splits, per, Q, kv, tail, wo, wl);
+  }
   return hipGetLastError();
 }
 

@@ -831,6 +831,22 @@ def test_decode_number_of_splits_is_the_librarys_choice(B, Hkv, T, pol):
         assert (O.float() - O2.float()).abs().max() <= 2 ** -8 * 1.01 * O2.float().abs().max()
 
 
+def test_decode_tail_of_a_batch_beyond_one_grid():
+    """40000 rows of one tile: the tail's planes of the grid no longer fit behind the rows' own."""
+    B, L = 40000, 64
+    sh = hb.make_shape(B, 1, 1, L)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    K, V, tk, tv = (torch.randn((B, 1, L, 128), device="cuda", generator=g).bfloat16() for _ in range(4))
+    Q = torch.randn((B, 1, 128), device="cuda", generator=g).bfloat16()
+    kv = hb.compress_kv(sh, hb.make_policy(sparse_frac_k=0.0, sparse_frac_v=0.0), K, V)
+    O, LSE = hb.decode_attn(sh, Q, kv, tail_k=tk, tail_v=tv, tail_len=33)
+    pick = torch.tensor([0, 1, 25534, 25535, 32767, 39999], device="cuda")
+    k, v = torch.cat([K[pick, 0], tk[pick, 0, :33]], 1).double(), torch.cat([V[pick, 0], tv[pick, 0, :33]], 1).double()
+    s = (k * Q[pick].double()).sum(-1) * 128 ** -0.5
+    assert_lse_close(LSE[pick, 0].cpu().numpy(), torch.logsumexp(s, 1).cpu().numpy(), "tail of a large batch lse")
+    assert_close(_f32(O[pick, 0]), (torch.softmax(s, 1)[:, :, None] * v).sum(1).cpu().numpy(), "tail of a large batch")
+
+
 def test_append_tiles_during_decode():
     """A cache allocated for 9 tiles, compressed with 4, then grown tile by tile (mixed tile kinds, the last
     one from a strided buffer); after every append decode equals the oracle's, and at the end pools and maps
