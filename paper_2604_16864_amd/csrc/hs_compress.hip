@@ -836,69 +836,146 @@ __device__ __forceinline__ int sparser_state(int map_entry, int target) {
   return rn == 2 ? HS_SKIP : rn + 1;
 }
 
+// Target states of a re-compression: tgt_k / tgt_v (device int8 [rows, T]) when given -- a pair that is not valid
+// leaves the tile as it is --; else the sign of map_k / map_v (maps the selection kernel wrote for a ranked target:
+// > 0 dense, < 0 2:4, 0 skipped) when given; else DENSE for the n_first first and n_last last tiles of the row and
+// frac_k / frac_v in between.
+struct RestateTarget {
+  const int8_t* tgt_k;
+  const int8_t* tgt_v;
+  const int32_t* map_k;
+  const int32_t* map_v;
+  int frac_k, frac_v, n_first, n_last;
+};
+// new states of tile t of a row; returns false if its explicit target pair is not valid
+__device__ __forceinline__ bool restate_tile(const RestateTarget& tg, const hs_kv_dev& src, int64_t row, int T, int t, int& sk, int& sv) {
+  const int64_t i = row * T + t;
+  bool ok = true;
+  int tk, tv;
+  if (tg.tgt_k != nullptr) {
+    tk = tg.tgt_k[i];
+    tv = tg.tgt_v[i];
+    if (tk < 0 || tk > 2 || tv < 0 || tv > 2 || (tk == HS_SKIP) != (tv == HS_SKIP)) {
+      ok = false;
+      tk = tv = HS_DENSE;  // no further pruning of this tile
+    }
+  } else if (tg.map_k != nullptr) {
+    const int a = tg.map_k[i], c = tg.map_v[i];
+    tk = a > 0 ? HS_DENSE : (a < 0 ? HS_SPARSE24 : HS_SKIP);
+    tv = c > 0 ? HS_DENSE : (c < 0 ? HS_SPARSE24 : HS_SKIP);
+  } else {
+    const bool prot = t < tg.n_first || t >= T - tg.n_last;
+    tk = prot ? HS_DENSE : tg.frac_k;
+    tv = prot ? HS_DENSE : tg.frac_v;
+  }
+  sk = sparser_state(src.k_map[i], tk);
+  sv = sparser_state(src.v_map[i], tv);
+  if (sk == HS_SKIP || sv == HS_SKIP) sk = sv = HS_SKIP;  // a tile leaves K and V together
+  return ok;
+}
+// a V tile that keeps its kind keeps its encoding bit
+__device__ __forceinline__ int keep_encoding(int mv, int mv_old) {
+  if (mv != 0 && (mv > 0) == (mv_old > 0) && hs_map_f16(mv_old)) mv = mv > 0 ? (mv | HS_MAP_F16) : -(-mv | HS_MAP_F16);
+  return mv;
+}
+
 // Maps of the re-compressed cache: slots in ascending tile order with one counter per pool
 // (Sec. III-B); a tile that keeps its kind keeps its encoding bit.  A tile for which a pool of dst
 // has no slot left is left out of both tensors, takes no slot, and bit 0 of *overflow is raised
-// (assign_slots_row).  Target of tile t: tgt_k / tgt_v (device int8 [rows, T]) when given -- a
-// pair that is not valid leaves the tile as it is and raises bit 1 --; else the sign of
-// tgt_map_k / tgt_map_v (maps the selection kernel wrote for a ranked target: > 0 dense, < 0 2:4,
-// 0 skipped) when given; else DENSE for the n_first first and n_last last tiles of the row and
-// frac_state_k / frac_state_v in between.  One workgroup per row.
-__global__ __launch_bounds__(256) void restate_kernel(int T, hs_kv_dev src, const int8_t* __restrict__ tgt_k,
-                                                      const int8_t* __restrict__ tgt_v,
-                                                      const int32_t* __restrict__ tgt_map_k,
-                                                      const int32_t* __restrict__ tgt_map_v, int frac_state_k,
-                                                      int frac_state_v, int n_first, int n_last, hs_kv_dev dst,
-                                                      int32_t* overflow) {
+// (assign_slots_row); an explicit pair that is not valid raises bit 1.  One workgroup per row.
+__global__ __launch_bounds__(256) void restate_kernel(int T, hs_kv_dev src, RestateTarget tg, hs_kv_dev dst, int32_t* overflow) {
   __shared__ SlotShared sm;
   const int row = blockIdx.x, tid = threadIdx.x;
-  const int32_t* skm = src.k_map + (int64_t)row * T;
   const int32_t* svm = src.v_map + (int64_t)row * T;
   int32_t* km = const_cast<int32_t*>(dst.k_map) + (int64_t)row * T;
   int32_t* vm = const_cast<int32_t*>(dst.v_map) + (int64_t)row * T;
   bool invalid = false;
   assign_slots_row(
       T, tid, dst.cap_dense_k, dst.cap_sparse_k, dst.cap_dense_v, dst.cap_sparse_v, sm, overflow,
-      [&](int t, int& sk, int& sv) {
-        int tk, tv;
-        if (tgt_k != nullptr) {
-          tk = tgt_k[(int64_t)row * T + t];
-          tv = tgt_v[(int64_t)row * T + t];
-          if (tk < 0 || tk > 2 || tv < 0 || tv > 2 || (tk == HS_SKIP) != (tv == HS_SKIP)) {
-            invalid = true;
-            tk = tv = HS_DENSE;  // no further pruning of this tile
-          }
-        } else if (tgt_map_k != nullptr) {
-          const int a = tgt_map_k[(int64_t)row * T + t], c = tgt_map_v[(int64_t)row * T + t];
-          tk = a > 0 ? HS_DENSE : (a < 0 ? HS_SPARSE24 : HS_SKIP);
-          tv = c > 0 ? HS_DENSE : (c < 0 ? HS_SPARSE24 : HS_SKIP);
-        } else {
-          const bool prot = t < n_first || t >= T - n_last;
-          tk = prot ? HS_DENSE : frac_state_k;
-          tv = prot ? HS_DENSE : frac_state_v;
-        }
-        sk = sparser_state(skm[t], tk);
-        sv = sparser_state(svm[t], tv);
-        if (sk == HS_SKIP || sv == HS_SKIP) sk = sv = HS_SKIP;  // a tile leaves K and V together
-      },
+      [&](int t, int& sk, int& sv) { invalid |= !restate_tile(tg, src, row, T, t, sk, sv); },
       [&](int t, int mk, int mv) {
-        const int mv_old = svm[t];
-        if (mv != 0 && (mv > 0) == (mv_old > 0) && hs_map_f16(mv_old)) mv = mv > 0 ? (mv | HS_MAP_F16) : -(-mv | HS_MAP_F16);
         km[t] = mk;
-        vm[t] = mv;
+        vm[t] = keep_encoding(mv, svm[t]);
       });
   if (invalid && overflow != nullptr) atomicOr(overflow, 2);
 }
 
 // One workgroup per tile: tiles that keep their kind are copied slot to slot; a dense tile that
 // became 2:4 is read from its dense slot (pool order) and pruned with the writers above.
-__global__ __launch_bounds__(256) void repack_kernel(int Hkv, int T, hs_kv_dev src, hs_kv_dev dst, int rule, int v_f16) {
-  __shared__ uint16_t vl[HS_BT * kVStride];
+// COUNT: the maps of dst are not written yet: the workgroup counts the row's new states itself, takes its tile's slots as
+// restate_kernel would hand them out and writes the tile's entries, which saves that launch.
+constexpr int kCountTiles = 4096;  // longest row that a workgroup counts (a byte of LDS per tile)
+template <bool COUNT>
+__global__ __launch_bounds__(256) void repack_kernel(int Hkv, int T, hs_kv_dev src, RestateTarget tg, hs_kv_dev dst, int rule, int v_f16,
+                                                     int32_t* overflow) {
+  __shared__ __attribute__((aligned(16))) uint16_t vl[HS_BT * kVStride];
+  static_assert(sizeof(vl) >= kCountTiles, "a byte per tile");
   const int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, a = l >> 4, r = l & 15;
   const int64_t row = (int64_t)b * Hkv + h;
   const int mk_old = src.k_map[row * T + t], mv_old_raw = src.v_map[row * T + t];
-  const int mk = dst.k_map[row * T + t], mv_raw = dst.v_map[row * T + t];
+  int mk, mv_raw;
+  if constexpr (COUNT) {
+    __shared__ int part[8][4], entry[2];
+    uint8_t* const states = reinterpret_cast<uint8_t*>(vl);
+    int n[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // dense K, 2:4 K, dense V, 2:4 V: of the row; of the tiles before this one
+    for (int i = tid; i < T; i += 256) {
+      int sk, sv;
+      const bool ok = restate_tile(tg, src, row, T, i, sk, sv);
+      if (!ok && i == t && overflow != nullptr) atomicOr(overflow, 2);
+      states[i] = (uint8_t)(sk | sv << 2);
+      const int c[4] = {sk == HS_DENSE, sk == HS_SPARSE24, sv == HS_DENSE, sv == HS_SPARSE24};
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        n[j] += c[j];
+        n[4 + j] += i < t ? c[j] : 0;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+      const int s_ = wave_scan_sum(n[j]);
+      if (l == 63) part[j][w] = s_;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; j++) n[j] = part[j][0] + part[j][1] + part[j][2] + part[j][3];
+    const int sk = states[t] & 3, sv = states[t] >> 2;
+    if (n[0] <= dst.cap_dense_k && n[1] <= dst.cap_sparse_k && n[2] <= dst.cap_dense_v && n[3] <= dst.cap_sparse_v) {
+      mk = sk == HS_DENSE ? n[4] + 1 : (sk == HS_SPARSE24 ? -(n[5] + 1) : 0);
+      mv_raw = sv == HS_DENSE ? n[6] + 1 : (sv == HS_SPARSE24 ? -(n[7] + 1) : 0);
+    } else {  // some tile of the row finds a pool full: walked in order, as assign_slots_row does
+      if (tid == 0) {
+        int c[4] = {0, 0, 0, 0}, ek = 0, ev = 0;
+        for (int i = 0; i <= t; i++) {
+          const int a_ = states[i] & 3, b_ = states[i] >> 2;
+          ek = ev = 0;
+          if (a_ == HS_SKIP) continue;
+          const bool room_k = a_ == HS_DENSE ? c[0] < dst.cap_dense_k : c[1] < dst.cap_sparse_k;
+          const bool room_v = b_ == HS_DENSE ? c[2] < dst.cap_dense_v : c[3] < dst.cap_sparse_v;
+          if (room_k && room_v) {
+            ek = a_ == HS_DENSE ? ++c[0] : -(++c[1]);
+            ev = b_ == HS_DENSE ? ++c[2] : -(++c[3]);
+          } else if (i == t && overflow != nullptr) {
+            atomicOr(overflow, 1);
+          }
+        }
+        entry[0] = ek;
+        entry[1] = ev;
+      }
+      __syncthreads();
+      mk = entry[0];
+      mv_raw = entry[1];
+    }
+    mv_raw = keep_encoding(mv_raw, mv_old_raw);
+    if (tid == 0) {
+      const_cast<int32_t*>(dst.k_map)[row * T + t] = mk;
+      const_cast<int32_t*>(dst.v_map)[row * T + t] = mv_raw;
+    }
+    __syncthreads();  // vl holds the V tile from here on
+  } else {
+    mk = dst.k_map[row * T + t];
+    mv_raw = dst.v_map[row * T + t];
+  }
   if (mk == 0 || mv_raw == 0) return;  // dropped (both tensors together)
   const int mv_old = hs_map_plain(mv_old_raw), mv = hs_map_plain(mv_raw);
   // ---- K ----
@@ -1137,11 +1214,18 @@ hipError_t hs_launch_recompress(int B, int Hkv, int T, hs_kv_dev src, const int8
                                 const int32_t* tgt_map_k, const int32_t* tgt_map_v, int frac_state_k, int frac_state_v,
                                 int n_first, int n_last, hs_kv_dev dst, int rule, int v_f16, int32_t* overflow,
                                 hipStream_t st) {
-  hipLaunchKernelGGL(restate_kernel, dim3(B * Hkv), dim3(256), 0, st, T, src, tgt_k, tgt_v, tgt_map_k, tgt_map_v,
-                     frac_state_k, frac_state_v, n_first, n_last, dst, overflow);
+  const RestateTarget tg{tgt_k, tgt_v, tgt_map_k, tgt_map_v, frac_state_k, frac_state_v, n_first, n_last};
+  // One launch while the entries that all workgroups read to count are few.  us, two launches / one (keys dense -> 2:4; V
+  // dense -> 2:4, V 2:4 already): 8 rows of 64 tiles 11.5 / 8.7, 9.4 / 6.6; of 512 42.3 / 40.2, 31.7 / 29.3; 16 rows
+  // of 512 76.4 / 81.6, 60.0 / 59.4; 8 rows of 1024 77.9 / 88.1, 61.6 / 67.4.
+  if (T <= kCountTiles && (double)B * Hkv * T * T <= (double)(2 << 20)) {
+    hipLaunchKernelGGL(repack_kernel<true>, dim3(T, Hkv, B), dim3(256), 0, st, Hkv, T, src, tg, dst, rule, v_f16, overflow);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(restate_kernel, dim3(B * Hkv), dim3(256), 0, st, T, src, tg, dst, overflow);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(repack_kernel, dim3(T, Hkv, B), dim3(256), 0, st, Hkv, T, src, dst, rule, v_f16);
+  hipLaunchKernelGGL(repack_kernel<false>, dim3(T, Hkv, B), dim3(256), 0, st, Hkv, T, src, tg, dst, rule, v_f16, overflow);
   return hipGetLastError();
 }
 

@@ -1563,6 +1563,53 @@ def test_selection_of_given_scores(T, first, last):
             assert (np.sign(np.asarray(km)[0, h]) == want[0]).all() and (np.sign(np.asarray(vm)[0, h]) == want[1]).all(), (h, skip, fk, fv)
 
 
+@pytest.mark.parametrize("Hkv,T", [(2, 1), (2, 40), (3, 257), (8, 600)])                 # one launch; (8, 600): two
+@pytest.mark.parametrize("room", [1.0, 0.6])
+def test_recompress_maps_are_those_of_a_walk_in_tile_order(Hkv, T, room):
+    """Slots of the new cache, the encoding bit of tiles that keep their kind, tiles left out where a pool is full,
+    and both bits of the flag, for explicit targets with invalid pairs among them."""
+    rng = np.random.default_rng(T)
+    sk, sv = _mixed_states(1, Hkv, T, seed=T, p_skip=0.2)
+    sh = hb.make_shape(1, Hkv, Hkv, 64 * T)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V = (torch.randn((1, Hkv, 64 * T, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
+    kv = hb.compress_kv(sh, hb.make_policy(state_k=sk, state_v=sv), K, V)
+    tk, tv = rng.integers(0, 3, (1, Hkv, T)).astype(np.int8), rng.integers(0, 3, (1, Hkv, T)).astype(np.int8)
+    tgt = hb.make_policy(state_k=torch.from_numpy(tk).cuda(), state_v=torch.from_numpy(tv).cuda())
+    rank = {1: 0, 2: 1, 0: 2}
+    new = np.zeros((2, Hkv, T), dtype=np.int64)
+    invalid = False
+    for h in range(Hkv):
+        for t in range(T):
+            a, b = int(tk[0, h, t]), int(tv[0, h, t])
+            if (a == 0) != (b == 0):
+                invalid, a, b = True, 1, 1
+            n = [max((int(s), x), key=lambda v: rank[v]) for s, x in ((sk[0, h, t], a), (sv[0, h, t], b))]
+            new[:, h, t] = 0 if 0 in n else n
+    caps = [0] + [max(1, int(np.ceil(room * (new[x] == k).sum(-1).max()))) for x, k in ((0, 1), (0, 2), (1, 1), (1, 2))]
+    over = torch.zeros(1, dtype=torch.int32, device="cuda")
+    out = hb.recompress_kv(sh, kv, tgt, counts=caps, overflow=over)
+    km, vm, f16 = lib_maps(out.k_map, out.v_map)
+    old = lib_maps(kv.k_map, kv.v_map)
+    full = False
+    for h in range(Hkv):
+        c = {(x, k): 0 for x in (0, 1) for k in (1, 2)}
+        for t in range(T):
+            a, b = new[:, h, t]
+            want = (0, 0)
+            if a:
+                if c[0, a] < caps[a] and c[1, b] < caps[2 + b]:
+                    c[0, a] += 1
+                    c[1, b] += 1
+                    want = (c[0, a] * (1 if a == 1 else -1), c[1, b] * (1 if b == 1 else -1))
+                else:
+                    full = True
+            assert (km[0, h, t], vm[0, h, t]) == want, (h, t)
+            if want[1] and (want[1] > 0) == (old[1][0, h, t] > 0):
+                assert f16[0, h, t] == old[2][0, h, t]
+    assert int(over.item()) == int(full) + 2 * int(invalid)
+
+
 def test_recompress_capacity_overflow_and_argument_errors():
     B, Hq, Hkv, L = 1, 4, 1, 64 * 8
     T = L // 64
