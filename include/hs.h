@@ -267,7 +267,8 @@ HS_API int hs_unpack_kv(const hs_shape* shape, const hs_kv* kv, void* K_out, voi
  * Query i sees token j iff tile(j) is not skipped and (!causal or
  * j <= i + L - Lq).  scale == 0 selects 1/sqrt(D) (Eq. 1).
  * O: bf16 [B, Hq, Lq, D]; LSE: fp32 [B, Hq, Lq] or NULL.  A query that sees no
- * token gets O = 0, LSE = -inf.  A pool of more than 4 GiB per (batch, kv head) row
+ * token gets O = 0, LSE = -inf; one that sees a score that is NaN gets O = NaN,
+ * LSE = NaN, also where the tiles are cut into ranges.  A pool of more than 4 GiB per (batch, kv head) row
  * (capacity x tile bytes) is HS_EUNSUPPORTED. */
 HS_API int hs_prefill_attn(const hs_shape* shape, int32_t Lq, float scale, int causal,
                     const void* Q, const hs_kv* kv, void* O, float* LSE,
@@ -300,7 +301,8 @@ HS_API int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t
 
 /* Decode attention (split-KV kernel + merge, Sec. IV-C): one query token per
  * (b, query head) against all L cached tokens.  Q, O: bf16 [B, Hq, D];
- * LSE: fp32 [B, Hq] or NULL.  n_splits == 0: the library picks (at most hs_decode_auto_splits).
+ * LSE: fp32 [B, Hq] or NULL.  Nothing seen: O = 0, LSE = -inf; a score that is NaN: O = NaN,
+ * LSE = NaN, for every n_splits.  n_splits == 0: the library picks (at most hs_decode_auto_splits).
  * workspace: hs_workspace_bytes(op 2, n_splits), 16-byte aligned (split partials;
  * no initial content needed).  Two calls in flight at once must not share one. */
 HS_API int hs_decode_attn(const hs_shape* shape, float scale, int32_t n_splits,

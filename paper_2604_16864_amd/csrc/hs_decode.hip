@@ -131,6 +131,7 @@ __device__ __forceinline__ void tile_compute(const TileRegs<KM, VM>& r, const ui
     }
   }
   // online softmax for column c (log2 domain)
+  const float m_prev = m_run;
   float mx = -INFINITY;
 #pragma unroll
   for (int m = 0; m < 4; m++)
@@ -138,9 +139,9 @@ __device__ __forceinline__ void tile_compute(const TileRegs<KM, VM>& r, const ui
     for (int i = 0; i < 4; i++) mx = fmaxf(mx, s[m][i]);
   mx = fmaxf(mx, __shfl_xor(mx, 16));
   mx = fmaxf(mx, __shfl_xor(mx, 32));
-  const float m_new = fmaxf(m_run, mx * scale_log2 - kShift);
-  const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first tile
-  m_run = m_new;
+  m_run = fmaxf(m_prev, mx * scale_log2 - kShift);
+  const float m_ref = m_run > -INFINITY ? m_run : 0.f;  // every score -inf so far: weights 0, not exp2(-inf + inf)
+  const float alpha = __builtin_amdgcn_exp2f(m_prev - m_ref);  // 0 on the first tile
   float psum = 0.f;
   // P^T as the B operand: element 8h+4u+i of lane group a <- token 16(2h+u)+4a+i.
   // Columns < 8 carry bf16(p), columns >= 8 carry bf16(p - bf16(p)), so that the sum of
@@ -150,7 +151,7 @@ __device__ __forceinline__ void tile_compute(const TileRegs<KM, VM>& r, const ui
   for (int m = 0; m < 4; m++)
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-      p[m][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[m][i], scale_log2, -m_new));
+      p[m][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[m][i], scale_log2, -m_ref));
       psum += p[m][i];
     }
   uint32_t pb[8];
@@ -280,14 +281,14 @@ __device__ __forceinline__ void tail_partial(const TailArgs& tail, int tail_len,
     float mx = sc;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    const float p = t < tail_len ? __builtin_amdgcn_exp2f(sc - mx) : 0.f;
+    const float p = t < tail_len ? __builtin_amdgcn_exp2f(sc - (mx > -INFINITY ? mx : 0.f)) : 0.f;
     float l = p;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
     sp[g][t] = p;
     if (t == 0) {
       sl[g] = l;
-      ws_l[(hq0 + g) * n_splits + slot] = l > 0.f ? (mx + __builtin_amdgcn_logf(l)) * kLn2 : -INFINITY;
+      ws_l[(hq0 + g) * n_splits + slot] = l == 0.f ? -INFINITY : (mx + __builtin_amdgcn_logf(l)) * kLn2;
     }
   }
   __syncthreads();
@@ -309,7 +310,7 @@ __device__ __forceinline__ void tail_partial(const TailArgs& tail, int tail_len,
     for (int i = 0; i < 4; i++) acc[i] = (sm_o[0][g][ch + i] + sm_o[1][g][ch + i]) + (sm_o[2][g][ch + i] + sm_o[3][g][ch + i]);
     const float l = sl[g];
     float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (l > 0.f) out = make_float4(acc[0] / l, acc[1] / l, acc[2] / l, acc[3] / l);
+    if (l != 0.f) out = make_float4(acc[0] / l, acc[1] / l, acc[2] / l, acc[3] / l);
     *reinterpret_cast<float4*>(ws_o + ((hq0 + g) * n_splits + slot) * HS_D + ch) = out;
   }
 }
@@ -607,18 +608,19 @@ __global__ __launch_bounds__(64 * NW, HS_DEC_OCC) void decode_split_kernel(int B
     float mstar = -INFINITY;
 #pragma unroll
     for (int ww = 0; ww < NW; ww++) mstar = fmaxf(mstar, sm_m[ww][g]);
+    // a wave without a reference has seen nothing (l and O are 0) or only NaN scores (l is NaN): neither is left out,
+    // and only l == 0 is an empty split, so that a NaN reaches O and LSE however the tiles are divided
+    const float mref = mstar > -INFINITY ? mstar : 0.f;
     float lsum = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-    if (mstar > -INFINITY) {
 #pragma unroll
-      for (int ww = 0; ww < NW; ww++) {
-        const float f = __builtin_amdgcn_exp2f(sm_m[ww][g] - mstar);
-        lsum += f * sm_l[ww][g];
+    for (int ww = 0; ww < NW; ww++) {
+      const float f = __builtin_amdgcn_exp2f(sm_m[ww][g] - mref);
+      lsum += f * sm_l[ww][g];
 #pragma unroll
-        for (int i = 0; i < 4; i++) acc[i] += f * sm_o[ww][g][ch + i];
-      }
+      for (int i = 0; i < 4; i++) acc[i] += f * sm_o[ww][g][ch + i];
     }
-    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-    const float lse = lsum > 0.f ? (mstar + __builtin_amdgcn_logf(lsum)) * kLn2 : -INFINITY;
+    const float inv = lsum == 0.f ? 0.f : 1.f / lsum;
+    const float lse = lsum == 0.f ? -INFINITY : (mstar + __builtin_amdgcn_logf(lsum)) * kLn2;
     if constexpr (DIRECT) {
       typedef hs_elem<F16> E;
       uint16_t* po = reinterpret_cast<uint16_t*>(ws_o) + hq * HS_D + ch;
@@ -634,7 +636,8 @@ __global__ __launch_bounds__(64 * NW, HS_DEC_OCC) void decode_split_kernel(int B
 
 // Merge of the split partials (Sec. IV-C "lightweight post-processing kernel"):
 // O = sum_s e^{LSE_s - M} O_s / sum_s e^{LSE_s - M}, M = max_s LSE_s, done in one pass with a
-// running reference per thread.  A row (one query of one head) is merged by SL split lanes of 32
+// running reference per thread.  A partial of LSE -inf is empty (its O is 0) and weighs nothing; one of LSE NaN makes
+// the row NaN.  A row (one query of one head) is merged by SL split lanes of 32
 // threads (4 channels each), which are combined in LDS; a workgroup takes R rows.  A thread requests U partials before
 // it looks at the first (a test per partial in front of its use made them wait for each other: 4.0 -> 3.2 us at 32 rows
 // x 32 splits, 16 -> 4.2 us at 256 splits).
@@ -666,19 +669,18 @@ __global__ __launch_bounds__(32 * SL * R) void merge_kernel(int64_t rows, int n_
     float Mn = M;
 #pragma unroll
     for (int u = 0; u < U; u++) Mn = fmaxf(Mn, lse[u]);
-    if (Mn > -INFINITY) {
-      const float fo = __expf(M - Mn);  // 0 while M is still -inf
-      den *= fo;
+    const float ref = Mn > -INFINITY ? Mn : 0.f;
+    const float fo = __expf(M - ref);  // 0 while M is still -inf
+    den *= fo;
 #pragma unroll
-      for (int i = 0; i < 4; i++) acc[i] *= fo;
+    for (int i = 0; i < 4; i++) acc[i] *= fo;
 #pragma unroll
-      for (int u = 0; u < U; u++) {
-        const float fn = __expf(lse[u] - Mn);  // 0 for a split that saw nothing
-        den += fn;
-        acc[0] += fn * v[u].x; acc[1] += fn * v[u].y; acc[2] += fn * v[u].z; acc[3] += fn * v[u].w;
-      }
-      M = Mn;
+    for (int u = 0; u < U; u++) {
+      const float fn = __expf(lse[u] - ref);  // 0 for a split that saw nothing
+      den += fn;
+      acc[0] += fn * v[u].x; acc[1] += fn * v[u].y; acc[2] += fn * v[u].z; acc[3] += fn * v[u].w;
     }
+    M = Mn;
   }
   if (SL > 1) {
     if ((tid & 31) == 0) { sm_ml[r][sl][0] = M; sm_ml[r][sl][1] = den; }
@@ -691,22 +693,21 @@ __global__ __launch_bounds__(32 * SL * R) void merge_kernel(int64_t rows, int n_
     den = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; i++) acc[i] = 0.f;
-    if (Mt > -INFINITY) {
+    const float ref = Mt > -INFINITY ? Mt : 0.f;
 #pragma unroll
-      for (int k = 0; k < SL; k++) {
-        const float f = __expf(sm_ml[r][k][0] - Mt);  // 0 for a split lane that saw nothing
-        const float4 v = *reinterpret_cast<const float4*>(&sm_acc[r][k][ch]);
-        den += f * sm_ml[r][k][1];
-        acc[0] += f * v.x; acc[1] += f * v.y; acc[2] += f * v.z; acc[3] += f * v.w;
-      }
+    for (int k = 0; k < SL; k++) {
+      const float f = __expf(sm_ml[r][k][0] - ref);  // 0 for a split lane that saw nothing
+      const float4 v = *reinterpret_cast<const float4*>(&sm_acc[r][k][ch]);
+      den += f * sm_ml[r][k][1];
+      acc[0] += f * v.x; acc[1] += f * v.y; acc[2] += f * v.z; acc[3] += f * v.w;
     }
     M = Mt;
   }
   if (!valid) return;
 #pragma unroll
-  for (int i = 0; i < 4; i++) acc[i] = den > 0.f ? acc[i] / den : 0.f;
+  for (int i = 0; i < 4; i++) acc[i] = den == 0.f ? 0.f : acc[i] / den;
   store4(O + row * HS_D + ch, hs_elem<F16>::pack2(acc[0], acc[1]), hs_elem<F16>::pack2(acc[2], acc[3]), ((uintptr_t)O & 7) == 0);
-  if (LSE != nullptr && (tid & 31) == 0) LSE[row] = den > 0.f ? M + __logf(den) : -INFINITY;
+  if (LSE != nullptr && (tid & 31) == 0) LSE[row] = den == 0.f ? -INFINITY : M + __logf(den);
 }
 
 

@@ -650,7 +650,8 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
     float lt = l_run[nb];
     lt += __shfl_xor(lt, 16);
     lt += __shfl_xor(lt, 32);
-    const float inv = lt > 0.f ? 1.f / lt : 0.f;
+    const float inv = lt == 0.f ? 0.f : 1.f / lt;  // 0: no token seen; a NaN score makes l NaN, and O and LSE with it
+    const float lse = lt == 0.f ? -INFINITY : (m_run[nb] + __builtin_amdgcn_logf(lt)) * kLn2;
     const int64_t qrow = ((int64_t)b * Hq + hq) * Lq + qpos + 16 * nb + c;
     if constexpr (SPLIT) {
       float* op = ws_o + (qrow * n_splits + split) * HS_D + 4 * a;
@@ -658,8 +659,7 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
       for (int mb = 0; mb < 8; mb++)
         *reinterpret_cast<float4*>(op + 16 * mb) =
             make_float4(o[mb][nb][0] * inv, o[mb][nb][1] * inv, o[mb][nb][2] * inv, o[mb][nb][3] * inv);
-      if (a == 0)
-        ws_l[qrow * n_splits + split] = lt > 0.f ? (m_run[nb] + __builtin_amdgcn_logf(lt)) * kLn2 : -INFINITY;
+      if (a == 0) ws_l[qrow * n_splits + split] = lse;
       continue;
     }
     uint16_t* op = O + qrow * HS_D + 4 * a;
@@ -669,8 +669,7 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
                                  E::pack2(o[mb][nb][2] * inv, o[mb][nb][3] * inv));
       *reinterpret_cast<uint2*>(op + 16 * mb) = v;
     }
-    if (LSE != nullptr && a == 0)
-      LSE[qrow] = lt > 0.f ? (m_run[nb] + __builtin_amdgcn_logf(lt)) * kLn2 : -INFINITY;
+    if (LSE != nullptr && a == 0) LSE[qrow] = lse;
   }
 }
 

@@ -847,6 +847,83 @@ def test_decode_tail_of_a_batch_beyond_one_grid():
     assert_close(_f32(O[pick, 0]), (torch.softmax(s, 1)[:, :, None] * v).sum(1).cpu().numpy(), "tail of a large batch")
 
 
+def _nan_case(T, Lq, dtype, seed):
+    """Two kv heads of two query heads.  kv head 0 holds one NaN key; of kv head 1's queries every third of head 2 is NaN and
+    (bf16) head 3 meets a tile in which every score is -inf.  Q, K, V as torch tensors on the CPU and the NaN key's token."""
+    L, dt = 64 * T, torch.float16 if dtype == "fp16" else torch.bfloat16
+    g = torch.Generator().manual_seed(seed)
+    Q, K, V = (torch.randn((1, n, m, 128), generator=g).to(dt) for n, m in ((4, Lq), (2, L), (2, L)))
+    tok = L - Lq // 2 - 1
+    K[0, 0, tok, 9] = float("nan")
+    Q[0, 2, ::3, 17] = float("nan")
+    if dtype == "bf16":
+        K[0, 1, :, 0] = 0
+        K[0, 1, 64:128, 0] = -1e30
+        Q[0, 2, :, 0], Q[0, 3, :, 0] = 0, 1e30
+    return Q, K, V, tok
+
+
+def _nan_reference(Q, K, V, visible):
+    """fp64 attention of Q [4, n, 128] over K, V [2, L, 128]; visible [n, L]."""
+    S = torch.matmul(Q.double(), K.double().repeat_interleave(2, 0).transpose(1, 2)) * 128 ** -0.5
+    S = torch.where(S < -1e30, float("-inf"), S).masked_fill(~visible, float("-inf"))    # beyond what fp32 holds
+    lse = torch.logsumexp(S, -1)
+    return torch.matmul(torch.softmax(S, -1), V.double().repeat_interleave(2, 0)), lse
+
+
+def _check_nan_rows(O, LSE, Or, Lr, what):
+    nan = torch.isnan(Lr)
+    assert nan.any() and (~nan).any()
+    assert torch.isnan(LSE[nan]).all() and torch.isnan(O[nan].float()).all(), what
+    assert_close(_f32(O[~nan]), Or[~nan].numpy(), what)
+    assert_lse_close(LSE[~nan].numpy(), Lr[~nan].numpy(), what)
+
+
+@pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict(sparse_frac_k=0.0)), ("bf16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0))])
+def test_prefill_nan_scores_come_out_however_the_tiles_are_cut(dtype, pol):
+    """A query that sees a NaN score has O and LSE NaN, in one range and in several; the others see nothing of it."""
+    import ctypes as C
+    T, Lq = 70, 128
+    Q, K, V, tok = _nan_case(T, Lq, dtype, 970)
+    sh = hb.make_shape(1, 4, 2, 64 * T, dtype=Q.dtype)
+    kv = hb.compress_kv(sh, hb.make_policy(**pol), K.cuda(), V.cuda())
+    Ku, Vu = (t.cpu()[0] for t in hb.unpack_kv(sh, kv))
+    at = 64 * T - Lq
+    Or, Lr = _nan_reference(Q[0], Ku, Vu, torch.arange(64 * T) <= at + torch.arange(Lq)[:, None])
+    Qd, kvs, one = Q.cuda(), kv.struct(), 4 * Lq * 129 * 4
+    assert hb.prefill_workspace_bytes(sh, Lq, at, kv) >= 5 * one
+    ws = torch.empty(5 * one, dtype=torch.uint8, device="cuda")
+    for n in (1, 2, 5):
+        O, LSE = torch.zeros_like(Qd), torch.zeros(Qd.shape[:3], device="cuda")
+        hb._check(hb.lib().hs_prefill_attn_ws(C.byref(sh), Lq, at, 0.0, 1, hb._ptr(Qd), C.byref(kvs), hb._ptr(O), hb._ptr(LSE), hb._ptr(ws),
+                                              n * one, hb._stream()))
+        _check_nan_rows(O.cpu()[0], LSE.cpu()[0], Or, Lr, f"prefill with NaN scores in {n} ranges")
+
+
+@pytest.mark.parametrize("T", [6, 70])
+@pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict(sparse_frac_k=0.0)), ("bf16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0))])
+def test_decode_nan_scores_come_out_however_the_tiles_are_split(T, dtype, pol):
+    Q, K, V, tok = _nan_case(T, 2, dtype, 980)
+    q = Q[:, :, 0].contiguous()
+    sh = hb.make_shape(1, 4, 2, 64 * T, dtype=Q.dtype)
+    kv = hb.compress_kv(sh, hb.make_policy(**pol), K.cuda(), V.cuda())
+    Ku, Vu = (t.cpu()[0] for t in hb.unpack_kv(sh, kv))
+    Or, Lr = _nan_reference(q[0][:, None], Ku, Vu, torch.ones(1, 64 * T, dtype=torch.bool))
+    for n in (1, 2, 5, 0):
+        O, LSE = hb.decode_attn(sh, q.cuda(), kv, n_splits=n)
+        _check_nan_rows(O.cpu()[0][:, None], LSE.cpu()[0][:, None], Or, Lr, f"decode with NaN scores, {n} splits")
+    # the same tokens again as a dense tail that follows a cache without them
+    tk, tv = torch.zeros(1, 2, 64, 128, dtype=Q.dtype), torch.zeros(1, 2, 64, 128, dtype=Q.dtype)
+    tk[:, :, :20], tv[:, :, :20] = K[:, :, tok - 19:tok + 1], V[:, :, tok - 19:tok + 1]
+    clean = K.clone()
+    clean[0, 0, tok, 9] = 1.0
+    kv = hb.compress_kv(sh, hb.make_policy(**pol), clean.cuda(), V.cuda())
+    Ku, Vu = (t.cpu()[0] for t in hb.unpack_kv(sh, kv))
+    Or, Lr = _nan_reference(q[0][:, None], torch.cat([Ku, tk[0, :, :20]], 1), torch.cat([Vu, tv[0, :, :20]], 1), torch.ones(1, 64 * T + 20, dtype=torch.bool))
+    O, LSE = hb.decode_attn(sh, q.cuda(), kv, tail_k=tk.cuda(), tail_v=tv.cuda(), tail_len=20)
+    _check_nan_rows(O.cpu()[0][:, None], LSE.cpu()[0][:, None], Or, Lr, "decode with NaN scores in the tail")
+
+
 def test_append_tiles_during_decode():
     """A cache allocated for 9 tiles, compressed with 4, then grown tile by tile (mixed tile kinds, the last
     one from a strided buffer); after every append decode equals the oracle's, and at the end pools and maps
