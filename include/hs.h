@@ -295,7 +295,7 @@ HS_API int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start
                        void* workspace, size_t workspace_bytes, void* stream);
 
 /* Workspace bytes with which hs_prefill_attn_ws uses as many ranges as serve the call best; 0 where
- * one is best.  Of kv only the capacities are read.  [host, pure] */
+ * one is best.  Of kv only the capacities and `uniform` are read.  [host, pure] */
 HS_API int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv,
                                size_t* bytes);
 

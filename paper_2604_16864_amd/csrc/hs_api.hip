@@ -86,8 +86,7 @@ size_t prefill_split_bytes(const hs_shape* s, int32_t Lq) {
 }
 
 int prefill_splits(const hs_shape* s, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv) {
-  return hs_prefill_auto_splits(s->B, s->Hq, s->Hkv, s->L / HS_BT, Lq, q_start, causal != 0,
-                                (int64_t)kv->cap_dense_k + kv->cap_sparse_k);
+  return hs_prefill_auto_splits(s->B, s->Hq, s->Hkv, s->L / HS_BT, Lq, q_start, causal != 0, hs_make_kv_dev(kv));
 }
 
 // shared body of the decode entry points; tail_len < 0: no dense tail

@@ -119,6 +119,20 @@ static inline hs_kv_dev hs_make_kv_dev(const hs_kv* kv) {
   return d;
 }
 
+// What the host can tell from the pools' sizes about the tiles a row keeps (the maps are on the device).  Pools of a
+// fraction policy hold exactly what it keeps: fewer slots than tiles = the rest is skipped; one slot per tile in both
+// tensors, and in one of them shared out between dense and 2:4 = nothing is skipped (so does `uniform`).  Anything else --
+// room beyond a slot per tile, as for states that come as device memory, or one pool of a slot per tile without the promise, as
+// for a cache that grows -- says nothing: any part of a row may be skipped, and rows may differ.
+enum hs_kept { HS_KEPT_ALL, HS_KEPT_FEWER, HS_KEPT_UNKNOWN };
+static inline hs_kept hs_kept_by_pools(const hs_kv_dev& kv, int T) {
+  const int64_t k = (int64_t)kv.cap_dense_k + kv.cap_sparse_k, v = (int64_t)kv.cap_dense_v + kv.cap_sparse_v;
+  if (kv.uniform) return HS_KEPT_ALL;
+  if (k < T || v < T) return HS_KEPT_FEWER;
+  const bool mixed = (kv.cap_dense_k > 0 && kv.cap_sparse_k > 0) || (kv.cap_dense_v > 0 && kv.cap_sparse_v > 0);
+  return mixed && k == T && v == T ? HS_KEPT_ALL : HS_KEPT_UNKNOWN;
+}
+
 // v_map entries: sign = pool (dense > 0, 2:4 < 0), magnitude = slot + 1, plus HS_MAP_F16 when the tile
 // is stored in fp16 encoding
 __host__ __device__ static inline bool hs_map_f16(int m) { return ((m < 0 ? -m : m) & HS_MAP_F16) != 0; }
@@ -178,5 +192,5 @@ hipError_t hs_launch_merge(int64_t rows, int n_splits, const float* ws_o, const 
 // n_splits > 1: the tiles of a workgroup are cut into so many ranges; ws = B * Hq * 64 Tq * n_splits * 129 floats
 hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start, float scale, int causal, const uint16_t* Q,
                              hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype, int n_splits, float* ws);
-// number of ranges that serve this shape best (1: do not split); cap_tiles: tiles a row's K pools can hold
-int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, int64_t cap_tiles);
+// number of ranges that serve this shape best (1: do not split); of kv the capacities and `uniform` are read
+int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv);

@@ -761,10 +761,13 @@ static hipError_t launch_split(dim3 grid, hipStream_t st, int B, int Hq, int Hkv
 // the number of workgroups (1 per compute unit is 256), measured on caches of 0.3 to 2.4 GB: 100 1.30, 128 1.14, 160
 // 1.035, 192 to 224 1.00, 256 1.03 (all-2:4 caches 50.7 us at 256 and 48.7 us at 192, dense 86.7 and 83.8 us, 8 x 128K
 // tokens with half of the tiles skipped 185 and 178 us), and a second, partly filled round costs: 264 1.36 (24 rows of 512
-// tiles: 51.8 us with 11 splits, 38.3 us with 10), 320 1.21, 384 1.075, 512 1.05.  A split whose tiles do not divide among
-// its waves costs about a quarter of what it wastes.  Small caches (fewer than 8 tiles per wave) do not gain from fewer than
-// 256 workgroups unless all tiles are dense, and rows with skipped tiles that are split by range want as many as fit.
-static int pick_splits(int64_t rows, int T, int most, bool dense, bool skips, int bycount_per) {
+// 2:4 tiles: 51.7 us with 11 splits, 38.0 with 10, 37.4 with the 8 it takes), 320 1.21, 384 1.075, 512 1.05.  A split whose
+// tiles do not divide among its waves costs about a quarter of what it wastes.  Small caches (fewer than 8 tiles per wave) do
+// not gain from fewer than 256 workgroups unless all tiles are dense, and rows with skipped tiles that are split by range want as
+// many as fit.  So do rows whose fill the host does not know (hs_kept_by_pools): where they differ, the longest one's splits
+// are the last to end (mixed tensors with room for every tile, filled to 25 to 100 %: 64 rows of 512 tiles 71.0 us with 3 splits,
+// 64.6 with 4; 24 rows 33.3 with 8, 28.4 with 10; all filled to 40 %, 8 rows of 1024: 23.0 with 24, 19.8 with 32).
+static int pick_splits(int64_t rows, int T, int most, bool dense, hs_kept kept, int bycount_per) {
   static const struct { double wgs, g; } kCurve[] = {{100, 1.30}, {128, 1.14}, {160, 1.035}, {192, 1.0}, {224, 1.005}, {256, 1.03},
                                                      {257, 1.36}, {320, 1.21}, {384, 1.075}, {512, 1.05}};
   const bool prefer_fewer = dense || rows * T >= 8192;
@@ -779,7 +782,8 @@ static int pick_splits(int64_t rows, int T, int most, bool dense, bool skips, in
         g = kCurve[i].g + (kCurve[i + 1].g - kCurve[i].g) * (w - kCurve[i].wgs) / (kCurve[i + 1].wgs - kCurve[i].wgs);
     const int per = (T + n - 1) / n;
     const bool by_count = per >= bycount_per;
-    if (w >= 192 && w <= 256 && (!prefer_fewer || (skips && !by_count))) g = 1.0 + (256 - w) * 1e-4;
+    if (w >= 192 && w <= 256 && (!prefer_fewer || kept == HS_KEPT_UNKNOWN || (kept == HS_KEPT_FEWER && !by_count)))
+      g = 1.0 + (256 - w) * 1e-4;
     const double waste = by_count ? 0.0 : (double)((per + 3) / 4) * 4 * n / T - 1.0;
     const double cost = g * (1.0 + 0.25 * waste);
     if (best_cost == 0.0 || cost < best_cost) { best = n; best_cost = cost; }
@@ -793,21 +797,22 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   const int km = kv.cap_dense_k == 0 ? 0 : (kv.cap_sparse_k == 0 ? 1 : 2);
   const int vm = kv.cap_dense_v == 0 ? 0 : (kv.cap_sparse_v == 0 ? 1 : 2);
   // Tiles by count on long splits only: the two passes over the maps at kernel start cost about 3 us, which the even
-  // shares win back (3-7 % of the kernel when tiles are skipped) from 128 tiles per split where the pools say
-  // that all-2:4 tensors have skipped tiles, and from 256 otherwise.  (Caches with room for every tile that are
-  // filled to different lengths, 2:4, 16 rows of up to 256 tiles: 72.6 us by count, 66.8 us by range; 64 rows of up to 128
-  // 138 / 133 us; 8 rows of up to 2048 261 / 266 us.)
-  const bool skips = (int64_t)kv.cap_dense_k + kv.cap_sparse_k < T;
-  const int bycount_per = km == 0 && vm == 0 && skips ? HS_DEC_BYCOUNT_MIN_PER : 2 * HS_DEC_BYCOUNT_MIN_PER;
-  if (auto_splits) n_work = pick_splits((int64_t)B * Hkv, T, n_work, km == 1 && vm == 1, skips, bycount_per);
+  // shares win back (3-7 % of the kernel when tiles are skipped) from 128 tiles per split for all-2:4 tensors and from 256
+  // otherwise.  us, by range / by count, 64 rows of 640 2:4 tiles in 4 splits: half skipped 67.6 / 65.7, three quarters
+  // 40.2 / 37.9, all but every eighth 29.1 / 22.8 (by range the skip pattern decides how even the waves' shares are), rows
+  // filled to 25 to 100 % 79.2 / 84.7.
+  const hs_kept kept = hs_kept_by_pools(kv, T);
+  const int bycount_per = km == 0 && vm == 0 && !kv.uniform ? HS_DEC_BYCOUNT_MIN_PER : 2 * HS_DEC_BYCOUNT_MIN_PER;
+  if (auto_splits) n_work = pick_splits((int64_t)B * Hkv, T, n_work, km == 1 && vm == 1, kept, bycount_per);
   // One workgroup of 8 waves per row and no merge launch, where that is faster than split + merge: very short rows (one
   // compute unit reads about 42 GB/s; us, split + merge / direct, 2:4: 1 row of 4 / 8 / 16 tiles 6.1 / 4.1, 6.0 / 5.4, 6.2 /
   // 8.2; dense, 4 / 8 tiles 6.3 / 5.4, 6.8 / 7.6), and rows numerous enough to fill the chip (256 rows of 8 / 32 / 96 tiles
   // 11.7 / 8.8, 27.5 / 25.4, 69.9 / 67.7; 200 rows of 192 tiles, half of them skipped, 60.2 by count / 58.6; 128 rows of
-  // 16 / 32 tiles 11.6 / 10.2, 17.4 / 17.4).  Longer rows are split or handed out by count.
+  // 16 / 32 tiles 11.6 / 10.2, 17.4 / 17.4).  Longer rows are split or handed out by count; so are those of 128 tiles or more
+  // that may have any pattern of skipped tiles (200 rows of 160, all but every eighth skipped: 19.1 by count / 25.7).
   const int short_row = km == 0 && vm == 0 ? 8 : 4;
   const bool direct = auto_splits && tail_len < 0 && phases == 3 &&
-                      (T <= short_row || (n_work == 1 && T < 2 * HS_DEC_BYCOUNT_MIN_PER) || ((int64_t)B * Hkv >= 128 && T <= 16));
+                      (T <= short_row || (n_work == 1 && T < (kept == HS_KEPT_UNKNOWN ? bycount_per : 2 * HS_DEC_BYCOUNT_MIN_PER)) || ((int64_t)B * Hkv >= 128 && T <= 16));
   if (direct) n_work = 1;
   const TailArgs tail{tail_k, tail_v, tail_lens, tail_len};
   const dim3 grid(n_work, Hkv, B + (tail_len >= 0 ? (B + n_work - 1) / n_work : 0));

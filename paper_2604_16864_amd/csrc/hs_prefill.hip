@@ -704,11 +704,18 @@ static hipError_t launch_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_st
 // ranges 56 us), and there the sum says one range too.  Beyond 512 workgroups one range is only
 // worse where a last, nearly empty round of equally long workgroups follows: queries at the end of a long context (2304
 // queries on 32768 tokens, 576 workgroups: 1116 / 828 us).  Skipped tiles cost nothing, so the tiles are counted by what
-// the pools can hold (75 % skipped, 1024 queries on 2048 tokens: 14 us unsplit, 18 us with the ranges that all tiles would ask for).
-int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, int64_t cap_tiles) {
+// the pools can hold.  Where that says nothing about how many are kept (hs_kept_by_pools) they count as a quarter: few enough
+// that a call does not get slower where three quarters are skipped, and where none is the best number is not far.  us, one range /
+// the chosen number / the number for all tiles, mixed tensors, none | half | three quarters | nine tenths skipped: 64 queries
+// on 32768 tokens 526 / 52 (16 ranges) / 47 (32) | 276 / 41 / 39 | 142 / 32 / 33 | 73 / 25 / 30; 256 queries on 8192 tokens
+// 137 / 51 (4) / 47 (8) | 79 / 38 / 38 | 45 / 30 / 33 | 29 / 24 / 29; 2 x 512 queries on 4096 tokens 74 / 74 (1) / 67 (2) |
+// 48 / 48 / 48 | 34 / 34 / 37 | 22 / 22 / 32.
+int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv) {
   const int64_t n_wg = (int64_t)(((Lq / 32) * (Hq / Hkv) + 3) / 4) * Hkv * B;
+  const int64_t cap_tiles = (int64_t)kv.cap_dense_k + kv.cap_sparse_k;
   int n_tiles = causal ? (q_start + Lq + HS_BT - 1) / HS_BT : T;  // of the last query
-  if (cap_tiles < n_tiles) n_tiles = (int)cap_tiles;
+  if (hs_kept_by_pools(kv, T) == HS_KEPT_UNKNOWN) n_tiles = (n_tiles + 3) / 4;
+  else if (cap_tiles < n_tiles) n_tiles = (int)cap_tiles;
   if (n_wg > 2048 || (n_wg > 512 && causal && q_start < 3 * (int64_t)Lq)) return 1;
   int best = 1;
   double best_us = 0.0;

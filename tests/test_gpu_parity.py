@@ -831,6 +831,23 @@ def test_decode_number_of_splits_is_the_librarys_choice(B, Hkv, T, pol):
         assert (O.float() - O2.float()).abs().max() <= 2 ** -8 * 1.01 * O2.float().abs().max()
 
 
+@pytest.mark.parametrize("B,Hkv,T,counts,n", [
+    (8, 8, 512, None, 4), (3, 8, 512, None, 10), (1, 8, 1024, None, 32), (4, 8, 512, None, 8),     # room for any states
+    (8, 8, 640, [0, 0, 640, 0, 640], 4),                                                           # a slot per tile, no promise
+    (8, 8, 512, [0, 128, 384, 128, 384], 3), (8, 8, 512, [128, 128, 256, 0, 384], 4)])             # fractions: nothing / a quarter skipped
+def test_decode_splits_of_caches_whose_fill_the_host_does_not_know(B, Hkv, T, counts, n):
+    """Pools with room beyond what a policy's fractions keep (states on the device, growing caches) do not count as full:
+    their rows get as many splits as fit the chip.  Counted by the partials that the split kernel writes."""
+    sh = hb.make_shape(B, Hkv, Hkv, 64 * T)
+    kv = hb.PackedKV(sh, counts or [0, T, T, T, T])
+    kv.uniform = 0
+    kv.k_map.zero_(), kv.v_map.zero_()                 # nothing kept: the pools are not looked at
+    Q = torch.randn((B, Hkv, 128), device="cuda").bfloat16()
+    ws = torch.full((hb.workspace_bytes(sh, 2, 0),), 255, dtype=torch.uint8, device="cuda")
+    hb.decode_attn(sh, Q, kv, workspace=ws, phases=1)
+    assert int((ws.view(torch.int32) != -1).sum()) == B * Hkv * 129 * n
+
+
 def test_decode_tail_of_a_batch_beyond_one_grid():
     """40000 rows of one tile: the tail's planes of the grid no longer fit behind the rows' own."""
     B, L = 40000, 64

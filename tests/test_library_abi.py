@@ -138,3 +138,20 @@ def test_prefill_workspace_rule(L):
     assert L.hs_prefill_workspace_bytes(C.byref(sh), 100, 0, 1, C.byref(kv), C.byref(n)) == -2
     assert L.hs_prefill_workspace_bytes(C.byref(sh), 64, 0, 1, None, C.byref(n)) == -1
     assert hb.workspace_bytes(sh, 1, 64) == 0         # the call without scratch needs none, as ever
+
+
+def test_prefill_ranges_of_caches_whose_fill_the_host_does_not_know(L):
+    """Pools with room for any state of every tile (states on the device) say nothing about how many tiles are kept:
+    fewer ranges than for a full cache, none where three quarters skipped would not pay for them."""
+    def ranges(B, T, Lq, caps, uniform=0):
+        sh, kv, n = hb.make_shape(B, 32, 8, 64 * T), hb.HsKV(), C.c_size_t(0)
+        kv.cap_dense_k, kv.cap_sparse_k, kv.cap_dense_v, kv.cap_sparse_v = caps
+        kv.uniform = uniform
+        assert L.hs_prefill_workspace_bytes(C.byref(sh), Lq, 64 * T - Lq, 1, C.byref(kv), C.byref(n)) == 0
+        return n.value // (B * 32 * Lq * 129 * 4)
+    for T in (64, 512):
+        known = [((0, T, 0, T), 1), ((T // 4, T - T // 4, 0, T), 0)]      # the promise; shares of a fraction policy
+        unknown = [((T, T, T, T), 0), ((0, T, 0, T), 0), ((T, 0, T, 0), 0), ((5, T, 5, T), 0)]
+        B, Lq, full, some = (1, 64, 32, 16) if T == 512 else (2, 512, 2, 0)
+        assert {ranges(B, T, Lq, *k) for k in known} == {full}
+        assert {ranges(B, T, Lq, *k) for k in unknown} == {some}
