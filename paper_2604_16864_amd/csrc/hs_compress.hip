@@ -904,12 +904,12 @@ __global__ __launch_bounds__(256) void restate_kernel(int T, hs_kv_dev src, Rest
 // became 2:4 is read from its dense slot (pool order) and pruned with the writers above.
 // COUNT: the maps of dst are not written yet: the workgroup counts the row's new states itself, takes its tile's slots as
 // restate_kernel would hand them out and writes the tile's entries, which saves that launch.
-constexpr int kCountTiles = 4096;  // longest row that a workgroup counts (a byte of LDS per tile)
+constexpr int kCountEntries = 2 << 20;  // map entries that all workgroups of a launch may read to count: rows of up to 1448 tiles
 template <bool COUNT>
 __global__ __launch_bounds__(256) void repack_kernel(int Hkv, int T, hs_kv_dev src, RestateTarget tg, hs_kv_dev dst, int rule, int v_f16,
                                                      int32_t* overflow) {
   __shared__ __attribute__((aligned(16))) uint16_t vl[HS_BT * kVStride];
-  static_assert(sizeof(vl) >= kCountTiles, "a byte per tile");
+  static_assert((int64_t)sizeof(vl) * sizeof(vl) >= kCountEntries, "a byte of vl per tile of the row");
   const int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, a = l >> 4, r = l & 15;
   const int64_t row = (int64_t)b * Hkv + h;
@@ -1215,10 +1215,11 @@ hipError_t hs_launch_recompress(int B, int Hkv, int T, hs_kv_dev src, const int8
                                 int n_first, int n_last, hs_kv_dev dst, int rule, int v_f16, int32_t* overflow,
                                 hipStream_t st) {
   const RestateTarget tg{tgt_k, tgt_v, tgt_map_k, tgt_map_v, frac_state_k, frac_state_v, n_first, n_last};
-  // One launch while the entries that all workgroups read to count are few.  us, two launches / one (keys dense -> 2:4; V
-  // dense -> 2:4, V 2:4 already): 8 rows of 64 tiles 11.5 / 8.7, 9.4 / 6.6; of 512 42.3 / 40.2, 31.7 / 29.3; 16 rows
-  // of 512 76.4 / 81.6, 60.0 / 59.4; 8 rows of 1024 77.9 / 88.1, 61.6 / 67.4.
-  if (T <= kCountTiles && (double)B * Hkv * T * T <= (double)(2 << 20)) {
+  // One launch while the entries that all workgroups read to count (rows x T x T) are few.  The line is where the worse of two
+  // forms breaks even.  us, two launches / one, K and V dense -> 2:4 | keys dense -> 2:4, V 2:4 already: 8 rows of 512 tiles (at
+  // the line) 44.2 / 44.4 | 33.6 / 31.2; 2 of 1024 (at the line) 28.9 / 25.4 | 21.3 / 18.8; 10 of 512 54.9 / 55.5 | 42.1 / 39.9;
+  // 6 of 724 46.9 / 49.3 | 36.4 / 36.3; 16 of 512 81.5 / 84.1 | 63.9 / 61.6; 64 of 256 152.5 / 155.4 | 133.0 / 127.6.
+  if ((double)B * Hkv * T * T <= (double)kCountEntries) {
     hipLaunchKernelGGL(repack_kernel<true>, dim3(T, Hkv, B), dim3(256), 0, st, Hkv, T, src, tg, dst, rule, v_f16, overflow);
     return hipGetLastError();
   }
