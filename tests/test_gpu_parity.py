@@ -484,6 +484,47 @@ def test_prefill_tiles_cut_into_ranges(n_ranges, B, G, T, Lq, q_start, causal, d
         assert torch.equal(O2.view(torch.int16), O.view(torch.int16)) and torch.equal(LSE2, LSE)
 
 
+@pytest.mark.parametrize("q_start", [None, 64 * 20 + 17])
+def test_prefill_entries_without_scratch_run_in_one_range(q_start, monkeypatch):
+    """A shape the library would cut into ranges, through the entries that get no scratch, too little of it or none to
+    be had: the one-range result, the same bits from each, and no write to a workspace that comes without a size."""
+    import ctypes as C
+    G, T, Lq, Hkv = 4, 40, 64, 2
+    L = 64 * T
+    Q, K, V = wl.make_qkv(1, G * Hkv, Hkv, L, 128, Lq, seed=931)
+    sh, kv, pk, pv, _ = compress_both(1, G * Hkv, Hkv, L, K, V)
+    Qd, at, kvs = _dev(Q), L - Lq if q_start is None else q_start, kv.struct()
+    one = G * Hkv * Lq * 129 * 4
+    assert hb.prefill_workspace_bytes(sh, Lq, at, kv) >= 2 * one
+    ws = torch.full((8 * one,), 255, dtype=torch.uint8, device="cuda")
+    lib, sp, q, w, st = hb.lib(), C.byref(sh), hb._ptr(Qd), hb._ptr(ws), hb._stream()
+    calls = {"at": lambda o, l: lib.hs_prefill_attn_at(sp, Lq, at, 0.0, 1, q, C.byref(kvs), o, l, w, st),
+             "no workspace": lambda o, l: lib.hs_prefill_attn_ws(sp, Lq, at, 0.0, 1, q, C.byref(kvs), o, l, None, 8 * one, st),
+             "no bytes": lambda o, l: lib.hs_prefill_attn_ws(sp, Lq, at, 0.0, 1, q, C.byref(kvs), o, l, w, 0, st),
+             "one range's bytes": lambda o, l: lib.hs_prefill_attn_ws(sp, Lq, at, 0.0, 1, q, C.byref(kvs), o, l, w, 2 * one - 1, st)}
+    if q_start is None:
+        calls["end"] = lambda o, l: lib.hs_prefill_attn(sp, Lq, 0.0, 1, q, C.byref(kvs), o, l, w, st)
+    got = {}
+    for name, call in calls.items():
+        O, LSE = torch.full_like(Qd, float("nan")), torch.full(Qd.shape[:3], float("nan"), device="cuda")
+        hb._check(call(hb._ptr(O), hb._ptr(LSE)))
+        got[name] = O, LSE
+    def full(nbytes, device):
+        raise torch.OutOfMemoryError("no scratch to be had")
+    monkeypatch.setattr(hb, "_workspace", full)
+    got["out of memory"] = hb.prefill_attn(sh, Qd, kv, q_start=q_start)
+    torch.cuda.synchronize()
+    assert (ws == 255).all()
+    rows = [(0, h, i) for h in range(G * Hkv) for i in range(0, Lq, 3)]
+    idx = tuple(np.array(rows).T)
+    Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=True, q_offset=at)
+    O0, L0 = got["at"]
+    assert_close(_f32(O0)[idx], Or, "prefill without scratch")
+    assert_lse_close(L0.cpu().numpy()[idx], Lr, "prefill without scratch lse")
+    for name, (O, LSE) in got.items():
+        assert torch.equal(O.view(torch.int16), O0.view(torch.int16)) and torch.equal(LSE, L0), name
+
+
 def test_decode_equals_last_prefill_row():
     B, Hq, Hkv, L = 1, 8, 2, 64 * 6
     Q, K, V = wl.make_qkv(B, Hq, Hkv, L, 128, L, seed=120)
@@ -831,6 +872,39 @@ def test_decode_number_of_splits_is_the_librarys_choice(B, Hkv, T, pol):
         assert (O.float() - O2.float()).abs().max() <= 2 ** -8 * 1.01 * O2.float().abs().max()
 
 
+@pytest.mark.parametrize("B,Hkv,T", [(1, 1, 4), (16, 8, 16), (64, 4, 100),                      # one workgroup per row
+                                     (3, 8, 72), (5, 8, 70), (33, 4, 40), (8, 8, 256), (1, 3, 301)])   # the library's split count
+@pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)),
+                                       ("bf16", dict(skip_frac=0.5, sparse_frac_k=0.5)), ("fp16", "empty")])
+def test_decode_default_call_against_64_bits(B, Hkv, T, dtype, pol):
+    """What the library chooses by itself, against fp64 attention over the unpacked cache (whose bytes the oracle pins)."""
+    G = 3
+    sh = hb.make_shape(B, G * Hkv, Hkv, 64 * T, dtype=torch.float16 if dtype == "fp16" else torch.bfloat16)
+    dt = hb.torch_dtype(sh)
+    g = torch.Generator(device="cuda").manual_seed(60 + T)
+    K, V = (torch.randn((B, Hkv, 64 * T, 128), device="cuda", generator=g).to(dt) for _ in range(2))
+    if pol == "empty":
+        s = np.full((B, Hkv, T), 2, dtype=np.int8)
+        s[::3, 0] = 0                                  # rows that hold nothing
+        s[:, :, 1::2] = 0
+        pol = dict(state_k=s, state_v=s)
+    kv = hb.compress_kv(sh, hb.make_policy(**pol), K, V)
+    del K, V
+    Q = torch.randn((B, G * Hkv, 128), device="cuda", generator=g).to(dt)
+    O, LSE = hb.decode_attn(sh, Q, kv)
+    Ku, Vu = hb.unpack_kv(sh, kv)
+    seen = (kv.k_map != 0).repeat_interleave(64, -1)
+    Or, Lr = torch.zeros(B, G * Hkv, 128, dtype=torch.float64), torch.full((B, G * Hkv), -np.inf, dtype=torch.float64)
+    for b in range(B):
+        for h in range(Hkv):
+            k, v, q = (x.double() for x in (Ku[b, h][seen[b, h]], Vu[b, h][seen[b, h]], Q[b, h * G:(h + 1) * G]))
+            if len(k):
+                S = q @ k.T * 128 ** -0.5
+                Or[b, h * G:(h + 1) * G], Lr[b, h * G:(h + 1) * G] = (torch.softmax(S, 1) @ v).cpu(), torch.logsumexp(S, 1).cpu()
+    assert_lse_close(LSE.cpu().numpy(), Lr.numpy(), "decode default call lse")
+    assert_close(_f32(O), Or.numpy(), "decode default call")
+
+
 @pytest.mark.parametrize("B,Hkv,T,counts,n", [
     (8, 8, 512, None, 4), (3, 8, 512, None, 10), (1, 8, 1024, None, 32), (4, 8, 512, None, 8),     # room for any states
     (8, 8, 640, [0, 0, 640, 0, 640], 4),                                                           # a slot per tile, no promise
@@ -1038,6 +1112,50 @@ def test_append_counts_what_the_row_holds(T, n, rows, state_k, state_v):
                     full = True
         assert (km == want[0]).all() and (vm == want[1]).all()
         assert int(over.item()) == int(full)
+
+
+def _pool_bytes_equal(a, b):
+    for name in ("k_dense", "k_nnz", "k_meta", "v_dense", "v_nnz", "v_meta", "k_map", "v_map"):
+        x, y = getattr(a, name), getattr(b, name)
+        assert (x is None) == (y is None) and (x is None or torch.equal(x, y)), name
+
+
+@pytest.mark.parametrize("state_k,state_v", [(2, 2), (1, 2)])
+def test_append_beyond_the_last_level_cache_in_one_launch(state_k, state_v):
+    """More than 256 MB of new K and V (read non-temporally) that one launch still counts: the bytes of shorter calls."""
+    B, Hkv, n, T = 16, 8, 64, 80                       # 128 rows x 64 tiles; 64 x 128 x 80 entries to count
+    sh = hb.make_shape(B, Hkv, Hkv, 64 * T)
+    g = torch.Generator(device="cuda").manual_seed(21)
+    K, V = (torch.randn((B, Hkv, 64 * n, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
+    got = []
+    for step in (n, 16):
+        kv = hb.PackedKV(sh, [0] + [n * (state_k == 1), n * (state_k == 2), n * (state_v == 1), n * (state_v == 2)])
+        kv.uniform = 0
+        for t in (kv.k_dense, kv.k_nnz, kv.k_meta, kv.v_dense, kv.v_nnz, kv.v_meta, kv.k_map, kv.v_map):
+            if t is not None:
+                t.zero_()
+        over = torch.zeros(1, dtype=torch.int32, device="cuda")
+        for i in range(0, n, step):
+            part = slice(64 * i, 64 * (i + step))
+            hb.append_tile(sh, kv, 5 + i, K[:, :, part], V[:, :, part], state_k=state_k, state_v=state_v, overflow=over)
+        assert int(over.item()) == 0
+        got.append(kv)
+    _pool_bytes_equal(*got)
+
+
+def test_append_of_one_tile_to_many_rows_beyond_the_last_level_cache():
+    """The same by a tile index per batch row: 8000 rows, against a compression of each half."""
+    B, Hkv = 1000, 8
+    sh, half = hb.make_shape(B, Hkv, Hkv, 64), hb.make_shape(B // 2, Hkv, Hkv, 64)
+    g = torch.Generator(device="cuda").manual_seed(22)
+    K, V = (torch.randn((B, Hkv, 64, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
+    kv = hb.PackedKV(sh, [0, 0, 1, 0, 1])
+    kv.uniform = 0
+    kv.k_map.zero_(), kv.v_map.zero_()
+    hb.append_tile(sh, kv, torch.zeros(B, dtype=torch.int32, device="cuda"), K, V)
+    parts = [hb.compress_kv(half, hb.make_policy(), K[i:i + B // 2], V[i:i + B // 2]) for i in (0, B // 2)]
+    for name in ("k_nnz", "k_meta", "v_nnz", "v_meta", "k_map", "v_map"):
+        assert torch.equal(getattr(kv, name), torch.cat([getattr(p, name) for p in parts])), name
 
 
 def test_batch_rows_of_different_length_decode_and_append():
