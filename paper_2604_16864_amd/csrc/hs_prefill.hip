@@ -60,13 +60,15 @@ __device__ __forceinline__ void split_hi_lo(float p0, float p1, const SplitConst
 // LDS staging ring.  One stage holds one tile: a K region then a V region, each 9 KiB (8 KiB of
 // values + 1 KiB of metadata) when every tile of that tensor is 2:4 and 16 KiB otherwise.  Two
 // workgroups share a compute unit's 160 KiB, so a ring may take 80 KiB: 3 stages when at least one
-// tensor is all 2:4 (tiles are requested 2 iterations before use), 2 otherwise.  4 would fit when both are: 1394 us
-// against 1378 us with 3 for a 16K prompt, 42.9 against 41.8 us for 2K (one tile less to wait for before the
-// first is worked on, less state per tile; two iterations cover the latency).
+// tensor is all 2:4, 2 otherwise.  With 3 stages a tile is requested two tiles ahead: with the barrier in mid-iteration (MID
+// below) one iteration before it is waited for, and nothing else is in flight then; with the barrier at the end nearly two,
+// and the tile behind it stays in flight.  A fourth stage would fit when both tensors are 2:4: a 2K prompt takes 43.4 us with
+// it and 41.7 with 3, one of 8K 357 and 352 (one tile less to wait for before the first is worked on, less state per tile);
+// longer ones differ by less than two runs of one side.
 template <int KM> constexpr int region_bytes() { return KM == 0 ? 9216 : 16384; }
 template <int KM, int VM> constexpr int stage_bytes() { return region_bytes<KM>() + region_bytes<VM>(); }
 #ifndef HS_MAX_STAGES
-#define HS_MAX_STAGES 3  // at most 2 tiles in flight behind the next one (see stage_wait)
+#define HS_MAX_STAGES 3  // at most 4: stage_wait leaves up to two tiles in flight
 #endif
 template <int KM, int VM> constexpr int n_stages() {
   constexpr int fit = 81920 / stage_bytes<KM, VM>();
@@ -175,7 +177,9 @@ __device__ __forceinline__ void stage_issue(uint32_t stage_w, const TileSrc& src
 }
 
 // Wait until all but the newest `tiles_in_flight` tiles' worth of this wave's direct-to-LDS loads
-// have landed (loads complete in order).  PER = loads per tile that every wave issues at least.
+// have landed (loads complete in order).  PER = loads per tile that every wave issues at least.  Two
+// tiles are left in flight by a ring of 4 stages only; without that case the loops of bf16 caches come out
+// up to 0.8 % slower (16K prompt 1326 against 1337 us).
 // Immediate: vmcnt in bits 3..0 and 15..14, the other counters left at their maxima.
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 template <int PER>
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
   constexpr int NS = n_stages<KM, VM>(), D = NS - 1;  // ring size, prefetch distance in tiles
   // MID: the per-tile barrier sits between softmax and GEMM2 instead of at the end of the
   // iteration, so that the next tile's K operands can be fetched from LDS while GEMM2 runs.  Needs
-  // the next tile requested at least two iterations ahead (NS >= 3: at least one tensor all 2:4).
+  // the next tile requested an iteration before that barrier (NS >= 3: at least one tensor all 2:4).
   // It is used where every V tile the workgroup meets takes one fp16 term of P (fp16 caches; rows
   // of a bf16 cache whose V tiles are all in fp16 encoding): with both GEMM2 forms in the loop,
   // or mixed V, no registers are left for the K prefetch.
@@ -525,7 +529,7 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
       }
       if (MID) {
         // The next tile must have landed in full (own loads, then everybody's: barrier) before its K
-        // operands are fetched; tiles requested after it may still be in flight.  The stage of the
+        // operands are fetched; with a ring of 3 it is the newest one requested.  The stage of the
         // previous tile is free from here on (all of its reads precede this barrier).
         int later = 0;
 #pragma unroll
