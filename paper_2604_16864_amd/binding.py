@@ -353,7 +353,8 @@ def unpack_kv(shape, kv):
 
 
 def prefill_workspace_bytes(shape, Lq, q_start, kv, causal=True):
-    """kv: PackedKV."""
+    """Scratch that prefill_attn takes for this call (hs_prefill_workspace_bytes): 0 where the queries fill the GPU, at
+    most 270 MB.  kv: PackedKV."""
     out = C.c_size_t(0)
     _check(lib().hs_prefill_workspace_bytes(C.byref(shape), Lq, q_start, int(bool(causal)), C.byref(kv.struct()), C.byref(out)))
     return out.value
@@ -361,7 +362,9 @@ def prefill_workspace_bytes(shape, Lq, q_start, kv, causal=True):
 
 def prefill_attn(shape, Q, kv, causal=True, scale=0.0, want_lse=True, out=None, lse=None, q_start=None):
     """Q: bf16 [B, Hq, Lq, D] contiguous.  Returns (O bf16 [B, Hq, Lq, D], LSE fp32 [B, Hq, Lq] or None).
-    q_start: position in the cache of the first query (default: the queries are the last Lq tokens)."""
+    q_start: position in the cache of the first query (default: the queries are the last Lq tokens).
+    Few queries on a long context take scratch from torch's allocator (prefill_workspace_bytes, at most 270 MB) for the
+    length of the call; without the memory for it the call runs all the same, on fewer workgroups."""
     assert Q.dtype == torch_dtype(shape) and Q.is_contiguous() and Q.is_cuda
     Lq = Q.shape[2]
     O = torch.empty_like(Q) if out is None else out
