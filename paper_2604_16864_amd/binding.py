@@ -115,10 +115,17 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# The raw handle of a device's current stream, without the stream object that torch.cuda.current_stream() builds around
+# it (2.9 us of a call whose kernels take 7).  Not public: a torch without them takes the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    """The current stream of the current device, as torch.cuda.current_stream().cuda_stream gives it without the
-    stream object around it (2.9 us of a call whose kernels take 7)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    """The current stream of the current device."""
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 BF16, FP16 = 0, 1

@@ -525,6 +525,15 @@ def test_prefill_entries_without_scratch_run_in_one_range(q_start, monkeypatch):
         assert torch.equal(O.view(torch.int16), O0.view(torch.int16)) and torch.equal(LSE, L0), name
 
 
+def test_calls_go_to_the_current_stream(monkeypatch):
+    for stream in (torch.cuda.default_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(stream):
+            handle = hb._stream()
+            with monkeypatch.context() as m:
+                m.setattr(hb, "_raw_stream", None)
+                assert handle == hb._stream() == stream.cuda_stream
+
+
 def test_decode_equals_last_prefill_row():
     B, Hq, Hkv, L = 1, 8, 2, 64 * 6
     Q, K, V = wl.make_qkv(B, Hq, Hkv, L, 128, L, seed=120)

@@ -155,3 +155,20 @@ def test_prefill_ranges_of_caches_whose_fill_the_host_does_not_know(L):
         B, Lq, full, some = (1, 64, 32, 16) if T == 512 else (2, 512, 2, 0)
         assert {ranges(B, T, Lq, *k) for k in known} == {full}
         assert {ranges(B, T, Lq, *k) for k in unknown} == {some}
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """A torch without the two non-public functions gets the stream from the public object."""
+    import torch
+
+    class Stream:
+        cuda_stream = 1234
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    for name in ("_raw_stream", "_current_device"):
+        with monkeypatch.context() as m:
+            m.setattr(hb, name, None)
+            assert hb._stream() == 1234
+    with monkeypatch.context() as m:
+        m.setattr(hb, "_raw_stream", lambda dev: 100 + dev)
+        m.setattr(hb, "_current_device", lambda: 3)
+        assert hb._stream() == 103
