@@ -108,6 +108,15 @@ def _time(torch, fn, reps, warm=1):
     return e0.elapsed_time(e1) * 1e-3 / reps
 
 
+def splits_taken(hb, torch, sh, kv, q, ws):
+    """Splits per row that decode uses by its own choice on this cache, counted by the partials the split kernel writes
+    (hs_decode_auto_splits is an upper bound).  ws: workspace of hs_workspace_bytes(op 2, 0)."""
+    words = ws.view(torch.int32)
+    words.fill_(-1)
+    hb.decode_attn(sh, q, kv, n_splits=0, workspace=ws, phases=1)
+    return int((words != -1).sum()) // (sh.B * sh.Hq * 129)
+
+
 LEGS = ("sk0_sv1", "block_sparsity_sweep", "decode_b8_128k", "prefill_64k", "prefill_16k", "chunked_prefill_128k",
         "paper_kernel_shape_b8_32k", "fp16_same_shape")
 PREFILL_REPS = 5          # timed repetitions of every prefill leg (after one warm-up)
@@ -130,8 +139,7 @@ def extra_legs(hb, torch, Q, K, V, qd, sh, args):
     B, Hq, Hkv, L = sh.B, sh.Hq, sh.Hkv, sh.L
     T = L // 64
     ws_c = torch.empty(max(16, hb.workspace_bytes(sh, 0)), dtype=torch.uint8, device="cuda")
-    n = hb.decode_auto_splits(sh)
-    ws_d = torch.empty(hb.workspace_bytes(sh, 2, n), dtype=torch.uint8, device="cuda")
+    ws_d = torch.empty(hb.workspace_bytes(sh, 2, 0), dtype=torch.uint8, device="cuda")
     Od = torch.empty_like(qd)
     flops1 = 4.0 * 128 * Hq * B * (L * (L + 1) / 2.0)
     if "sk0_sv1" in legs:
@@ -141,7 +149,7 @@ def extra_legs(hb, torch, Q, K, V, qd, sh, args):
         kvm = [hb.compress_kv(sh, pol, K, V, workspace=ws_c) for _ in range(6)]
         O = torch.empty_like(Q)
         t_p = _time(torch, lambda i: hb.prefill_attn(sh, Q, kvm[i % 6], causal=True, want_lse=False, out=O), PREFILL_REPS)
-        t_d = _time(torch, lambda i: hb.decode_attn(sh, qd, kvm[i % 6], n_splits=n, want_lse=False, out=Od, workspace=ws_d), 24, warm=6)
+        t_d = _time(torch, lambda i: hb.decode_attn(sh, qd, kvm[i % 6], n_splits=0, want_lse=False, out=Od, workspace=ws_d), 24, warm=6)
         res["sk0_sv1_same_workload"] = {"prefill_ms": t_p * 1e3, "decode_us": t_d * 1e6,
                                         "prefill_mfma_frac": prefill_floor_s(flops1 / 2, flops1 / 2) / t_p,
                                         "decode_GBps": packed_bytes(B, Hkv, T, cts) / t_d / 1e9,
@@ -152,7 +160,7 @@ def extra_legs(hb, torch, Q, K, V, qd, sh, args):
         cts1 = hb.tile_counts(sh, pol1)
         kv_dec = [hb.recompress_kv(sh, kvm[i], pol1) for i in range(6)]
         t_r = _time(torch, lambda i: hb.recompress_kv(sh, kvm[i % 6], pol1, out=kv_dec[i % 6]), 12, warm=2)
-        t_d2 = _time(torch, lambda i: hb.decode_attn(sh, qd, kv_dec[i % 6], n_splits=n, want_lse=False, out=Od, workspace=ws_d), 24, warm=6)
+        t_d2 = _time(torch, lambda i: hb.decode_attn(sh, qd, kv_dec[i % 6], n_splits=0, want_lse=False, out=Od, workspace=ws_d), 24, warm=6)
         res["sk0_sv1_prefill_then_sk1_sv1_decode"] = {
             "recompress_us": t_r * 1e6,
             "recompress_GBps": (packed_bytes(B, Hkv, T, cts) + packed_bytes(B, Hkv, T, cts1)) / t_r / 1e9,
@@ -168,7 +176,7 @@ def extra_legs(hb, torch, Q, K, V, qd, sh, args):
             cts = hb.tile_counts(sh, pol)
             kvs_ = [hb.compress_kv(sh, pol, K, V, workspace=ws_c) for _ in range(6)]
             t_p = _time(torch, lambda i: hb.prefill_attn(sh, Q, kvs_[i % 6], causal=True, want_lse=False, out=O), PREFILL_REPS)
-            t_d = _time(torch, lambda i: hb.decode_attn(sh, qd, kvs_[i % 6], n_splits=n, want_lse=False, out=Od, workspace=ws_d), 24, warm=6)
+            t_d = _time(torch, lambda i: hb.decode_attn(sh, qd, kvs_[i % 6], n_splits=0, want_lse=False, out=Od, workspace=ws_d), 24, warm=6)
             sweep_s.append({"S": S, "prefill_ms": t_p * 1e3, "decode_us": t_d * 1e6, "packed_MB": packed_bytes(B, Hkv, T, cts) / 1e6,
                             "ideal_prefill_speedup": 4.0 / (4.0 - 2 * S), "ideal_decode_speedup": 1.0 / (1.0 - 0.4375 * S)})
             del kvs_
@@ -188,8 +196,7 @@ def extra_legs(hb, torch, Q, K, V, qd, sh, args):
         V3 = torch.randn((B3, Hkv, L3, 128), device="cuda", dtype=torch.bfloat16, generator=g)
         q3 = torch.randn((B3, Hq, 128), device="cuda", dtype=torch.bfloat16, generator=g)
         ws3 = torch.empty(hb.workspace_bytes(sh3, 0), dtype=torch.uint8, device="cuda")
-        n3 = hb.decode_auto_splits(sh3)
-        wsd3 = torch.empty(hb.workspace_bytes(sh3, 2, n3), dtype=torch.uint8, device="cuda")
+        wsd3 = torch.empty(hb.workspace_bytes(sh3, 2, 0), dtype=torch.uint8, device="cuda")
         O3 = torch.empty_like(q3)
         sweep = []
         for name3, kw in (("dense", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)), ("skip0", dict(skip_frac=0.0)),
@@ -200,7 +207,7 @@ def extra_legs(hb, torch, Q, K, V, qd, sh, args):
             c3 = hb.tile_counts(sh3, p3)
             kv3 = hb.PackedKV(sh3, c3)
             t_c = _time(torch, lambda i: hb.compress_kv(sh3, p3, K3, V3, out=kv3, workspace=ws3), 5)
-            t = _time(torch, lambda i: hb.decode_attn(sh3, q3, kv3, n_splits=n3, want_lse=False, out=O3, workspace=wsd3), 8, warm=2)
+            t = _time(torch, lambda i: hb.decode_attn(sh3, q3, kv3, n_splits=0, want_lse=False, out=O3, workspace=wsd3), 8, warm=2)
             nb = packed_bytes(B3, Hkv, L3 // 64, c3)
             dense_b = 2 * B3 * Hkv * L3 * 128 * 2
             ranked = kw.get("skip_frac", 0.0) > 0
@@ -297,8 +304,7 @@ def extra_legs(hb, torch, Q, K, V, qd, sh, args):
         O5 = torch.empty_like(Q5)
         o5 = torch.empty_like(q5)
         ws5 = torch.empty(hb.workspace_bytes(sh5, 0), dtype=torch.uint8, device="cuda")
-        n5 = hb.decode_auto_splits(sh5)
-        wsd5 = torch.empty(hb.workspace_bytes(sh5, 2, n5), dtype=torch.uint8, device="cuda")
+        wsd5 = torch.empty(hb.workspace_bytes(sh5, 2, 0), dtype=torch.uint8, device="cuda")
         flops5 = 4.0 * 128 * Hq * B5 * (L5 * (L5 + 1) / 2.0)
         b8 = []
         for name5, kw in (("dense", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)), ("sk0_sv1", dict(sparse_frac_k=0.0)), ("2:4", dict())):
@@ -306,7 +312,7 @@ def extra_legs(hb, torch, Q, K, V, qd, sh, args):
             c5 = hb.tile_counts(sh5, p5)
             kv5 = hb.compress_kv(sh5, p5, K5, V5, workspace=ws5)
             t_p = _time(torch, lambda i: hb.prefill_attn(sh5, Q5, kv5, causal=True, want_lse=False, out=O5), PREFILL_REPS)
-            t_d = _time(torch, lambda i: hb.decode_attn(sh5, q5, kv5, n_splits=n5, want_lse=False, out=o5, workspace=wsd5), 10, warm=2)
+            t_d = _time(torch, lambda i: hb.decode_attn(sh5, q5, kv5, n_splits=0, want_lse=False, out=o5, workspace=wsd5), 10, warm=2)
             nb = packed_bytes(B5, Hkv, L5 // 64, c5)
             b8.append({"case": name5, "prefill_ms": t_p * 1e3, "prefill_dense_equiv_TFLOPs": flops5 / t_p / 1e12,
                        "decode_us": t_d * 1e6, "decode_GBps": nb / t_d / 1e9, "hbm_frac": nb / t_d / 1e9 / HBM_PEAK_GBPS})
@@ -332,7 +338,7 @@ def extra_legs(hb, torch, Q, K, V, qd, sh, args):
             c6 = hb.tile_counts(sh6, p6)
             kv6 = [hb.compress_kv(sh6, p6, K6, V6, workspace=ws_c) for _ in range(6)]
             t_p = _time(torch, lambda i: hb.prefill_attn(sh6, Q6, kv6[i % 6], causal=True, want_lse=False, out=O6), PREFILL_REPS)
-            t_d = _time(torch, lambda i: hb.decode_attn(sh6, q6, kv6[i % 6], n_splits=n, want_lse=False, out=o6, workspace=ws_d), 24, warm=6)
+            t_d = _time(torch, lambda i: hb.decode_attn(sh6, q6, kv6[i % 6], n_splits=0, want_lse=False, out=o6, workspace=ws_d), 24, warm=6)
             nb = packed_bytes(B, Hkv, T, c6)
             f16.append({"case": name6, "prefill_ms": t_p * 1e3, "prefill_dense_equiv_TFLOPs": flops1 / t_p / 1e12,
                         "decode_us": t_d * 1e6, "decode_GBps": nb / t_d / 1e9})
@@ -402,14 +408,14 @@ def main():
     counts = hb.tile_counts(sh, pol)
     kvs = [hb.PackedKV(sh, counts) for _ in range(args.copies)]
     ws_c = torch.empty(max(16, hb.workspace_bytes(sh, 0)), dtype=torch.uint8, device="cuda")
-    n_splits = hb.decode_auto_splits(sh)
-    ws_d = torch.zeros(hb.workspace_bytes(sh, 2, n_splits), dtype=torch.uint8, device="cuda")
+    ws_d = torch.zeros(hb.workspace_bytes(sh, 2, 0), dtype=torch.uint8, device="cuda")
     O = torch.empty_like(Q)
     Od = torch.empty_like(qd)
     lse_d = torch.empty((B, Hq), dtype=torch.float32, device="cuda")
     for kv in kvs:                                # every buffer holds a valid cache before timing
         hb.compress_kv(sh, pol, K, V, out=kv, workspace=ws_c)
     torch.cuda.synchronize()
+    n_splits = splits_taken(hb, torch, sh, kvs[0], qd, ws_d)
 
     def step(i, ev=None):
         kv_w = kvs[i % args.copies]               # compressed + prefilled this step
@@ -419,7 +425,7 @@ def main():
         if ev: ev[1].record()
         hb.prefill_attn(sh, Q, kv_w, causal=True, want_lse=False, out=O)
         if ev: ev[2].record()
-        hb.decode_attn(sh, qd, kv_r, n_splits=n_splits, out=Od, lse=lse_d, workspace=ws_d)
+        hb.decode_attn(sh, qd, kv_r, n_splits=0, out=Od, lse=lse_d, workspace=ws_d)
         if ev: ev[3].record()
 
     for i in range(args.warmup):
@@ -439,23 +445,23 @@ def main():
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     n_rep = max(args.steps, 16)
     for i in range(args.copies):
-        hb.decode_attn(sh, qd, kvs[i], n_splits=n_splits, out=Od, lse=lse_d, workspace=ws_d, phases=1)
+        hb.decode_attn(sh, qd, kvs[i], n_splits=0, out=Od, lse=lse_d, workspace=ws_d, phases=1)
     e0.record()
     for i in range(n_rep):
-        hb.decode_attn(sh, qd, kvs[i % args.copies], n_splits=n_splits, out=Od, lse=lse_d, workspace=ws_d, phases=1)
+        hb.decode_attn(sh, qd, kvs[i % args.copies], n_splits=0, out=Od, lse=lse_d, workspace=ws_d, phases=1)
     e1.record()
     torch.cuda.synchronize()
     t_ds = np.array([e0.elapsed_time(e1) / n_rep]) * 1e-3
     e0.record()
     for i in range(n_rep):
-        hb.decode_attn(sh, qd, kvs[i % args.copies], n_splits=n_splits, out=Od, lse=lse_d, workspace=ws_d, phases=2)
+        hb.decode_attn(sh, qd, kvs[i % args.copies], n_splits=0, out=Od, lse=lse_d, workspace=ws_d, phases=2)
     e1.record()
     torch.cuda.synchronize()
     t_dm = e0.elapsed_time(e1) / n_rep * 1e-3
     # whole decode calls back to back, as a decode loop issues them (still one cold cache per call)
     e0.record()
     for i in range(n_rep):
-        hb.decode_attn(sh, qd, kvs[i % args.copies], n_splits=n_splits, out=Od, lse=lse_d, workspace=ws_d)
+        hb.decode_attn(sh, qd, kvs[i % args.copies], n_splits=0, out=Od, lse=lse_d, workspace=ws_d)
     e1.record()
     torch.cuda.synchronize()
     t_dc = e0.elapsed_time(e1) / n_rep * 1e-3
@@ -478,13 +484,14 @@ def main():
     # store per workgroup), over rotating cold buffers of the same size
     n_tiles = B * Hkv * T
     arena = torch.empty(args.copies * n_tiles * 18432, dtype=torch.uint8, device="cuda").fill_(1)
-    probe_sink = torch.zeros(16 + 512 * n_splits * Hkv * B, dtype=torch.float32, device="cuda")
+    n_probe = hb.decode_auto_splits(sh) * Hkv * B   # divides the tiles evenly, which the probe asks for
+    probe_sink = torch.zeros(16 + 512 * n_probe, dtype=torch.float32, device="cuda")
     views = [arena[i * n_tiles * 18432:(i + 1) * n_tiles * 18432] for i in range(args.copies)]
     for v in views:
-        hb.probe_stream_read(v, n_tiles, n_splits * Hkv * B, True, probe_sink)
+        hb.probe_stream_read(v, n_tiles, n_probe, True, probe_sink)
     e0.record()
     for i in range(n_rep):
-        hb.probe_stream_read(views[i % args.copies], n_tiles, n_splits * Hkv * B, True, probe_sink)
+        hb.probe_stream_read(views[i % args.copies], n_tiles, n_probe, True, probe_sink)
     e1.record()
     torch.cuda.synchronize()
     t_probe = e0.elapsed_time(e1) / n_rep * 1e-3
@@ -550,11 +557,11 @@ def main():
         pre_dense = e[0].elapsed_time(e[1]) * 1e-3 / reps
         # decode: each launch reads a buffer last touched >= 4 x 134 MB ago
         for i in range(n_d):
-            hb.decode_attn(sh, qd, kvd[i], n_splits=n_splits, out=Od, lse=lse_d, workspace=ws_d)
+            hb.decode_attn(sh, qd, kvd[i], n_splits=0, out=Od, lse=lse_d, workspace=ws_d)
         reps = max(10, args.steps)
         e[0].record()
         for i in range(reps):
-            hb.decode_attn(sh, qd, kvd[i % n_d], n_splits=n_splits, out=Od, lse=lse_d, workspace=ws_d)
+            hb.decode_attn(sh, qd, kvd[i % n_d], n_splits=0, out=Od, lse=lse_d, workspace=ws_d)
         e[1].record()
         torch.cuda.synchronize()
         dec_dense = e[0].elapsed_time(e[1]) * 1e-3 / reps
