@@ -441,16 +441,40 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
             for (int m = 0; m < 4; m++)
               s[m][nb] = E::template smma<1>(ak[2 * m + 1], qb[nb][1].q[0], qb[nb][1].q[1], s[m][nb], kidx[m]);
         } else {
+          if (KM == 1) {
+            // Row blocks 2 and 3 take the registers of 0 and 1 and are requested while the block between is multiplied: a block
+            // read just in front of its products leaves the wave waiting for the LDS four times a tile (both tensors dense,
+            // 8K prompt 516 -> 498 us).  Not where the kind is looked at per tile: the two arms then want different registers
+            // for the operands and the loop spills (2:4 values, half of the keys dense, 398 -> 437).
+            if (!MID) {
 #pragma unroll
-          for (int m = 0; m < 4; m++) {
-            uint4 a4[4];
+              for (int i = 0; i < 8; i++) ak[i] = kl[i * 64 + l];
+            }
 #pragma unroll
-            for (int st = 0; st < 4; st++) a4[st] = MID && m < 2 ? ak[4 * m + st] : kl[(4 * m + st) * 64 + l];
+            for (int m = 0; m < 4; m++) {
 #pragma unroll
-            for (int st = 0; st < 4; st++)
+              for (int st = 0; st < 4; st++)
 #pragma unroll
-              for (int nb = 0; nb < NB; nb++)
-                s[m][nb] = E::mma(a4[st], qb[nb][st >> 1].q[st & 1], s[m][nb]);
+                for (int nb = 0; nb < NB; nb++)
+                  s[m][nb] = E::mma(ak[4 * (m & 1) + st], qb[nb][st >> 1].q[st & 1], s[m][nb]);
+              if (m < 2) {
+#pragma unroll
+                for (int st = 0; st < 4; st++) ak[4 * m + st] = kl[(4 * (m + 2) + st) * 64 + l];
+                __builtin_amdgcn_sched_barrier(0);
+              }
+            }
+          } else {
+#pragma unroll
+            for (int m = 0; m < 4; m++) {
+              uint4 a4[4];
+#pragma unroll
+              for (int st = 0; st < 4; st++) a4[st] = kl[(4 * m + st) * 64 + l];
+#pragma unroll
+              for (int st = 0; st < 4; st++)
+#pragma unroll
+                for (int nb = 0; nb < NB; nb++)
+                  s[m][nb] = E::mma(a4[st], qb[nb][st >> 1].q[st & 1], s[m][nb]);
+            }
           }
         }
         if (V_EARLY) {  // V operands: on their way while the softmax runs
@@ -590,9 +614,18 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
                 }
           }
         } else {
+          // V of one kind: four row blocks are in flight, and the registers of a block are requested anew while the next one is
+          // multiplied (read block by block, as mixed tensors do for want of registers, each of the eight waits for the LDS: both
+          // tensors dense, 8K prompt 498 -> 485 us, 2:4 keys with dense values 432 -> 418).
+          constexpr bool PIPE = VM == 1;
+          if (PIPE) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) av[i] = vl[i * 64 + l];
+            __builtin_amdgcn_sched_barrier(0);
+          }
 #pragma unroll
           for (int mb = 0; mb < 8; mb++) {
-            const uint4 a0 = vl[(2 * mb) * 64 + l], a1 = vl[(2 * mb + 1) * 64 + l];
+            const uint4 a0 = PIPE ? av[2 * (mb & 3)] : vl[(2 * mb) * 64 + l], a1 = PIPE ? av[2 * (mb & 3) + 1] : vl[(2 * mb + 1) * 64 + l];
             if (v_f16) {
 #pragma unroll
               for (int h = 0; h < 2; h++)
@@ -606,6 +639,13 @@ __global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, i
 #pragma unroll
                   for (int nb = 0; nb < NB; nb++)
                     o[mb][nb] = E::mma(h == 0 ? a0 : a1, t2 == 0 ? ph[nb].q[h] : pl[nb].q[h], o[mb][nb]);
+            }
+            if (PIPE) {
+              if (mb >= 1 && mb < 5) {
+#pragma unroll
+                for (int h = 0; h < 2; h++) av[2 * ((mb - 1) & 3) + h] = vl[(2 * (mb + 3) + h) * 64 + l];
+              }
+              __builtin_amdgcn_sched_barrier(0);
             }
           }
         }
