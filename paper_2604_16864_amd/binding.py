@@ -1,4 +1,5 @@
-"""ctypes binding over libhs.so: argument marshalling only.
+"""Binding over libhs.so: argument marshalling only, the per-call part of it in native code (csrc/hs_torch.cpp), the rest
+through ctypes.
 
 Every step of the hot path runs in the library's HIP kernels; PyTorch supplies
 device memory and the stream.  There is no fallback: if the library has not
@@ -13,6 +14,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libhs.so")
 _lib = None
+_native = None        # the native marshalling module, bound to the library's entry points
 
 SKIP, DENSE, SPARSE24 = 0, 1, 2
 TILE = 64
@@ -84,7 +86,7 @@ EXPORTS = {
 
 def lib():
     """The loaded C-ABI library.  Raises if libhs.so is missing (no CPU fallback)."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError(f"{_LIB_PATH} is not built: run `python -m paper_2604_16864_amd.build` "
@@ -94,8 +96,33 @@ def lib():
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
-        _lib = L
+        try:
+            from . import _hs_torch
+        except ImportError as e:
+            raise RuntimeError(f"the binding's native part is not built ({e}): run `python -m paper_2604_16864_amd.build`") from e
+        _hs_torch.bind(tuple(C.cast(getattr(L, name), C.c_void_p).value for name in _NATIVE_ENTRIES), HsShape, PackedKV)
+        _lib, _native = L, _hs_torch
     return _lib
+
+
+# entry points that the native part calls, in the order it has them
+_NATIVE_ENTRIES = ("hs_kv_bytes", "hs_workspace_bytes", "hs_decode_auto_splits", "hs_decode_attn", "hs_decode_attn_static",
+                   "hs_decode_attn_tail", "hs_decode_attn_tail_rows", "hs_prefill_workspace_bytes", "hs_prefill_attn_ws",
+                   "hs_append_tiles", "hs_append_tile_rows")
+
+
+def _fast():
+    """The native marshalling functions.  Each returns None for a call that it leaves to the code here."""
+    if _native is None:
+        lib()
+    return _native
+
+
+def _done(r):
+    """What a native call returned: its result, or the library's status to raise."""
+    if type(r) is int:
+        _check(r)
+    return r
 
 
 class HsError(RuntimeError):
@@ -229,9 +256,18 @@ def decode_auto_splits(shape):
 class PackedKV:
     """Caller-owned device buffers of a packed cache (torch uint8 / int32 tensors)."""
 
-    def __init__(self, shape, counts, device="cuda"):
+    def __init__(self, shape, counts, device="cuda", _like=None):
         self.shape = shape
         self.counts = list(counts)
+        T = shape.L // TILE
+        # slot == tile index: nothing skipped, one kind of tile per tensor
+        self.uniform = int(counts[0] == 0 and (counts[1] == 0 or counts[2] == 0) and (counts[3] == 0 or counts[4] == 0)
+                           and max(counts[1], counts[2]) == T and max(counts[3], counts[4]) == T)
+        bufs = None if _like is None else _fast().pools(shape, self.counts, _like)      # on the device of the tensor _like
+        if bufs is not None:
+            (self.k_dense, self.k_nnz, self.k_meta, self.k_map, self.v_dense, self.v_nnz, self.v_meta, self.v_map,
+             self.nbytes) = bufs
+            return
         nb = kv_bytes(shape, counts)
         rows_T = (shape.B, shape.Hkv, shape.L // TILE)
 
@@ -243,10 +279,6 @@ class PackedKV:
         self.k_map = torch.empty(rows_T, dtype=torch.int32, device=device)
         self.v_map = torch.empty(rows_T, dtype=torch.int32, device=device)
         self.nbytes = sum(nb)
-        T = shape.L // TILE
-        # slot == tile index: nothing skipped, one kind of tile per tensor
-        self.uniform = int(counts[0] == 0 and (counts[1] == 0 or counts[2] == 0) and (counts[3] == 0 or counts[4] == 0)
-                           and max(counts[1], counts[2]) == T and max(counts[3], counts[4]) == T)
 
     def struct(self):
         return HsKV(_ptr(self.k_dense), _ptr(self.k_nnz), _ptr(self.k_meta), _ptr(self.k_map),
@@ -263,7 +295,7 @@ def compress_kv(shape, policy, K, V, out=None, workspace=None):
     assert K.dtype == torch_dtype(shape) and V.dtype == K.dtype and K.is_cuda and V.is_cuda
     assert K.stride(-1) == 1 and V.stride(-1) == 1 and K.stride() == V.stride()
     if out is None:
-        out = PackedKV(shape, tile_counts(shape, policy), K.device)
+        out = PackedKV(shape, tile_counts(shape, policy), K.device, K)
     if workspace is None:
         workspace = _workspace(workspace_bytes(shape, 0), K.device)
     strides = (C.c_int64 * 3)(K.stride(0), K.stride(1), K.stride(2))
@@ -279,6 +311,8 @@ def append_tile(shape, kv, tile, K_tile, V_tile, state_k=SPARSE24, state_v=SPARS
                 overflow=None):
     """K_tile, V_tile: bf16 device tensors [B, Hkv, 64 n, D] (last dim contiguous); fills tiles tile .. tile + n - 1
     of kv.  overflow: optional int32 device tensor (1 element) raised when a row's pool is full."""
+    if _done(_fast().append(shape, kv, tile, K_tile, V_tile, state_k, state_v, element_rule, overflow)) is not None:
+        return
     assert K_tile.dtype == torch_dtype(shape) and V_tile.dtype == K_tile.dtype and K_tile.stride() == V_tile.stride()
     n = K_tile.shape[2] // TILE
     assert K_tile.stride(-1) == 1 and tuple(K_tile.shape) == (shape.B, shape.Hkv, TILE * n, shape.D) and n >= 1
@@ -311,7 +345,7 @@ def recompress_kv(shape, kv, target, counts=None, overflow=None, out=None, works
             if target.sparse_frac_v == 1.0:
                 counts[3] = min(counts[3], prot)
     if out is None:
-        out = PackedKV(shape, counts, kv.k_map.device)
+        out = PackedKV(shape, counts, kv.k_map.device, kv.k_map)
     counts = out.counts
     # slot == tile survives when nothing was skipped before and each tensor ends up in one kind
     whole = not target.state_k and target.skip_frac == 0.0 and target.sparse_frac_k in (0.0, 1.0) and target.sparse_frac_v in (0.0, 1.0)
@@ -372,6 +406,15 @@ def prefill_attn(shape, Q, kv, causal=True, scale=0.0, want_lse=True, out=None, 
     q_start: position in the cache of the first query (default: the queries are the last Lq tokens).
     Few queries on a long context take scratch from torch's allocator (prefill_workspace_bytes, at most 270 MB) for the
     length of the call; without the memory for it the call runs all the same, on fewer workgroups."""
+    r = _fast().prefill(shape, Q, kv, causal, scale, want_lse, out, lse, q_start, None)
+    if type(r) is tuple and len(r) == 1:    # the scratch it wants
+        try:
+            ws = _workspace(r[0], Q.device)
+        except torch.OutOfMemoryError:      # the call also works without: fewer workgroups, no scratch
+            ws = False
+        r = _fast().prefill(shape, Q, kv, causal, scale, want_lse, out, lse, q_start, ws)
+    if r is not None:
+        return _done(r)
     assert Q.dtype == torch_dtype(shape) and Q.is_contiguous() and Q.is_cuda
     Lq = Q.shape[2]
     O = torch.empty_like(Q) if out is None else out
@@ -397,6 +440,10 @@ def decode_attn(shape, Q, kv, scale=0.0, n_splits=0, want_lse=True, out=None, ls
     """Q: bf16 [B, Hq, D] contiguous.  Returns (O bf16 [B, Hq, D], LSE fp32 [B, Hq] or None).
     phases: 3 = whole call; 1 = split-KV kernel only, 2 = merge kernel only (benchmarking).
     tail_k, tail_v (bf16 [B, Hkv, 64, D]) with tail_len: dense tail of not yet compressed tokens."""
+    if phases == 3:
+        r = _fast().decode(shape, Q, kv, scale, n_splits, want_lse, out, lse, workspace, tail_k, tail_v, tail_len)
+        if r is not None:
+            return _done(r)
     assert Q.dtype == torch_dtype(shape) and Q.is_contiguous() and Q.is_cuda
     O = torch.empty_like(Q) if out is None else out
     if lse is None and want_lse:
@@ -435,6 +482,9 @@ STATIC_SCRATCH_BYTES = 4 << 20
 def decode_attn_static(shape, Q, kv, scale=0.0, n_splits=0, out=None, lse=None):
     """hs_decode_attn_static: decode attention whose split partials live in the library's static device
     array.  out (bf16 [B, Hq, D]) and lse (fp32 [B, Hq] or None) are the caller's: nothing is allocated."""
+    r = _fast().decode_static(shape, Q, kv, scale, n_splits, out, lse)
+    if r is not None:
+        return _done(r)
     assert Q.dtype == torch_dtype(shape) and Q.is_contiguous() and Q.is_cuda and out is not None
     kvs = kv.struct()
     _check(lib().hs_decode_attn_static(C.byref(shape), float(scale), int(n_splits), _ptr(Q), C.byref(kvs), _ptr(out),

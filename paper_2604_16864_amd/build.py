@@ -1,12 +1,14 @@
-"""Builds libhs.so (the C-ABI library) for gfx950 with hipcc, in-tree."""
+"""Builds libhs.so (the C-ABI library) for gfx950 with hipcc and _hs_torch.so (the binding's native part), in-tree."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhs.so")
+NATIVE = os.path.join(HERE, "_hs_torch.so")
 SOURCES = ["hs_api.hip", "hs_compress.hip", "hs_decode.hip", "hs_prefill.hip", "hs_prefill_mixed.hip", "hs_probe.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
@@ -19,10 +21,23 @@ FLAGS = [
 FILE_FLAGS = {"hs_prefill.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"]}
 
 
+def native_command():
+    """The C++ compiler's command line for the Python module, against the torch that is installed."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
+            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
+            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "hs_torch.cpp"),
+            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", NATIVE]
+
+
 def build_lib(verbose=True, extra=()):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
-    procs = []
+    procs = [("hs_torch.cpp", subprocess.Popen(native_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))]
     for src in SOURCES:
         obj = os.path.join(CSRC, src.replace(".hip", ".o"))
         objs.append(obj)
@@ -34,7 +49,7 @@ def build_lib(verbose=True, extra=()):
         if verbose and out.strip():
             print(out)
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}")
+            raise RuntimeError(f"the compiler failed on {src}")
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     subprocess.check_call(cmd)
     return LIB

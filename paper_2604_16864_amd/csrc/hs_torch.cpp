@@ -1,0 +1,347 @@
+// Argument marshalling of the Python binding in native code: the per-call part of decode, prefill, append, compress and
+// re-compress.  What a call on a small cache costs is mostly this part: in Python with ctypes a decode call of 7 us of
+// kernels took 13.3 us (8 data_ptr() calls and a ctypes structure for the cache, three allocations, two library calls).
+//
+// Every function returns None for a call it does not take as it is (other types than exact tensors, an argument that fails a
+// check of the binding, a number that is neither int nor float), and the binding's Python code then takes it, so what is
+// accepted, what is refused and with which error is written down in one place only.  Nothing is kept between calls but the
+// types and the library's entry points.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/core/Tensor.h>
+#include <ATen/ops/empty.h>
+#include <ATen/ops/empty_like.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "hs.h"
+
+namespace {
+
+struct Entries {  // of libhs.so, as the binding has loaded it
+  decltype(&hs_kv_bytes) kv_bytes;
+  decltype(&hs_workspace_bytes) workspace_bytes;
+  decltype(&hs_decode_auto_splits) auto_splits;
+  decltype(&hs_decode_attn) decode;
+  decltype(&hs_decode_attn_static) decode_static;
+  decltype(&hs_decode_attn_tail) decode_tail;
+  decltype(&hs_decode_attn_tail_rows) decode_tail_rows;
+  decltype(&hs_prefill_workspace_bytes) prefill_workspace;
+  decltype(&hs_prefill_attn_ws) prefill;
+  decltype(&hs_append_tiles) append;
+  decltype(&hs_append_tile_rows) append_rows;
+} g_hs;
+PyTypeObject *g_shape_type, *g_kv_type;
+
+enum { S_K_DENSE, S_K_NNZ, S_K_META, S_K_MAP, S_V_DENSE, S_V_NNZ, S_V_META, S_V_MAP, S_COUNTS, S_UNIFORM, N_NAMES };
+const char* const kNames[N_NAMES] = {"k_dense", "k_nnz", "k_meta", "k_map", "v_dense", "v_nnz", "v_meta", "v_map", "counts", "uniform"};
+PyObject* g_names[N_NAMES];
+
+bool exact_tensor(PyObject* o) { return THPVariable_CheckExact(o); }
+bool none_or_tensor(PyObject* o) { return o == Py_None || exact_tensor(o); }
+const at::Tensor& tensor(PyObject* o) { return THPVariable_Unpack(o); }
+void* address(PyObject* o) { return o == Py_None ? nullptr : tensor(o).data_ptr(); }
+
+bool get_int(PyObject* o, int32_t* v) {  // a Python int in range; bool is one
+  if (!PyLong_Check(o)) return false;
+  int over = 0;
+  const long x = PyLong_AsLongAndOverflow(o, &over);
+  if (over != 0 || x < INT32_MIN || x > INT32_MAX) return false;
+  *v = (int32_t)x;
+  return true;
+}
+bool get_float(PyObject* o, float* v) {
+  if (PyFloat_Check(o)) { *v = (float)PyFloat_AS_DOUBLE(o); return true; }
+  int32_t i;
+  if (!get_int(o, &i)) return false;
+  *v = (float)i;
+  return true;
+}
+
+bool get_shape(PyObject* o, hs_shape* s) {  // the bytes of the binding's ctypes structure
+  if (Py_TYPE(o) != g_shape_type) return false;
+  Py_buffer b;
+  if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) { PyErr_Clear(); return false; }
+  const bool ok = b.len == (Py_ssize_t)sizeof(hs_shape);
+  if (ok) memcpy(s, b.buf, sizeof(*s));
+  PyBuffer_Release(&b);
+  return ok;
+}
+
+// the cache's buffers as the object holds them now
+bool get_kv(PyObject* o, hs_kv* kv) {
+  if (Py_TYPE(o) != g_kv_type) return false;
+  void** ptr[8] = {&kv->k_dense, &kv->k_nnz, &kv->k_meta, (void**)&kv->k_map, &kv->v_dense, &kv->v_nnz, &kv->v_meta, (void**)&kv->v_map};
+  bool ok = true;
+  for (int i = 0; i < N_NAMES && ok; i++) {
+    PyObject* a = PyObject_GetAttr(o, g_names[i]);
+    if (a == nullptr) { PyErr_Clear(); return false; }
+    if (i < 8) {
+      ok = none_or_tensor(a);
+      if (ok) *ptr[i] = address(a);  // the object keeps the tensor alive
+    } else if (i == S_COUNTS) {
+      ok = PyList_CheckExact(a) && PyList_GET_SIZE(a) >= 5 && get_int(PyList_GET_ITEM(a, 1), &kv->cap_dense_k) &&
+           get_int(PyList_GET_ITEM(a, 2), &kv->cap_sparse_k) && get_int(PyList_GET_ITEM(a, 3), &kv->cap_dense_v) &&
+           get_int(PyList_GET_ITEM(a, 4), &kv->cap_sparse_v);
+    } else {
+      ok = get_int(a, &kv->uniform);
+    }
+    Py_DECREF(a);
+  }
+  return ok;
+}
+
+at::ScalarType element_type(const hs_shape& s) { return s.dtype == HS_FP16 ? at::kHalf : at::kBFloat16; }
+bool query_ok(const at::Tensor& q, const hs_shape& s) { return q.scalar_type() == element_type(s) && q.is_contiguous() && q.is_cuda(); }
+void* current_stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
+at::Tensor bytes_beside(const at::Tensor& t, size_t n) { return at::empty({(int64_t)n}, t.options().dtype(at::kByte)); }
+
+template <class F>
+int without_gil(F&& call) {  // a launch may wait for room in the queue
+  int rc;
+  Py_BEGIN_ALLOW_THREADS
+  rc = call();
+  Py_END_ALLOW_THREADS
+  return rc;
+}
+
+// (O, LSE) or the library's status
+PyObject* result(int rc, PyObject* out, const at::Tensor& o, PyObject* lse_arg, const at::Tensor& lse) {
+  if (rc != 0) return PyLong_FromLong(rc);
+  PyObject* a;
+  PyObject* b;
+  if (out != Py_None) { a = out; Py_INCREF(a); } else if ((a = THPVariable_Wrap(o)) == nullptr) return nullptr;
+  if (lse_arg != Py_None || !lse.defined()) { b = lse_arg; Py_INCREF(b); }
+  else if ((b = THPVariable_Wrap(lse)) == nullptr) { Py_DECREF(a); return nullptr; }
+  PyObject* r = PyTuple_New(2);
+  if (r == nullptr) { Py_DECREF(a); Py_DECREF(b); return nullptr; }
+  PyTuple_SET_ITEM(r, 0, a);
+  PyTuple_SET_ITEM(r, 1, b);
+  return r;
+}
+
+// decode(shape, Q, kv, scale, n_splits, want_lse, out, lse, workspace, tail_k, tail_v, tail_len)
+PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+  HANDLE_TH_ERRORS
+  hs_shape s;
+  hs_kv kv;
+  float scale;
+  int32_t n_splits;
+  if (n_args != 12 || !exact_tensor(a[1]) || !get_shape(a[0], &s) || !get_float(a[3], &scale) || !get_int(a[4], &n_splits) ||
+      !PyBool_Check(a[5]))
+    Py_RETURN_NONE;
+  for (int i = 6; i < 11; i++)
+    if (!none_or_tensor(a[i])) Py_RETURN_NONE;
+  const at::Tensor& q = tensor(a[1]);
+  if (!query_ok(q, s) || q.dim() < 2 || !get_kv(a[2], &kv)) Py_RETURN_NONE;
+  const bool has_tail = a[11] != Py_None;
+  int32_t tail_len = 0;
+  const at::Tensor* rows = nullptr;
+  if (has_tail) {
+    for (int i = 9; i < 11; i++) {
+      if (a[i] == Py_None) continue;
+      const at::Tensor& t = tensor(a[i]);
+      if (t.scalar_type() != q.scalar_type() || !t.is_contiguous() || t.dim() != 4 || t.size(0) != s.B || t.size(1) != s.Hkv ||
+          t.size(2) != 64 || t.size(3) != s.D)
+        Py_RETURN_NONE;
+    }
+    if (exact_tensor(a[11])) {
+      rows = &tensor(a[11]);
+      if (rows->scalar_type() != at::kInt || !rows->is_cuda() || rows->numel() != s.B || !rows->is_contiguous()) Py_RETURN_NONE;
+    } else if (!get_int(a[11], &tail_len)) {
+      Py_RETURN_NONE;
+    }
+  }
+  at::Tensor o, lse, ws;
+  void* ws_ptr;
+  if (a[8] == Py_None) {
+    size_t need = 0;
+    const int n = has_tail ? (n_splits != 0 ? n_splits : g_hs.auto_splits(&s)) + 1 : n_splits;
+    if (g_hs.workspace_bytes(&s, 2, n, &need) != 0) Py_RETURN_NONE;
+    ws = bytes_beside(q, need);
+    ws_ptr = ws.data_ptr();
+  } else {
+    ws_ptr = address(a[8]);
+  }
+  if (a[6] == Py_None) o = at::empty_like(q);
+  if (a[7] == Py_None && a[5] == Py_True) lse = at::empty({q.size(0), q.size(1)}, q.options().dtype(at::kFloat));
+  void* o_ptr = a[6] == Py_None ? o.data_ptr() : address(a[6]);
+  float* lse_ptr = (float*)(lse.defined() ? lse.data_ptr() : address(a[7]));
+  const void *q_ptr = q.data_ptr(), *tk = address(a[9]), *tv = address(a[10]);
+  const int32_t* lens = rows != nullptr ? (const int32_t*)rows->data_ptr() : nullptr;
+  void* st = current_stream();
+  const int rc = without_gil([&] {
+    if (!has_tail) return g_hs.decode(&s, scale, n_splits, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, st);
+    if (rows != nullptr) return g_hs.decode_tail_rows(&s, scale, n_splits, q_ptr, &kv, tk, tv, lens, o_ptr, lse_ptr, ws_ptr, st);
+    return g_hs.decode_tail(&s, scale, n_splits, q_ptr, &kv, tk, tv, tail_len, o_ptr, lse_ptr, ws_ptr, st);
+  });
+  return result(rc, a[6], o, a[7], lse);
+  END_HANDLE_TH_ERRORS
+}
+
+// decode_static(shape, Q, kv, scale, n_splits, out, lse)
+PyObject* decode_static(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+  HANDLE_TH_ERRORS
+  hs_shape s;
+  hs_kv kv;
+  float scale;
+  int32_t n_splits;
+  if (n_args != 7 || !exact_tensor(a[1]) || !get_shape(a[0], &s) || !get_float(a[3], &scale) || !get_int(a[4], &n_splits) ||
+      !exact_tensor(a[5]) || !none_or_tensor(a[6]))
+    Py_RETURN_NONE;
+  const at::Tensor& q = tensor(a[1]);
+  if (!query_ok(q, s) || !get_kv(a[2], &kv)) Py_RETURN_NONE;
+  const void* q_ptr = q.data_ptr();
+  void *o_ptr = address(a[5]), *st = current_stream();
+  float* lse_ptr = (float*)address(a[6]);
+  const int rc = without_gil([&] { return g_hs.decode_static(&s, scale, n_splits, q_ptr, &kv, o_ptr, lse_ptr, st); });
+  return result(rc, a[5], at::Tensor(), a[6], at::Tensor());
+  END_HANDLE_TH_ERRORS
+}
+
+// prefill(shape, Q, kv, causal, scale, want_lse, out, lse, q_start, scratch): scratch None = not asked for yet, then the
+// bytes the call wants are returned if it wants any; a tensor, or False for a call that runs without.
+PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+  HANDLE_TH_ERRORS
+  hs_shape s;
+  hs_kv kv;
+  float scale;
+  if (n_args != 10 || !exact_tensor(a[1]) || !get_shape(a[0], &s) || !PyBool_Check(a[3]) || !get_float(a[4], &scale) ||
+      !PyBool_Check(a[5]) || !none_or_tensor(a[6]) || !none_or_tensor(a[7]) || !(a[9] == Py_False || none_or_tensor(a[9])))
+    Py_RETURN_NONE;
+  const at::Tensor& q = tensor(a[1]);
+  if (!query_ok(q, s) || q.dim() != 4 || q.size(2) > INT32_MAX || !get_kv(a[2], &kv)) Py_RETURN_NONE;
+  const int32_t Lq = (int32_t)q.size(2);
+  int32_t at_pos = s.L - Lq;
+  if (a[8] != Py_None && !get_int(a[8], &at_pos)) Py_RETURN_NONE;
+  const int causal = a[3] == Py_True;
+  size_t need = 0;
+  void* ws_ptr = nullptr;
+  if (a[9] == Py_None) {
+    if (g_hs.prefill_workspace(&s, Lq, at_pos, causal, &kv, &need) != 0) Py_RETURN_NONE;
+    if (need != 0) return Py_BuildValue("(n)", (Py_ssize_t)need);
+  } else if (a[9] != Py_False) {
+    ws_ptr = address(a[9]);
+    need = (size_t)tensor(a[9]).nbytes();
+  }
+  at::Tensor o, lse;
+  if (a[6] == Py_None) o = at::empty_like(q);
+  if (a[7] == Py_None && a[5] == Py_True) lse = at::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(at::kFloat));
+  void* o_ptr = a[6] == Py_None ? o.data_ptr() : address(a[6]);
+  float* lse_ptr = (float*)(lse.defined() ? lse.data_ptr() : address(a[7]));
+  const void* q_ptr = q.data_ptr();
+  void* st = current_stream();
+  const int rc = without_gil([&] { return g_hs.prefill(&s, Lq, at_pos, scale, causal, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, need, st); });
+  return result(rc, a[6], o, a[7], lse);
+  END_HANDLE_TH_ERRORS
+}
+
+// append(shape, kv, tile, K, V, state_k, state_v, element_rule, overflow) -> status
+PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+  HANDLE_TH_ERRORS
+  hs_shape s;
+  hs_kv kv;
+  int32_t state_k, state_v, rule, tile = 0;
+  if (n_args != 9 || !get_shape(a[0], &s) || !exact_tensor(a[3]) || !exact_tensor(a[4]) || !get_int(a[5], &state_k) ||
+      !get_int(a[6], &state_v) || !get_int(a[7], &rule) || !none_or_tensor(a[8]))
+    Py_RETURN_NONE;
+  const at::Tensor &k = tensor(a[3]), &v = tensor(a[4]);
+  if (k.scalar_type() != element_type(s) || v.scalar_type() != k.scalar_type() || k.dim() != 4 || k.strides() != v.strides() ||
+      k.stride(3) != 1 || k.size(0) != s.B || k.size(1) != s.Hkv || k.size(3) != s.D || k.size(2) < 64 || k.size(2) % 64 != 0 ||
+      k.size(2) / 64 > INT32_MAX || !get_kv(a[1], &kv))
+    Py_RETURN_NONE;
+  const int32_t n = (int32_t)(k.size(2) / 64);
+  const at::Tensor* rows = nullptr;
+  if (exact_tensor(a[2])) {
+    rows = &tensor(a[2]);
+    if (n != 1 || rows->scalar_type() != at::kInt || !rows->is_cuda() || rows->numel() != s.B || !rows->is_contiguous()) Py_RETURN_NONE;
+  } else if (!get_int(a[2], &tile)) {
+    Py_RETURN_NONE;
+  }
+  const int64_t strides[3] = {k.stride(0), k.stride(1), k.stride(2)};
+  const void *kp = k.data_ptr(), *vp = v.data_ptr();
+  const int32_t* at_rows = rows != nullptr ? (const int32_t*)rows->data_ptr() : nullptr;
+  int32_t* over = (int32_t*)address(a[8]);
+  void* st = current_stream();
+  const int rc = without_gil([&] {
+    if (rows != nullptr) return g_hs.append_rows(&s, at_rows, state_k, state_v, rule, kp, vp, strides, &kv, over, st);
+    return g_hs.append(&s, tile, n, state_k, state_v, rule, kp, vp, strides, &kv, over, st);
+  });
+  return PyLong_FromLong(rc);
+  END_HANDLE_TH_ERRORS
+}
+
+// pools(shape, counts, like): the eight buffers of a cache beside the tensor `like` (None for an empty pool) and their bytes
+PyObject* pools(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+  HANDLE_TH_ERRORS
+  hs_shape s;
+  int32_t counts[5];
+  if (n_args != 3 || !get_shape(a[0], &s) || !PyList_CheckExact(a[1]) || PyList_GET_SIZE(a[1]) != 5 || !exact_tensor(a[2])) Py_RETURN_NONE;
+  for (int i = 0; i < 5; i++)
+    if (!get_int(PyList_GET_ITEM(a[1], i), &counts[i])) Py_RETURN_NONE;
+  size_t bytes[8], total = 0;
+  if (g_hs.kv_bytes(&s, counts, bytes) != 0) Py_RETURN_NONE;
+  const auto opt = tensor(a[2]).options();
+  PyObject* r = PyTuple_New(9);
+  if (r == nullptr) return nullptr;
+  try {
+    for (int i = 0; i < 8; i++) {
+      const bool map = i == S_K_MAP || i == S_V_MAP;
+      PyObject* t;
+      if (map) t = THPVariable_Wrap(at::empty({s.B, s.Hkv, s.L / 64}, opt.dtype(at::kInt)));
+      else if (bytes[i] != 0) t = THPVariable_Wrap(at::empty({(int64_t)bytes[i]}, opt.dtype(at::kByte)));
+      else { t = Py_None; Py_INCREF(t); }
+      if (t == nullptr) { Py_DECREF(r); return nullptr; }
+      PyTuple_SET_ITEM(r, i, t);
+      total += bytes[i];
+    }
+  } catch (...) {
+    Py_DECREF(r);
+    throw;
+  }
+  PyTuple_SET_ITEM(r, 8, PyLong_FromSize_t(total));
+  return r;
+  END_HANDLE_TH_ERRORS
+}
+
+// bind(addresses in the order of Entries, HsShape, PackedKV)
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+  constexpr Py_ssize_t n = sizeof(Entries) / sizeof(void*);
+  if (n_args != 3 || !PyTuple_Check(a[0]) || PyTuple_GET_SIZE(a[0]) != n || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
+    PyErr_SetString(PyExc_TypeError, "bind(addresses, shape type, cache type)");
+    return nullptr;
+  }
+  void* p[n];
+  for (Py_ssize_t i = 0; i < n; i++) {
+    p[i] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(a[0], i));
+    if (p[i] == nullptr) {
+      if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null entry");
+      return nullptr;
+    }
+  }
+  memcpy(&g_hs, p, sizeof(p));
+  Py_INCREF(a[1]);
+  Py_INCREF(a[2]);
+  Py_XDECREF(g_shape_type);
+  Py_XDECREF(g_kv_type);
+  g_shape_type = (PyTypeObject*)a[1];
+  g_kv_type = (PyTypeObject*)a[2];
+  Py_RETURN_NONE;
+}
+
+#define HS_FN(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
+PyMethodDef kMethods[] = {HS_FN(bind), HS_FN(decode), HS_FN(decode_static), HS_FN(prefill), HS_FN(append), HS_FN(pools),
+                          {nullptr, nullptr, 0, nullptr}};
+PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_hs_torch", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__hs_torch() {
+  for (int i = 0; i < N_NAMES; i++) {
+    g_names[i] = PyUnicode_InternFromString(kNames[i]);
+    if (g_names[i] == nullptr) return nullptr;
+  }
+  return PyModule_Create(&kModule);
+}

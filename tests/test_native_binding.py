@@ -1,0 +1,124 @@
+"""The native part of the binding against the binding's own Python code: the same calls through both give the same bits, and
+whatever the native part does not take as it is goes on to the Python code, which accepts or refuses it as before."""
+import pytest
+import torch
+
+from paper_2604_16864_amd import binding as hb
+
+
+class _PythonOnly:
+    """Leaves every call to the Python code."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+def _shape(dtype=hb.BF16):
+    return hb.make_shape(2, 8, 2, 64 * 12, dtype=dtype)
+
+
+def test_calls_the_native_part_leaves_alone_are_refused_as_before():
+    hb.lib()
+    sh = _shape()
+    kv = hb.PackedKV(sh, [0, 0, 12, 0, 12], "cpu")
+    q = torch.zeros(2, 8, 128, dtype=torch.bfloat16)
+    bad = [q,                                                     # not on the GPU
+           q.to(torch.float16), q.float(), q.transpose(0, 1)]
+    for t in bad:
+        with pytest.raises(AssertionError):
+            hb.decode_attn(sh, t, kv)
+        with pytest.raises(AssertionError):
+            hb.decode_attn_static(sh, t, kv, out=torch.empty_like(q))
+        with pytest.raises(AssertionError):
+            hb.prefill_attn(sh, t[:, :, None], kv)
+    tile = torch.zeros(2, 2, 64, 128, dtype=torch.bfloat16)
+    for k, v in ((tile[:, :, :63], tile[:, :, :63]), (tile.float(), tile.float()), (tile, tile.transpose(0, 1)), (tile[:1], tile[:1])):
+        with pytest.raises(AssertionError):
+            hb.append_tile(sh, kv, 0, k, v)
+    with pytest.raises(AttributeError):
+        hb.decode_attn(sh, q.tolist(), kv)
+    n = hb._fast()
+    assert n.decode(sh, q, kv, 0.0, 0, True, None, None, None, None, None, None) is None
+    assert n.decode(sh, q, object(), 0.0, 0, True, None, None, None, None, None, None) is None
+    assert n.decode(q, q, kv, 0.0, 0, True, None, None, None, None, None, None) is None
+    assert n.prefill() is None and n.append(1, 2) is None and n.pools(sh, [0, 0, 12, 0], q) is None
+
+
+@pytest.mark.parametrize("counts", [[0, 0, 12, 0, 12], [0, 12, 0, 5, 7], [3, 9, 0, 0, 9]])
+def test_pools_made_natively_are_the_same(counts):
+    sh = _shape()
+    a, b = hb.PackedKV(sh, counts, "cpu", torch.empty(1)), hb.PackedKV(sh, counts, "cpu")
+    assert (a.nbytes, a.counts, a.uniform) == (b.nbytes, b.counts, b.uniform)
+    for name in ("k_dense", "k_nnz", "k_meta", "k_map", "v_dense", "v_nnz", "v_meta", "v_map"):
+        x, y = getattr(a, name), getattr(b, name)
+        assert (x is None) == (y is None)
+        assert x is None or (x.shape == y.shape and x.dtype == y.dtype and x.device == y.device)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("policy", [dict(), dict(sparse_frac_k=0.5, skip_frac=0.25)])
+def test_native_and_python_calls_give_the_same_bits(dtype, policy, monkeypatch):
+    sh = hb.make_shape(2, 8, 2, 64 * 12, dtype=dtype)
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def normal(*shape):
+        return torch.randn(shape, device="cuda", generator=g).to(dtype)
+    K, V, q, Q, tk, tv = (normal(*s) for s in ((2, 2, 768, 128), (2, 2, 768, 128), (2, 8, 128), (2, 8, 128, 128), (2, 2, 64, 128),
+                                               (2, 2, 64, 128)))
+    lens = torch.tensor([7, 64], dtype=torch.int32, device="cuda")
+    old = torch.tensor([4, 9], dtype=torch.int32, device="cuda")
+    ws = torch.empty(hb.workspace_bytes(sh, 2, 5), dtype=torch.uint8, device="cuda")
+
+    def calls():
+        kv = hb.compress_kv(sh, hb.make_policy(**policy), K, V)
+        held = dict(out=torch.empty_like(q), lse=torch.empty(2, 8, device="cuda"))
+        yield hb.decode_attn(sh, q, kv)
+        yield hb.decode_attn(sh, q, kv, scale=1, n_splits=3, want_lse=False)
+        yield hb.decode_attn(sh, q, kv, n_splits=4, workspace=ws, tail_k=tk, tail_v=tv, tail_len=33, **held)
+        yield hb.decode_attn(sh, q, kv, tail_k=tk, tail_v=tv, tail_len=lens)
+        yield hb.decode_attn(sh, q, kv, tail_len=0)
+        yield hb.decode_attn_static(sh, q, kv, out=torch.empty_like(q), lse=torch.empty(2, 8, device="cuda"))
+        yield hb.prefill_attn(sh, Q, kv)
+        yield hb.prefill_attn(sh, Q, kv, causal=False, scale=0.1, want_lse=False, q_start=192)
+        yield hb.prefill_attn(sh, torch.nn.Parameter(Q), kv, q_start=64)
+        sk = torch.zeros(2, 2, 12, dtype=torch.int8)
+        sk[:, :, :4] = hb.SPARSE24
+        grow = hb.compress_kv(sh, hb.make_policy(state_k=sk.numpy(), state_v=sk.numpy()), K, V,
+                              out=hb.PackedKV(sh, [0, 2, 12, 2, 12], "cuda"))
+        hb.append_tile(sh, grow, old, tk, tv)
+        hb.append_tile(sh, grow, 5, K[:, :, :128], V[:, :, :128], state_k=hb.DENSE)
+        yield hb.unpack_kv(sh, grow)
+        yield hb.unpack_kv(sh, hb.recompress_kv(sh, kv, hb.make_policy()))
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        native = list(calls())
+    stream.synchronize()
+    with monkeypatch.context() as m:
+        m.setattr(hb, "_native", _PythonOnly())
+        python = list(calls())
+    torch.cuda.synchronize()
+    assert len(native) == len(python)
+    for i, (a, b) in enumerate(zip(native, python)):
+        for x, y in zip(a, b):
+            assert (x is None) == (y is None), i
+            assert x is None or (type(x) is type(y) and x.dtype == y.dtype and torch.equal(x.view(torch.uint8), y.view(torch.uint8))), i
+
+
+@pytest.mark.gpu
+def test_library_errors_are_raised_through_the_native_part():
+    sh = _shape()
+    kv = hb.compress_kv(sh, hb.make_policy(), torch.zeros(2, 2, 768, 128, dtype=torch.bfloat16, device="cuda"),
+                        torch.zeros(2, 2, 768, 128, dtype=torch.bfloat16, device="cuda"))
+    q = torch.zeros(2, 8, 128, dtype=torch.bfloat16, device="cuda")
+    for kw in (dict(n_splits=-1), dict(scale=-1.0)):
+        with pytest.raises(hb.HsError):
+            hb.decode_attn(sh, q, kv, **kw)
+    with pytest.raises(hb.HsError):
+        hb.decode_attn(sh, q, kv, tail_len=65)
+    with pytest.raises(hb.HsError):
+        hb.prefill_attn(sh, torch.zeros(2, 8, 100, 128, dtype=torch.bfloat16, device="cuda"), kv)
+    with pytest.raises(hb.HsError):                              # a uniform cache does not grow
+        hb.append_tile(sh, kv, 3, torch.zeros(2, 2, 64, 128, dtype=torch.bfloat16, device="cuda"),
+                       torch.zeros(2, 2, 64, 128, dtype=torch.bfloat16, device="cuda"))
