@@ -1,7 +1,15 @@
 // Prefill attention: number of tile ranges, choice of the kernel, and the kernels of tensors with one kind of tile.
+#include <math.h>
+
 #include "hs_prefill_kernel.h"
 
-// Ranges to cut a workgroup's tiles into, from what was measured on 2:4 tensors (32/8 heads): a tile takes a workgroup
+static int tiles_to_expect(int T, int seen, const hs_kv_dev& kv) {  // of `seen` tiles, how many to reckon with: what the pools can hold (below)
+  const int64_t cap_tiles = (int64_t)kv.cap_dense_k + kv.cap_sparse_k;
+  if (hs_kept_by_pools(kv, T) == HS_KEPT_UNKNOWN) return (seen + 3) / 4;
+  return cap_tiles < seen ? (int)cap_tiles : seen;
+}
+
+// Most ranges to cut a workgroup's tiles into, from what was measured on 2:4 tensors (32/8 heads): a tile takes a workgroup
 // 1.0 us alone on its compute unit and 1.2 us beside a second one, so 512 workgroups at a time are two on every unit;
 // splitting costs 8 us for the merge launch and the caller's scratch (5 us on the GPU alone) and 0.028 us per workgroup
 // for writing and reading its 66 KB of partials.
@@ -19,10 +27,7 @@
 // 48 / 48 / 48 | 34 / 34 / 37 | 22 / 22 / 32.
 int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv) {
   const int64_t n_wg = (int64_t)(((Lq / 32) * (Hq / Hkv) + 3) / 4) * Hkv * B;
-  const int64_t cap_tiles = (int64_t)kv.cap_dense_k + kv.cap_sparse_k;
-  int n_tiles = causal ? (q_start + Lq + HS_BT - 1) / HS_BT : T;  // of the last query
-  if (hs_kept_by_pools(kv, T) == HS_KEPT_UNKNOWN) n_tiles = (n_tiles + 3) / 4;
-  else if (cap_tiles < n_tiles) n_tiles = (int)cap_tiles;
+  const int n_tiles = tiles_to_expect(T, causal ? (q_start + Lq + HS_BT - 1) / HS_BT : T, kv);  // of the last query
   if (n_wg > 2048 || (n_wg > 512 && causal && q_start < 3 * (int64_t)Lq)) return 1;
   int best = 1;
   double best_us = 0.0;
@@ -35,11 +40,52 @@ int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, i
   return best;
 }
 
+namespace {
+
+// Slabs of 32 queries (NB = 2) or of 16 (NB = 1), and in how many of the allowed ranges.  A tile takes a workgroup of NB = 1
+// three quarters of the time for half of the work, so NB = 1 pays where NB = 2 has too few workgroups: one or none per compute
+// unit, or a short second half of the work.  Measured, 32/8 heads, 2:4 tensors, us of NB = 2 / NB = 1 at the better number of
+// ranges of each: whole prompts of 64 / 256 / 512 / 1024 / 1536 / 2048 / 4096 tokens 7.4 / 6.1, 10.3 / 8.0, 14.3 / 11.1, 22.4 /
+// 19.1, 32.7 / 26.7, 41.5 / 39.1, 94.0 / 122; 64 queries on 1024 / 2048 / 8192 / 32768 tokens 14.4 / 12.1, 17.1 / 14.7, 25.4 /
+// 23.3, 39.4 / 39.0; 512 queries on 2048 / 32768 tokens 31.8 (4 ranges) / 27.8 (1), 179 / 220; 4 prompts of 512 tokens 19.8 /
+// 21.9, 13 of 192 21.2 / 21.4; both tensors dense, 1024 / 2048 tokens 26.1 / 20.7, 51.5 / 48.7; dense ends 30.1 / 22.5, 52.3 / 44.4.
+// The sum below gives these times to within 15 % (us): a workgroup starts in kStart, a tile takes it kAlone with a compute unit
+// to itself and kPair beside a second one; 512 run at a time, the longest first, so the call ends with the longest, or when the
+// whole is worked off, or with a pile of k + 1 where round k + 1 is just begun (queries at the end of a long context: all
+// workgroups equally long); ranges add the merge launch and the partials.
+struct PrefillPlan { int nb, n_splits; };
+PrefillPlan plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv, int most) {
+  static const double kStart[3] = {0, 5.3, 7.2}, kAlone[3] = {0, 0.70, 0.905}, kPair[3] = {0, 0.82, 1.13};
+  const int seen = causal ? (q_start + Lq + HS_BT - 1) / HS_BT : T;  // tiles of the last query
+  const double share = (double)tiles_to_expect(T, seen, kv) / seen;
+  const double longest = seen * share, shortest = (causal ? seen - (Lq / HS_BT - 1) : seen) * share;
+  PrefillPlan best = {2, 1};
+  double best_us = 0.0;
+  for (int nb = 2; nb >= 1; nb--) {
+    const double n_wg = (double)((int64_t)((Lq / (16 * nb) * (int64_t)(Hq / Hkv) + 3) / 4) * Hkv * B);
+    for (int n = 1; n <= most; n++) {
+      const double wgs = n_wg * n;
+      double us = longest / n * (wgs <= 256 ? kAlone[nb] : kPair[nb]) + kStart[nb];
+      us = fmax(us, (longest + shortest) / 2 / n * kPair[nb] * wgs / 512 + ceil(wgs / 512) * kStart[nb]);
+      for (int k = 1; 512 * k < wgs; k++)
+        us = fmax(us, (k + 1) * ((longest - (longest - shortest) * 512 * k / wgs) / n * kPair[nb] + kStart[nb]));
+      if (n > 1) us += 3.0 + 0.014 * nb * wgs;
+      if (nb == 1) us *= 1.03;  // the wider slab where the two are even
+      if (best_us == 0.0 || us < best_us) { best = {nb, n}; best_us = us; }
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
 hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start, float scale, int causal, const uint16_t* Q,
                              hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype, int n_splits, float* ws) {
   const bool f16 = dtype == HS_FP16;
   const float sl2 = scale * kLog2e;
   const int Lq = Tq * HS_BT;
+  const PrefillPlan plan = plan_prefill(B, Hq, Hkv, T, Lq, q_start, causal, kv, n_splits);
+  n_splits = plan.n_splits;
   const int km = kv.cap_dense_k == 0 ? 0 : (kv.cap_sparse_k == 0 ? 1 : 2);
   const int vm = kv.cap_dense_v == 0 ? 0 : (kv.cap_sparse_v == 0 ? 1 : 2);
   const int64_t rows = (int64_t)B * Hq * Lq;
@@ -49,7 +95,9 @@ hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start,
 #define HS_GO(KM_, VM_)                                                                                                  \
   e = launch_prefill<KM_, VM_, 2>(B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l); \
   break
-  switch (km * 3 + vm) {
+  if (plan.nb == 1)
+    e = hs_launch_prefill_narrow(km, vm, B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l);
+  else switch (km * 3 + vm) {
     case 0: HS_GO(0, 0);
     case 1: HS_GO(0, 1);
     case 3: HS_GO(1, 0);

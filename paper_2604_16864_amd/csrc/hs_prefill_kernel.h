@@ -2,8 +2,8 @@
 // the first, possibly 2:4-sparse, operand of the matrix instruction) with the mixed
 // dense/sparse dispatch of Sec. III-C-2, online softmax, and tile skipping.
 //
-// Work decomposition: a "slab" is 16 NB consecutive query positions of one query head (NB = 2:
-// 32 positions); a wave owns one slab, keeps Q^T (B operand of GEMM1), the running softmax
+// Work decomposition: a "slab" is 16 NB consecutive query positions of one query head (NB = 2: 32 positions; NB = 1 where
+// these would leave compute units idle, hs_prefill.hip); a wave owns one slab, keeps Q^T (B operand of GEMM1), the running softmax
 // state and O^T (128 x 16 NB fp32) in registers for the whole kernel.  The 4 waves of a
 // workgroup take 4 consecutive slabs in (position-tile, head-in-group) order, so for a GQA
 // group of 4 they are the 4 query heads of one position tile and share every KV tile, which is
@@ -213,7 +213,8 @@ union B16 {  // one B operand of the 16x16x64 sparse instruction = two of the de
 // (the specialised all-dense / all-sparse kernels of Sec. IV-C-3, chosen per tensor so that the
 // keys-dense / values-2:4 setting of Sec. V-A carries no dynamic dispatch).
 // NB: column blocks (of 16 queries) per wave: a wave owns a slab of 16*NB query positions of one
-// head.  NB = 2 fits 2 waves per SIMD (NB = 4, 1 wave per SIMD, measured 1.3-1.4x slower).
+// head.  NB = 2 fits 2 waves per SIMD (NB = 4, 1 wave per SIMD, measured 1.3-1.4x slower; NB = 3 at 2 waves spills: 16K prompt
+// 1346 -> 1529 us); NB = 1 takes 0.7 of its time for half of the work.
 // F16: element type of the cache (hs_elem).  A V tile of a bf16 cache may be stored in fp16 encoding
 // (HS_MAP_F16 in its map entry).  Against fp16 V the numerators have 11 significant bits and enter
 // GEMM2 as one fp16 term; against bf16 V they enter as two bf16 terms.  The reference is kept
@@ -223,7 +224,7 @@ union B16 {  // one B operand of the 16x16x64 sparse instruction = two of the de
 // writes a normalised fp32 partial output and its log-sum-exp (ws_o [row][split][128], ws_l
 // [row][split], row = (b, query head, query)) for the merge kernel instead of O and LSE.
 template <int KM, int VM, int NB, bool F16, bool SPLIT>
-__global__ __launch_bounds__(256, NB == 2 ? 2 : 1) void prefill_kernel(int Hq, int Hkv, int T, int Lq, int off,
+__global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T, int Lq, int off,
                                                                       float scale_log2, int causal,
                                                                       const uint16_t* __restrict__ Q, hs_kv_dev kv,
                                                                       uint16_t* __restrict__ O,

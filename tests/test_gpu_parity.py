@@ -484,6 +484,53 @@ def test_prefill_tiles_cut_into_ranges(n_ranges, B, G, T, Lq, q_start, causal, d
         assert torch.equal(O2.view(torch.int16), O.view(torch.int16)) and torch.equal(LSE2, LSE)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("pol", [dict(), dict(sparse_frac_k=0.0), dict(sparse_frac_v=0.0), dict(sparse_frac_k=0.0, sparse_frac_v=0.0),
+                                 dict(sparse_frac_k=0.5, sparse_frac_v=0.5), dict(sparse_frac_k=0.5), dict(dense_first_tiles=1, dense_last_tiles=1)])
+def test_prefill_slabs_of_16_and_of_32_queries(pol, dtype):
+    """The same prompts as one batch, whose workgroups fill the GPU twice with slabs of 32 queries, and one by one, too few for
+    that, with slabs of 16: both against the oracle, every kind of tensor."""
+    B, Hq, Hkv, L = 16, 32, 8, 256
+    Q, K, V = wl.make_qkv(B, Hq, Hkv, L, 128, L, seed=1201, dtype=dtype)
+    V[:, :, ::61, 3] = 0x0001                         # in bf16: values that fp16 does not hold, in every tile
+    V[1::2] = wl.make_qkv(B // 2, Hq, Hkv, L, 128, L, seed=1202, dtype=dtype)[2]
+    sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, K, V, dtype=dtype, **pol)
+    wide, wide_l = hb.prefill_attn(sh, _dev(Q, dtype), kv)
+    rows = wl.sample_rows(B, Hq, L, 600, seed=1203, extra=[(0, 0, 0), (1, 31, L - 1), (1, 5, 15), (0, 5, 16), (1, 6, 31), (0, 7, 63)])
+    idx = tuple(np.array(rows).T)
+    Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=True)
+    assert_close(_f32(wide)[idx], Or, "slabs of 32")
+    assert_lse_close(wide_l.cpu().numpy()[idx], Lr, "slabs of 32 lse")
+    one, narrow, narrow_l = hb.make_shape(1, Hq, Hkv, L, dtype=sh.dtype), [], []
+    for b in range(2):
+        kv1 = hb.compress_kv(one, hb.make_policy(**pol), _dev(K[b:b + 1], dtype), _dev(V[b:b + 1], dtype))
+        O, LSE = hb.prefill_attn(one, _dev(Q[b:b + 1], dtype), kv1)
+        narrow.append(O)
+        narrow_l.append(LSE)
+    pick = np.array([r[0] < 2 for r in rows])
+    idx = tuple(i[pick] for i in idx)
+    assert_close(_f32(torch.cat(narrow))[idx], Or[pick], "slabs of 16")
+    assert_lse_close(torch.cat(narrow_l).cpu().numpy()[idx], Lr[pick], "slabs of 16 lse")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,Lq,q_start,causal", [
+    (1, 5, 5, 192, 192, None, True),                  # groups of one head: a workgroup's waves at different positions
+    (1, 21, 3, 320, 320, None, True),                 # 7 heads: slabs that do not divide among the waves
+    (2, 6, 2, 640, 64, 64 * 4 + 33, True),            # off the tile grid
+    (1, 8, 1, 1024, 64, None, False),                 # not causal, in ranges
+    (1, 64, 8, 16384, 128, None, True),               # long enough that ranges of the wide slab are the better ones
+])
+def test_prefill_slab_choice_over_shapes(B, Hq, Hkv, L, Lq, q_start, causal):
+    Q, K, V = wl.make_qkv(B, Hq, Hkv, L, 128, Lq, seed=1210 + Hq, k_outliers=True)
+    sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, K, V)
+    O, LSE = hb.prefill_attn(sh, _dev(Q), kv, causal=causal, q_start=q_start)
+    rows = wl.sample_rows(B, Hq, Lq, 200, seed=1211, extra=[(0, 0, 0), (B - 1, Hq - 1, Lq - 1), (0, Hq - 1, 16), (0, 0, 15)])
+    idx = tuple(np.array(rows).T)
+    Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=causal, **({} if q_start is None else {"q_offset": q_start}))
+    assert_close(_f32(O)[idx], Or, "slab choice")
+    assert_lse_close(LSE.cpu().numpy()[idx], Lr, "slab choice lse")
+
+
 @pytest.mark.parametrize("q_start", [None, 64 * 20 + 17])
 def test_prefill_entries_without_scratch_run_in_one_range(q_start, monkeypatch):
     """A shape the library would cut into ranges, through the entries that get no scratch, too little of it or none to
