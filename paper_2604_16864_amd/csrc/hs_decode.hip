@@ -340,13 +340,21 @@ constexpr int kScanBatch = 2048;  // tiles of the row looked at per scan step: 8
 // NW: waves per workgroup.  4: the partial of a split goes to ws_o / ws_l.  8: the workgroup has the whole row (one
 // split, no tail) and writes O and LSE itself (handed in as ws_o, ws_l): no merge launch.
 template <int KM, int VM, int MODE, bool F16, int NW>
-__global__ __launch_bounds__(64 * NW, HS_DEC_OCC) void decode_split_kernel(int B, int z0, int Hq, int Hkv, int T, float scale_log2,
+__global__ __launch_bounds__(64 * NW, HS_DEC_OCC) void decode_split_kernel(int B, int z0, int turn, int Hq, int Hkv, int T, float scale_log2,
                                                                              int n_splits, int per,
                                                                              const uint16_t* __restrict__ Q,
                                                                              hs_kv_dev kv, TailArgs tail,
                                                                              float* __restrict__ ws_o,
                                                                              float* __restrict__ ws_l) {
-  const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z + z0;
+  const int hkv = blockIdx.y, b = blockIdx.z + z0;
+  // Workgroups go round-robin over the 8 XCDs by their index: with an even number of splits the same splits of every row
+  // meet on an XCD (with 8 of them, split s on XCD s), and where rows differ in length the XCDs of the late splits have little to
+  // do.  So every 8 / gcd(splits, 8) rows the splits start one further on (turn - 1 = log2 of that).  us, before / after: 16 sequences of 4K to 16K
+  // tokens, 2 splits 67.5 / 66.5; 8 of 8K to 32K, 4 splits 67.8 / 64.4; 4 of them, 8 splits 43.6 / 37.0; 2 of 2K to 8K 12.3 / 11.8.  Rows of
+  // one length are 1 to 2 % faster without (32K tokens with dense ends 12.9 / 13.1), so the launcher asks for it (turn > 0)
+  // where rows may differ.
+  int split = blockIdx.x;
+  if (MODE == kByRange && NW == 4 && turn > 0) split = (split + ((b * Hkv + hkv) >> (turn - 1))) % (int)gridDim.x;
   const int tid = threadIdx.x, l = tid & 63, a = l >> 4, c = l & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, scalar: branches on it stay scalar
   const int G = Hq / Hkv;
@@ -741,17 +749,17 @@ hipError_t hs_static_scratch(void** ptr, size_t* bytes) {
 
 // Workspace: [partial O (normalised) [B*Hq][n_splits][128] fp32][partial LSE [B*Hq][n_splits] fp32].
 template <int KM, int VM, int MODE, int NW>
-static hipError_t launch_split(dim3 grid, hipStream_t st, int B, int Hq, int Hkv, int T, float sl2, int n_splits, int per,
+static hipError_t launch_split(dim3 grid, hipStream_t st, int B, int turn, int Hq, int Hkv, int T, float sl2, int n_splits, int per,
                                const uint16_t* Q, const hs_kv_dev& kv, const TailArgs& tail, float* wo, float* wl, bool f16) {
   // planes B .. grid.z - 1 are the tail's; a grid has at most 65535, so batches of more than half of that take a second launch
   const unsigned all = grid.z;
   for (unsigned z0 = 0; z0 < all; z0 += grid.z) {
     grid.z = all - z0 > 65535u ? (unsigned)B : all - z0;
     if (f16)
-      hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, true, NW>), grid, dim3(64 * NW), 0, st, B, (int)z0, Hq, Hkv, T, sl2,
+      hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, true, NW>), grid, dim3(64 * NW), 0, st, B, (int)z0, turn, Hq, Hkv, T, sl2,
                          n_splits, per, Q, kv, tail, wo, wl);
     else
-      hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, false, NW>), grid, dim3(64 * NW), 0, st, B, (int)z0, Hq, Hkv, T, sl2,
+      hipLaunchKernelGGL((decode_split_kernel<KM, VM, MODE, false, NW>), grid, dim3(64 * NW), 0, st, B, (int)z0, turn, Hq, Hkv, T, sl2,
                          n_splits, per, Q, kv, tail, wo, wl);
   }
   return hipGetLastError();
@@ -826,9 +834,10 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   float* wl = direct ? LSE : wo + (size_t)B * Hq * n_splits * HS_D;
   hipError_t e = hipSuccess;
   if (phases & 1) {
+  const int turn = kept == HS_KEPT_UNKNOWN && n_work % 2 == 0 ? (n_work % 8 == 0 ? 1 : (n_work % 4 == 0 ? 2 : 3)) : 0;
   const bool by_count = per >= bycount_per;
 #define HS_SPLIT(KM_, VM_, MODE_, NW_) \
-  launch_split<KM_, VM_, MODE_, NW_>(grid, st, B, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16)
+  launch_split<KM_, VM_, MODE_, NW_>(grid, st, B, turn, Hq, Hkv, T, sl2, n_splits, per, Q, kv, tail, wo, wl, f16)
 #define HS_GO_DYN(KM_, VM_)                                                                                            \
   e = direct ? HS_SPLIT(KM_, VM_, kByRange, 8)                                                                         \
              : (by_count ? HS_SPLIT(KM_, VM_, kByCount, 4) : HS_SPLIT(KM_, VM_, kByRange, 4));                         \

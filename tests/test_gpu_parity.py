@@ -1214,6 +1214,34 @@ def test_append_of_one_tile_to_many_rows_beyond_the_last_level_cache():
         assert torch.equal(getattr(kv, name), torch.cat([getattr(p, name) for p in parts])), name
 
 
+@pytest.mark.parametrize("n_splits", [2, 4, 6, 8, 12, 16])
+@pytest.mark.parametrize("B,Hkv,dense", [(3, 3, False), (7, 1, True), (2, 8, False)])
+def test_splits_of_rows_that_may_differ_start_further_on_from_row_to_row(n_splits, B, Hkv, dense):
+    """Every split of every row is worked on once, whatever the row it starts at: rows of different length, one of them empty,
+    even numbers of splits with every power of two in them, more and fewer than the rows have tiles."""
+    G, T = 2, 19
+    L = 64 * T
+    Q, K, V = wl.make_qkv(B, G * Hkv, Hkv, L, 128, 1, seed=1230 + B)
+    q = Q[:, :, 0, :].copy()
+    sk = np.full((B, Hkv, T), orc.DENSE if dense else orc.SPARSE24, dtype=np.int8)
+    sv = np.full((B, Hkv, T), orc.SPARSE24, dtype=np.int8)
+    for i in range(B * Hkv):
+        held = (7 * i) % (T + 1)
+        sk.reshape(-1, T)[i, held:] = 0
+        sv.reshape(-1, T)[i, held:] = 0
+    sh = hb.make_shape(B, G * Hkv, Hkv, L)
+    kv = hb.compress_kv(sh, hb.make_policy(state_k=sk, state_v=sv), _dev(K), _dev(V), out=hb.PackedKV(sh, [0, T, T, T, T]))
+    pk, pv, _ = orc.compress_kv(K, V, state_k=sk, state_v=sv)
+    _, tk, tv = wl.make_qkv(B, G * Hkv, Hkv, 64, 128, 1, seed=1231)
+    for tail in (None, np.arange(1, B + 1, dtype=np.int32)):
+        kw = {} if tail is None else dict(tail_k=_dev(tk), tail_v=_dev(tv), tail_len=torch.from_numpy(tail).cuda())
+        O, LSE = hb.decode_attn(sh, _dev(q), kv, n_splits=n_splits, **kw)
+        torch.cuda.synchronize()
+        Or, Lr = orc.attention_decode(q, pk, pv, **({} if tail is None else dict(tail_k=tk, tail_v=tv, tail_len=tail)))
+        assert_close(_f32(O), Or, f"{n_splits} splits of rows that differ")
+        assert_lse_close(LSE.cpu().numpy(), Lr, f"{n_splits} splits of rows that differ lse")
+
+
 def test_batch_rows_of_different_length_decode_and_append():
     """A batch whose sequences hold 3, 9 and 6 tiles and 17, 0 and 64 tail tokens: decode with one tail
     length per batch row; the row with the full tail (and only that one) appends it at its own position;
