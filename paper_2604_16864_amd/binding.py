@@ -100,7 +100,7 @@ def lib():
             from . import _hs_torch
         except ImportError as e:
             raise RuntimeError(f"the binding's native part is not built ({e}): run `python -m paper_2604_16864_amd.build`") from e
-        _hs_torch.bind(tuple(C.cast(getattr(L, name), C.c_void_p).value for name in _NATIVE_ENTRIES), HsShape, PackedKV)
+        _hs_torch.bind(tuple(C.cast(getattr(L, name), C.c_void_p).value for name in _NATIVE_ENTRIES), HsShape, HsPolicy, PackedKV)
         _lib, _native = L, _hs_torch
     return _lib
 
@@ -108,7 +108,7 @@ def lib():
 # entry points that the native part calls, in the order it has them
 _NATIVE_ENTRIES = ("hs_kv_bytes", "hs_workspace_bytes", "hs_decode_auto_splits", "hs_decode_attn", "hs_decode_attn_static",
                    "hs_decode_attn_tail", "hs_decode_attn_tail_rows", "hs_prefill_workspace_bytes", "hs_prefill_attn_ws",
-                   "hs_append_tiles", "hs_append_tile_rows")
+                   "hs_append_tiles", "hs_append_tile_rows", "hs_tile_counts", "hs_compress_kv", "hs_recompress_kv")
 
 
 def _fast():
@@ -280,6 +280,14 @@ class PackedKV:
         self.v_map = torch.empty(rows_T, dtype=torch.int32, device=device)
         self.nbytes = sum(nb)
 
+    @classmethod
+    def _filled(cls, shape, made):
+        """A cache that a native call has made: (counts, buffers, uniform)."""
+        kv = cls.__new__(cls)
+        kv.shape = shape
+        kv.counts, (kv.k_dense, kv.k_nnz, kv.k_meta, kv.k_map, kv.v_dense, kv.v_nnz, kv.v_meta, kv.v_map, kv.nbytes), kv.uniform = made
+        return kv
+
     def struct(self):
         return HsKV(_ptr(self.k_dense), _ptr(self.k_nnz), _ptr(self.k_meta), _ptr(self.k_map),
                     _ptr(self.v_dense), _ptr(self.v_nnz), _ptr(self.v_meta), _ptr(self.v_map),
@@ -292,6 +300,10 @@ def _workspace(nbytes, device):
 
 def compress_kv(shape, policy, K, V, out=None, workspace=None):
     """K, V: bf16 device tensors [B, Hkv, L, D] (last dim contiguous).  Returns PackedKV."""
+    if out is None and workspace is None:
+        made = _done(_fast().compress(shape, policy, K, V))
+        if made is not None:
+            return PackedKV._filled(shape, made)
     assert K.dtype == torch_dtype(shape) and V.dtype == K.dtype and K.is_cuda and V.is_cuda
     assert K.stride(-1) == 1 and V.stride(-1) == 1 and K.stride() == V.stride()
     if out is None:
@@ -344,6 +356,10 @@ def recompress_kv(shape, kv, target, counts=None, overflow=None, out=None, works
                 counts[1] = min(counts[1], prot)
             if target.sparse_frac_v == 1.0:
                 counts[3] = min(counts[3], prot)
+    if out is None and workspace is None:
+        made = _done(_fast().recompress(shape, kv, target, counts, overflow))
+        if made is not None:
+            return PackedKV._filled(shape, made)
     if out is None:
         out = PackedKV(shape, counts, kv.k_map.device, kv.k_map)
     counts = out.counts

@@ -1,6 +1,7 @@
 // Argument marshalling of the Python binding in native code: the per-call part of decode, prefill, append, compress and
 // re-compress.  What a call on a small cache costs is mostly this part: in Python with ctypes a decode call of 7 us of
-// kernels took 13.3 us (8 data_ptr() calls and a ctypes structure for the cache, three allocations, two library calls).
+// kernels took 13.3 us (8 data_ptr() calls and a ctypes structure for the cache, three allocations, two library calls) and takes
+// 9 here, compressing 2K tokens 16.1 and 10.3.
 //
 // Every function returns None for a call it does not take as it is (other types than exact tensors, an argument that fails a
 // check of the binding, a number that is neither int nor float), and the binding's Python code then takes it, so what is
@@ -32,8 +33,11 @@ struct Entries {  // of libhs.so, as the binding has loaded it
   decltype(&hs_prefill_attn_ws) prefill;
   decltype(&hs_append_tiles) append;
   decltype(&hs_append_tile_rows) append_rows;
+  decltype(&hs_tile_counts) tile_counts;
+  decltype(&hs_compress_kv) compress;
+  decltype(&hs_recompress_kv) recompress;
 } g_hs;
-PyTypeObject *g_shape_type, *g_kv_type;
+PyTypeObject *g_shape_type, *g_policy_type, *g_kv_type;
 
 enum { S_K_DENSE, S_K_NNZ, S_K_META, S_K_MAP, S_V_DENSE, S_V_NNZ, S_V_META, S_V_MAP, S_COUNTS, S_UNIFORM, N_NAMES };
 const char* const kNames[N_NAMES] = {"k_dense", "k_nnz", "k_meta", "k_map", "v_dense", "v_nnz", "v_meta", "v_map", "counts", "uniform"};
@@ -60,14 +64,22 @@ bool get_float(PyObject* o, float* v) {
   return true;
 }
 
-bool get_shape(PyObject* o, hs_shape* s) {  // the bytes of the binding's ctypes structure
-  if (Py_TYPE(o) != g_shape_type) return false;
+bool get_struct(PyObject* o, PyTypeObject* type, void* s, size_t size) {  // the bytes of one of the binding's ctypes structures
+  if (Py_TYPE(o) != type) return false;
   Py_buffer b;
   if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) { PyErr_Clear(); return false; }
-  const bool ok = b.len == (Py_ssize_t)sizeof(hs_shape);
-  if (ok) memcpy(s, b.buf, sizeof(*s));
+  const bool ok = b.len == (Py_ssize_t)size;
+  if (ok) memcpy(s, b.buf, size);
   PyBuffer_Release(&b);
   return ok;
+}
+bool get_shape(PyObject* o, hs_shape* s) { return get_struct(o, g_shape_type, s, sizeof(*s)); }
+bool get_policy(PyObject* o, hs_policy* p) { return get_struct(o, g_policy_type, p, sizeof(*p)); }
+bool get_counts(PyObject* o, int32_t c[5]) {
+  if (!PyList_CheckExact(o) || PyList_GET_SIZE(o) != 5) return false;
+  for (int i = 0; i < 5; i++)
+    if (!get_int(PyList_GET_ITEM(o, i), &c[i])) return false;
+  return true;
 }
 
 // the cache's buffers as the object holds them now
@@ -273,26 +285,28 @@ PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   END_HANDLE_TH_ERRORS
 }
 
-// pools(shape, counts, like): the eight buffers of a cache beside the tensor `like` (None for an empty pool) and their bytes
-PyObject* pools(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
-  HANDLE_TH_ERRORS
-  hs_shape s;
-  int32_t counts[5];
-  if (n_args != 3 || !get_shape(a[0], &s) || !PyList_CheckExact(a[1]) || PyList_GET_SIZE(a[1]) != 5 || !exact_tensor(a[2])) Py_RETURN_NONE;
-  for (int i = 0; i < 5; i++)
-    if (!get_int(PyList_GET_ITEM(a[1], i), &counts[i])) Py_RETURN_NONE;
+// The eight buffers of a cache beside the tensor `like`, as a tuple in the order of kNames (None for an empty pool) with their
+// bytes behind them, and the cache as the library sees it.  nullptr with no Python error: a count the library refuses.
+PyObject* make_pools(const hs_shape& s, const int32_t counts[5], const at::Tensor& like, int uniform, hs_kv* kv) {
   size_t bytes[8], total = 0;
-  if (g_hs.kv_bytes(&s, counts, bytes) != 0) Py_RETURN_NONE;
-  const auto opt = tensor(a[2]).options();
+  if (g_hs.kv_bytes(&s, counts, bytes) != 0) return nullptr;
+  const auto opt = like.options();
+  void** ptr[8] = {&kv->k_dense, &kv->k_nnz, &kv->k_meta, (void**)&kv->k_map, &kv->v_dense, &kv->v_nnz, &kv->v_meta, (void**)&kv->v_map};
   PyObject* r = PyTuple_New(9);
   if (r == nullptr) return nullptr;
   try {
     for (int i = 0; i < 8; i++) {
       const bool map = i == S_K_MAP || i == S_V_MAP;
       PyObject* t;
-      if (map) t = THPVariable_Wrap(at::empty({s.B, s.Hkv, s.L / 64}, opt.dtype(at::kInt)));
-      else if (bytes[i] != 0) t = THPVariable_Wrap(at::empty({(int64_t)bytes[i]}, opt.dtype(at::kByte)));
-      else { t = Py_None; Py_INCREF(t); }
+      *ptr[i] = nullptr;
+      if (map || bytes[i] != 0) {
+        const at::Tensor b = map ? at::empty({s.B, s.Hkv, s.L / 64}, opt.dtype(at::kInt)) : at::empty({(int64_t)bytes[i]}, opt.dtype(at::kByte));
+        *ptr[i] = b.data_ptr();
+        t = THPVariable_Wrap(b);
+      } else {
+        t = Py_None;
+        Py_INCREF(t);
+      }
       if (t == nullptr) { Py_DECREF(r); return nullptr; }
       PyTuple_SET_ITEM(r, i, t);
       total += bytes[i];
@@ -302,15 +316,112 @@ PyObject* pools(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     throw;
   }
   PyTuple_SET_ITEM(r, 8, PyLong_FromSize_t(total));
+  kv->cap_dense_k = counts[1]; kv->cap_sparse_k = counts[2]; kv->cap_dense_v = counts[3]; kv->cap_sparse_v = counts[4];
+  kv->uniform = uniform;
+  return r;
+}
+
+// slot == tile index: nothing skipped, one kind of tile per tensor
+int counts_uniform(const int32_t c[5], int32_t T) {
+  const int32_t k = c[1] > c[2] ? c[1] : c[2], v = c[3] > c[4] ? c[3] : c[4];
+  return c[0] == 0 && (c[1] == 0 || c[2] == 0) && (c[3] == 0 || c[4] == 0) && k == T && v == T;
+}
+
+// pools(shape, counts, like): the buffers of a cache that the caller fills
+PyObject* pools(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+  HANDLE_TH_ERRORS
+  hs_shape s;
+  hs_kv kv;
+  int32_t counts[5];
+  if (n_args != 3 || !get_shape(a[0], &s) || !get_counts(a[1], counts) || !exact_tensor(a[2])) Py_RETURN_NONE;
+  PyObject* r = make_pools(s, counts, tensor(a[2]), 0, &kv);
+  if (r == nullptr && !PyErr_Occurred()) Py_RETURN_NONE;
   return r;
   END_HANDLE_TH_ERRORS
 }
 
-// bind(addresses in the order of Entries, HsShape, PackedKV)
+// (counts, pools, uniform) of a new cache, or the library's status; takes the reference to `bufs`
+PyObject* new_cache(int rc, const int32_t c[5], PyObject* bufs, int uniform) {
+  if (rc != 0) {
+    Py_DECREF(bufs);
+    return PyLong_FromLong(rc);
+  }
+  return Py_BuildValue("([iiiii]Ni)", c[0], c[1], c[2], c[3], c[4], bufs, uniform);
+}
+
+// compress(shape, policy, K, V) -> (counts, pools, uniform); a policy of fractions, into a new cache
+PyObject* compress(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+  HANDLE_TH_ERRORS
+  hs_shape s;
+  hs_policy pol;
+  hs_kv kv;
+  if (n_args != 4 || !get_shape(a[0], &s) || !get_policy(a[1], &pol) || pol.state_k != nullptr || !exact_tensor(a[2]) || !exact_tensor(a[3]))
+    Py_RETURN_NONE;
+  const at::Tensor &k = tensor(a[2]), &v = tensor(a[3]);
+  if (k.scalar_type() != element_type(s) || v.scalar_type() != k.scalar_type() || !k.is_cuda() || !v.is_cuda() || k.dim() != 4 ||
+      k.stride(3) != 1 || k.strides() != v.strides())
+    Py_RETURN_NONE;
+  int32_t counts[5];
+  size_t need = 0;
+  if (g_hs.tile_counts(&s, &pol, counts) != 0 || g_hs.workspace_bytes(&s, 0, 0, &need) != 0) Py_RETURN_NONE;
+  const int uniform = counts_uniform(counts, s.L / 64);
+  PyObject* bufs = make_pools(s, counts, k, uniform, &kv);
+  if (bufs == nullptr) {
+    if (PyErr_Occurred()) return nullptr;
+    Py_RETURN_NONE;
+  }
+  at::Tensor ws;
+  try {
+    ws = bytes_beside(k, need < 16 ? 16 : need);
+  } catch (...) {
+    Py_DECREF(bufs);
+    throw;
+  }
+  const int64_t strides[3] = {k.stride(0), k.stride(1), k.stride(2)};
+  const void *kp = k.data_ptr(), *vp = v.data_ptr();
+  void *wp = ws.data_ptr(), *st = current_stream();
+  const int rc = without_gil([&] { return g_hs.compress(&s, &pol, kp, vp, strides, &kv, wp, st); });
+  return new_cache(rc, counts, bufs, uniform);
+  END_HANDLE_TH_ERRORS
+}
+
+// recompress(shape, cache, target, counts, overflow) -> (counts, pools, uniform); a target of whole fractions, into a new cache
+PyObject* recompress(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+  HANDLE_TH_ERRORS
+  hs_shape s;
+  hs_policy pol;
+  hs_kv src, dst;
+  int32_t c[5];
+  if (n_args != 5 || !get_shape(a[0], &s) || !get_kv(a[1], &src) || !get_policy(a[2], &pol) || pol.state_k != nullptr ||
+      pol.tile_scores != nullptr || !get_counts(a[3], c) || !none_or_tensor(a[4]))
+    Py_RETURN_NONE;
+  PyObject* map = PyObject_GetAttr(a[1], g_names[S_K_MAP]);
+  if (map == nullptr) return nullptr;
+  if (!exact_tensor(map)) { Py_DECREF(map); Py_RETURN_NONE; }
+  const at::Tensor like = tensor(map);
+  Py_DECREF(map);
+  const int32_t T = s.L / 64, k = c[1] > c[2] ? c[1] : c[2], v = c[3] > c[4] ? c[3] : c[4];
+  const bool whole = pol.skip_frac == 0.0 && (pol.sparse_frac_k == 0.0 || pol.sparse_frac_k == 1.0) &&
+                     (pol.sparse_frac_v == 0.0 || pol.sparse_frac_v == 1.0);
+  // slot == tile survives when nothing was skipped before and each tensor ends up in one kind
+  const int uniform = src.uniform != 0 && whole && (c[1] == 0 || c[2] == 0) && (c[3] == 0 || c[4] == 0) && k == T && v == T;
+  PyObject* bufs = make_pools(s, c, like, uniform, &dst);
+  if (bufs == nullptr) {
+    if (PyErr_Occurred()) return nullptr;
+    Py_RETURN_NONE;
+  }
+  int32_t* over = (int32_t*)address(a[4]);
+  void* st = current_stream();
+  const int rc = without_gil([&] { return g_hs.recompress(&s, &pol, &src, &dst, nullptr, over, st); });
+  return new_cache(rc, c, bufs, uniform);
+  END_HANDLE_TH_ERRORS
+}
+
+// bind(addresses in the order of Entries, HsShape, HsPolicy, PackedKV)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   constexpr Py_ssize_t n = sizeof(Entries) / sizeof(void*);
-  if (n_args != 3 || !PyTuple_Check(a[0]) || PyTuple_GET_SIZE(a[0]) != n || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
-    PyErr_SetString(PyExc_TypeError, "bind(addresses, shape type, cache type)");
+  if (n_args != 4 || !PyTuple_Check(a[0]) || PyTuple_GET_SIZE(a[0]) != n || !PyType_Check(a[1]) || !PyType_Check(a[2]) || !PyType_Check(a[3])) {
+    PyErr_SetString(PyExc_TypeError, "bind(addresses, shape type, policy type, cache type)");
     return nullptr;
   }
   void* p[n];
@@ -322,17 +433,17 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     }
   }
   memcpy(&g_hs, p, sizeof(p));
-  Py_INCREF(a[1]);
-  Py_INCREF(a[2]);
-  Py_XDECREF(g_shape_type);
-  Py_XDECREF(g_kv_type);
-  g_shape_type = (PyTypeObject*)a[1];
-  g_kv_type = (PyTypeObject*)a[2];
+  PyTypeObject** types[3] = {&g_shape_type, &g_policy_type, &g_kv_type};
+  for (int i = 0; i < 3; i++) {
+    Py_INCREF(a[1 + i]);
+    Py_XDECREF(*types[i]);
+    *types[i] = (PyTypeObject*)a[1 + i];
+  }
   Py_RETURN_NONE;
 }
 
 #define HS_FN(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
-PyMethodDef kMethods[] = {HS_FN(bind), HS_FN(decode), HS_FN(decode_static), HS_FN(prefill), HS_FN(append), HS_FN(pools),
+PyMethodDef kMethods[] = {HS_FN(bind), HS_FN(decode), HS_FN(decode_static), HS_FN(prefill), HS_FN(append), HS_FN(pools), HS_FN(compress), HS_FN(recompress),
                           {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_hs_torch", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
 

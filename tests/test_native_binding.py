@@ -41,6 +41,12 @@ def test_calls_the_native_part_leaves_alone_are_refused_as_before():
     assert n.decode(sh, q, kv, 0.0, 0, True, None, None, None, None, None, None) is None
     assert n.decode(sh, q, object(), 0.0, 0, True, None, None, None, None, None, None) is None
     assert n.decode(q, q, kv, 0.0, 0, True, None, None, None, None, None, None) is None
+    k = torch.zeros(2, 2, 768, 128, dtype=torch.bfloat16)
+    for a, b in ((k, k), (k.float(), k.float()), (k, k.transpose(0, 1)), (k[..., ::2], k[..., ::2])):
+        with pytest.raises(AssertionError):
+            hb.compress_kv(sh, hb.make_policy(), a, b)
+    assert n.compress(sh, hb.make_policy(), k, k) is None and n.compress(sh, sh, k, k) is None
+    assert n.recompress(sh, kv, hb.make_policy(), (0, 0, 12, 0, 12), None) is None
     assert n.prefill() is None and n.append(1, 2) is None and n.pools(sh, [0, 0, 12, 0], q) is None
 
 
@@ -89,7 +95,10 @@ def test_native_and_python_calls_give_the_same_bits(dtype, policy, monkeypatch):
         hb.append_tile(sh, grow, old, tk, tv)
         hb.append_tile(sh, grow, 5, K[:, :, :128], V[:, :, :128], state_k=hb.DENSE)
         yield hb.unpack_kv(sh, grow)
-        yield hb.unpack_kv(sh, hb.recompress_kv(sh, kv, hb.make_policy()))
+        for made in (kv, hb.recompress_kv(sh, kv, hb.make_policy()), hb.recompress_kv(sh, kv, hb.make_policy(dense_first_tiles=2)),
+                     hb.recompress_kv(sh, kv, hb.make_policy(sparse_frac_k=0.0), counts=[0, 12, 12, 12, 12])):
+            yield hb.unpack_kv(sh, made)
+            yield made.k_map, made.v_map, torch.tensor(made.counts + [made.uniform, made.nbytes])
     stream = torch.cuda.Stream()
     stream.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(stream):
@@ -109,8 +118,8 @@ def test_native_and_python_calls_give_the_same_bits(dtype, policy, monkeypatch):
 @pytest.mark.gpu
 def test_library_errors_are_raised_through_the_native_part():
     sh = _shape()
-    kv = hb.compress_kv(sh, hb.make_policy(), torch.zeros(2, 2, 768, 128, dtype=torch.bfloat16, device="cuda"),
-                        torch.zeros(2, 2, 768, 128, dtype=torch.bfloat16, device="cuda"))
+    K = torch.zeros(2, 2, 768, 128, dtype=torch.bfloat16, device="cuda")
+    kv = hb.compress_kv(sh, hb.make_policy(), K, K)
     q = torch.zeros(2, 8, 128, dtype=torch.bfloat16, device="cuda")
     for kw in (dict(n_splits=-1), dict(scale=-1.0)):
         with pytest.raises(hb.HsError):
@@ -119,6 +128,13 @@ def test_library_errors_are_raised_through_the_native_part():
         hb.decode_attn(sh, q, kv, tail_len=65)
     with pytest.raises(hb.HsError):
         hb.prefill_attn(sh, torch.zeros(2, 8, 100, 128, dtype=torch.bfloat16, device="cuda"), kv)
+    for kw in (dict(skip_frac=2.0), dict(sparse_frac_k=-0.5), dict(dense_first_tiles=-1)):
+        with pytest.raises(hb.HsError):
+            hb.compress_kv(sh, hb.make_policy(**kw), K, K)
+        with pytest.raises(hb.HsError):
+            hb.recompress_kv(sh, kv, hb.make_policy(**kw), counts=[0, 0, 12, 0, 12])
+    with pytest.raises(hb.HsError):                              # ranks tiles, without scores
+        hb.recompress_kv(sh, kv, hb.make_policy(skip_frac=0.5))
     with pytest.raises(hb.HsError):                              # a uniform cache does not grow
         hb.append_tile(sh, kv, 3, torch.zeros(2, 2, 64, 128, dtype=torch.bfloat16, device="cuda"),
                        torch.zeros(2, 2, 64, 128, dtype=torch.bfloat16, device="cuda"))
