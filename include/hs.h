@@ -294,8 +294,8 @@ HS_API int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start
                        const void* Q, const hs_kv* kv, void* O, float* LSE,
                        void* workspace, size_t workspace_bytes, void* stream);
 
-/* Workspace bytes with which hs_prefill_attn_ws uses as many ranges as serve the call best; 0 where
- * one is best.  At most 4096 workgroups write partials, 128 queries x 516 bytes each: never more than
+/* Workspace bytes with which hs_prefill_attn_ws may use as many ranges as can serve the call best (it may
+ * take fewer); 0 where one is best.  At most 4096 workgroups write partials, 128 queries x 516 bytes each: never more than
  * 270532608 bytes.  Of kv only the capacities and `uniform` are read.  [host, pure] */
 HS_API int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv,
                                size_t* bytes);

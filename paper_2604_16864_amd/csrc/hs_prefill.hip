@@ -13,7 +13,8 @@ static int tiles_to_expect(int T, int seen, const hs_kv_dev& kv) {  // of `seen`
 // 1.0 us alone on its compute unit and 1.2 us beside a second one, so 512 workgroups at a time are two on every unit;
 // splitting costs 8 us for the merge launch and the caller's scratch (5 us on the GPU alone) and 0.028 us per workgroup
 // for writing and reading its 66 KB of partials.
-// The number of ranges that makes this sum smallest is taken.  Measured, one range / the chosen number: 64 queries on
+// The number of ranges that makes this sum smallest is what the workspace is sized for; plan_prefill below takes it or fewer.
+// Measured with slabs of 32 queries, one range / the chosen number: 64 queries on
 // 32768 tokens 501 / 41.5 us (32 ranges), on 2048 tokens 37 / 18.8 us (8); 256 queries on 32768 tokens 504 / 101 us (8);
 // 1024 queries on 32768 tokens 510 / 347 us (2); whole prompts of 256 to 2048 tokens are fastest unsplit (2048: 46 us, two
 // ranges 56 us), and there the sum says one range too.  Beyond 512 workgroups one range is only
