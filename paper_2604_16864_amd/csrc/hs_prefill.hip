@@ -71,7 +71,10 @@ PrefillPlan plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int
       for (int k = 1; 512 * k < wgs; k++)
         us = fmax(us, (k + 1) * ((longest - (longest - shortest) * 512 * k / wgs) / n * kPair[nb] + kStart[nb]));
       if (n > 1) us += 3.0 + 0.014 * nb * wgs;
-      if (nb == 1) us *= 1.03;  // the wider slab where the two are even
+      // The wider slab in all the ranges allowed where things are even; ranges of the narrow one, two to a compute unit, are
+      // where the sum is least sure (128 queries x 4 heads on 47104 tokens 25.8 / 28.0, 256 x 4 on 32768 29.6 / 27.0).
+      if (nb == 1) us *= n > 1 && wgs > 256 ? 1.12 : 1.03;
+      else if (n != most) us *= 1.03;
       if (best_us == 0.0 || us < best_us) { best = {nb, n}; best_us = us; }
     }
   }
