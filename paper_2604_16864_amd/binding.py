@@ -423,9 +423,10 @@ def prefill_attn(shape, Q, kv, causal=True, scale=0.0, want_lse=True, out=None, 
     Few queries on a long context take scratch from torch's allocator (prefill_workspace_bytes, at most 270 MB) for the
     length of the call; without the memory for it the call runs all the same, on fewer workgroups."""
     r = _fast().prefill(shape, Q, kv, causal, scale, want_lse, out, lse, q_start, None)
-    if type(r) is tuple and len(r) == 1:    # the scratch it wants
+    if type(r) is tuple and len(r) == 3:    # the scratch it wants, and the outputs, which are made before it
+        need, out, lse = r
         try:
-            ws = _workspace(r[0], Q.device)
+            ws = _workspace(need, Q.device)
         except torch.OutOfMemoryError:      # the call also works without: fewer workgroups, no scratch
             ws = False
         r = _fast().prefill(shape, Q, kv, causal, scale, want_lse, out, lse, q_start, ws)

@@ -213,8 +213,9 @@ PyObject* decode_static(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   END_HANDLE_TH_ERRORS
 }
 
-// prefill(shape, Q, kv, causal, scale, want_lse, out, lse, q_start, scratch): scratch None = not asked for yet, then the
-// bytes the call wants are returned if it wants any; a tensor, or False for a call that runs without.
+// prefill(shape, Q, kv, causal, scale, want_lse, out, lse, q_start, scratch): scratch None = not asked for yet; if the call wants
+// any, (bytes, O, LSE) is returned with the outputs to hand in again: they come before the scratch, which the call can do
+// without.  A tensor, or False for a call that runs without.
 PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   HANDLE_TH_ERRORS
   hs_shape s;
@@ -231,16 +232,22 @@ PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   const int causal = a[3] == Py_True;
   size_t need = 0;
   void* ws_ptr = nullptr;
+  if (a[9] == Py_None && g_hs.prefill_workspace(&s, Lq, at_pos, causal, &kv, &need) != 0) Py_RETURN_NONE;
+  at::Tensor o, lse;
+  if (a[6] == Py_None) o = at::empty_like(q);
+  if (a[7] == Py_None && a[5] == Py_True) lse = at::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(at::kFloat));
   if (a[9] == Py_None) {
-    if (g_hs.prefill_workspace(&s, Lq, at_pos, causal, &kv, &need) != 0) Py_RETURN_NONE;
-    if (need != 0) return Py_BuildValue("(n)", (Py_ssize_t)need);
+    if (need != 0) {
+      PyObject* outs = result(0, a[6], o, a[7], lse);
+      if (outs == nullptr) return nullptr;
+      PyObject* r = Py_BuildValue("(nOO)", (Py_ssize_t)need, PyTuple_GET_ITEM(outs, 0), PyTuple_GET_ITEM(outs, 1));
+      Py_DECREF(outs);
+      return r;
+    }
   } else if (a[9] != Py_False) {
     ws_ptr = address(a[9]);
     need = (size_t)tensor(a[9]).nbytes();
   }
-  at::Tensor o, lse;
-  if (a[6] == Py_None) o = at::empty_like(q);
-  if (a[7] == Py_None && a[5] == Py_True) lse = at::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(at::kFloat));
   void* o_ptr = a[6] == Py_None ? o.data_ptr() : address(a[6]);
   float* lse_ptr = (float*)(lse.defined() ? lse.data_ptr() : address(a[7]));
   const void* q_ptr = q.data_ptr();

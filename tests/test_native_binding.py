@@ -116,6 +116,30 @@ def test_native_and_python_calls_give_the_same_bits(dtype, policy, monkeypatch):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_prefill_makes_its_outputs_before_it_takes_scratch(native, monkeypatch):
+    """The call can do without scratch but not without its outputs: where memory holds one of them, they have it."""
+    sh = hb.make_shape(1, 8, 2, 64 * 40)
+    K = torch.randn(1, 2, sh.L, 128, device="cuda").to(torch.bfloat16)
+    kv = hb.compress_kv(sh, hb.make_policy(), K, K)
+    Q = torch.randn(1, 8, 64, 128, device="cuda").to(torch.bfloat16)
+    assert hb.prefill_workspace_bytes(sh, 64, sh.L - 64, kv) > 0
+    before, held = torch.cuda.memory_allocated(), []
+
+    def none_left(nbytes, device):
+        held.append(torch.cuda.memory_allocated() - before)
+        raise torch.OutOfMemoryError("no scratch to be had")
+    monkeypatch.setattr(hb, "_workspace", none_left)
+    if not native:
+        monkeypatch.setattr(hb, "_native", _PythonOnly())
+    for want_lse in (True, False):
+        O, LSE = hb.prefill_attn(sh, Q, kv, want_lse=want_lse)
+        assert held.pop() == torch.cuda.memory_allocated() - before >= O.nbytes + (LSE.nbytes if want_lse else 0) and (LSE is None) != want_lse
+        assert torch.isfinite(O).all()
+        del O, LSE
+
+
+@pytest.mark.gpu
 def test_library_errors_are_raised_through_the_native_part():
     sh = _shape()
     K = torch.zeros(2, 2, 768, 128, dtype=torch.bfloat16, device="cuda")
