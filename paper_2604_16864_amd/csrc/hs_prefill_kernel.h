@@ -241,10 +241,15 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
   constexpr float kShift = 4.f;
   constexpr float kRedo = 0x1p15f;
   // FLAG: "a column has no reference yet" is kept as one scalar flag, tested once in front of the softmax, instead of a
-  // comparison and a select per column in it.  us with the comparisons / the flag: all 2:4, 16K prompt 1318 / 1305, 16 prompts
-  // of 1K 157 / 150; 2:4 with dense ends, 8K 391 / 379; with a tensor all dense the flag costs registers that are not there
-  // (keys dense, 8K 409 / 433; both dense 486 / 490).
-  constexpr bool FLAG = (KM == 0 && VM == 0) || KM == 2 || VM == 2;
+  // comparison and a select per column in it; LITERAL: the causal mask compares with literals instead of with 16 constants
+  // held in registers.  us with neither / both: all 2:4, 16K prompt 1318 / 1305, 16 prompts of 1K 157 / 150; bf16 with mixed values
+  // (2:4 with dense ends) 8K 404 / 375, 192 queries on 25728 tokens 83.1 / 76.5.  With a tensor all dense the flag costs registers
+  // that are not there (keys dense, 8K 409 / 433; both dense 486 / 490).  Other mixed tensors in slabs of 32 lose by both: fp16
+  // with dense ends 356.5 / 352.2 at 8K, but 158.1 / 163.3 for 1408 queries on 9024 tokens and 85.3 / 87.7 for 192 on 25728; half of
+  // the keys dense, 128 queries on 6912 tokens 31.4 / 32.2, fp16, 16 x 512 on 3776 88.7 / 90.4, 8K 399.6 / 401.2.
+  constexpr bool MIXED = KM == 2 || VM == 2;
+  constexpr bool FLAG = (KM == 0 && VM == 0) || (MIXED && (NB == 1 || (VM == 2 && !F16)));
+  constexpr bool LITERAL = FLAG || !MIXED;
   constexpr int QS = 16 * NB;  // query positions per slab
   constexpr int NS = n_stages<KM, VM>(), D = NS - 1;  // ring size, prefetch distance in tiles
   // MID: the per-tile barrier sits between softmax and GEMM2 instead of at the end of the
@@ -499,14 +504,15 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
         __builtin_amdgcn_s_setprio(HS_PRIO_VALU);
         // causal mask inside a tile that reaches past the slab's first query
         if (causal && HS_BT * j + HS_BT - 1 > qpos + off) {
-          const int lim = qpos + off - HS_BT * j + c - 4 * a;  // query 16nb+c sees in-tile token 16m+4a+i iff 16m+i <= lim + 16nb
+          // query 16nb+c sees in-tile token 16m+4a+i iff 16m+4a+i <= lim + 16nb
+          const int lim = qpos + off - HS_BT * j + c, lim_a = lim - 4 * a;
 #pragma unroll
           for (int nb = 0; nb < NB; nb++)
 #pragma unroll
             for (int m = 0; m < 4; m++)
 #pragma unroll
               for (int i = 0; i < 4; i++)
-                if (16 * m + i - 16 * nb > lim) s[m][nb][i] = -INFINITY;
+                if (LITERAL ? 16 * m + i - 16 * nb > lim_a : 16 * m + 4 * a + i > lim + 16 * nb) s[m][nb][i] = -INFINITY;
         }
         // ---------------- P = exp2(S*scale - m_run), reference m_run updated lazily ----------------
         // P is first computed against the current reference of each query column, with no look at
