@@ -286,7 +286,7 @@ HS_API int hs_prefill_attn_at(const hs_shape* shape, int32_t Lq, int32_t q_start
 
 /* hs_prefill_attn_at for callers that hand over scratch memory.  A call with few queries on a long context (a
  * chat turn, a small chunk) has too few query blocks to fill the GPU; with a workspace of
- * hs_prefill_workspace_bytes the tiles are cut into ranges that run side by side, and their partial
+ * hs_prefill_plan's bytes the tiles are cut into ranges that run side by side, and their partial
  * results are merged (the split of decode, Sec. IV-C).  workspace: device, 16-byte aligned, no
  * initial content needed, not shared between two calls in flight.  With fewer bytes (or NULL)
  * fewer ranges (or one) are used: any size is accepted. */
@@ -294,11 +294,17 @@ HS_API int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start
                        const void* Q, const hs_kv* kv, void* O, float* LSE,
                        void* workspace, size_t workspace_bytes, void* stream);
 
-/* Workspace bytes with which hs_prefill_attn_ws may use as many ranges as can serve the call best (it may
- * take fewer); 0 where one is best.  At most 4096 workgroups write partials, 128 queries x 516 bytes each: never more than
+/* Workspace bytes that hs_prefill_attn_ws never takes more than; 0 where it runs in one range whatever it is given.
+ * At most 4096 workgroups write partials, 128 queries x 516 bytes each: never more than
  * 270532608 bytes.  Of kv only the capacities and `uniform` are read.  [host, pure] */
 HS_API int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv,
                                size_t* bytes);
+
+/* What hs_prefill_attn_ws does with a workspace of workspace_bytes (SIZE_MAX: as much as it can use): *slab = query positions
+ * a wavefront works on (16 or 32), *ranges, *bytes = the workspace that these ranges take, 0 for one.  With a workspace of
+ * *bytes it does the same.  Any of the three may be NULL.  Of kv only the capacities and `uniform` are read.  [host, pure] */
+HS_API int hs_prefill_plan(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv, size_t workspace_bytes,
+                    int32_t* slab, int32_t* ranges, size_t* bytes);
 
 /* Decode attention (split-KV kernel + merge, Sec. IV-C): one query token per
  * (b, query head) against all L cached tokens.  Q, O: bf16 [B, Hq, D];

@@ -71,6 +71,8 @@ EXPORTS = {
                                      C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "hs_prefill_workspace_bytes": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_int, C.POINTER(HsKV),
                                              C.POINTER(C.c_size_t)]),
+    "hs_prefill_plan": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_int, C.POINTER(HsKV), C.c_size_t,
+                                  C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_size_t)]),
     "hs_decode_attn": (C.c_int, [C.POINTER(HsShape), C.c_float, C.c_int32, C.c_void_p, C.POINTER(HsKV), C.c_void_p,
                                  C.c_void_p, C.c_void_p, C.c_void_p]),
     "hs_decode_attn_static": (C.c_int, [C.POINTER(HsShape), C.c_float, C.c_int32, C.c_void_p, C.POINTER(HsKV), C.c_void_p,
@@ -107,7 +109,7 @@ def lib():
 
 # entry points that the native part calls, in the order it has them
 _NATIVE_ENTRIES = ("hs_kv_bytes", "hs_workspace_bytes", "hs_decode_auto_splits", "hs_decode_attn", "hs_decode_attn_static",
-                   "hs_decode_attn_tail", "hs_decode_attn_tail_rows", "hs_prefill_workspace_bytes", "hs_prefill_attn_ws",
+                   "hs_decode_attn_tail", "hs_decode_attn_tail_rows", "hs_prefill_plan", "hs_prefill_attn_ws",
                    "hs_append_tiles", "hs_append_tile_rows", "hs_tile_counts", "hs_compress_kv", "hs_recompress_kv")
 
 
@@ -409,12 +411,17 @@ def unpack_kv(shape, kv):
     return K, V
 
 
+def prefill_plan(shape, Lq, q_start, kv, causal=True, workspace_bytes=C.c_size_t(-1).value):
+    """(slab, ranges, bytes) of hs_prefill_plan: how a prefill call with that much scratch runs.  kv: PackedKV."""
+    slab, ranges, need = C.c_int32(0), C.c_int32(0), C.c_size_t(0)
+    _check(lib().hs_prefill_plan(C.byref(shape), Lq, q_start, int(bool(causal)), C.byref(kv.struct()), workspace_bytes, C.byref(slab),
+                                 C.byref(ranges), C.byref(need)))
+    return slab.value, ranges.value, need.value
+
+
 def prefill_workspace_bytes(shape, Lq, q_start, kv, causal=True):
-    """Scratch that prefill_attn takes for this call (hs_prefill_workspace_bytes): 0 where the queries fill the GPU, at
-    most 270 MB.  kv: PackedKV."""
-    out = C.c_size_t(0)
-    _check(lib().hs_prefill_workspace_bytes(C.byref(shape), Lq, q_start, int(bool(causal)), C.byref(kv.struct()), C.byref(out)))
-    return out.value
+    """Scratch that prefill_attn takes for this call: 0 where the queries fill the GPU, at most 270 MB.  kv: PackedKV."""
+    return prefill_plan(shape, Lq, q_start, kv, causal)[2]
 
 
 def prefill_attn(shape, Q, kv, causal=True, scale=0.0, want_lse=True, out=None, lse=None, q_start=None):
@@ -439,9 +446,7 @@ def prefill_attn(shape, Q, kv, causal=True, scale=0.0, want_lse=True, out=None, 
         lse = Q.new_empty(Q.shape[:3], dtype=torch.float32)
     kvs = kv.struct()
     at = shape.L - Lq if q_start is None else int(q_start)
-    need = C.c_size_t(0)
-    _check(lib().hs_prefill_workspace_bytes(C.byref(shape), Lq, at, int(bool(causal)), C.byref(kvs), C.byref(need)))
-    need, ws = need.value, None
+    need, ws = prefill_workspace_bytes(shape, Lq, at, kv, causal), None
     if need:
         try:
             ws = _workspace(need, Q.device)

@@ -85,8 +85,16 @@ size_t prefill_split_bytes(const hs_shape* s, int32_t Lq) {
   return (size_t)s->B * s->Hq * (size_t)Lq * (HS_D + 1) * sizeof(float);
 }
 
-int prefill_splits(const hs_shape* s, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv) {
-  return hs_prefill_auto_splits(s->B, s->Hq, s->Hkv, s->L / HS_BT, Lq, q_start, causal != 0, hs_make_kv_dev(kv));
+int prefill_args(const hs_shape* s, int32_t Lq, int32_t q_start) {
+  if (Lq <= 0 || Lq > s->L || q_start < 0 || q_start > s->L - Lq) return HS_EINVAL;
+  return Lq % HS_BT != 0 ? HS_EUNSUPPORTED : HS_OK;
+}
+
+// as many tile ranges as serve the call, or as the workspace has room for
+hs_prefill_choice prefill_plan(const hs_shape* s, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv, size_t workspace_bytes) {
+  const size_t fit = workspace_bytes / prefill_split_bytes(s, Lq);
+  return hs_plan_prefill(s->B, s->Hq, s->Hkv, s->L / HS_BT, Lq, q_start, causal != 0, hs_make_kv_dev(kv),
+                         fit < 1 ? 1 : (fit > 65535 ? 65535 : (int)fit));
 }
 
 // shared body of the decode entry points; tail_len < 0: no dense tail
@@ -406,10 +414,25 @@ int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t q_star
                                size_t* bytes) {
   const int rc = check_shape(shape);
   if (rc != HS_OK) return rc;
-  if (bytes == nullptr || kv == nullptr || Lq <= 0 || Lq > shape->L || q_start < 0 || q_start > shape->L - Lq) return HS_EINVAL;
-  if (Lq % HS_BT != 0) return HS_EUNSUPPORTED;
-  const int n = prefill_splits(shape, Lq, q_start, causal, kv);
+  if (bytes == nullptr || kv == nullptr) return HS_EINVAL;
+  const int bad = prefill_args(shape, Lq, q_start);
+  if (bad != HS_OK) return bad;
+  const int n = hs_prefill_auto_splits(shape->B, shape->Hq, shape->Hkv, shape->L / HS_BT, Lq, q_start, causal != 0, hs_make_kv_dev(kv));
   *bytes = n > 1 ? (size_t)n * prefill_split_bytes(shape, Lq) : 0;
+  return HS_OK;
+}
+
+int hs_prefill_plan(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv, size_t workspace_bytes,
+                    int32_t* slab, int32_t* ranges, size_t* bytes) {
+  const int rc = check_shape(shape);
+  if (rc != HS_OK) return rc;
+  if (kv == nullptr) return HS_EINVAL;
+  const int bad = prefill_args(shape, Lq, q_start);
+  if (bad != HS_OK) return bad;
+  const hs_prefill_choice how = prefill_plan(shape, Lq, q_start, causal, kv, workspace_bytes);
+  if (slab != nullptr) *slab = 16 * how.nb;
+  if (ranges != nullptr) *ranges = how.n_splits;
+  if (bytes != nullptr) *bytes = how.n_splits > 1 ? (size_t)how.n_splits * prefill_split_bytes(shape, Lq) : 0;
   return HS_OK;
 }
 
@@ -420,9 +443,8 @@ int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start, float
   rc = check_kv(shape, kv);
   if (rc != HS_OK) return rc;
   if (Q == nullptr || O == nullptr || (((uintptr_t)Q | (uintptr_t)O | (uintptr_t)workspace) & 15u)) return HS_EINVAL;
-  if (Lq <= 0 || Lq > shape->L) return HS_EINVAL;
-  if (q_start < 0 || q_start > shape->L - Lq) return HS_EINVAL;
-  if (Lq % HS_BT != 0) return HS_EUNSUPPORTED;
+  const int bad = prefill_args(shape, Lq, q_start);
+  if (bad != HS_OK) return bad;
   // the prefill kernel addresses a tile inside its row's pool with a 32-bit byte offset
   if ((int64_t)kv->cap_dense_k * HS_TILE_DENSE_BYTES > (int64_t)1 << 32 ||
       (int64_t)kv->cap_dense_v * HS_TILE_DENSE_BYTES > (int64_t)1 << 32 ||
@@ -431,16 +453,10 @@ int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start, float
     return HS_EUNSUPPORTED;
   if (!(scale >= 0.f)) return HS_EINVAL;
   if (scale == 0.f) scale = 1.0f / sqrtf((float)HS_D);
-  // as many tile ranges as fill the chip, or as the workspace has room for
-  int n_splits = 1;
-  if (workspace != nullptr) {
-    n_splits = prefill_splits(shape, Lq, q_start, causal, kv);
-    const size_t fit = workspace_bytes / prefill_split_bytes(shape, Lq);
-    if ((size_t)n_splits > fit) n_splits = fit > 1 ? (int)fit : 1;
-  }
+  const hs_prefill_choice how = prefill_plan(shape, Lq, q_start, causal, kv, workspace == nullptr ? 0 : workspace_bytes);
   const hipError_t e = hs_launch_prefill(shape->B, shape->Hq, shape->Hkv, shape->L / HS_BT, Lq / HS_BT, q_start, scale,
                                          causal != 0, (const uint16_t*)Q, hs_make_kv_dev(kv), (uint16_t*)O, LSE,
-                                         (hipStream_t)stream, shape->dtype, n_splits, (float*)workspace);
+                                         (hipStream_t)stream, shape->dtype, how, (float*)workspace);
   if (e != hipSuccess) return hip_fail(e);
   return HS_OK;
 }

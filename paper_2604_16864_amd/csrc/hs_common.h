@@ -189,9 +189,13 @@ hipError_t hs_launch_stream_read(const uint8_t* buf, int n_tiles, int n_workgrou
 hipError_t hs_launch_merge(int64_t rows, int n_splits, const float* ws_o, const float* ws_l, uint16_t* O, float* LSE,
                            hipStream_t st, int dtype);
 // q_start: position in the cache of the first query (query i sees tokens <= q_start + i when causal)
-// n_splits > 1: the tiles of a workgroup may be cut into so many ranges; ws = B * Hq * 64 Tq * n_splits * 129 floats
+// nb: column blocks of 16 queries per wave, 1 or 2; n_splits > 1: the tiles of a workgroup are cut into so many ranges;
+// ws = B * Hq * 64 Tq * n_splits * 129 floats
+struct hs_prefill_choice { int nb, n_splits; };
 hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start, float scale, int causal, const uint16_t* Q,
-                             hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype, int n_splits, float* ws);
+                             hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype, hs_prefill_choice how, float* ws);
+// what serves this shape best with a workspace for `fit` ranges; of kv the capacities and `uniform` are read
+hs_prefill_choice hs_plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv, int fit);
 // its kernels for tensors with both kinds of tile (km, vm: 0 all 2:4, 1 all dense, 2 mixed; one of them is 2)
 hipError_t hs_launch_prefill_mixed(int km, int vm, int B, int Hq, int Hkv, int T, int Lq, int q_start, float scale_log2, int causal,
                                    const uint16_t* Q, const hs_kv_dev& kv, uint16_t* O, float* LSE, hipStream_t st, bool f16,
@@ -200,5 +204,5 @@ hipError_t hs_launch_prefill_mixed(int km, int vm, int B, int Hq, int Hkv, int T
 hipError_t hs_launch_prefill_narrow(int km, int vm, int B, int Hq, int Hkv, int T, int Lq, int q_start, float scale_log2, int causal,
                                     const uint16_t* Q, const hs_kv_dev& kv, uint16_t* O, float* LSE, hipStream_t st, bool f16,
                                     int n_splits, float* ws_o, float* ws_l);
-// most ranges that serve this shape (1: do not split); of kv the capacities and `uniform` are read
+// most ranges that it chooses from (1: do not split)
 int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv);

@@ -13,7 +13,8 @@ static int tiles_to_expect(int T, int seen, const hs_kv_dev& kv) {  // of `seen`
 // 1.0 us alone on its compute unit and 1.2 us beside a second one, so 512 workgroups at a time are two on every unit;
 // splitting costs 8 us for the merge launch and the caller's scratch (5 us on the GPU alone) and 0.028 us per workgroup
 // for writing and reading its 66 KB of partials.
-// The number of ranges that makes this sum smallest is what the workspace is sized for; plan_prefill below takes it or fewer.
+// The number of ranges that makes this sum smallest is the most that hs_plan_prefill below chooses from.  It was fitted to slabs of
+// 32 alone and its terms are rounded up where the other sum's are not: its part is to keep the scratch small.
 // Measured with slabs of 32 queries, one range / the chosen number: 64 queries on
 // 32768 tokens 501 / 41.5 us (32 ranges), on 2048 tokens 37 / 18.8 us (8); 256 queries on 32768 tokens 504 / 101 us (8);
 // 1024 queries on 32768 tokens 510 / 347 us (2); whole prompts of 256 to 2048 tokens are fastest unsplit (2048: 46 us, two
@@ -41,9 +42,7 @@ int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, i
   return best;
 }
 
-namespace {
-
-// Slabs of 32 queries (NB = 2) or of 16 (NB = 1), and in how many of the allowed ranges.  A tile takes a workgroup of NB = 1
+// Slabs of 32 queries (NB = 2) or of 16 (NB = 1), and in how many ranges (at most `fit`).  A tile takes a workgroup of NB = 1
 // three quarters of the time for half of the work, so NB = 1 pays where NB = 2 has too few workgroups: one or none per compute
 // unit, or a short second half of the work.  Measured, 32/8 heads, 2:4 tensors, us of NB = 2 / NB = 1 at the better number of
 // ranges of each: whole prompts of 64 / 256 / 512 / 1024 / 1536 / 2048 / 4096 tokens 7.4 / 6.1, 10.3 / 8.0, 14.3 / 11.1, 22.4 /
@@ -54,22 +53,26 @@ namespace {
 // to itself and kPair beside a second one; 512 run at a time, the longest first, so the call ends with the longest, or when the
 // whole is worked off, or with a pile of k + 1 where round k + 1 is just begun (queries at the end of a long context: all
 // workgroups equally long); ranges add the merge launch and the partials.
-struct PrefillPlan { int nb, n_splits; };
-PrefillPlan plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv, int most) {
+// The margins go by what the shape allows and not by `fit`, so a workspace of the size of the choice leads to the same choice.
+hs_prefill_choice hs_plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv, int fit) {
   static const double kStart[3] = {0, 5.3, 7.2}, kAlone[3] = {0, 0.70, 0.905}, kPair[3] = {0, 0.82, 1.13};
+  const int most = hs_prefill_auto_splits(B, Hq, Hkv, T, Lq, q_start, causal, kv);
   const int seen = causal ? (q_start + Lq + HS_BT - 1) / HS_BT : T;  // tiles of the last query
   const double share = (double)tiles_to_expect(T, seen, kv) / seen;
   const double longest = seen * share, shortest = (causal ? seen - (Lq / HS_BT - 1) : seen) * share;
-  PrefillPlan best = {2, 1};
+  hs_prefill_choice best = {2, 1};
   double best_us = 0.0;
   for (int nb = 2; nb >= 1; nb--) {
     const double n_wg = (double)((int64_t)((Lq / (16 * nb) * (int64_t)(Hq / Hkv) + 3) / 4) * Hkv * B);
-    for (int n = 1; n <= most; n++) {
-      const double wgs = n_wg * n;
+    for (int n = 1; n <= most && n <= fit; n++) {
+      const double wgs = n_wg * n, rounds = ceil(wgs / 512);
       double us = longest / n * (wgs <= 256 ? kAlone[nb] : kPair[nb]) + kStart[nb];
-      us = fmax(us, (longest + shortest) / 2 / n * kPair[nb] * wgs / 512 + ceil(wgs / 512) * kStart[nb]);
-      for (int k = 1; 512 * k < wgs; k++)
-        us = fmax(us, (k + 1) * ((longest - (longest - shortest) * 512 * k / wgs) / n * kPair[nb] + kStart[nb]));
+      us = fmax(us, (longest + shortest) / 2 / n * kPair[nb] * wgs / 512 + rounds * kStart[nb]);
+      if (rounds > 1) {  // (k + 1) (first - k fall), k = 1 .. rounds - 1: largest beside its vertex, or at an end
+        const double first = longest / n * kPair[nb] + kStart[nb], fall = (longest - shortest) * 512 / wgs / n * kPair[nb];
+        const double k = fmin(fmax(fall > 0.0 ? floor((first / fall - 1) / 2) : rounds, 1.0), rounds - 1);
+        us = fmax(us, fmax((k + 1) * (first - k * fall), k + 1 < rounds ? (k + 2) * (first - (k + 1) * fall) : 0.0));
+      }
       if (n > 1) us += 3.0 + 0.014 * nb * wgs;
       // The wider slab in all the ranges allowed where things are even; ranges of the narrow one, two to a compute unit, are
       // where the sum is least sure (128 queries x 4 heads on 47104 tokens 25.8 / 28.0, 256 x 4 on 32768 29.6 / 27.0).
@@ -81,15 +84,12 @@ PrefillPlan plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int
   return best;
 }
 
-}  // namespace
-
 hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start, float scale, int causal, const uint16_t* Q,
-                             hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype, int n_splits, float* ws) {
+                             hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype, hs_prefill_choice how, float* ws) {
   const bool f16 = dtype == HS_FP16;
   const float sl2 = scale * kLog2e;
   const int Lq = Tq * HS_BT;
-  const PrefillPlan plan = plan_prefill(B, Hq, Hkv, T, Lq, q_start, causal, kv, n_splits);
-  n_splits = plan.n_splits;
+  const int n_splits = how.n_splits;
   const int km = kv.cap_dense_k == 0 ? 0 : (kv.cap_sparse_k == 0 ? 1 : 2);
   const int vm = kv.cap_dense_v == 0 ? 0 : (kv.cap_sparse_v == 0 ? 1 : 2);
   const int64_t rows = (int64_t)B * Hq * Lq;
@@ -99,7 +99,7 @@ hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start,
 #define HS_GO(KM_, VM_)                                                                                                  \
   e = launch_prefill<KM_, VM_, 2>(B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l); \
   break
-  if (plan.nb == 1)
+  if (how.nb == 1)
     e = hs_launch_prefill_narrow(km, vm, B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l);
   else switch (km * 3 + vm) {
     case 0: HS_GO(0, 0);

@@ -29,7 +29,7 @@ struct Entries {  // of libhs.so, as the binding has loaded it
   decltype(&hs_decode_attn_static) decode_static;
   decltype(&hs_decode_attn_tail) decode_tail;
   decltype(&hs_decode_attn_tail_rows) decode_tail_rows;
-  decltype(&hs_prefill_workspace_bytes) prefill_workspace;
+  decltype(&hs_prefill_plan) prefill_plan;
   decltype(&hs_prefill_attn_ws) prefill;
   decltype(&hs_append_tiles) append;
   decltype(&hs_append_tile_rows) append_rows;
@@ -232,7 +232,7 @@ PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   const int causal = a[3] == Py_True;
   size_t need = 0;
   void* ws_ptr = nullptr;
-  if (a[9] == Py_None && g_hs.prefill_workspace(&s, Lq, at_pos, causal, &kv, &need) != 0) Py_RETURN_NONE;
+  if (a[9] == Py_None && g_hs.prefill_plan(&s, Lq, at_pos, causal, &kv, SIZE_MAX, nullptr, nullptr, &need) != 0) Py_RETURN_NONE;
   at::Tensor o, lse;
   if (a[6] == Py_None) o = at::empty_like(q);
   if (a[7] == Py_None && a[5] == Py_True) lse = at::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(at::kFloat));

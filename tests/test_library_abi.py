@@ -157,6 +157,41 @@ def test_prefill_ranges_of_caches_whose_fill_the_host_does_not_know(L):
         assert {ranges(B, T, Lq, *k) for k in unknown} == {some}
 
 
+def test_prefill_scratch_is_what_the_call_uses(L):
+    """The binding asks for the workspace of the plan, and a call that gets exactly that much runs by the same plan."""
+    def plan(B, Hq, Hkv, T, Lq, caps=None, causal=True, q_start=None):
+        sh = hb.make_shape(B, Hq, Hkv, 64 * T)
+        kv = hb.PackedKV(sh, caps or [0, 0, T, 0, T], "cpu")
+        at = 64 * T - Lq if q_start is None else q_start
+        slab, ranges, need = hb.prefill_plan(sh, Lq, at, kv, causal)
+        one, most = B * Hq * Lq * 129 * 4, C.c_size_t(0)
+        assert slab in (16, 32) and need == (ranges * one if ranges > 1 else 0)
+        assert L.hs_prefill_workspace_bytes(C.byref(sh), Lq, at, int(causal), C.byref(kv.struct()), C.byref(most)) == 0 and need <= most.value
+        assert hb.prefill_workspace_bytes(sh, Lq, at, kv, causal) == need
+        for room in (need, max(need, one) + one - 1, most.value):
+            assert hb.prefill_plan(sh, Lq, at, kv, causal, room) == (slab, ranges, need)
+        assert hb.prefill_plan(sh, Lq, at, kv, causal, 0)[1:] == (1, 0)
+        for n in range(2, ranges):
+            assert hb.prefill_plan(sh, Lq, at, kv, causal, n * one)[1] <= n
+        return slab, ranges
+    assert plan(1, 32, 8, 512, 64) == (32, 32)
+    assert plan(1, 32, 8, 32, 512) == (16, 1)                # a bound of two ranges, run in one
+    assert plan(1, 32, 8, 128, 64) == (16, 8)                # a bound of 16
+    for Hkv, G in ((8, 4), (1, 1), (3, 7), (2, 8)):
+        for T, Lq in ((1, 64), (9, 128), (70, 64), (402, 192), (300, 2304), (2048, 64)):
+            for B in (1, 2, 13):
+                for caps in ([0, 0, T, 0, T], [0, T, 0, T, 0], [0, T, T, T, T], [0, T // 3, T - T // 3, 0, T], [T // 2, 0, T - T // 2, 0, T - T // 2]):
+                    plan(B, G * Hkv, Hkv, T, Lq, caps)
+    plan(2, 8, 2, 300, 128, causal=False, q_start=64 * 30 + 17)
+    sh = hb.make_shape(1, 32, 8, 1024)
+    kv = hb.PackedKV(sh, [0, 0, 16, 0, 16], "cpu")
+    for bad in ((64, 1024), (0, 0), (100, 0), (64, -1)):
+        with pytest.raises(hb.HsError):
+            hb.prefill_plan(sh, *bad, kv)
+    assert L.hs_prefill_plan(C.byref(sh), 64, 0, 1, None, 0, None, None, None) == -1
+    assert L.hs_prefill_plan(C.byref(sh), 64, 0, 1, C.byref(kv.struct()), 0, None, None, None) == 0
+
+
 def test_current_stream_without_the_raw_handle(monkeypatch):
     """A torch without the two non-public functions gets the stream from the public object."""
     import torch

@@ -127,6 +127,7 @@ def test_prefill_makes_its_outputs_before_it_takes_scratch(native, monkeypatch):
     before, held = torch.cuda.memory_allocated(), []
 
     def none_left(nbytes, device):
+        assert nbytes == hb.prefill_workspace_bytes(sh, 64, sh.L - 64, kv)      # what the call uses and no more
         held.append(torch.cuda.memory_allocated() - before)
         raise torch.OutOfMemoryError("no scratch to be had")
     monkeypatch.setattr(hb, "_workspace", none_left)
