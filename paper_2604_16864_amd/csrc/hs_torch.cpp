@@ -110,14 +110,14 @@ bool query_ok(const at::Tensor& q, const hs_shape& s) { return q.scalar_type() =
 void* current_stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 at::Tensor bytes_beside(const at::Tensor& t, size_t n) { return at::empty({(int64_t)n}, t.options().dtype(at::kByte)); }
 
-template <class F>
-int without_gil(F&& call) {  // a launch may wait for room in the queue
-  int rc;
-  Py_BEGIN_ALLOW_THREADS
-  rc = call();
-  Py_END_ALLOW_THREADS
-  return rc;
-}
+// Other threads run while memory is allocated and the kernels are launched: the allocator may wait for the GPU (when it gives
+// cached blocks back) and a launch for room in the queue, and what they wait for may be up to another thread.
+struct NoGil {
+  PyThreadState* state = PyEval_SaveThread();
+  NoGil() = default;
+  NoGil(const NoGil&) = delete;
+  ~NoGil() { PyEval_RestoreThread(state); }
+};
 
 // (O, LSE) or the library's status
 PyObject* result(int rc, PyObject* out, const at::Tensor& o, PyObject* lse_arg, const at::Tensor& lse) {
@@ -166,29 +166,28 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
       Py_RETURN_NONE;
     }
   }
-  at::Tensor o, lse, ws;
-  void* ws_ptr;
-  if (a[8] == Py_None) {
-    size_t need = 0;
+  const bool own_ws = a[8] == Py_None, own_o = a[6] == Py_None, own_lse = a[7] == Py_None && a[5] == Py_True;
+  size_t need = 0;
+  if (own_ws) {
     const int n = has_tail ? (n_splits != 0 ? n_splits : g_hs.auto_splits(&s)) + 1 : n_splits;
     if (g_hs.workspace_bytes(&s, 2, n, &need) != 0) Py_RETURN_NONE;
-    ws = bytes_beside(q, need);
-    ws_ptr = ws.data_ptr();
-  } else {
-    ws_ptr = address(a[8]);
   }
-  if (a[6] == Py_None) o = at::empty_like(q);
-  if (a[7] == Py_None && a[5] == Py_True) lse = at::empty({q.size(0), q.size(1)}, q.options().dtype(at::kFloat));
-  void* o_ptr = a[6] == Py_None ? o.data_ptr() : address(a[6]);
-  float* lse_ptr = (float*)(lse.defined() ? lse.data_ptr() : address(a[7]));
+  void *ws_ptr = address(a[8]), *o_ptr = address(a[6]);
+  float* lse_ptr = (float*)address(a[7]);
   const void *q_ptr = q.data_ptr(), *tk = address(a[9]), *tv = address(a[10]);
   const int32_t* lens = rows != nullptr ? (const int32_t*)rows->data_ptr() : nullptr;
-  void* st = current_stream();
-  const int rc = without_gil([&] {
-    if (!has_tail) return g_hs.decode(&s, scale, n_splits, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, st);
-    if (rows != nullptr) return g_hs.decode_tail_rows(&s, scale, n_splits, q_ptr, &kv, tk, tv, lens, o_ptr, lse_ptr, ws_ptr, st);
-    return g_hs.decode_tail(&s, scale, n_splits, q_ptr, &kv, tk, tv, tail_len, o_ptr, lse_ptr, ws_ptr, st);
-  });
+  at::Tensor o, lse, ws;
+  int rc;
+  {
+    NoGil others_run;
+    if (own_ws) { ws = bytes_beside(q, need); ws_ptr = ws.data_ptr(); }
+    if (own_o) { o = at::empty_like(q); o_ptr = o.data_ptr(); }
+    if (own_lse) { lse = at::empty({q.size(0), q.size(1)}, q.options().dtype(at::kFloat)); lse_ptr = (float*)lse.data_ptr(); }
+    void* st = current_stream();
+    if (!has_tail) rc = g_hs.decode(&s, scale, n_splits, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, st);
+    else if (rows != nullptr) rc = g_hs.decode_tail_rows(&s, scale, n_splits, q_ptr, &kv, tk, tv, lens, o_ptr, lse_ptr, ws_ptr, st);
+    else rc = g_hs.decode_tail(&s, scale, n_splits, q_ptr, &kv, tk, tv, tail_len, o_ptr, lse_ptr, ws_ptr, st);
+  }
   return result(rc, a[6], o, a[7], lse);
   END_HANDLE_TH_ERRORS
 }
@@ -208,7 +207,11 @@ PyObject* decode_static(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   const void* q_ptr = q.data_ptr();
   void *o_ptr = address(a[5]), *st = current_stream();
   float* lse_ptr = (float*)address(a[6]);
-  const int rc = without_gil([&] { return g_hs.decode_static(&s, scale, n_splits, q_ptr, &kv, o_ptr, lse_ptr, st); });
+  int rc;
+  {
+    NoGil others_run;
+    rc = g_hs.decode_static(&s, scale, n_splits, q_ptr, &kv, o_ptr, lse_ptr, st);
+  }
   return result(rc, a[5], at::Tensor(), a[6], at::Tensor());
   END_HANDLE_TH_ERRORS
 }
@@ -233,27 +236,28 @@ PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   size_t need = 0;
   void* ws_ptr = nullptr;
   if (a[9] == Py_None && g_hs.prefill_plan(&s, Lq, at_pos, causal, &kv, SIZE_MAX, nullptr, nullptr, &need) != 0) Py_RETURN_NONE;
-  at::Tensor o, lse;
-  if (a[6] == Py_None) o = at::empty_like(q);
-  if (a[7] == Py_None && a[5] == Py_True) lse = at::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(at::kFloat));
-  if (a[9] == Py_None) {
-    if (need != 0) {
-      PyObject* outs = result(0, a[6], o, a[7], lse);
-      if (outs == nullptr) return nullptr;
-      PyObject* r = Py_BuildValue("(nOO)", (Py_ssize_t)need, PyTuple_GET_ITEM(outs, 0), PyTuple_GET_ITEM(outs, 1));
-      Py_DECREF(outs);
-      return r;
-    }
-  } else if (a[9] != Py_False) {
+  const bool own_o = a[6] == Py_None, own_lse = a[7] == Py_None && a[5] == Py_True, outputs_only = need != 0;
+  if (exact_tensor(a[9])) {
     ws_ptr = address(a[9]);
     need = (size_t)tensor(a[9]).nbytes();
   }
-  void* o_ptr = a[6] == Py_None ? o.data_ptr() : address(a[6]);
-  float* lse_ptr = (float*)(lse.defined() ? lse.data_ptr() : address(a[7]));
+  void* o_ptr = address(a[6]);
+  float* lse_ptr = (float*)address(a[7]);
   const void* q_ptr = q.data_ptr();
-  void* st = current_stream();
-  const int rc = without_gil([&] { return g_hs.prefill(&s, Lq, at_pos, scale, causal, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, need, st); });
-  return result(rc, a[6], o, a[7], lse);
+  at::Tensor o, lse;
+  int rc = 0;
+  {
+    NoGil others_run;
+    if (own_o) { o = at::empty_like(q); o_ptr = o.data_ptr(); }
+    if (own_lse) { lse = at::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(at::kFloat)); lse_ptr = (float*)lse.data_ptr(); }
+    if (!outputs_only)
+      rc = g_hs.prefill(&s, Lq, at_pos, scale, causal, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, need, current_stream());
+  }
+  PyObject* r = result(rc, a[6], o, a[7], lse);
+  if (!outputs_only || r == nullptr) return r;
+  PyObject* first = Py_BuildValue("(nOO)", (Py_ssize_t)need, PyTuple_GET_ITEM(r, 0), PyTuple_GET_ITEM(r, 1));
+  Py_DECREF(r);
+  return first;
   END_HANDLE_TH_ERRORS
 }
 
@@ -284,47 +288,52 @@ PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   const int32_t* at_rows = rows != nullptr ? (const int32_t*)rows->data_ptr() : nullptr;
   int32_t* over = (int32_t*)address(a[8]);
   void* st = current_stream();
-  const int rc = without_gil([&] {
-    if (rows != nullptr) return g_hs.append_rows(&s, at_rows, state_k, state_v, rule, kp, vp, strides, &kv, over, st);
-    return g_hs.append(&s, tile, n, state_k, state_v, rule, kp, vp, strides, &kv, over, st);
-  });
+  int rc;
+  {
+    NoGil others_run;
+    rc = rows != nullptr ? g_hs.append_rows(&s, at_rows, state_k, state_v, rule, kp, vp, strides, &kv, over, st)
+                         : g_hs.append(&s, tile, n, state_k, state_v, rule, kp, vp, strides, &kv, over, st);
+  }
   return PyLong_FromLong(rc);
   END_HANDLE_TH_ERRORS
 }
 
-// The eight buffers of a cache beside the tensor `like`, as a tuple in the order of kNames (None for an empty pool) with their
-// bytes behind them, and the cache as the library sees it.  nullptr with no Python error: a count the library refuses.
-PyObject* make_pools(const hs_shape& s, const int32_t counts[5], const at::Tensor& like, int uniform, hs_kv* kv) {
-  size_t bytes[8], total = 0;
-  if (g_hs.kv_bytes(&s, counts, bytes) != 0) return nullptr;
+// The eight buffers of a cache, in the order of kNames; an empty pool has none.
+struct Pools {
+  at::Tensor t[8];
+  size_t bytes[8];
+};
+
+// They are made beside the tensor `like`, from the bytes that hs_kv_bytes has given (without the GIL); kv: the cache as the library sees it.
+void make_pools(const hs_shape& s, const int32_t counts[5], const at::Tensor& like, int uniform, Pools* p, hs_kv* kv) {
   const auto opt = like.options();
   void** ptr[8] = {&kv->k_dense, &kv->k_nnz, &kv->k_meta, (void**)&kv->k_map, &kv->v_dense, &kv->v_nnz, &kv->v_meta, (void**)&kv->v_map};
-  PyObject* r = PyTuple_New(9);
-  if (r == nullptr) return nullptr;
-  try {
-    for (int i = 0; i < 8; i++) {
-      const bool map = i == S_K_MAP || i == S_V_MAP;
-      PyObject* t;
-      *ptr[i] = nullptr;
-      if (map || bytes[i] != 0) {
-        const at::Tensor b = map ? at::empty({s.B, s.Hkv, s.L / 64}, opt.dtype(at::kInt)) : at::empty({(int64_t)bytes[i]}, opt.dtype(at::kByte));
-        *ptr[i] = b.data_ptr();
-        t = THPVariable_Wrap(b);
-      } else {
-        t = Py_None;
-        Py_INCREF(t);
-      }
-      if (t == nullptr) { Py_DECREF(r); return nullptr; }
-      PyTuple_SET_ITEM(r, i, t);
-      total += bytes[i];
-    }
-  } catch (...) {
-    Py_DECREF(r);
-    throw;
+  for (int i = 0; i < 8; i++) {
+    const bool map = i == S_K_MAP || i == S_V_MAP;
+    if (map || p->bytes[i] != 0)
+      p->t[i] = map ? at::empty({s.B, s.Hkv, s.L / 64}, opt.dtype(at::kInt)) : at::empty({(int64_t)p->bytes[i]}, opt.dtype(at::kByte));
+    *ptr[i] = p->t[i].defined() ? p->t[i].data_ptr() : nullptr;
   }
-  PyTuple_SET_ITEM(r, 8, PyLong_FromSize_t(total));
   kv->cap_dense_k = counts[1]; kv->cap_sparse_k = counts[2]; kv->cap_dense_v = counts[3]; kv->cap_sparse_v = counts[4];
   kv->uniform = uniform;
+}
+
+// The buffers as a tuple (None for an empty pool) with their bytes behind them.
+PyObject* wrap_pools(const Pools& p) {
+  PyObject* r = PyTuple_New(9);
+  if (r == nullptr) return nullptr;
+  size_t total = 0;
+  for (int i = 0; i < 8; i++) {
+    PyObject* t = Py_None;
+    if (p.t[i].defined()) t = THPVariable_Wrap(p.t[i]);
+    else Py_INCREF(t);
+    if (t == nullptr) { Py_DECREF(r); return nullptr; }
+    PyTuple_SET_ITEM(r, i, t);
+    total += p.bytes[i];
+  }
+  PyObject* n = PyLong_FromSize_t(total);
+  if (n == nullptr) { Py_DECREF(r); return nullptr; }
+  PyTuple_SET_ITEM(r, 8, n);
   return r;
 }
 
@@ -340,19 +349,23 @@ PyObject* pools(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   hs_shape s;
   hs_kv kv;
   int32_t counts[5];
-  if (n_args != 3 || !get_shape(a[0], &s) || !get_counts(a[1], counts) || !exact_tensor(a[2])) Py_RETURN_NONE;
-  PyObject* r = make_pools(s, counts, tensor(a[2]), 0, &kv);
-  if (r == nullptr && !PyErr_Occurred()) Py_RETURN_NONE;
-  return r;
+  Pools p;
+  if (n_args != 3 || !get_shape(a[0], &s) || !get_counts(a[1], counts) || !exact_tensor(a[2]) || g_hs.kv_bytes(&s, counts, p.bytes) != 0)
+    Py_RETURN_NONE;
+  const at::Tensor& like = tensor(a[2]);
+  {
+    NoGil others_run;
+    make_pools(s, counts, like, 0, &p, &kv);
+  }
+  return wrap_pools(p);
   END_HANDLE_TH_ERRORS
 }
 
-// (counts, pools, uniform) of a new cache, or the library's status; takes the reference to `bufs`
-PyObject* new_cache(int rc, const int32_t c[5], PyObject* bufs, int uniform) {
-  if (rc != 0) {
-    Py_DECREF(bufs);
-    return PyLong_FromLong(rc);
-  }
+// (counts, pools, uniform) of a new cache, or the library's status
+PyObject* new_cache(int rc, const int32_t c[5], const Pools& p, int uniform) {
+  if (rc != 0) return PyLong_FromLong(rc);
+  PyObject* bufs = wrap_pools(p);
+  if (bufs == nullptr) return nullptr;
   return Py_BuildValue("([iiiii]Ni)", c[0], c[1], c[2], c[3], c[4], bufs, uniform);
 }
 
@@ -370,25 +383,20 @@ PyObject* compress(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     Py_RETURN_NONE;
   int32_t counts[5];
   size_t need = 0;
-  if (g_hs.tile_counts(&s, &pol, counts) != 0 || g_hs.workspace_bytes(&s, 0, 0, &need) != 0) Py_RETURN_NONE;
-  const int uniform = counts_uniform(counts, s.L / 64);
-  PyObject* bufs = make_pools(s, counts, k, uniform, &kv);
-  if (bufs == nullptr) {
-    if (PyErr_Occurred()) return nullptr;
+  Pools p;
+  if (g_hs.tile_counts(&s, &pol, counts) != 0 || g_hs.workspace_bytes(&s, 0, 0, &need) != 0 || g_hs.kv_bytes(&s, counts, p.bytes) != 0)
     Py_RETURN_NONE;
-  }
-  at::Tensor ws;
-  try {
-    ws = bytes_beside(k, need < 16 ? 16 : need);
-  } catch (...) {
-    Py_DECREF(bufs);
-    throw;
-  }
+  const int uniform = counts_uniform(counts, s.L / 64);
   const int64_t strides[3] = {k.stride(0), k.stride(1), k.stride(2)};
   const void *kp = k.data_ptr(), *vp = v.data_ptr();
-  void *wp = ws.data_ptr(), *st = current_stream();
-  const int rc = without_gil([&] { return g_hs.compress(&s, &pol, kp, vp, strides, &kv, wp, st); });
-  return new_cache(rc, counts, bufs, uniform);
+  int rc;
+  {
+    NoGil others_run;
+    make_pools(s, counts, k, uniform, &p, &kv);
+    const at::Tensor ws = bytes_beside(k, need < 16 ? 16 : need);
+    rc = g_hs.compress(&s, &pol, kp, vp, strides, &kv, ws.data_ptr(), current_stream());
+  }
+  return new_cache(rc, counts, p, uniform);
   END_HANDLE_TH_ERRORS
 }
 
@@ -399,8 +407,9 @@ PyObject* recompress(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   hs_policy pol;
   hs_kv src, dst;
   int32_t c[5];
+  Pools p;
   if (n_args != 5 || !get_shape(a[0], &s) || !get_kv(a[1], &src) || !get_policy(a[2], &pol) || pol.state_k != nullptr ||
-      pol.tile_scores != nullptr || !get_counts(a[3], c) || !none_or_tensor(a[4]))
+      pol.tile_scores != nullptr || !get_counts(a[3], c) || !none_or_tensor(a[4]) || g_hs.kv_bytes(&s, c, p.bytes) != 0)
     Py_RETURN_NONE;
   PyObject* map = PyObject_GetAttr(a[1], g_names[S_K_MAP]);
   if (map == nullptr) return nullptr;
@@ -412,15 +421,14 @@ PyObject* recompress(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
                      (pol.sparse_frac_v == 0.0 || pol.sparse_frac_v == 1.0);
   // slot == tile survives when nothing was skipped before and each tensor ends up in one kind
   const int uniform = src.uniform != 0 && whole && (c[1] == 0 || c[2] == 0) && (c[3] == 0 || c[4] == 0) && k == T && v == T;
-  PyObject* bufs = make_pools(s, c, like, uniform, &dst);
-  if (bufs == nullptr) {
-    if (PyErr_Occurred()) return nullptr;
-    Py_RETURN_NONE;
-  }
   int32_t* over = (int32_t*)address(a[4]);
-  void* st = current_stream();
-  const int rc = without_gil([&] { return g_hs.recompress(&s, &pol, &src, &dst, nullptr, over, st); });
-  return new_cache(rc, c, bufs, uniform);
+  int rc;
+  {
+    NoGil others_run;
+    make_pools(s, c, like, uniform, &p, &dst);
+    rc = g_hs.recompress(&s, &pol, &src, &dst, nullptr, over, current_stream());
+  }
+  return new_cache(rc, c, p, uniform);
   END_HANDLE_TH_ERRORS
 }
 

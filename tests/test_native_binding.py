@@ -1,5 +1,8 @@
 """The native part of the binding against the binding's own Python code: the same calls through both give the same bits, and
 whatever the native part does not take as it is goes on to the Python code, which accepts or refuses it as before."""
+import threading
+import time
+
 import pytest
 import torch
 
@@ -59,6 +62,39 @@ def test_pools_made_natively_are_the_same(counts):
         x, y = getattr(a, name), getattr(b, name)
         assert (x is None) == (y is None)
         assert x is None or (x.shape == y.shape and x.dtype == y.dtype and x.device == y.device)
+
+
+def test_other_threads_run_while_the_native_part_allocates():
+    """An allocation may wait for the GPU, and the GPU for what another thread has yet to do.  Made slow here by torch's option that
+    fills new memory."""
+    sh = hb.make_shape(1, 8, 8, 64 * 4096)
+    like, ticks, stop = torch.empty(1), [], threading.Event()
+    pools = hb._fast().pools
+
+    def tick():
+        while not stop.wait(0.001):
+            ticks.append(time.perf_counter())
+    before, n = torch.are_deterministic_algorithms_enabled(), torch.get_num_threads()
+    t = threading.Thread(target=tick)
+    t.start()
+    try:
+        torch.use_deterministic_algorithms(True)
+        torch.set_num_threads(1)                               # 1 GB by one thread: far above the 5 ms after which threads change
+        t0 = time.perf_counter()
+        bufs = pools(sh, [0, 4096, 0, 4096, 0], like)
+        t1 = time.perf_counter()
+    finally:
+        torch.set_num_threads(n)
+        torch.use_deterministic_algorithms(before)
+        stop.set()
+        t.join()
+    assert bufs is not None
+    assert any(t0 + 0.25 * (t1 - t0) < x < t1 - 0.25 * (t1 - t0) for x in ticks)
+
+
+def test_an_allocation_that_fails_is_raised():
+    with pytest.raises(RuntimeError, match="alloc"):
+        hb._fast().pools(hb.make_shape(4096, 8, 8, 64 << 24), [0, 1 << 24, 0, 1 << 24, 0], torch.empty(1))     # beyond any address space
 
 
 @pytest.mark.gpu
