@@ -2,11 +2,15 @@
 through ctypes.
 
 Every step of the hot path runs in the library's HIP kernels; PyTorch supplies
-device memory and the stream.  There is no fallback: if the library has not
-been built, `lib()` raises.
+device memory and the stream.  There is no fallback for them: if the library has not
+been built, `lib()` raises.  The native part only marshals: without it the same calls
+go through ctypes, with a warning.
 """
 import ctypes as C
 import os
+import sys
+import types
+import warnings
 
 import numpy as np
 import torch
@@ -98,12 +102,7 @@ def lib():
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
-        try:
-            from . import _hs_torch
-        except ImportError as e:
-            raise RuntimeError(f"the binding's native part is not built ({e}): run `python -m paper_2604_16864_amd.build`") from e
-        _hs_torch.bind(tuple(C.cast(getattr(L, name), C.c_void_p).value for name in _NATIVE_ENTRIES), HsShape, HsPolicy, PackedKV)
-        _lib, _native = L, _hs_torch
+        _lib, _native = L, _load_native(L)
     return _lib
 
 
@@ -111,6 +110,27 @@ def lib():
 _NATIVE_ENTRIES = ("hs_kv_bytes", "hs_workspace_bytes", "hs_decode_auto_splits", "hs_decode_attn", "hs_decode_attn_static",
                    "hs_decode_attn_tail", "hs_decode_attn_tail_rows", "hs_prefill_plan", "hs_prefill_attn_ws",
                    "hs_append_tiles", "hs_append_tile_rows", "hs_tile_counts", "hs_compress_kv", "hs_recompress_kv")
+
+
+# what calls it
+_NATIVE_CALLS = ("decode", "decode_static", "prefill", "append", "pools", "compress", "recompress")
+
+
+def _load_native(L):
+    """The native marshalling module bound to the library L.  It holds for the torch and the Python it was built against; with others,
+    or where it is not built, every call goes through the code here, which costs a small call up to 6 us more."""
+    here = f"torch {torch.__version__}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+    try:
+        from . import _hs_torch
+        why = None if _hs_torch.built_for == here else f"it was built for {_hs_torch.built_for}, this is {here}"
+    except (ImportError, AttributeError) as e:
+        why = str(e)
+    if why is not None:
+        warnings.warn(f"the binding runs without its native part ({why}): small calls take longer; `python -m paper_2604_16864_amd.build` "
+                      "builds it", RuntimeWarning, stacklevel=3)
+        return types.SimpleNamespace(**{name: lambda *args: None for name in _NATIVE_CALLS})
+    _hs_torch.bind(tuple(C.cast(getattr(L, name), C.c_void_p).value for name in _NATIVE_ENTRIES), HsShape, HsPolicy, PackedKV)
+    return _hs_torch
 
 
 def _fast():

@@ -29,7 +29,7 @@ def native_command():
     root = os.path.dirname(torch.__file__)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
-            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DHS_TORCH_VERSION="{torch.__version__}"', "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
             "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
             "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
             "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "hs_torch.cpp"),
@@ -39,21 +39,27 @@ def native_command():
 def build_lib(verbose=True, extra=()):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
-    procs = [("hs_torch.cpp", subprocess.Popen(native_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))]
+    procs, failed = [], []
     for src in SOURCES:
         obj = os.path.join(CSRC, src.replace(".hip", ".o"))
         objs.append(obj)
         cmd = [hipcc, *FLAGS, *FILE_FLAGS.get(src, []), *extra, "-DHS_BUILD", "-c", os.path.join(CSRC, src), "-o", obj]
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    try:
+        procs.append(("hs_torch.cpp", subprocess.Popen(native_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    except OSError as e:                    # no such compiler
+        failed.append(f"hs_torch.cpp ({e})")
     for src, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if verbose and out.strip():
             print(out)
         if p.returncode != 0:
-            raise RuntimeError(f"the compiler failed on {src}")
-    cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
-    subprocess.check_call(cmd)
+            failed.append(src)
+    if not set(failed) & set(SOURCES):      # the library does not need the native part: it is there also where that one cannot be built
+        subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB])
+    if failed:
+        raise RuntimeError(f"the compiler failed on {', '.join(failed)}")
     return LIB
 
 

@@ -3,10 +3,9 @@
 // kernels took 13.3 us (8 data_ptr() calls and a ctypes structure for the cache, three allocations, two library calls) and takes
 // 9 here, compressing 2K tokens 16.1 and 10.3.
 //
-// Every function returns None for a call it does not take as it is (other types than exact tensors, an argument that fails a
-// check of the binding, a number that is neither int nor float), and the binding's Python code then takes it, so what is
-// accepted, what is refused and with which error is written down in one place only.  Nothing is kept between calls but the
-// types and the library's entry points.
+// Every function repeats the binding's checks and returns None for a call that fails one or that it does not take as it is (other
+// types than exact tensors, a number that is neither int nor float); the binding's Python code then takes it, so which error a
+// refused call raises is written down there only.  Nothing is kept between calls but the types and the library's entry points.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -464,10 +463,19 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_hs_torch", nullptr, -1, kMethods
 
 }  // namespace
 
+#define HS_STR_(x) #x
+#define HS_STR(x) HS_STR_(x)
+
 PyMODINIT_FUNC PyInit__hs_torch() {
   for (int i = 0; i < N_NAMES; i++) {
     g_names[i] = PyUnicode_InternFromString(kNames[i]);
     if (g_names[i] == nullptr) return nullptr;
   }
-  return PyModule_Create(&kModule);
+  PyObject* m = PyModule_Create(&kModule);
+  // what the binding compares before it uses the module
+  if (m != nullptr && PyModule_AddStringConstant(m, "built_for", "torch " HS_TORCH_VERSION ", Python " HS_STR(PY_MAJOR_VERSION) "." HS_STR(PY_MINOR_VERSION)) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
 }

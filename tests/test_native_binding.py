@@ -1,7 +1,9 @@
 """The native part of the binding against the binding's own Python code: the same calls through both give the same bits, and
 whatever the native part does not take as it is goes on to the Python code, which accepts or refuses it as before."""
+import sys
 import threading
 import time
+import types
 
 import pytest
 import torch
@@ -62,6 +64,37 @@ def test_pools_made_natively_are_the_same(counts):
         x, y = getattr(a, name), getattr(b, name)
         assert (x is None) == (y is None)
         assert x is None or (x.shape == y.shape and x.dtype == y.dtype and x.device == y.device)
+
+
+@pytest.mark.parametrize("how", ["another torch", "not built", "of before"])
+def test_without_a_native_part_that_fits_calls_go_through_python(how, monkeypatch):
+    """A native part that was built against another torch, or none at all, is left alone with a warning; the library works."""
+    hb.lib()
+    name = "paper_2604_16864_amd._hs_torch"
+    other = types.ModuleType(name)
+    other.bind = lambda *a: pytest.fail("a module of another torch was used")
+    if how == "another torch":
+        other.built_for = sys.modules[name].built_for.replace("torch ", "torch 1")
+    monkeypatch.setitem(sys.modules, name, None if how == "not built" else other)       # None: the import fails
+    monkeypatch.delattr(sys.modules["paper_2604_16864_amd"], "_hs_torch", raising=False)
+    monkeypatch.setattr(hb, "_lib", None)
+    monkeypatch.setattr(hb, "_native", None)
+    with pytest.warns(RuntimeWarning, match="native part"):
+        sh = _shape()
+        assert hb.tile_counts(sh, hb.make_policy()) == [0, 0, 12, 0, 12]
+    kv = hb.PackedKV(sh, [0, 0, 12, 0, 12], "cpu", torch.empty(1))
+    assert kv.nbytes == sum(hb.kv_bytes(sh, kv.counts)) and kv.k_nnz.device.type == "cpu"
+    q = torch.zeros(2, 8, 128, dtype=torch.bfloat16)
+    for call in (lambda: hb.decode_attn(sh, q, kv), lambda: hb.decode_attn_static(sh, q, kv, out=q), lambda: hb.prefill_attn(sh, q[:, :, None], kv),
+                 lambda: hb.append_tile(sh, kv, 0, q, q), lambda: hb.compress_kv(sh, hb.make_policy(), q, q)):
+        with pytest.raises((AssertionError, IndexError)):
+            call()
+
+
+def test_the_native_part_is_used_where_it_fits():
+    hb.lib()
+    assert type(hb._native) is types.ModuleType and hb._native.built_for.startswith(f"torch {torch.__version__}, Python 3")
+    assert all(callable(getattr(hb._native, name)) for name in hb._NATIVE_CALLS)
 
 
 def test_other_threads_run_while_the_native_part_allocates():
