@@ -168,6 +168,7 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   const bool own_ws = a[8] == Py_None, own_o = a[6] == Py_None, own_lse = a[7] == Py_None && a[5] == Py_True;
   size_t need = 0;
   if (own_ws) {
+    if (has_tail && n_splits == INT32_MAX) Py_RETURN_NONE;  // one more for the tail is no int32_t; the library refuses it
     const int n = has_tail ? (n_splits != 0 ? n_splits : g_hs.auto_splits(&s)) + 1 : n_splits;
     if (g_hs.workspace_bytes(&s, 2, n, &need) != 0) Py_RETURN_NONE;
   }

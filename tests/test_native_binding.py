@@ -218,8 +218,9 @@ def test_library_errors_are_raised_through_the_native_part():
     for kw in (dict(n_splits=-1), dict(scale=-1.0)):
         with pytest.raises(hb.HsError):
             hb.decode_attn(sh, q, kv, **kw)
-    with pytest.raises(hb.HsError):
-        hb.decode_attn(sh, q, kv, tail_len=65)
+    for kw in (dict(tail_len=65), dict(tail_len=0, n_splits=2**31 - 1)):
+        with pytest.raises(hb.HsError):
+            hb.decode_attn(sh, q, kv, **kw)
     with pytest.raises(hb.HsError):
         hb.prefill_attn(sh, torch.zeros(2, 8, 100, 128, dtype=torch.bfloat16, device="cuda"), kv)
     for kw in (dict(skip_frac=2.0), dict(sparse_frac_k=-0.5), dict(dense_first_tiles=-1)):
