@@ -1,5 +1,6 @@
 """The native part of the binding against the binding's own Python code: the same calls through both give the same bits, and
 whatever the native part does not take as it is goes on to the Python code, which accepts or refuses it as before."""
+import collections
 import sys
 import threading
 import time
@@ -16,6 +17,20 @@ class _PythonOnly:
 
     def __getattr__(self, name):
         return lambda *a: None
+
+
+class _Recorder:
+    """Notes which native functions are called and whether each took its call."""
+
+    def __init__(self, native):
+        self.native, self.calls = native, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            r = getattr(self.native, name)(*args)
+            self.calls.append((name, r is not None))
+            return r
+        return call
 
 
 def _shape(dtype=hb.BF16):
@@ -168,11 +183,22 @@ def test_native_and_python_calls_give_the_same_bits(dtype, policy, monkeypatch):
                      hb.recompress_kv(sh, kv, hb.make_policy(sparse_frac_k=0.0), counts=[0, 12, 12, 12, 12])):
             yield hb.unpack_kv(sh, made)
             yield made.k_map, made.v_map, torch.tensor(made.counts + [made.uniform, made.nbytes])
-    stream = torch.cuda.Stream()
+    stream, record = torch.cuda.Stream(), _Recorder(hb._fast())
     stream.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(stream):
+    with torch.cuda.stream(stream), monkeypatch.context() as m:
+        m.setattr(hb, "_native", record)
         native = list(calls())
-    stream.synchronize()
+        stream.synchronize()
+        took = collections.Counter(name for name, taken in record.calls if taken)
+        assert all(taken for _, taken in record.calls)          # every call was the native part's
+        assert took.pop("prefill") >= 3                         # twice where a call wants scratch
+        assert took == dict(compress=1, decode=5, decode_static=1, append=2, recompress=3)
+        record.calls.clear()                                    # what it leaves to the Python code, but for the new cache's buffers
+        sk = torch.full((2, 2, 12), hb.SPARSE24, dtype=torch.int8, device="cuda")
+        hb.compress_kv(sh, hb.make_policy(state_k=sk, state_v=sk), K, V)
+        hb.recompress_kv(sh, hb.compress_kv(sh, hb.make_policy(), K, V), hb.make_policy(state_k=sk, state_v=sk))
+        stream.synchronize()
+        assert record.calls == [("compress", False), ("pools", True), ("compress", True), ("recompress", False), ("pools", True)]
     with monkeypatch.context() as m:
         m.setattr(hb, "_native", _PythonOnly())
         python = list(calls())
