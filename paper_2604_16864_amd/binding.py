@@ -77,6 +77,8 @@ EXPORTS = {
                                              C.POINTER(C.c_size_t)]),
     "hs_prefill_plan": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_int, C.POINTER(HsKV), C.c_size_t,
                                   C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_size_t)]),
+    "hs_prefill_attn_planned": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_float, C.c_int, C.c_void_p, C.POINTER(HsKV),
+                                          C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_int32, C.c_int32, C.c_void_p]),
     "hs_decode_attn": (C.c_int, [C.POINTER(HsShape), C.c_float, C.c_int32, C.c_void_p, C.POINTER(HsKV), C.c_void_p,
                                  C.c_void_p, C.c_void_p, C.c_void_p]),
     "hs_decode_attn_static": (C.c_int, [C.POINTER(HsShape), C.c_float, C.c_int32, C.c_void_p, C.POINTER(HsKV), C.c_void_p,
@@ -474,6 +476,21 @@ def prefill_attn(shape, Q, kv, causal=True, scale=0.0, want_lse=True, out=None, 
             need = 0
     _check(lib().hs_prefill_attn_ws(C.byref(shape), Lq, at, float(scale), int(bool(causal)), _ptr(Q), C.byref(kvs), _ptr(O),
                                     _ptr(lse), _ptr(ws), need, _stream()))
+    return O, lse
+
+
+def prefill_attn_planned(shape, Q, kv, slab, ranges, causal=True, scale=0.0, q_start=None, workspace=None):
+    """prefill_attn by a given plan (hs_prefill_attn_planned): slab = 16 or 32 query positions per wavefront, ranges of the tiles.
+    For tests and measurements.  Returns (O, LSE)."""
+    assert Q.dtype == torch_dtype(shape) and Q.is_contiguous() and Q.is_cuda
+    Lq = Q.shape[2]
+    O, lse = torch.empty_like(Q), Q.new_empty(Q.shape[:3], dtype=torch.float32)
+    if workspace is None and ranges > 1:
+        workspace = _workspace(ranges * shape.B * shape.Hq * Lq * (HEAD_DIM + 1) * 4, Q.device)
+    kvs = kv.struct()
+    _check(lib().hs_prefill_attn_planned(C.byref(shape), Lq, shape.L - Lq if q_start is None else int(q_start), float(scale),
+                                         int(bool(causal)), _ptr(Q), C.byref(kvs), _ptr(O), _ptr(lse), _ptr(workspace),
+                                         0 if workspace is None else workspace.nbytes, int(slab), int(ranges), _stream()))
     return O, lse
 
 

@@ -127,6 +127,34 @@ int decode_common(const hs_shape* shape, float scale, int32_t n_splits, const vo
   return HS_OK;
 }
 
+// shared body of the prefill entry points; given: the plan to run by, or NULL
+int prefill_common(const hs_shape* shape, int32_t Lq, int32_t q_start, float scale, int causal, const void* Q, const hs_kv* kv,
+                   void* O, float* LSE, void* workspace, size_t workspace_bytes, const hs_prefill_choice* given, void* stream) {
+  int rc = check_shape(shape);
+  if (rc != HS_OK) return rc;
+  rc = check_kv(shape, kv);
+  if (rc != HS_OK) return rc;
+  if (Q == nullptr || O == nullptr || (((uintptr_t)Q | (uintptr_t)O | (uintptr_t)workspace) & 15u)) return HS_EINVAL;
+  const int bad = prefill_args(shape, Lq, q_start);
+  if (bad != HS_OK) return bad;
+  // the prefill kernel addresses a tile inside its row's pool with a 32-bit byte offset
+  if ((int64_t)kv->cap_dense_k * HS_TILE_DENSE_BYTES > (int64_t)1 << 32 ||
+      (int64_t)kv->cap_dense_v * HS_TILE_DENSE_BYTES > (int64_t)1 << 32 ||
+      (int64_t)kv->cap_sparse_k * HS_TILE_NNZ_BYTES > (int64_t)1 << 32 ||
+      (int64_t)kv->cap_sparse_v * HS_TILE_NNZ_BYTES > (int64_t)1 << 32)
+    return HS_EUNSUPPORTED;
+  if (!(scale >= 0.f)) return HS_EINVAL;
+  if (scale == 0.f) scale = 1.0f / sqrtf((float)HS_D);
+  if (workspace == nullptr) workspace_bytes = 0;
+  if (given != nullptr && given->n_splits > 1 && workspace_bytes / prefill_split_bytes(shape, Lq) < (size_t)given->n_splits) return HS_EINVAL;
+  const hs_prefill_choice how = given != nullptr ? *given : prefill_plan(shape, Lq, q_start, causal, kv, workspace_bytes);
+  const hipError_t e = hs_launch_prefill(shape->B, shape->Hq, shape->Hkv, shape->L / HS_BT, Lq / HS_BT, q_start, scale,
+                                         causal != 0, (const uint16_t*)Q, hs_make_kv_dev(kv), (uint16_t*)O, LSE,
+                                         (hipStream_t)stream, shape->dtype, how, (float*)workspace);
+  if (e != hipSuccess) return hip_fail(e);
+  return HS_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -438,27 +466,15 @@ int hs_prefill_plan(const hs_shape* shape, int32_t Lq, int32_t q_start, int caus
 
 int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start, float scale, int causal, const void* Q,
                        const hs_kv* kv, void* O, float* LSE, void* workspace, size_t workspace_bytes, void* stream) {
-  int rc = check_shape(shape);
-  if (rc != HS_OK) return rc;
-  rc = check_kv(shape, kv);
-  if (rc != HS_OK) return rc;
-  if (Q == nullptr || O == nullptr || (((uintptr_t)Q | (uintptr_t)O | (uintptr_t)workspace) & 15u)) return HS_EINVAL;
-  const int bad = prefill_args(shape, Lq, q_start);
-  if (bad != HS_OK) return bad;
-  // the prefill kernel addresses a tile inside its row's pool with a 32-bit byte offset
-  if ((int64_t)kv->cap_dense_k * HS_TILE_DENSE_BYTES > (int64_t)1 << 32 ||
-      (int64_t)kv->cap_dense_v * HS_TILE_DENSE_BYTES > (int64_t)1 << 32 ||
-      (int64_t)kv->cap_sparse_k * HS_TILE_NNZ_BYTES > (int64_t)1 << 32 ||
-      (int64_t)kv->cap_sparse_v * HS_TILE_NNZ_BYTES > (int64_t)1 << 32)
-    return HS_EUNSUPPORTED;
-  if (!(scale >= 0.f)) return HS_EINVAL;
-  if (scale == 0.f) scale = 1.0f / sqrtf((float)HS_D);
-  const hs_prefill_choice how = prefill_plan(shape, Lq, q_start, causal, kv, workspace == nullptr ? 0 : workspace_bytes);
-  const hipError_t e = hs_launch_prefill(shape->B, shape->Hq, shape->Hkv, shape->L / HS_BT, Lq / HS_BT, q_start, scale,
-                                         causal != 0, (const uint16_t*)Q, hs_make_kv_dev(kv), (uint16_t*)O, LSE,
-                                         (hipStream_t)stream, shape->dtype, how, (float*)workspace);
-  if (e != hipSuccess) return hip_fail(e);
-  return HS_OK;
+  return prefill_common(shape, Lq, q_start, scale, causal, Q, kv, O, LSE, workspace, workspace_bytes, nullptr, stream);
+}
+
+int hs_prefill_attn_planned(const hs_shape* shape, int32_t Lq, int32_t q_start, float scale, int causal, const void* Q,
+                            const hs_kv* kv, void* O, float* LSE, void* workspace, size_t workspace_bytes, int32_t slab, int32_t ranges,
+                            void* stream) {
+  if ((slab != 16 && slab != 32) || ranges < 1 || ranges > 65535) return HS_EINVAL;
+  const hs_prefill_choice how = {slab / 16, ranges};
+  return prefill_common(shape, Lq, q_start, scale, causal, Q, kv, O, LSE, workspace, workspace_bytes, &how, stream);
 }
 
 int hs_decode_attn(const hs_shape* shape, float scale, int32_t n_splits, const void* Q, const hs_kv* kv, void* O,

@@ -42,6 +42,23 @@ def assert_lse_close(lse, ref, what):
     assert np.allclose(lse[~inf], ref[~inf], rtol=1e-4, atol=1e-4), (what, np.abs(lse[~inf] - ref[~inf]).max())
 
 
+def _prefill(sh, Q, kv, causal=True, scale=0.0, q_start=None):
+    """hb.prefill_attn, whose result the test holds against the oracle, after the kernels that the library did not choose for so
+    small a call (slabs of 16 and of 32 queries, in one range and in two) have been held against it: as close to it as each has to be
+    to the oracle, head by head."""
+    O, LSE = hb.prefill_attn(sh, Q, kv, causal=causal, scale=scale, q_start=q_start)
+    ref, lref = _f32(O), LSE.cpu().numpy()
+    assert np.isfinite(ref).all()
+    for slab in (16, 32):
+        for n in (1, 2):
+            Os, Ls = hb.prefill_attn_planned(sh, Q, kv, slab, n, causal=causal, scale=scale, q_start=q_start)
+            err = np.abs(_f32(Os) - ref)
+            assert (err.max((2, 3)) <= MAX_TOL * np.abs(ref).max((2, 3))).all(), (slab, n)
+            assert (err.mean((2, 3)) <= MEAN_TOL * np.abs(ref).mean((2, 3))).all(), (slab, n)
+            assert_lse_close(Ls.cpu().numpy(), lref, (slab, n))
+    return O, LSE
+
+
 def compress_both(B, Hq, Hkv, L, K, V, dtype="bf16", **pol):
     sh = hb.make_shape(B, Hq, Hkv, L, dtype=hb.FP16 if dtype == "fp16" else hb.BF16)
     lib_pol = dict(pol)
@@ -376,7 +393,7 @@ def test_decode_cfg1_full_size():
 def _prefill_case(B, Hq, Hkv, L, Lq, seed, causal=True, rows=None, **pol):
     Q, K, V = wl.make_qkv(B, Hq, Hkv, L, 128, Lq, seed=seed)
     sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, K, V, **pol)
-    O, LSE = hb.prefill_attn(sh, _dev(Q), kv, causal=causal)
+    O, LSE = _prefill(sh, _dev(Q), kv, causal=causal)
     torch.cuda.synchronize()
     if rows is None:
         rows = [(b, h, i) for b in range(B) for h in range(Hq) for i in range(Lq)]
@@ -430,7 +447,7 @@ def test_prefill_queries_placed_inside_a_capacity_cache(q_start, Lq):
     sk, sv = _mixed_states(B, Hkv, T_cap, seed=251, p_skip=0.1)
     sk[:, :, T_now:], sv[:, :, T_now:] = 0, 0
     sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, K, V, state_k=sk, state_v=sv)
-    O, LSE = hb.prefill_attn(sh, _dev(Q), kv, q_start=q_start)
+    O, LSE = _prefill(sh, _dev(Q), kv, q_start=q_start)
     torch.cuda.synchronize()
     rows = [(b, h, i) for b in range(B) for h in range(Hq) for i in range(Lq)]
     Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=True, q_offset=q_start)
@@ -443,14 +460,19 @@ def test_prefill_queries_placed_inside_a_capacity_cache(q_start, Lq):
                 hb.prefill_attn(sh, _dev(Q), kv, q_start=bad)
 
 
+@pytest.mark.parametrize("slab", [None, 16, 32])                  # None: what the library picks for the room it gets
 @pytest.mark.parametrize("n_ranges", [2, 5, 0])                   # 0: as many as the library picks
 @pytest.mark.parametrize("B,G,T,Lq,q_start,causal,dtype,pol", [
     (1, 4, 40, 64, None, True, "bf16", dict()),                            # a short turn at the end of a context
     (2, 3, 33, 128, 64 * 20 + 17, True, "fp16", dict(sparse_frac_k=0.0)),  # off the tile grid, a group with idle waves
     (1, 1, 70, 64, 0, False, "bf16", dict(sparse_frac_k=0.5, sparse_frac_v=0.5)),
     (1, 8, 48, 192, None, True, "bf16", "states"),                         # ranges without a kept tile, queries that see nothing
+    (1, 4, 40, 128, 64 * 30 + 5, True, "fp16", dict()),
+    (1, 2, 36, 64, None, True, "bf16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)),
+    (1, 2, 36, 64, None, True, "bf16", dict(sparse_frac_v=0.0)),
+    (1, 2, 36, 64, 64 * 2 + 63, True, "fp16", dict(dense_first_tiles=1, dense_last_tiles=4)),              # more ranges than tiles in sight
 ])
-def test_prefill_tiles_cut_into_ranges(n_ranges, B, G, T, Lq, q_start, causal, dtype, pol):
+def test_prefill_tiles_cut_into_ranges(slab, n_ranges, B, G, T, Lq, q_start, causal, dtype, pol):
     import ctypes as C
     Hkv, L = 2, 64 * T
     Q, K, V = wl.make_qkv(B, G * Hkv, Hkv, L, 128, Lq, seed=900 + T, dtype=dtype)
@@ -465,13 +487,20 @@ def test_prefill_tiles_cut_into_ranges(n_ranges, B, G, T, Lq, q_start, causal, d
     Qd, at = _dev(Q, dtype), L - Lq if q_start is None else q_start
     need = hb.prefill_workspace_bytes(sh, Lq, at, kv, causal)
     one = B * G * Hkv * Lq * 129 * 4
-    assert need >= 2 * one                            # the library does cut these shapes
-    n = n_ranges or need // one
+    n = n_ranges or max(need // one, 1)
+    if q_start != 64 * 2 + 63:
+        assert need >= 2 * one                        # the library does cut these shapes
+    elif slab is not None:
+        n = n_ranges or 8
     ws = torch.full((n * one + 64,), 255, dtype=torch.uint8, device="cuda")
     O, LSE = torch.full_like(Qd, float("nan")), torch.full(Qd.shape[:3], float("nan"), device="cuda")
     kvs = kv.struct()
-    hb._check(hb.lib().hs_prefill_attn_ws(C.byref(sh), Lq, at, 0.0, int(causal), hb._ptr(Qd), C.byref(kvs), hb._ptr(O), hb._ptr(LSE),
-                                          hb._ptr(ws), n * one, hb._stream()))
+    args = (C.byref(sh), Lq, at, 0.0, int(causal), hb._ptr(Qd), C.byref(kvs), hb._ptr(O), hb._ptr(LSE), hb._ptr(ws), n * one)
+    if slab is None:
+        assert hb.prefill_plan(sh, Lq, at, kv, causal, n * one)[1] <= n
+        hb._check(hb.lib().hs_prefill_attn_ws(*args, hb._stream()))
+    else:
+        hb._check(hb.lib().hs_prefill_attn_planned(*args, slab, n, hb._stream()))
     torch.cuda.synchronize()
     assert (ws[n * one:] == 255).all()                # nothing past the bytes it was given
     rows = [(b, h, i) for b in range(B) for h in range(G * Hkv) for i in range(0, Lq, 3)]
@@ -479,7 +508,7 @@ def test_prefill_tiles_cut_into_ranges(n_ranges, B, G, T, Lq, q_start, causal, d
     Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=causal, **({} if q_start is None else {"q_offset": q_start}))
     assert_close(_f32(O)[idx], Or, f"prefill in {n} ranges")
     assert_lse_close(LSE.cpu().numpy()[idx], Lr, f"prefill in {n} ranges lse")
-    if n_ranges == 0:                                 # the binding's own call takes the same way
+    if n_ranges == 0 and slab is None:                # the binding's own call takes the same way
         O2, LSE2 = hb.prefill_attn(sh, Qd, kv, causal=causal, q_start=q_start)
         assert torch.equal(O2.view(torch.int16), O.view(torch.int16)) and torch.equal(LSE2, LSE)
 
@@ -523,7 +552,7 @@ def test_prefill_slabs_of_16_and_of_32_queries(pol, dtype):
 def test_prefill_slab_choice_over_shapes(B, Hq, Hkv, L, Lq, q_start, causal):
     Q, K, V = wl.make_qkv(B, Hq, Hkv, L, 128, Lq, seed=1210 + Hq, k_outliers=True)
     sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, K, V)
-    O, LSE = hb.prefill_attn(sh, _dev(Q), kv, causal=causal, q_start=q_start)
+    O, LSE = _prefill(sh, _dev(Q), kv, causal=causal, q_start=q_start)
     rows = wl.sample_rows(B, Hq, Lq, 200, seed=1211, extra=[(0, 0, 0), (B - 1, Hq - 1, Lq - 1), (0, Hq - 1, 16), (0, 0, 15)])
     idx = tuple(np.array(rows).T)
     Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=causal, **({} if q_start is None else {"q_offset": q_start}))
@@ -1026,7 +1055,9 @@ def _check_nan_rows(O, LSE, Or, Lr, what):
     assert_lse_close(LSE[~nan].numpy(), Lr[~nan].numpy(), what)
 
 
-@pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict(sparse_frac_k=0.0)), ("bf16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0))])
+@pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict(sparse_frac_k=0.0)), ("bf16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)),
+                                       ("fp16", dict()), ("bf16", dict(sparse_frac_v=0.0)), ("bf16", dict(dense_first_tiles=1, dense_last_tiles=4)),
+                                       ("fp16", dict(sparse_frac_k=0.5))])
 def test_prefill_nan_scores_come_out_however_the_tiles_are_cut(dtype, pol):
     """A query that sees a NaN score has O and LSE NaN, in one range and in several; the others see nothing of it."""
     import ctypes as C
@@ -1045,6 +1076,9 @@ def test_prefill_nan_scores_come_out_however_the_tiles_are_cut(dtype, pol):
         hb._check(hb.lib().hs_prefill_attn_ws(C.byref(sh), Lq, at, 0.0, 1, hb._ptr(Qd), C.byref(kvs), hb._ptr(O), hb._ptr(LSE), hb._ptr(ws),
                                               n * one, hb._stream()))
         _check_nan_rows(O.cpu()[0], LSE.cpu()[0], Or, Lr, f"prefill with NaN scores in {n} ranges")
+        for slab in (16, 32):
+            O, LSE = hb.prefill_attn_planned(sh, Qd, kv, slab, n)
+            _check_nan_rows(O.cpu()[0], LSE.cpu()[0], Or, Lr, f"prefill with NaN scores in {n} ranges, slabs of {slab}")
 
 
 @pytest.mark.parametrize("T", [6, 70])
@@ -1434,7 +1468,7 @@ def test_random_shapes_and_policies(seed):
             assert ((gaps > 1e-12) | (gaps == 0)).all()
     check_packed_bit_exact(sh, kv, pk, pv)
     causal = bool(rng.integers(0, 4))          # mostly causal
-    O, LSE = hb.prefill_attn(sh, _dev(Q), kv, causal=causal)
+    O, LSE = _prefill(sh, _dev(Q), kv, causal=causal)
     n_rows = min(96, B * Hq * Lq)
     flat = rng.choice(B * Hq * Lq, size=n_rows, replace=False)
     rows = [(int(f // (Hq * Lq)), int((f // Lq) % Hq), int(f % Lq)) for f in flat]
@@ -1614,7 +1648,7 @@ def test_fp16_all_stages(pol):
     V[0, 1, 8:12, 7] = wl.f32_to_f16_bits(np.array([6e-8, -6e-8, 1e-7, 0], dtype=np.float32))        # subnormals
     sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, K, V, dtype="fp16", **pol)
     check_packed_bit_exact(sh, kv, pk, pv)
-    O, LSE = hb.prefill_attn(sh, _dev(Q, "fp16"), kv)
+    O, LSE = _prefill(sh, _dev(Q, "fp16"), kv)
     torch.cuda.synchronize()
     rows = wl.sample_rows(B, Hq, L, 160, seed=181, extra=[(0, 0, 0), (B - 1, Hq - 1, L - 1)])
     Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=True)
@@ -1645,7 +1679,7 @@ def test_fp16_large_logits_and_long_flat_rows():
     ramp = np.linspace(0.05, 6.0, L, dtype=np.float32)[None, None, :, None]     # logits grow to the hundreds
     Kb = wl.f32_to_f16_bits(Kf * ramp)
     sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, Kb, V, dtype="fp16")
-    O, LSE = hb.prefill_attn(sh, _dev(Q, "fp16"), kv)
+    O, LSE = _prefill(sh, _dev(Q, "fp16"), kv)
     Od, LSEd = hb.decode_attn(sh, _dev(Q[:, :, -1, :].copy(), "fp16"), kv)
     torch.cuda.synchronize()
     rows = [(0, h, i) for h in range(Hq) for i in range(0, L, 7)] + [(0, h, L - 1) for h in range(Hq)]
@@ -1660,7 +1694,7 @@ def test_fp16_large_logits_and_long_flat_rows():
     Kz[0, 0, 100] = wl.f32_to_f16_bits(Q[0, 0, -1].view(np.float16).astype(np.float32) * 1.23)
     sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, Kz, V, dtype="fp16", sparse_frac_k=0.0, sparse_frac_v=0.0)
     Od, LSEd = hb.decode_attn(sh, _dev(Q[:, :, -1, :].copy(), "fp16"), kv, n_splits=1)
-    O, LSE = hb.prefill_attn(sh, _dev(Q, "fp16"), kv)
+    O, LSE = _prefill(sh, _dev(Q, "fp16"), kv)
     torch.cuda.synchronize()
     Odr, Ldr = orc.attention_decode(Q[:, :, -1, :].copy(), pk, pv)
     assert_close(_f32(Od), Odr, "fp16 decode flat row")
@@ -1698,7 +1732,7 @@ def test_bf16_cache_with_both_v_tile_encodings(pol, planted):
     live = pv.map != 0
     assert (flagged & live).any() and (~flagged & live).any()
     check_packed_bit_exact(sh, kv, pk, pv)
-    O, LSE = hb.prefill_attn(sh, _dev(Q), kv)
+    O, LSE = _prefill(sh, _dev(Q), kv)
     torch.cuda.synchronize()
     rows = wl.sample_rows(B, Hq, L, 200, seed=192, extra=[(0, 0, 0), (B - 1, Hq - 1, L - 1)])
     Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=True)
@@ -1940,7 +1974,7 @@ def test_single_tile_and_odd_batch_shapes():
         Q, K, V = wl.make_qkv(B, Hq, Hkv, L, 128, L, seed=130 + B)
         sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, K, V)
         check_packed_bit_exact(sh, kv, pk, pv)
-        O, LSE = hb.prefill_attn(sh, _dev(Q), kv)
+        O, LSE = _prefill(sh, _dev(Q), kv)
         q = Q[:, :, -1, :].copy()
         Od, LSEd = hb.decode_attn(sh, _dev(q), kv)
         torch.cuda.synchronize()
@@ -1962,7 +1996,7 @@ def test_scale_argument_and_large_logits():
     Kbig[:, :, 64 * 4:64 * 5] = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(K[:, :, 64 * 4:64 * 5]) * 96.0)
     sh, kv, pk, pv, _ = compress_both(B, Hq, Hkv, L, Kbig, V)
     for scale in (0.0, 0.25):
-        O, LSE = hb.prefill_attn(sh, _dev(Q), kv, scale=scale)
+        O, LSE = _prefill(sh, _dev(Q), kv, scale=scale)
         Od, LSEd = hb.decode_attn(sh, _dev(Q[:, :, -1, :].copy()), kv, scale=scale)
         torch.cuda.synchronize()
         rows = [(0, h, i) for h in range(Hq) for i in range(L)]
@@ -2036,6 +2070,12 @@ def test_argument_errors_on_device_calls():
     kvs = kv.struct()
     Qd = _dev(Q)
     O = torch.empty_like(Qd)
+    one = sh.B * sh.Hq * 64 * 129 * 4
+    ws = torch.empty(2 * one, dtype=torch.uint8, device="cuda")
+    for slab, n, w, room in ((8, 1, ws, 2 * one), (48, 1, ws, 2 * one), (32, 0, ws, 2 * one), (16, 65536, ws, 2 * one), (16, 3, ws, 2 * one),
+                             (32, 2, ws, 2 * one - 1), (32, 2, None, 2 * one)):      # no such slab, no such ranges, no room for them
+        assert hb.lib().hs_prefill_attn_planned(C.byref(sh), 64, 0, 0.0, 1, hb._ptr(Qd), C.byref(kvs), hb._ptr(O), None, hb._ptr(w), room, slab, n,
+                                                None) == -1
     assert hb.lib().hs_prefill_attn(C.byref(sh), 100, 0.0, 1, hb._ptr(Qd), C.byref(kvs), hb._ptr(O), None, None, None) == -2
     assert hb.lib().hs_prefill_attn(C.byref(sh), 512, 0.0, 1, hb._ptr(Qd), C.byref(kvs), hb._ptr(O), None, None, None) == -1
     # a pool of more than 4 GiB per (batch, kv head) row: prefill addresses tiles with 32-bit offsets
