@@ -214,7 +214,7 @@ union B16 {  // one B operand of the 16x16x64 sparse instruction = two of the de
 // keys-dense / values-2:4 setting of Sec. V-A carries no dynamic dispatch).
 // NB: column blocks (of 16 queries) per wave: a wave owns a slab of 16*NB query positions of one
 // head.  NB = 2 fits 2 waves per SIMD (NB = 4, 1 wave per SIMD, measured 1.3-1.4x slower; NB = 3 at 2 waves spills: 16K prompt
-// 1346 -> 1529 us); NB = 1 takes 0.7 of its time for half of the work.
+// 1346 -> 1529 us); NB = 1 takes three quarters of its time for half of the work.
 // F16: element type of the cache (hs_elem).  A V tile of a bf16 cache may be stored in fp16 encoding
 // (HS_MAP_F16 in its map entry).  Against fp16 V the numerators have 11 significant bits and enter
 // GEMM2 as one fp16 term; against bf16 V they enter as two bf16 terms.  The reference is kept
