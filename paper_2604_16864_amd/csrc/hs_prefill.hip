@@ -52,7 +52,7 @@ int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, i
 // The sum below is fitted to 2:4 tensors.  It is up to 18 % low on these examples (4 prompts of 512 tokens 16.2 / 18.0, 13 of 192
 // 17.5 / 19.9), and of 500 drawn calls of every kind 90 % lie between 0.93 and 1.1 of the time on 2:4 tensors, 0.75 and 1.05 on
 // mixed and dense ones; what matters is the difference of the two slabs, where most of that cancels.  Of those 500, all of which it
-// put in slabs of 16, the mean gain over slabs of 32 in all the ranges allowed is 1.20, and 9 are 2 to 7.5 % slower (4 x 192 queries
+// put in slabs of 16, the mean gain over slabs of 32 in all the ranges allowed is 1.20, and ten are 2 to 7.5 % slower (4 x 192 queries
 // of 40/8 heads on 3584 tokens with dense ends, fp16, 57.2 / 61.5; 4 x 64 of 7/1 on 13760, values dense, 32.6 / 35.2).
 // Its terms (us): a workgroup starts in kStart, a tile takes it kAlone with a compute unit
 // to itself and kPair beside a second one; 512 run at a time, the longest first, so the call ends with the longest, or when the
