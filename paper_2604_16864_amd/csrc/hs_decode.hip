@@ -222,96 +222,114 @@ struct TailArgs {
   int len;
 };
 
-// Partial of the dense tail of one (batch, kv head) row, written as split `slot`: plain fp32 attention of its G query
-// heads over tail_len tokens.  One workgroup of 256 threads, latency-bound (32 KB of input, 3 barriers), so everything
-// it reads from memory is requested at once, in 16-byte (K) and coalesced 4-byte (V) loads, before the first barrier.
-// It runs as one more workgroup per row of the split kernel, beside the others, instead of as a launch of its own in
-// front of the merge (7.9 us at 16 rows x 8 heads, 6.2 us at 4 x 8): calls of 74.6 -> 66.1 us and 65.5 -> 59.6 us there.
-//   scores   thread = (token tid / 4, quarter of the channels tid % 4), quarters summed across lanes
-//   softmax  wave w = heads w and w + 4, lane = token
-//   output   thread = (tokens 16 (tid / 64) .. +15, channels 2 (tid % 64), +1), the four token quarters summed in LDS
+// Q^T of one (batch, kv head) row as the B operand: columns 0..G-1 and 8..8+G-1 both hold head column % 8 of the group
+// (GEMM2 over the tiles gives the second copy the low-order half of P).  hq0: the group's first query head.
+__device__ __forceinline__ void load_q(const uint16_t* __restrict__ Q, int64_t hq0, int G, int a, int c, uint4 (&qb)[4]) {
+  const int head = c & 7;
+  const bool valid = head < G;
+  const uint16_t* q = Q + (hq0 + (valid ? head : 0)) * HS_D + 8 * a;
+#pragma unroll
+  for (int s = 0; s < 4; s++) qb[s] = valid ? *reinterpret_cast<const uint4*>(q + 32 * s) : make_uint4(0, 0, 0, 0);
+}
+
+// A wave's share of the dense tail of one row: tokens 16 q .. 16 q + 15 of the tail buffer, all query heads of the group, into the
+// combine's slots (reference, sum, unnormalised O^T per column).  Everything it reads is requested at once; the scores come from
+// the 16-bit matrix instruction like those of a dense tile, O^T from the 32-bit one, so that P keeps its 32 bits:
+// its k is a lane group's token i (the accumulators of the scores are its B operand as they stand), its row r of block mb is channel
+// 8 r + mb, so that a lane reads 8 consecutive channels of 4 tokens.  Tokens from tail_len on are not read.
+// Latency-bound, one chain of load, products, exponentials, products.  The same on the vector ALU, with q and P in LDS, read
+// the LDS once more per head and was the last to end: us a call, then / now, 8 rows of 256 tiles with a tail, 4 heads a row
+// 14.1 / 12.5, 8 heads 16.1 / 12.8; 128 rows of 16 tiles 13.7 / 12.4, 15.9 / 12.8; 8 rows of 32 tiles 8.3 / 7.6, 10.1 / 7.6; with one
+// head a row the same.
 template <bool F16>
-__device__ __forceinline__ void tail_partial(const TailArgs& tail, int tail_len, int G, int64_t row, int64_t hq0, float scale_log2,
-                                             const uint16_t* __restrict__ Q, float (&sm_o)[4][8][HS_D], int n_splits, int slot,
-                                             float* __restrict__ ws_o, float* __restrict__ ws_l) {
+__device__ __forceinline__ void tail_piece(const TailArgs& tail, int tail_len, int64_t row, int q, const uint4 (&qb)[4], float scale_log2,
+                                           int l, float (&sm_o)[8][HS_D], float (&sm_m)[8], float (&sm_l)[8]) {
   typedef hs_elem<F16> E;
-  constexpr int kQRow = 4 * 36;  // a head's 128 channels in LDS: quarters 36 floats apart, so that the four lanes of a token
-                                 // read from different banks
-  __shared__ __attribute__((aligned(16))) float sq[8][kQRow];
-  __shared__ float sp[8][HS_BT];
-  __shared__ float sl[8];
-  const int tid = threadIdx.x, w = tid >> 6;
-  const int tok = tid >> 2, qd = tid & 3;
-  const uint16_t* tk = tail.k + row * HS_BT * HS_D + tok * HS_D + 32 * qd;
-  const uint16_t* tv = tail.v + row * HS_BT * HS_D + 2 * (tid & 63);
-  uint4 kk[4];
+  const int a = l >> 4, c = l & 15, left = tail_len - 16 * q;  // left: wave-uniform
+  float m = -INFINITY, sum = 0.f;
+  f32x4_t o[8];
 #pragma unroll
-  for (int i = 0; i < 4; i++) kk[i] = tok < tail_len ? *reinterpret_cast<const uint4*>(tk + 8 * i) : make_uint4(0, 0, 0, 0);
-  uint32_t vv[16];
+  for (int mb = 0; mb < 8; mb++) o[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  if (left > 0) {
+    const uint16_t* tk = tail.k + (row * HS_BT + 16 * q + c) * HS_D + 8 * a;
+    const uint16_t* tv = tail.v + (row * HS_BT + 16 * q + 4 * a) * HS_D + 8 * c;
+    uint4 kk[4], vv[4];
 #pragma unroll
-  for (int i = 0; i < 16; i++)
-    vv[i] = 16 * w + i < tail_len ? *reinterpret_cast<const uint32_t*>(tv + (16 * w + i) * HS_D) : 0u;
-  for (int i = tid; i < G * (HS_D / 2); i += 256) {
-    const uint32_t pair = *reinterpret_cast<const uint32_t*>(Q + hq0 * HS_D + 2 * i);
-    const int g = i / (HS_D / 2), c = 2 * (i % (HS_D / 2));
-    float* d = &sq[g][(c >> 5) * 36 + (c & 31)];
-    d[0] = E::lo_f32(pair);
-    d[1] = E::hi_f32(pair);
-  }
-  __syncthreads();
-  for (int g = 0; g < G; g++) {
-    float acc = 0.f;
+    for (int s = 0; s < 4; s++) kk[s] = c < left ? *reinterpret_cast<const uint4*>(tk + 32 * s) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; i++) vv[i] = 4 * a + i < left ? *reinterpret_cast<const uint4*>(tv + i * HS_D) : make_uint4(0, 0, 0, 0);
+    f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < 4; st++) s = E::mma(kk[st], qb[st], s);
+    float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-      const float4 q0 = *reinterpret_cast<const float4*>(&sq[g][36 * qd + 8 * i]);
-      const float4 q1 = *reinterpret_cast<const float4*>(&sq[g][36 * qd + 8 * i + 4]);
-      acc = fmaf(E::lo_f32(kk[i].x), q0.x, acc); acc = fmaf(E::hi_f32(kk[i].x), q0.y, acc);
-      acc = fmaf(E::lo_f32(kk[i].y), q0.z, acc); acc = fmaf(E::hi_f32(kk[i].y), q0.w, acc);
-      acc = fmaf(E::lo_f32(kk[i].z), q1.x, acc); acc = fmaf(E::hi_f32(kk[i].z), q1.y, acc);
-      acc = fmaf(E::lo_f32(kk[i].w), q1.z, acc); acc = fmaf(E::hi_f32(kk[i].w), q1.w, acc);
+      if (4 * a + i >= left) s[i] = -INFINITY;
+      mx = fmaxf(mx, s[i]);
     }
-    acc += __shfl_xor(acc, 1);
-    acc += __shfl_xor(acc, 2);
-    if (qd == 0) sp[g][tok] = tok < tail_len ? acc * scale_log2 : -INFINITY;
-  }
-  __syncthreads();
-  for (int g = w; g < G; g += 4) {
-    const int t = tid & 63;
-    const float sc = sp[g][t];
-    float mx = sc;
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    m = mx * scale_log2;
+    const float ref = m > -INFINITY ? m : 0.f;  // every score -inf: weights 0, not exp2(-inf + inf)
+    float p[4];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    const float p = t < tail_len ? __builtin_amdgcn_exp2f(sc - (mx > -INFINITY ? mx : 0.f)) : 0.f;
-    float l = p;
+    for (int i = 0; i < 4; i++) {
+      p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], scale_log2, -ref));
+      sum += p[i];
+    }
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
-    sp[g][t] = p;
-    if (t == 0) {
-      sl[g] = l;
-      ws_l[(hq0 + g) * n_splits + slot] = l == 0.f ? -INFINITY : (mx + __builtin_amdgcn_logf(l)) * kLn2;
+    for (int i = 0; i < 4; i++) {
+      const uint32_t d[4] = {vv[i].x, vv[i].y, vv[i].z, vv[i].w};
+#pragma unroll
+      for (int mb = 0; mb < 8; mb++)
+        o[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(mb & 1 ? E::hi_f32(d[mb >> 1]) : E::lo_f32(d[mb >> 1]), p[i], o[mb], 0, 0, 0);
     }
   }
-  __syncthreads();
-  for (int g = 0; g < G; g++) {
-    float a0 = 0.f, a1 = 0.f;
+  if (c < 8) {
+    if (a == 0) { sm_m[c] = m; sm_l[c] = sum; }
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-      const float p = sp[g][16 * w + i];
-      a0 = fmaf(p, E::lo_f32(vv[i]), a0);
-      a1 = fmaf(p, E::hi_f32(vv[i]), a1);
+    for (int i = 0; i < 4; i++) {
+      float4* d = reinterpret_cast<float4*>(&sm_o[c][8 * (4 * a + i)]);
+      d[0] = make_float4(o[0][i], o[1][i], o[2][i], o[3][i]);
+      d[1] = make_float4(o[4][i], o[5][i], o[6][i], o[7][i]);
     }
-    *reinterpret_cast<float2*>(&sm_o[w][g][2 * (tid & 63)]) = make_float2(a0, a1);
   }
-  __syncthreads();
+}
+
+// Combines the N parts that the waves have left in LDS and writes the row's partial of split `slot`, or (DIRECT) its O and LSE.
+// Thread = (head tid / 32, 4 channels).  part_m, part_l, part_o: of N parts, 8 heads each.
+template <bool F16, bool DIRECT>
+__device__ __forceinline__ void combine_parts(int tid, int N, int G, int64_t hq0, const float (*part_m)[8], const float (*part_l)[8],
+                                              const float (*part_o)[8][HS_D], int n_splits, int slot, float* __restrict__ ws_o,
+                                              float* __restrict__ ws_l) {
   const int g = tid >> 5, ch = (tid & 31) * 4;
-  if (g < G) {
-    float acc[4];
+  if (g >= G) return;
+  const int64_t hq = hq0 + g;
+  float mstar = -INFINITY;
+  for (int k = 0; k < N; k++) mstar = fmaxf(mstar, part_m[k][g]);
+  // a part without a reference has seen nothing (l and O are 0) or only NaN scores (l is NaN): neither is left out,
+  // and only l == 0 is an empty split, so that a NaN reaches O and LSE however the tiles are divided
+  const float mref = mstar > -INFINITY ? mstar : 0.f;
+  float lsum = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < N; k++) {
+    const float f = __builtin_amdgcn_exp2f(part_m[k][g] - mref);
+    lsum += f * part_l[k][g];
 #pragma unroll
-    for (int i = 0; i < 4; i++) acc[i] = (sm_o[0][g][ch + i] + sm_o[1][g][ch + i]) + (sm_o[2][g][ch + i] + sm_o[3][g][ch + i]);
-    const float l = sl[g];
-    float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (l != 0.f) out = make_float4(acc[0] / l, acc[1] / l, acc[2] / l, acc[3] / l);
-    *reinterpret_cast<float4*>(ws_o + ((hq0 + g) * n_splits + slot) * HS_D + ch) = out;
+    for (int i = 0; i < 4; i++) acc[i] += f * part_o[k][g][ch + i];
+  }
+  const float inv = lsum == 0.f ? 0.f : 1.f / lsum;
+  const float lse = lsum == 0.f ? -INFINITY : (mstar + __builtin_amdgcn_logf(lsum)) * kLn2;
+  if constexpr (DIRECT) {
+    typedef hs_elem<F16> E;
+    uint16_t* po = reinterpret_cast<uint16_t*>(ws_o) + hq * HS_D + ch;
+    store4(po, E::pack2(acc[0] * inv, acc[1] * inv), E::pack2(acc[2] * inv, acc[3] * inv), ((uintptr_t)ws_o & 7) == 0);
+    if (ws_l != nullptr && (tid & 31) == 0) ws_l[hq] = lse;
+  } else {
+    float* po = ws_o + (hq * n_splits + slot) * HS_D + ch;
+    *reinterpret_cast<float4*>(po) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+    if ((tid & 31) == 0) ws_l[hq * n_splits + slot] = lse;
   }
 }
 
@@ -338,9 +356,11 @@ constexpr int kListCap = 2048;  // tiles listed in LDS at a time (kByCount); lon
 constexpr int kScanBatch = 2048;  // tiles of the row looked at per scan step: 8 per thread
 
 // NW: waves per workgroup.  4: the partial of a split goes to ws_o / ws_l.  8: the workgroup has the whole row (one
-// split, no tail) and writes O and LSE itself (handed in as ws_o, ws_l): no merge launch.
+// split, and the row's dense tail) and writes O and LSE itself (handed in as ws_o, ws_l): no merge launch.
+// waves_per_eu: what the registers allow, as the most too: the scheduler otherwise goes by what the LDS would allow, and orders the loads
+// of a mixed tensor's tiles worse (4 sequences of 32K tokens, half of the keys dense, 58.7 / 58.3 us).
 template <int KM, int VM, int MODE, bool F16, int NW>
-__global__ __launch_bounds__(64 * NW, HS_DEC_OCC) void decode_split_kernel(int B, int z0, int turn, int Hq, int Hkv, int T, float scale_log2,
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HS_DEC_OCC, HS_DEC_OCC))) void decode_split_kernel(int B, int z0, int turn, int Hq, int Hkv, int T, float scale_log2,
                                                                              int n_splits, int per,
                                                                              const uint16_t* __restrict__ Q,
                                                                              hs_kv_dev kv, TailArgs tail,
@@ -359,287 +379,269 @@ __global__ __launch_bounds__(64 * NW, HS_DEC_OCC) void decode_split_kernel(int B
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, scalar: branches on it stay scalar
   const int G = Hq / Hkv;
   constexpr bool DIRECT = NW == 8;
-  __shared__ __attribute__((aligned(16))) float sm_o[NW][8][HS_D];
+  constexpr int kParts = DIRECT ? NW + 4 : NW;  // the waves', and the dense tail's where it does not have a workgroup of its own
+  __shared__ __attribute__((aligned(16))) float sm_o[kParts][8][HS_D];
+  __shared__ float sm_m[kParts][8], sm_l[kParts][8];
   const int n_work = gridDim.x;  // partial slots of the cache's tiles; the tail's is the next one
-  if constexpr (!DIRECT) {
-    if (b >= B) {  // the whole workgroup
-      const int64_t t_row = ((int64_t)(b - B) * Hkv + hkv) * n_work + split;
-      if (t_row >= (int64_t)B * Hkv) return;
-      const int tb = (int)(t_row / Hkv);
-      const int len = tail.lens != nullptr ? min(max(tail.lens[tb], 0), HS_BT) : tail.len;
-      tail_partial<F16>(tail, len, G, t_row, (int64_t)tb * Hq + (t_row - (int64_t)tb * Hkv) * G, scale_log2, Q, sm_o, n_splits, n_work,
-                        ws_o, ws_l);
-      return;
-    }
-  }
-  const int64_t row = (int64_t)b * Hkv + hkv;
-  const int t_begin = split * per, t_end = min(T, t_begin + per);
+  auto tail_length = [&](int of) -> int {
+    return __builtin_amdgcn_readfirstlane(tail.lens != nullptr ? min(max(tail.lens[of], 0), HS_BT) : tail.len);
+  };
+  // Where the results go, in registers from the start: left to itself the compiler reads the two pointers from the kernel's arguments
+  // in front of the last stores, and the launch ends 0.2 to 0.4 us later (16 sequences of 4K to 16K tokens with tails 66.0 / 66.5 us,
+  // 128 rows of 49 tiles 17.3 / 17.6).
+  typedef __attribute__((address_space(1))) float* global_t;
+  global_t to_o = (global_t)ws_o, to_l = (global_t)ws_l;
+  asm volatile("" : "+s"(to_o), "+s"(to_l));
+  // the row, its group's first query head, and the partial slot that this workgroup writes
+  int64_t row = (int64_t)b * Hkv + hkv, hq0 = (int64_t)b * Hq + hkv * G;
+  int slot = split, n_parts = NW;
+  if (!DIRECT && __builtin_expect(b >= B, 0)) {  // the whole workgroup: the dense tail of a row
+    row = ((int64_t)(b - B) * Hkv + hkv) * n_work + split;
+    if (row >= (int64_t)B * Hkv) return;
+    __builtin_amdgcn_s_setprio(3);  // one short chain beside waves that stream: last, it would be what the launch ends with (16 x 2K tokens, one head a row, 17.6 / 16.8)
+    const int tb = (int)(row / Hkv);
+    hq0 = (int64_t)tb * Hq + (row - (int64_t)tb * Hkv) * G;
+    slot = n_work;
+    uint4 qt[4];
+    load_q(Q, hq0, G, a, c, qt);
+    tail_piece<F16>(tail, tail_length(tb), row, w, qt, scale_log2, l, sm_o[w], sm_m[w], sm_l[w]);
+  } else {
+      const int t_begin = split * per, t_end = min(T, t_begin + per);
 
-  // Q^T as the B operand: columns 0..G-1 and 8..8+G-1 both hold head (hkv*G + column%8);
-  // the second copy carries the low-order half of P in GEMM2.
-  uint4 qb[4];  // dense k-steps s = 0..3 (channels 32s + 8a + e); sparse kb uses steps 2kb, 2kb+1
-  {
-    const int head = c & 7;
-    const bool valid = head < G;
-    const uint16_t* q = Q + ((int64_t)b * Hq + hkv * G + (valid ? head : 0)) * HS_D + 8 * a;
+    uint4 qb[4];  // dense k-steps s = 0..3 (channels 32s + 8a + e); sparse kb uses steps 2kb, 2kb+1
+    load_q(Q, hq0, G, a, c, qb);
+
+    f32x4_t o[8];
 #pragma unroll
-    for (int s = 0; s < 4; s++) qb[s] = valid ? *reinterpret_cast<const uint4*>(q + 32 * s) : make_uint4(0, 0, 0, 0);
-  }
+    for (int i = 0; i < 8; i++) o[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
 
-  f32x4_t o[8];
-#pragma unroll
-  for (int i = 0; i < 8; i++) o[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
-
-  // A tile's form: bit 0 = K tile dense, bit 1 = V tile dense, bit 2 = V tile stored in bf16 encoding (bf16
-  // caches only; a V tile of a bf16 cache is normally stored in fp16 encoding, HS_MAP_F16).  The tiles are
-  // worked through one form at a time ("sweeps"): the loads and matrix instructions of a sweep are all of one
-  // type, no branch sits between them, and each sweep keeps as many tiles in flight as its operands leave
-  // registers for.  The softmax recurrence does not care in which order tiles arrive.
-  auto form_of = [](int mk, int mv) -> int { return (mk > 0 ? 1 : 0) | (mv > 0 ? 2 : 0) | ((!F16 && !hs_map_f16(mv)) ? 4 : 0); };
-  constexpr bool kMixed = KM == 2 || VM == 2;
-  constexpr int kFirstForm = (KM == 1 ? 1 : 0) | (VM == 1 ? 2 : 0);  // swept first: it also notes which other forms occur
-  // One sweep.  The tiles come as a sequence of map entry pairs numbered [first, last): `entry(i, mk, mv)` yields
-  // pair i; wave w takes every NW-th pair starting at first + w.  Returns (COLLECT) the set of forms among them.
-  // SPEC (uniform caches, first sweep): where the wave's first tiles sit is known without the maps (slot ==
-  // tile), only their form is not (the encoding bit of the V map of a bf16 cache), so the first round is a
-  // straight-line copy of its own that issues their loads at once, behind the map read instead of after it
-  // and with no ballot or branch in front of them (4-6 % of the kernel at the 32K-context shape, fp16 caches,
-  // which have no map to wait for, included).  If one of the tiles turns out to be of another form (a V tile
-  // that fp16 cannot hold) the sweep returns kGuessFailed before it has touched the accumulators, and is run
-  // again without guessing.
-  constexpr unsigned kGuessFailed = 1u << 31;
-  auto sweep = [&](auto form_c, auto collect_c, auto spec_c, int first, int last, auto entry) -> unsigned {
-    constexpr int kForm = decltype(form_c)::value;
-    constexpr bool COLLECT = decltype(collect_c)::value;
-    constexpr bool SPEC = decltype(spec_c)::value;
-    constexpr int KK = kForm & 1, VK = (kForm >> 1) & 1, kEnc = (kForm & 4) ? 0 : 1;
-    // Tiles in flight per wave.  Measured on the 32K-context shape: depth 1, 2, 3 and 4 (the deeper ones at
-    // 1 wave per SIMD) all land within run-to-run noise, and even a variant with the arithmetic removed is only
-    // ~10 % faster: the kernel is bound by the load stream.  A kernel for mixed tensors runs at 2 waves per
-    // SIMD, where only two 2:4 tiles (or one tile with a dense operand) fit.
-    constexpr int DEPTH = kMixed || NW == 8 ? ((KK == 0 && VK == 0) ? 2 : 1) : HS_DEC_DEPTH;
-    TileRegs<KK, VK> ring[DEPTH];
-    unsigned seen = 0;
-// what the two copies of a round below share: the form ballots, and the loop that consumes the tiles in
-// flight and refills their ring slots from `act`
+    // A tile's form: bit 0 = K tile dense, bit 1 = V tile dense, bit 2 = V tile stored in bf16 encoding (bf16
+    // caches only; a V tile of a bf16 cache is normally stored in fp16 encoding, HS_MAP_F16).  The tiles are
+    // worked through one form at a time ("sweeps"): the loads and matrix instructions of a sweep are all of one
+    // type, no branch sits between them, and each sweep keeps as many tiles in flight as its operands leave
+    // registers for.  The softmax recurrence does not care in which order tiles arrive.
+    auto form_of = [](int mk, int mv) -> int { return (mk > 0 ? 1 : 0) | (mv > 0 ? 2 : 0) | ((!F16 && !hs_map_f16(mv)) ? 4 : 0); };
+    constexpr bool kMixed = KM == 2 || VM == 2;
+    constexpr int kFirstForm = (KM == 1 ? 1 : 0) | (VM == 1 ? 2 : 0);  // swept first: it also notes which other forms occur
+    // One sweep.  The tiles come as a sequence of map entry pairs numbered [first, last): `entry(i, mk, mv)` yields
+    // pair i; wave w takes every NW-th pair starting at first + w.  Returns (COLLECT) the set of forms among them.
+    // SPEC (uniform caches, first sweep): where the wave's first tiles sit is known without the maps (slot ==
+    // tile), only their form is not (the encoding bit of the V map of a bf16 cache), so the first round is a
+    // straight-line copy of its own that issues their loads at once, behind the map read instead of after it
+    // and with no ballot or branch in front of them (4-6 % of the kernel at the 32K-context shape, fp16 caches,
+    // which have no map to wait for, included).  If one of the tiles turns out to be of another form (a V tile
+    // that fp16 cannot hold) the sweep returns kGuessFailed before it has touched the accumulators, and is run
+    // again without guessing.
+    constexpr unsigned kGuessFailed = 1u << 31;
+    auto sweep = [&](auto form_c, auto collect_c, auto spec_c, int first, int last, auto entry) -> unsigned {
+      constexpr int kForm = decltype(form_c)::value;
+      constexpr bool COLLECT = decltype(collect_c)::value;
+      constexpr bool SPEC = decltype(spec_c)::value;
+      constexpr int KK = kForm & 1, VK = (kForm >> 1) & 1, kEnc = (kForm & 4) ? 0 : 1;
+      // Tiles in flight per wave.  Measured on the 32K-context shape: depth 1, 2, 3 and 4 (the deeper ones at
+      // 1 wave per SIMD) all land within run-to-run noise, and even a variant with the arithmetic removed is only
+      // ~10 % faster: the kernel is bound by the load stream.  A kernel for mixed tensors runs at 2 waves per
+      // SIMD, where only two 2:4 tiles (or one tile with a dense operand) fit.
+      constexpr int DEPTH = kMixed || NW == 8 ? ((KK == 0 && VK == 0) ? 2 : 1) : HS_DEC_DEPTH;
+      TileRegs<KK, VK> ring[DEPTH];
+      unsigned seen = 0;
+  // what the two copies of a round below share: the form ballots, and the loop that consumes the tiles in
+  // flight and refills their ring slots from `act`
 #define HS_ROUND_BALLOTS                                                                                              \
-  const int form_v = form_of(mk_v, mv_v);                                                                             \
-  unsigned long long act = __ballot(mk_v != 0 && form_v == kForm);                                                    \
-  if (COLLECT) {                                                                                                      \
-    _Pragma("unroll") for (int f = 0; f < 8; f++)                                                                     \
-      if (f != kForm && form_allowed<KM, VM, F16>(f)) seen |= (__ballot(mk_v != 0 && form_v == f) != 0ull ? 1u : 0u) << f; \
-  }
+    const int form_v = form_of(mk_v, mv_v);                                                                             \
+    unsigned long long act = __ballot(mk_v != 0 && form_v == kForm);                                                    \
+    if (COLLECT) {                                                                                                      \
+      _Pragma("unroll") for (int f = 0; f < 8; f++)                                                                     \
+        if (f != kForm && form_allowed<KM, VM, F16>(f)) seen |= (__ballot(mk_v != 0 && form_v == f) != 0ull ? 1u : 0u) << f; \
+    }
 #define HS_ROUND_CONSUME                                                                                              \
-  bool go = have[0];                                                                                                  \
-  while (go) {                                                                                                        \
-    _Pragma("unroll") for (int d = 0; d < DEPTH; d++) {                                                               \
-      if (go && have[d]) { /* tiles are consumed in issue order: the first empty slot ends the round */               \
-        tile_compute<KK, VK, F16, kEnc>(ring[d], qb, scale_log2, c, o, m_run, l_run);                                 \
-        have[d] = act != 0ull;                                                                                        \
-        if (have[d]) {                                                                                                \
-          const int i = __builtin_ctzll(act);                                                                         \
-          act &= act - 1;                                                                                             \
-          tile_load<KK, VK>(ring[d], kv, row, __builtin_amdgcn_readlane(mk_v, i), __builtin_amdgcn_readlane(mv_v, i), l); \
-        }                                                                                                             \
-      } else {                                                                                                        \
-        go = false;                                                                                                   \
-      }                                                                                                               \
-    }                                                                                                                 \
-  }
-    int base = first + w;
-    if constexpr (SPEC) {
-      if (base < last) {  // first round, tiles guessed
+    bool go = have[0];                                                                                                  \
+    while (go) {                                                                                                        \
+      _Pragma("unroll") for (int d = 0; d < DEPTH; d++) {                                                               \
+        if (go && have[d]) { /* tiles are consumed in issue order: the first empty slot ends the round */               \
+          tile_compute<KK, VK, F16, kEnc>(ring[d], qb, scale_log2, c, o, m_run, l_run);                                 \
+          have[d] = act != 0ull;                                                                                        \
+          if (have[d]) {                                                                                                \
+            const int i = __builtin_ctzll(act);                                                                         \
+            act &= act - 1;                                                                                             \
+            tile_load<KK, VK>(ring[d], kv, row, __builtin_amdgcn_readlane(mk_v, i), __builtin_amdgcn_readlane(mv_v, i), l); \
+          }                                                                                                             \
+        } else {                                                                                                        \
+          go = false;                                                                                                   \
+        }                                                                                                               \
+      }                                                                                                                 \
+    }
+      int base = first + w;
+      if constexpr (SPEC) {
+        if (base < last) {  // first round, tiles guessed
+          const int i_mine = base + NW * l;
+          int mk_v = 0, mv_v = 0;
+          if (i_mine < last) entry(i_mine, mk_v, mv_v);
+          bool have[DEPTH];
+          unsigned long long guessed = 0ull;
+#pragma unroll
+          for (int d = 0; d < DEPTH; d++) {
+            const int t = base + NW * d;
+            have[d] = t < last;
+            if (have[d]) {
+              guessed |= 1ull << d;
+              tile_load<KK, VK>(ring[d], kv, row, KK == 0 ? -(t + 1) : t + 1, VK == 0 ? -(t + 1) : t + 1, l);
+            }
+          }
+          HS_ROUND_BALLOTS
+          if constexpr (!F16)  // an fp16 cache has one encoding: nothing to guess wrong
+            if ((act & ((1ull << DEPTH) - 1ull)) != guessed) return kGuessFailed;
+          act &= ~guessed;
+          HS_ROUND_CONSUME
+          base += 64 * NW;
+        }
+      }
+      for (; base < last; base += 64 * NW) {  // up to 64 tiles of this wave per round
         const int i_mine = base + NW * l;
         int mk_v = 0, mv_v = 0;
         if (i_mine < last) entry(i_mine, mk_v, mv_v);
+        // Tile kinds must reach the branches below as scalar (wave-uniform) values: matrix
+        // instructions ignore the EXEC mask, so a branch the compiler treats as divergent would run
+        // both the dense and the 2:4 instruction on every tile.  Lane values are therefore read
+        // with v_readlane, never with a lane shuffle.
+        HS_ROUND_BALLOTS
         bool have[DEPTH];
-        unsigned long long guessed = 0ull;
 #pragma unroll
         for (int d = 0; d < DEPTH; d++) {
-          const int t = base + NW * d;
-          have[d] = t < last;
+          have[d] = act != 0ull;
           if (have[d]) {
-            guessed |= 1ull << d;
-            tile_load<KK, VK>(ring[d], kv, row, KK == 0 ? -(t + 1) : t + 1, VK == 0 ? -(t + 1) : t + 1, l);
+            const int i = __builtin_ctzll(act);
+            act &= act - 1;
+            tile_load<KK, VK>(ring[d], kv, row, __builtin_amdgcn_readlane(mk_v, i), __builtin_amdgcn_readlane(mv_v, i), l);
           }
         }
-        HS_ROUND_BALLOTS
-        if constexpr (!F16)  // an fp16 cache has one encoding: nothing to guess wrong
-          if ((act & ((1ull << DEPTH) - 1ull)) != guessed) return kGuessFailed;
-        act &= ~guessed;
         HS_ROUND_CONSUME
-        base += 64 * NW;
       }
-    }
-    for (; base < last; base += 64 * NW) {  // up to 64 tiles of this wave per round
-      const int i_mine = base + NW * l;
-      int mk_v = 0, mv_v = 0;
-      if (i_mine < last) entry(i_mine, mk_v, mv_v);
-      // Tile kinds must reach the branches below as scalar (wave-uniform) values: matrix
-      // instructions ignore the EXEC mask, so a branch the compiler treats as divergent would run
-      // both the dense and the 2:4 instruction on every tile.  Lane values are therefore read
-      // with v_readlane, never with a lane shuffle.
-      HS_ROUND_BALLOTS
-      bool have[DEPTH];
-#pragma unroll
-      for (int d = 0; d < DEPTH; d++) {
-        have[d] = act != 0ull;
-        if (have[d]) {
-          const int i = __builtin_ctzll(act);
-          act &= act - 1;
-          tile_load<KK, VK>(ring[d], kv, row, __builtin_amdgcn_readlane(mk_v, i), __builtin_amdgcn_readlane(mv_v, i), l);
-        }
-      }
-      HS_ROUND_CONSUME
-    }
 #undef HS_ROUND_BALLOTS
 #undef HS_ROUND_CONSUME
-    return seen;
-  };
-  auto all_sweeps = [&](int first, int last, auto entry) {
-    constexpr bool kGuess = HS_DEC_EARLY && MODE == kUniform;
-    unsigned seen = sweep(std::integral_constant<int, kFirstForm>{}, std::true_type{}, std::integral_constant<bool, kGuess>{},
-                          first, last, entry);
-    if (kGuess && !F16 && seen == kGuessFailed)
-      seen = sweep(std::integral_constant<int, kFirstForm>{}, std::true_type{}, std::false_type{}, first, last, entry);
-    static_for_forms<KM, VM, F16, kFirstForm>([&](auto form_c) {
-      if ((seen >> decltype(form_c)::value) & 1u) sweep(form_c, std::false_type{}, std::false_type{}, first, last, entry);
-    });
-  };
-  auto from_map = [&](int t, int& mk, int& mv) {
-    if (MODE == kUniform) {  // promised by the caller: no tile skipped, one kind per tensor, slot == tile
-      mk = KM == 0 ? -(t + 1) : t + 1;
-      mv = F16 ? (VM == 0 ? -(t + 1) : t + 1) : kv.v_map[row * T + t];  // bf16: encoding bit
-    } else {
-      mk = kv.k_map[row * T + t];
-      mv = kv.v_map[row * T + t];
-    }
-  };
-  if constexpr (MODE != kByCount) {
-    all_sweeps(t_begin, t_end, from_map);
-  } else {
-    __shared__ int2 sm_list[kListCap];  // (k_map, v_map) entries of this workgroup's tiles, in tile order
-    __shared__ int sm_cnt[36];          // [0..3] kept tiles per wave (count pass); [4 + 4 j + w] per scan segment
-    const int* kmap = kv.k_map + row * T;
-    const int* vmap = kv.v_map + row * T;
-    const unsigned long long lanes_below = (1ull << l) - 1ull;
-    // pass 1: kept tiles of the row
-    int mine_cnt = 0;
-    for (int b0 = 0; b0 < T; b0 += kScanBatch) {
-#pragma unroll
-      for (int j = 0; j < 8; j++) {
-        const int t = b0 + 256 * j + tid;
-        const int mk = t < T ? kmap[t] : 0;
-        const int mv = t < T ? vmap[t] : 0;  // not needed yet: fetched so that pass 2 finds both maps in the L2
-        asm volatile("" ::"v"(mv));
-        mine_cnt += __builtin_popcountll(__ballot(mk != 0));
+      return seen;
+    };
+    auto all_sweeps = [&](int first, int last, auto entry) {
+      constexpr bool kGuess = HS_DEC_EARLY && MODE == kUniform;
+      unsigned seen = sweep(std::integral_constant<int, kFirstForm>{}, std::true_type{}, std::integral_constant<bool, kGuess>{},
+                            first, last, entry);
+      if (kGuess && !F16 && seen == kGuessFailed)
+        seen = sweep(std::integral_constant<int, kFirstForm>{}, std::true_type{}, std::false_type{}, first, last, entry);
+      static_for_forms<KM, VM, F16, kFirstForm>([&](auto form_c) {
+        if ((seen >> decltype(form_c)::value) & 1u) sweep(form_c, std::false_type{}, std::false_type{}, first, last, entry);
+      });
+    };
+    auto from_map = [&](int t, int& mk, int& mv) {
+      if (MODE == kUniform) {  // promised by the caller: no tile skipped, one kind per tensor, slot == tile
+        mk = KM == 0 ? -(t + 1) : t + 1;
+        mv = F16 ? (VM == 0 ? -(t + 1) : t + 1) : kv.v_map[row * T + t];  // bf16: encoding bit
+      } else {
+        mk = kv.k_map[row * T + t];
+        mv = kv.v_map[row * T + t];
       }
-    }
-    if (l == 0) sm_cnt[w] = mine_cnt;
-    __syncthreads();
-    const int n_kept = sm_cnt[0] + sm_cnt[1] + sm_cnt[2] + sm_cnt[3];
-    const int lo = (int)((int64_t)n_kept * split / n_work), hi = (int)((int64_t)n_kept * (split + 1) / n_work);
-    if (n_kept == T) {  // nothing skipped: a tile's number is its index, no list needed
-      all_sweeps(lo, hi, from_map);
-    } else
-    for (int r0 = lo; r0 < hi; r0 += kListCap) {  // workgroup-uniform bounds: every thread takes the same trips
-      const int r1 = min(hi, r0 + kListCap);
-      // pass 2: list the tiles numbered [r0, r1)
-      int carried = 0;  // kept tiles before the scan step
-      for (int b0 = 0; b0 < T && carried < r1; b0 += kScanBatch) {
-        int mk8[8], mv8[8];  // read again in every pass (from L2 by now) rather than held across the tile loop
+    };
+    if constexpr (MODE != kByCount) {
+      all_sweeps(t_begin, t_end, from_map);
+    } else {
+      __shared__ int2 sm_list[kListCap];  // (k_map, v_map) entries of this workgroup's tiles, in tile order
+      __shared__ int sm_cnt[36];          // [0..3] kept tiles per wave (count pass); [4 + 4 j + w] per scan segment
+      const int* kmap = kv.k_map + row * T;
+      const int* vmap = kv.v_map + row * T;
+      const unsigned long long lanes_below = (1ull << l) - 1ull;
+      // pass 1: kept tiles of the row
+      int mine_cnt = 0;
+      for (int b0 = 0; b0 < T; b0 += kScanBatch) {
 #pragma unroll
         for (int j = 0; j < 8; j++) {
           const int t = b0 + 256 * j + tid;
-          mk8[j] = t < T ? kmap[t] : 0;
-          mv8[j] = t < T ? vmap[t] : 0;
+          const int mk = t < T ? kmap[t] : 0;
+          const int mv = t < T ? vmap[t] : 0;  // not needed yet: fetched so that pass 2 finds both maps in the L2
+          asm volatile("" ::"v"(mv));
+          mine_cnt += __builtin_popcountll(__ballot(mk != 0));
         }
-        unsigned long long kept[8];
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-          kept[j] = __ballot(mk8[j] != 0);
-          if (l == 0) sm_cnt[4 + 4 * j + w] = __builtin_popcountll(kept[j]);
-        }
-        __syncthreads();
-        int run = carried;  // tile t = b0 + 256 j + 64 w + l: segments in (j, w) order are in tile order
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-          int before = run;
-#pragma unroll
-          for (int ww = 0; ww < 4; ww++) {
-            const int c_seg = sm_cnt[4 + 4 * j + ww];
-            if (ww < w) before += c_seg;
-            run += c_seg;
-          }
-          const int number = before + __builtin_popcountll(kept[j] & lanes_below);
-          if (mk8[j] != 0 && number >= r0 && number < r1) sm_list[number - r0] = make_int2(mk8[j], mv8[j]);
-        }
-        carried = run;
-        __syncthreads();  // the counts are rewritten by the next scan step
       }
-      const int n_list = r1 - r0;
-      // the same sweeps, over the list: pair i goes to wave i % 4
-      auto from_list = [&](int i, int& mk, int& mv) {
-        const int2 e = sm_list[i];
-        mk = e.x;
-        mv = e.y;
-      };
-      all_sweeps(0, n_list, from_list);
-      __syncthreads();  // the list is rewritten by the next pass
+      if (l == 0) sm_cnt[w] = mine_cnt;
+      __syncthreads();
+      const int n_kept = sm_cnt[0] + sm_cnt[1] + sm_cnt[2] + sm_cnt[3];
+      const int lo = (int)((int64_t)n_kept * split / n_work), hi = (int)((int64_t)n_kept * (split + 1) / n_work);
+      if (n_kept == T) {  // nothing skipped: a tile's number is its index, no list needed
+        all_sweeps(lo, hi, from_map);
+      } else
+      for (int r0 = lo; r0 < hi; r0 += kListCap) {  // workgroup-uniform bounds: every thread takes the same trips
+        const int r1 = min(hi, r0 + kListCap);
+        // pass 2: list the tiles numbered [r0, r1)
+        int carried = 0;  // kept tiles before the scan step
+        for (int b0 = 0; b0 < T && carried < r1; b0 += kScanBatch) {
+          int mk8[8], mv8[8];  // read again in every pass (from L2 by now) rather than held across the tile loop
+#pragma unroll
+          for (int j = 0; j < 8; j++) {
+            const int t = b0 + 256 * j + tid;
+            mk8[j] = t < T ? kmap[t] : 0;
+            mv8[j] = t < T ? vmap[t] : 0;
+          }
+          unsigned long long kept[8];
+#pragma unroll
+          for (int j = 0; j < 8; j++) {
+            kept[j] = __ballot(mk8[j] != 0);
+            if (l == 0) sm_cnt[4 + 4 * j + w] = __builtin_popcountll(kept[j]);
+          }
+          __syncthreads();
+          int run = carried;  // tile t = b0 + 256 j + 64 w + l: segments in (j, w) order are in tile order
+#pragma unroll
+          for (int j = 0; j < 8; j++) {
+            int before = run;
+#pragma unroll
+            for (int ww = 0; ww < 4; ww++) {
+              const int c_seg = sm_cnt[4 + 4 * j + ww];
+              if (ww < w) before += c_seg;
+              run += c_seg;
+            }
+            const int number = before + __builtin_popcountll(kept[j] & lanes_below);
+            if (mk8[j] != 0 && number >= r0 && number < r1) sm_list[number - r0] = make_int2(mk8[j], mv8[j]);
+          }
+          carried = run;
+          __syncthreads();  // the counts are rewritten by the next scan step
+        }
+        const int n_list = r1 - r0;
+        // the same sweeps, over the list: pair i goes to wave i % 4
+        auto from_list = [&](int i, int& mk, int& mv) {
+          const int2 e = sm_list[i];
+          mk = e.x;
+          mv = e.y;
+        };
+        all_sweeps(0, n_list, from_list);
+        __syncthreads();  // the list is rewritten by the next pass
+      }
     }
-  }
 
-  // ---------------- combine: lane groups, hi/lo columns, then the 4 waves ----------------
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
+    // ---------------- combine: lane groups, hi/lo columns, then the 4 waves ----------------
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
 #pragma unroll
-  for (int i = 0; i < 8; i++)
+    for (int i = 0; i < 8; i++)
 #pragma unroll
-    for (int j = 0; j < 4; j++) {  // column c + column c^8 (rotate by 8 inside the 16-lane row)
-      const int other = __builtin_amdgcn_mov_dpp(__float_as_int(o[i][j]), 0x128, 0xf, 0xf, true);
-      o[i][j] += __int_as_float(other);
+      for (int j = 0; j < 4; j++) {  // column c + column c^8 (rotate by 8 inside the 16-lane row)
+        const int other = __builtin_amdgcn_mov_dpp(__float_as_int(o[i][j]), 0x128, 0xf, 0xf, true);
+        o[i][j] += __int_as_float(other);
+      }
+
+    if (c < 8) {
+      if (a == 0) { sm_m[w][c] = m_run; sm_l[w][c] = l_run; }
+#pragma unroll
+      for (int mb = 0; mb < 8; mb++)
+        *reinterpret_cast<float4*>(&sm_o[w][c][16 * mb + 4 * a]) = make_float4(o[mb][0], o[mb][1], o[mb][2], o[mb][3]);
     }
-
-  __shared__ float sm_m[NW][8], sm_l[NW][8];
-  if (c < 8) {
-    if (a == 0) { sm_m[w][c] = m_run; sm_l[w][c] = l_run; }
-#pragma unroll
-    for (int mb = 0; mb < 8; mb++)
-      *reinterpret_cast<float4*>(&sm_o[w][c][16 * mb + 4 * a]) = make_float4(o[mb][0], o[mb][1], o[mb][2], o[mb][3]);
+    if constexpr (DIRECT) {
+      if (tail.len >= 0) {  // by the waves that have no tile where the row has few
+        n_parts = NW + 4;
+        const int q = NW - 1 - w;
+        if (q < 4) tail_piece<F16>(tail, tail_length(b), row, q, qb, scale_log2, l, sm_o[NW + q], sm_m[NW + q], sm_l[NW + q]);
+      }
+    }
   }
   __syncthreads();
-  // thread -> (head g = tid / 32, 4 channels)
-  const int g = tid >> 5, ch = (tid & 31) * 4;
-  const int64_t hq = (int64_t)b * Hq + hkv * G + (g < G ? g : 0);
-  if (g < G) {
-    float mstar = -INFINITY;
-#pragma unroll
-    for (int ww = 0; ww < NW; ww++) mstar = fmaxf(mstar, sm_m[ww][g]);
-    // a wave without a reference has seen nothing (l and O are 0) or only NaN scores (l is NaN): neither is left out,
-    // and only l == 0 is an empty split, so that a NaN reaches O and LSE however the tiles are divided
-    const float mref = mstar > -INFINITY ? mstar : 0.f;
-    float lsum = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ww = 0; ww < NW; ww++) {
-      const float f = __builtin_amdgcn_exp2f(sm_m[ww][g] - mref);
-      lsum += f * sm_l[ww][g];
-#pragma unroll
-      for (int i = 0; i < 4; i++) acc[i] += f * sm_o[ww][g][ch + i];
-    }
-    const float inv = lsum == 0.f ? 0.f : 1.f / lsum;
-    const float lse = lsum == 0.f ? -INFINITY : (mstar + __builtin_amdgcn_logf(lsum)) * kLn2;
-    if constexpr (DIRECT) {
-      typedef hs_elem<F16> E;
-      uint16_t* po = reinterpret_cast<uint16_t*>(ws_o) + hq * HS_D + ch;
-      store4(po, E::pack2(acc[0] * inv, acc[1] * inv), E::pack2(acc[2] * inv, acc[3] * inv), ((uintptr_t)ws_o & 7) == 0);
-      if (ws_l != nullptr && (tid & 31) == 0) ws_l[hq] = lse;
-    } else {
-      float* po = ws_o + (hq * n_splits + split) * HS_D + ch;
-      *reinterpret_cast<float4*>(po) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
-      if ((tid & 31) == 0) ws_l[hq * n_splits + split] = lse;
-    }
-  }
+  combine_parts<F16, DIRECT>(tid, n_parts, G, hq0, sm_m, sm_l, sm_o, n_splits, slot, (float*)to_o, (float*)to_l);
 }
 
 // Merge of the split partials (Sec. IV-C "lightweight post-processing kernel"):
@@ -818,12 +820,15 @@ hipError_t hs_launch_decode(int B, int Hq, int Hkv, int T, float scale, int n_wo
   // 11.7 / 8.8, 27.5 / 25.4, 69.9 / 67.7; 200 rows of 192 tiles, half of them skipped, 60.2 by count / 58.6; 128 rows of
   // 16 / 32 tiles 11.6 / 10.2, 17.4 / 17.4).  Longer rows are split or handed out by count; so are those of 128 tiles or more
   // that may have any pattern of skipped tiles (200 rows of 160, all but every eighth skipped: 19.1 by count / 25.7).
-  const int short_row = km == 0 && vm == 0 ? 8 : 4;
-  const bool direct = auto_splits && tail_len < 0 && phases == 3 &&
+  // A dense tail goes to the waves that have no tile, so it costs little up to 6 tiles (us with the caller's buffers, split + merge /
+  // direct, 8 rows of 5 / 6 / 7 tiles 6.5 / 5.7, 6.5 / 6.3, 6.5 / 6.4, 32 rows 7.6 / 7.1, 7.7 / 7.7, 7.7 / 8.0; 4 tiles, dense 8.5 / 7.8, dense
+  // keys 7.7 / 7.2, dense ends 8.5 / 7.7; 256 rows of 8 / 32 / 96 tiles 12.9 / 11.0, 29.1 / 28.8, 74.2 / 71.4, 200 rows of 64 tiles 40.4 / 40.6).
+  const int short_row = km == 0 && vm == 0 ? (tail_len < 0 ? 8 : 6) : 4;
+  const bool direct = auto_splits && phases == 3 &&
                       (T <= short_row || (n_work == 1 && T < (kept == HS_KEPT_UNKNOWN ? bycount_per : 2 * HS_DEC_BYCOUNT_MIN_PER)) || ((int64_t)B * Hkv >= 128 && T <= 16));
   if (direct) n_work = 1;
   const TailArgs tail{tail_k, tail_v, tail_lens, tail_len};
-  const dim3 grid(n_work, Hkv, B + (tail_len >= 0 ? (B + n_work - 1) / n_work : 0));
+  const dim3 grid(n_work, Hkv, B + (tail_len >= 0 && !direct ? (B + n_work - 1) / n_work : 0));
   const bool f16 = dtype == HS_FP16;
   const float sl2 = scale * kLog2e;
   const int per = (T + n_work - 1) / n_work;

@@ -905,6 +905,41 @@ def test_decode_tail_workgroups_of_every_row(B, Hkv, G, T, n_splits, dtype):
         assert_lse_close(LSE.cpu().numpy()[b], Lr[b], f"decode tail of {n} in row {b} lse")
 
 
+@pytest.mark.parametrize("B,Hkv,G,T,dtype,pol", [
+    (7, 1, 1, 1, "bf16", dict()), (7, 2, 8, 6, "fp16", dict()), (7, 1, 5, 7, "bf16", dict()),            # one workgroup a row | splits
+    (7, 1, 4, 4, "fp16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)), (7, 1, 3, 5, "bf16", dict(sparse_frac_k=0.0)),
+    (7, 3, 7, 3, "bf16", dict(dense_first_tiles=1, dense_last_tiles=4)), (7, 19, 2, 16, "bf16", dict())])
+def test_decode_tail_in_the_rows_own_workgroup(B, Hkv, G, T, dtype, pol):
+    """The library's choice of route on both sides of its edges, with tails of every kind; every workgroup's 16-token
+    pieces, heads that do not fill the matrix columns, and an infinite value or a NaN score in the tail, as in 64 bits."""
+    sh = hb.make_shape(B, G * Hkv, Hkv, 64 * T, dtype=torch.float16 if dtype == "fp16" else torch.bfloat16)
+    dt, lens = hb.torch_dtype(sh), [0, 1, 15, 16, 17, 63, 64]
+    g = torch.Generator(device="cuda").manual_seed(70 + T)
+    K, V = (torch.randn((B, Hkv, 64 * T, 128), device="cuda", generator=g).to(dt) for _ in range(2))
+    tk, tv = (torch.randn((B, Hkv, 64, 128), device="cuda", generator=g).to(dt) for _ in range(2))
+    Q = torch.randn((B, G * Hkv, 128), device="cuda", generator=g).to(dt)
+    for b, n in enumerate(lens):                      # tokens past a row's tail must not be looked at
+        tk[b, :, n:], tv[b, :, n:] = float("nan"), float("inf")
+    tv[5, -1, 62, 7], tv[6, -1, 3, 127], tk[4, 0, 16, 9] = float("inf"), float("-inf"), float("nan")
+    kv = hb.compress_kv(sh, hb.make_policy(**pol), K, V)
+    Ku, Vu = hb.unpack_kv(sh, kv)
+    O, LSE = hb.decode_attn(sh, Q, kv, tail_k=tk, tail_v=tv, tail_len=torch.tensor(lens, dtype=torch.int32, device="cuda"))
+    O, LSE = O.double().cpu(), LSE.double().cpu()
+    for b, n in enumerate(lens):
+        for h in range(Hkv):
+            k, v, q = (x.double().cpu() for x in (torch.cat([Ku[b, h], tk[b, h, :n]]), torch.cat([Vu[b, h], tv[b, h, :n]]), Q[b, h * G:(h + 1) * G]))
+            S = q @ k.T * 128 ** -0.5
+            Or, Lr = (torch.softmax(S, 1)[:, :, None] * v).sum(1), torch.logsumexp(S, 1)
+            got, lse = O[b, h * G:(h + 1) * G], LSE[b, h * G:(h + 1) * G]
+            fin = torch.isfinite(Or)
+            assert torch.equal(torch.isnan(got), torch.isnan(Or)) and torch.equal(got[torch.isinf(Or)], Or[torch.isinf(Or)]), (b, h)
+            assert torch.equal(torch.isnan(lse), torch.isnan(Lr)), (b, h)
+            if fin.any():
+                assert_close(got[fin].numpy(), Or[fin].numpy(), f"tail of {n} in row {b}, kv head {h}")
+            if torch.isfinite(Lr).all():
+                assert_lse_close(lse.numpy(), Lr.numpy(), f"tail of {n} in row {b}, kv head {h} lse")
+
+
 @pytest.mark.parametrize("B,Hkv,T", [(1, 1, 1), (2, 1, 8), (1, 2, 9), (16, 8, 16), (64, 4, 5), (64, 4, 127), (50, 4, 160)])
 @pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict()), ("bf16", dict(sparse_frac_k=0.0)), ("fp16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)),
                                        ("bf16", dict(sparse_frac_k=0.5, sparse_frac_v=0.5)), ("fp16", dict(skip_frac=0.5)), ("bf16", "empty")])
