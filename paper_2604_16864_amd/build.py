@@ -9,7 +9,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhs.so")
 NATIVE = os.path.join(HERE, "_hs_torch.so")
-SOURCES = ["hs_api.hip", "hs_compress.hip", "hs_decode.hip", "hs_prefill.hip", "hs_prefill_mixed.hip", "hs_prefill_narrow.hip", "hs_probe.hip"]
+SOURCES = ["hs_api.hip", "hs_compress.hip", "hs_decode.hip", "hs_prefill.hip", "hs_prefill_mixed.hip", "hs_prefill_narrow.hip", "hs_prefill_narrow_mixed.hip", "hs_probe.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -18,9 +18,11 @@ FLAGS = [
 ]
 # The scheduler's own register trackers: the prefill loops of tensors with one kind of tile come out 0.5 to 5 % faster with them
 # (1K prompt 22.9 -> 22.4 us, 16 prompts of 1K 157 -> 150), those of mixed tensors 1 to 3 % slower (8K prompt, dense ends 379 -> 391); with slabs
-# of 16 queries every kind gains up to 1.5 % (512 tokens 11.06 -> 10.97, dense ends 13.96 -> 13.85).
+# of 16 queries every kind gains up to 1.5 % (512 tokens 11.06 -> 10.97, dense ends 13.96 -> 13.85).  Mixed tensors in slabs of 16 want the
+# scheduler that looks for parallel instructions (256 queries on 1024 tokens, half of the keys dense 19.9 with the plain one's
+# max-ilp, 18.2 with the trackers, 17.9; fp16, dense ends, 512 tokens 14.1 / 13.1 / 12.6).
 _TRACKERS = ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"]
-FILE_FLAGS = {"hs_prefill.hip": _TRACKERS, "hs_prefill_narrow.hip": _TRACKERS}
+FILE_FLAGS = {"hs_prefill.hip": _TRACKERS, "hs_prefill_narrow.hip": _TRACKERS, "hs_prefill_narrow_mixed.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]}
 
 
 def native_command():

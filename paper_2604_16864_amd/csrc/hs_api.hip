@@ -472,8 +472,10 @@ int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start, float
 int hs_prefill_attn_planned(const hs_shape* shape, int32_t Lq, int32_t q_start, float scale, int causal, const void* Q,
                             const hs_kv* kv, void* O, float* LSE, void* workspace, size_t workspace_bytes, int32_t slab, int32_t ranges,
                             void* stream) {
-  if ((slab != 16 && slab != 32) || ranges < 1 || ranges > 65535) return HS_EINVAL;
-  const hs_prefill_choice how = {slab / 16, ranges};
+  const int teams = slab & HS_TWO_TEAMS ? 2 : 1;
+  slab &= ~HS_TWO_TEAMS;
+  if ((slab != 16 && slab != 32) || ranges < 1 || ranges > 65535 || (teams == 2 && (slab != 16 || ranges != 1))) return HS_EINVAL;
+  const hs_prefill_choice how = {slab / 16, ranges, teams};
   return prefill_common(shape, Lq, q_start, scale, causal, Q, kv, O, LSE, workspace, workspace_bytes, &how, stream);
 }
 

@@ -189,9 +189,9 @@ hipError_t hs_launch_stream_read(const uint8_t* buf, int n_tiles, int n_workgrou
 hipError_t hs_launch_merge(int64_t rows, int n_splits, const float* ws_o, const float* ws_l, uint16_t* O, float* LSE,
                            hipStream_t st, int dtype);
 // q_start: position in the cache of the first query (query i sees tokens <= q_start + i when causal)
-// nb: column blocks of 16 queries per wave, 1 or 2; n_splits > 1: the tiles of a workgroup are cut into so many ranges;
+// nb: column blocks of 16 queries per wave, 1 or 2; teams: of 4 waves per workgroup, 2 with nb = 1 only; n_splits > 1: the tiles of a workgroup are cut into so many ranges;
 // ws = B * Hq * 64 Tq * n_splits * 129 floats
-struct hs_prefill_choice { int nb, n_splits; };
+struct hs_prefill_choice { int nb, n_splits, teams; };
 hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start, float scale, int causal, const uint16_t* Q,
                              hs_kv_dev kv, uint16_t* O, float* LSE, hipStream_t st, int dtype, hs_prefill_choice how, float* ws);
 // what serves this shape best with a workspace for `fit` ranges; of kv the capacities and `uniform` are read
@@ -200,9 +200,12 @@ hs_prefill_choice hs_plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_s
 hipError_t hs_launch_prefill_mixed(int km, int vm, int B, int Hq, int Hkv, int T, int Lq, int q_start, float scale_log2, int causal,
                                    const uint16_t* Q, const hs_kv_dev& kv, uint16_t* O, float* LSE, hipStream_t st, bool f16,
                                    int n_splits, float* ws_o, float* ws_l);
-// the same for all kinds with slabs of 16 queries
-hipError_t hs_launch_prefill_narrow(int km, int vm, int B, int Hq, int Hkv, int T, int Lq, int q_start, float scale_log2, int causal,
+// the same for all kinds with slabs of 16 queries, by one team of four waves or by two (teams); _mixed as above
+hipError_t hs_launch_prefill_narrow(int teams, int km, int vm, int B, int Hq, int Hkv, int T, int Lq, int q_start, float scale_log2, int causal,
                                     const uint16_t* Q, const hs_kv_dev& kv, uint16_t* O, float* LSE, hipStream_t st, bool f16,
                                     int n_splits, float* ws_o, float* ws_l);
+hipError_t hs_launch_prefill_narrow_mixed(int teams, int km, int vm, int B, int Hq, int Hkv, int T, int Lq, int q_start, float scale_log2, int causal,
+                                          const uint16_t* Q, const hs_kv_dev& kv, uint16_t* O, float* LSE, hipStream_t st, bool f16,
+                                          int n_splits, float* ws_o, float* ws_l);
 // most ranges that it chooses from (1: do not split)
 int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv);

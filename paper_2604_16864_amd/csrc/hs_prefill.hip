@@ -42,7 +42,7 @@ int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, i
   return best;
 }
 
-// Slabs of 32 queries (NB = 2) or of 16 (NB = 1), and in how many ranges (at most `fit`).  A tile takes a workgroup of NB = 1
+// Slabs of 32 queries (NB = 2) or of 16 (NB = 1), those by one team of waves or by two, and in how many ranges (at most `fit`).  A tile takes a workgroup of NB = 1
 // three quarters of the time for half of the work, so NB = 1 pays where NB = 2 has too few workgroups: one or none per compute
 // unit, or a short second half of the work.  Measured, 32/8 heads, 2:4 tensors, us of NB = 2 / NB = 1 at the better number of
 // ranges of each: whole prompts of 64 / 256 / 512 / 1024 / 1536 / 2048 / 4096 tokens 7.4 / 6.1, 10.3 / 8.0, 14.3 / 11.1, 22.4 /
@@ -58,32 +58,40 @@ int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, i
 // to itself and kPair beside a second one; 512 run at a time, the longest first, so the call ends with the longest, or when the
 // whole is worked off, or with a pile of k + 1 where round k + 1 is just begun (queries at the end of a long context: all
 // workgroups equally long); ranges add the merge launch and the partials.
+// Two teams of waves per workgroup (one workgroup per compute unit, which takes two tiles in little more than the time one team takes
+// for one) where slabs of 16 leave each compute unit one workgroup or none; one team / two, us: 64 workgroups of 16 tiles 15.5 / 13.4,
+// 128 of up to 32 26.7 / 21.7, half of the keys dense 31.3 / 24.3, dense ends 31.3 / 24.0, 128 of up to 8 10.8 / 10.3, 13.2 / 12.0; of up to 4
+// tiles 7.9 / 8.2.  Not with more workgroups than compute units, which fill the chip by themselves (prompt of 1024 tokens 18.4 / 20.1, 336
+// workgroups of 40 tiles 35.4 / 36.7), and not in ranges: their tiles come from HBM, and both teams wait for the slower one's at every
+// barrier (3 x 128 queries x 8 heads on 33088 tokens, half of them skipped, 45 / 58; 64 queries x 32 heads on 4096 17.1 / 17.0).
 // The margins go by what the shape allows and not by `fit`, so a workspace of the size of the choice leads to the same choice.
 hs_prefill_choice hs_plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv, int fit) {
-  static const double kStart[3] = {0, 5.3, 7.2}, kAlone[3] = {0, 0.70, 0.905}, kPair[3] = {0, 0.82, 1.13};
+  static const struct { int nb, teams, at_once; double start, alone, pair; } kWays[3] = {
+      {2, 1, 512, 7.2, 0.905, 1.13}, {1, 1, 512, 5.3, 0.70, 0.82}, {1, 2, 256, 6.9, 0.47, 0.47}};
   const int most = hs_prefill_auto_splits(B, Hq, Hkv, T, Lq, q_start, causal, kv);
   const int seen = causal ? (q_start + Lq + HS_BT - 1) / HS_BT : T;  // tiles of the last query
   const double share = (double)tiles_to_expect(T, seen, kv) / seen;
   const double longest = seen * share, shortest = (causal ? seen - (Lq / HS_BT - 1) : seen) * share;
-  hs_prefill_choice best = {2, 1};
+  hs_prefill_choice best = {2, 1, 1};
   double best_us = 0.0;
-  for (int nb = 2; nb >= 1; nb--) {
-    const double n_wg = (double)((int64_t)((Lq / (16 * nb) * (int64_t)(Hq / Hkv) + 3) / 4) * Hkv * B);
+  for (const auto& w : kWays) {
+    const double n_wg = (double)((int64_t)((Lq / (16 * w.nb) * (int64_t)(Hq / Hkv) + 3) / 4) * Hkv * B);
     for (int n = 1; n <= most && n <= fit; n++) {
-      const double wgs = n_wg * n, rounds = ceil(wgs / 512);
-      double us = longest / n * (wgs <= 256 ? kAlone[nb] : kPair[nb]) + kStart[nb];
-      us = fmax(us, (longest + shortest) / 2 / n * kPair[nb] * wgs / 512 + rounds * kStart[nb]);
+      const double wgs = n_wg * n, rounds = ceil(wgs / w.at_once);
+      if (w.teams == 2 && (n > 1 || rounds > 1)) break;
+      double us = longest / n * (wgs <= 256 ? w.alone : w.pair) + w.start;
+      us = fmax(us, (longest + shortest) / 2 / n * w.pair * wgs / w.at_once + rounds * w.start);
       if (rounds > 1) {  // (k + 1) (first - k fall), k = 1 .. rounds - 1: largest beside its vertex, or at an end
-        const double first = longest / n * kPair[nb] + kStart[nb], fall = (longest - shortest) * 512 / wgs / n * kPair[nb];
+        const double first = longest / n * w.pair + w.start, fall = (longest - shortest) * w.at_once / wgs / n * w.pair;
         const double k = fmin(fmax(fall > 0.0 ? floor((first / fall - 1) / 2) : rounds, 1.0), rounds - 1);
         us = fmax(us, fmax((k + 1) * (first - k * fall), k + 1 < rounds ? (k + 2) * (first - (k + 1) * fall) : 0.0));
       }
-      if (n > 1) us += 3.0 + 0.014 * nb * wgs;
+      if (n > 1) us += 3.0 + 0.014 * w.nb * wgs;
       // The wider slab in all the ranges allowed where things are even; ranges of the narrow one, two to a compute unit, are
       // where the sum is least sure (128 queries x 4 heads on 47104 tokens 25.8 / 28.0, 256 x 4 on 32768 29.6 / 27.0).
-      if (nb == 1) us *= n > 1 && wgs > 256 ? 1.12 : 1.03;
+      if (w.nb == 1) us *= n > 1 && wgs > 256 ? 1.12 : (w.teams == 2 ? 1.05 : 1.03);
       else if (n != most) us *= 1.03;
-      if (best_us == 0.0 || us < best_us) { best = {nb, n}; best_us = us; }
+      if (best_us == 0.0 || us < best_us) { best = {w.nb, n, w.teams}; best_us = us; }
     }
   }
   return best;
@@ -105,7 +113,7 @@ hipError_t hs_launch_prefill(int B, int Hq, int Hkv, int T, int Tq, int q_start,
   e = launch_prefill<KM_, VM_, 2>(B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l); \
   break
   if (how.nb == 1)
-    e = hs_launch_prefill_narrow(km, vm, B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l);
+    e = hs_launch_prefill_narrow(how.teams, km, vm, B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l);
   else switch (km * 3 + vm) {
     case 0: HS_GO(0, 0);
     case 1: HS_GO(0, 1);

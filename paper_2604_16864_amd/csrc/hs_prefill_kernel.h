@@ -220,16 +220,22 @@ union B16 {  // one B operand of the 16x16x64 sparse instruction = two of the de
 // GEMM2 as one fp16 term; against bf16 V they enter as two bf16 terms.  The reference is kept
 // kShift binades under the running maximum and renewed before a numerator can reach the fp16
 // maximum (constants below).
+// TEAMS (2 with NB = 1 and without SPLIT only): two teams of 4 waves share the workgroup's slabs and take its tiles in turn, each with a ring of its own, and
+// combine through LDS at the end.  A wave alone on its SIMD leaves it idle most of a tile's time (1500 clocks, ~220 instructions
+// and 16 products), so where a call has no second workgroup for a compute unit, 512 threads take two tiles in the time that 256
+// take for 1.3; what bounds the pair is the LDS (90 KB read and written a tile, 720 clocks) and the barrier all 8 waves meet at.
+// Slabs of 32 spill and lose (64 queries on 32768 tokens 39 / 39, 512 on 2048 36 / 33 against 22 with slabs of 16).
 // SPLIT: the tiles a workgroup may look at are cut into gridDim.y ranges, one workgroup per range; each
 // writes a normalised fp32 partial output and its log-sum-exp (ws_o [row][split][128], ws_l
 // [row][split], row = (b, query head, query)) for the merge kernel instead of O and LSE.
-template <int KM, int VM, int NB, bool F16, bool SPLIT>
-__global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T, int Lq, int off,
+template <int KM, int VM, int NB, int TEAMS, bool F16, bool SPLIT>
+__global__ __launch_bounds__(256 * TEAMS, 2) void prefill_kernel(int Hq, int Hkv, int T, int Lq, int off,
                                                                       float scale_log2, int causal,
                                                                       const uint16_t* __restrict__ Q, hs_kv_dev kv,
                                                                       uint16_t* __restrict__ O,
                                                                       float* __restrict__ LSE, float* __restrict__ ws_o,
                                                                       float* __restrict__ ws_l) {
+  static_assert(TEAMS == 1 || (NB == 1 && !SPLIT), "two teams: slabs of 16 in one range");
   typedef hs_elem<F16> E;
   typedef hs_elem<true> E16;
   // Reference = running maximum - kShift at the time it was last renewed; it is renewed when a lane's
@@ -260,9 +266,11 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
   // or mixed V, no registers are left for the K prefetch.
   constexpr bool MID_OK = KM != 2 && VM != 2 && NS >= 3;
   constexpr int kStage = stage_bytes<KM, VM>();
-  __shared__ __attribute__((aligned(16))) uint8_t lds[NS * kStage];
+  __shared__ __attribute__((aligned(16))) uint8_t lds_all[TEAMS * NS * kStage];
   const int tid = threadIdx.x, l = tid & 63, a = l >> 4, c = l & 15;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, scalar: branches on it stay scalar
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, scalar: branches on it stay scalar
+  const int w = TEAMS == 1 ? wave : wave & 3, team = TEAMS == 1 ? 0 : wave >> 2;
+  uint8_t* const lds = lds_all + team * (NS * kStage);
   const int G = Hq / Hkv;
   // kv head = block index mod Hkv: workgroups go round-robin over the 8 XCDs, so with 8 kv heads (or a
   // divisor of 8) each XCD's L2 streams the tiles of its own heads only (measured 1-2.5 % faster)
@@ -348,7 +356,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
     wrem = __ballot(wk != 0 && grp == wgroup);
     wbase = base;
   };
-  auto next_tile = [&]() -> int {  // next tile (<= t_last, not skipped) in the order above, or -1
+  auto next_of_all = [&]() -> int {  // next tile (<= t_last, not skipped) in the order above, or -1
     for (;;) {
       if (wrem != 0) {
         const int t = __builtin_ctzll(wrem);
@@ -364,6 +372,17 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
       if (wgroup > 2) return -1;
       window_load(t_lo);
     }
+  };
+  // Two teams take the tiles in turn; each walks the whole order and passes over the other's.
+  bool pass_over = TEAMS > 1 && team != 0, unpaired = false;  // unpaired: the last tile of team 0 has none beside it
+  auto next_tile = [&]() -> int {
+    if (TEAMS == 1) return next_of_all();
+    if (pass_over && next_of_all() < 0) return -1;
+    const bool after_other = pass_over && team != 0;
+    pass_over = true;
+    const int t = next_of_all();
+    unpaired = after_other && t < 0;
+    return t;
   };
   int st = 0;
   window_load(t_lo);
@@ -402,7 +421,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
     constexpr bool MID = decltype(mid_tag)::value, ONLY16 = F16 || decltype(only16_tag)::value;
     // 2:4 V operands are fetched from LDS before the softmax, unless the K prefetch of MID mode
     // already holds the registers (both together spill; measured no gain there)
-    constexpr bool V_EARLY = F16 && VM == 0 && !MID;
+    constexpr bool V_EARLY = F16 && VM == 0 && !MID && NB > 1;
     // Whole rows of 2:4 tiles, slabs of 16: the score accumulators of the next tile are cleared among the products of GEMM2,
     // where the vector ALU is idle, instead of in front of GEMM1 (the sparse instruction accumulates in place): 512 tokens
     // 10.94 -> 10.70 us, 1024 tokens 18.9 -> 18.4.  Elsewhere the registers or the scheduling it costs are worth more (slabs of
@@ -438,6 +457,17 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
       const uint4* kl = reinterpret_cast<const uint4*>(lds + st * kStage);
       const uint4* vl = reinterpret_cast<const uint4*>(lds + st * kStage + region_bytes<KM>());
       B16 ph[NB], pl[NB];
+      // V_TOP (slabs of 16, 2:4 V beside K of one kind): V's operands are requested first of all, so that they are there when the
+      // softmax ends.  Two teams: 512 queries on 2048 tokens 22.8 -> 21.9 us, 192 on 896 13.1 -> 12.6; one team, all 2:4, fp16: 192 on 896
+      // 13.8 -> 13.4, 1024 tokens 18.1 -> 17.8.  One team of a bf16 cache, whose registers it fills, loses (1344 queries on 2560 tokens 35.3 -> 36.6), and so does one beside dense keys (16 x 320 on 448 13.1 -> 13.5).
+      constexpr bool V_TOP = NB == 1 && VM == 0 && KM != 2 && (TEAMS == 2 || (F16 && KM == 0));
+      if (V_TOP && ok) {
+        if (!MID) k_fetch(st);
+#pragma unroll
+        for (int i = 0; i < 8; i++) av[i] = vl[i * 64 + l];
+        vix = vl[512 + l];
+        __builtin_amdgcn_sched_barrier(0);
+      }
       if (ok) {
         // ---------------- GEMM1: S^T[64 tokens x 16 NB queries] ----------------
         __builtin_amdgcn_s_setprio(HS_PRIO_MFMA);
@@ -445,7 +475,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
         Scores& s = CLEARED ? s_kept : s_tile;
         if (!CLEARED) clear(s);
         if (k_sparse) {
-          if (!MID) k_fetch(st);
+          if (!MID && !V_TOP) k_fetch(st);
           const int kidx[4] = {(int)kix.x, (int)kix.y, (int)kix.z, (int)kix.w};
           // 4 NB independent accumulators between the two instructions that share one
 #pragma unroll
@@ -464,7 +494,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
             // read just in front of its products leaves the wave waiting for the LDS four times a tile (both tensors dense,
             // 8K prompt 516 -> 498 us).  Not where the kind is looked at per tile: the two arms then want different registers
             // for the operands and the loop spills (2:4 values, half of the keys dense, 398 -> 437).
-            if (!MID) {
+            if (!MID && !V_TOP) {
 #pragma unroll
               for (int i = 0; i < 8; i++) ak[i] = kl[i * 64 + l];
             }
@@ -602,7 +632,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
       if (ok) {
         __builtin_amdgcn_s_setprio(HS_PRIO_MFMA);
         if (v_sparse) {
-          if (!V_EARLY) {
+          if (!V_EARLY && !V_TOP) {
 #pragma unroll
             for (int i = 0; i < 8; i++) av[i] = vl[i * 64 + l];
             vix = vl[512 + l];
@@ -727,6 +757,62 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
     main_loop(std::false_type{}, std::false_type{});
   }
 
+  if constexpr (TEAMS > 1) {
+    // The teams have met at a barrier per tile; the one with a tile less makes up for it.  Then each hands half of its O^T (and all
+    // of its references and sums, lane by lane) to its counterpart of the same slab through LDS and finishes the other half.
+    if (unpaired) __syncthreads();
+    __syncthreads();
+    float4* const ex = reinterpret_cast<float4*>(lds_all);
+    constexpr int kVec = 4 * NB * 64;  // float4 per wave
+    float* const exl = reinterpret_cast<float*>(ex + 8 * kVec);
+    auto give = [&](auto from) {
+#pragma unroll
+      for (int mb = 0; mb < 4; mb++)
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++) {
+          const f32x4_t x = o[decltype(from)::value + mb][nb];
+          ex[wave * kVec + (mb * NB + nb) * 64 + l] = make_float4(x[0], x[1], x[2], x[3]);
+        }
+    };
+    if (team == 0) give(std::integral_constant<int, 4>{});
+    else give(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int nb = 0; nb < NB; nb++) {
+      exl[((wave * NB + nb) * 2) * 64 + l] = m_run[nb];
+      exl[((wave * NB + nb) * 2 + 1) * 64 + l] = l_run[nb];
+    }
+    __syncthreads();
+    if (!valid) return;
+    const int other = wave ^ 4;
+    auto finish = [&](auto from) {
+      constexpr int kFrom = decltype(from)::value;
+#pragma unroll
+      for (int nb = 0; nb < NB; nb++) {
+        const float m_other = exl[((other * NB + nb) * 2) * 64 + l], l_other = exl[((other * NB + nb) * 2 + 1) * 64 + l];
+        // a team without a reference has seen nothing (l and O are 0) or only NaN scores (l is NaN)
+        const float m = fmaxf(m_run[nb], m_other), ref = m > -INFINITY ? m : 0.f;
+        const float f = __builtin_amdgcn_exp2f(m_run[nb] - ref), fo = __builtin_amdgcn_exp2f(m_other - ref);
+        float lt = l_run[nb] * f + l_other * fo;
+        lt += __shfl_xor(lt, 16);
+        lt += __shfl_xor(lt, 32);
+        const float inv = lt == 0.f ? 0.f : 1.f / lt;
+        const float lse = lt == 0.f ? -INFINITY : (m + __builtin_amdgcn_logf(lt)) * kLn2;
+        const int64_t qrow = ((int64_t)b * Hq + hq) * Lq + qpos + 16 * nb + c;
+        const float g = f * inv, go = fo * inv;
+#pragma unroll
+        for (int mb = 0; mb < 4; mb++) {
+          const float4 y = ex[other * kVec + (mb * NB + nb) * 64 + l];
+          const f32x4_t x = o[kFrom + mb][nb];
+          const float r0 = x[0] * g + y.x * go, r1 = x[1] * g + y.y * go, r2 = x[2] * g + y.z * go, r3 = x[3] * g + y.w * go;
+          *reinterpret_cast<uint2*>(O + qrow * HS_D + 4 * a + 16 * (kFrom + mb)) = make_uint2(E::pack2(r0, r1), E::pack2(r2, r3));
+        }
+        if (LSE != nullptr && a == 0 && kFrom == 0) LSE[qrow] = lse;
+      }
+    };
+    if (team == 0) finish(std::integral_constant<int, 0>{});
+    else finish(std::integral_constant<int, 4>{});
+    return;
+  }
   // ---------------- epilogue: O = O^T / l, LSE ----------------
   if (!valid) return;
 #pragma unroll
@@ -759,7 +845,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(int Hq, int Hkv, int T,
 
 }  // namespace
 
-template <int KM, int VM, int NB>
+template <int KM, int VM, int NB, int TEAMS = 1>
 static hipError_t launch_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, float sl2, int causal, const uint16_t* Q,
                                  const hs_kv_dev& kv, uint16_t* O, float* LSE, hipStream_t st, bool f16, int n_splits, float* ws_o,
                                  float* ws_l) {
@@ -767,10 +853,14 @@ static hipError_t launch_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_st
   const int n_groups = ((Lq / (16 * NB)) * G + 3) / 4;
   const dim3 grid(n_groups * Hkv, n_splits, B);
 #define HS_LAUNCH(F16_, SPLIT_)                                                                                            \
-  hipLaunchKernelGGL((prefill_kernel<KM, VM, NB, F16_, SPLIT_>), grid, dim3(256), 0, st, Hq, Hkv, T, Lq, q_start, sl2, causal, \
+  hipLaunchKernelGGL((prefill_kernel<KM, VM, NB, TEAMS, F16_, SPLIT_>), grid, dim3(256 * TEAMS), 0, st, Hq, Hkv, T, Lq, q_start, sl2, causal, \
                      Q, kv, O, LSE, ws_o, ws_l)
   if (n_splits > 1) {
-    if (f16) HS_LAUNCH(true, true); else HS_LAUNCH(false, true);
+    if constexpr (TEAMS == 1) {
+      if (f16) HS_LAUNCH(true, true); else HS_LAUNCH(false, true);
+    } else {
+      return hipErrorInvalidValue;
+    }
   } else {
     if (f16) HS_LAUNCH(true, false); else HS_LAUNCH(false, false);
   }

@@ -1,20 +1,20 @@
-// Prefill attention with slabs of 16 queries, for calls with few query blocks (the rule is in hs_prefill.hip).
+// Prefill attention with slabs of 16 queries, for calls with few query blocks (the rule is in hs_prefill.hip): tensors of one kind.
 #include "hs_prefill_kernel.h"
 
-hipError_t hs_launch_prefill_narrow(int km, int vm, int B, int Hq, int Hkv, int T, int Lq, int q_start, float sl2, int causal,
+hipError_t hs_launch_prefill_narrow(int teams, int km, int vm, int B, int Hq, int Hkv, int T, int Lq, int q_start, float sl2, int causal,
                                     const uint16_t* Q, const hs_kv_dev& kv, uint16_t* O, float* LSE, hipStream_t st, bool f16,
                                     int n_splits, float* ws_o, float* ws_l) {
-#define HS_GO(KM_, VM_) \
-  return launch_prefill<KM_, VM_, 1>(B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l)
+#define HS_GO_TEAMS(KM_, VM_, TEAMS_) \
+  launch_prefill<KM_, VM_, 1, TEAMS_>(B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l)
+#define HS_GO(KM_, VM_) return teams == 2 ? HS_GO_TEAMS(KM_, VM_, 2) : HS_GO_TEAMS(KM_, VM_, 1)
   switch (km * 3 + vm) {
     case 0: HS_GO(0, 0);
     case 1: HS_GO(0, 1);
-    case 2: HS_GO(0, 2);
     case 3: HS_GO(1, 0);
     case 4: HS_GO(1, 1);
-    case 6: HS_GO(2, 0);
-    case 7: HS_GO(2, 1);
-    default: HS_GO(2, 2);  // dense K beside mixed V too, as in hs_prefill_mixed.hip
+    default:
+      return hs_launch_prefill_narrow_mixed(teams, km, vm, B, Hq, Hkv, T, Lq, q_start, sl2, causal, Q, kv, O, LSE, st, f16, n_splits, ws_o, ws_l);
   }
 #undef HS_GO
+#undef HS_GO_TEAMS
 }

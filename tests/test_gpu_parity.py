@@ -513,6 +513,47 @@ def test_prefill_tiles_cut_into_ranges(slab, n_ranges, B, G, T, Lq, q_start, cau
         assert torch.equal(O2.view(torch.int16), O.view(torch.int16)) and torch.equal(LSE2, LSE)
 
 
+@pytest.mark.parametrize("T,Lq,q_start,causal,G", [(1, 64, None, True, 4), (2, 128, None, True, 3), (7, 64, 64 * 3 + 17, True, 1),
+                                                    (66, 128, None, True, 2), (67, 64, 5, False, 5)])
+@pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict()), ("bf16", "states"), ("fp16", "states"), ("fp16", dict(sparse_frac_k=0.0)),
+                                       ("bf16", dict(sparse_frac_v=0.0)), ("bf16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)),
+                                       ("bf16", dict(sparse_frac_k=0.5)), ("bf16", dict(sparse_frac_v=0.5, skip_frac=0.3))])
+def test_prefill_two_teams_of_waves(T, Lq, q_start, causal, G, dtype, pol):
+    """Two teams that take a workgroup's tiles in turn: no tile, one, an odd number, more than a window of the maps; every kind
+    and both encodings of V; groups with idle waves; queries that see nothing."""
+    Hkv, L = 2, 64 * T
+    Q, K, V = wl.make_qkv(1, G * Hkv, Hkv, L, 128, Lq, seed=1300 + T, dtype=dtype)
+    V[:, 1, ::67, 5] = 0x0001                         # in bf16: values that fp16 does not hold
+    if pol == "states":
+        sk, sv = _mixed_states(1, Hkv, T, seed=1301)
+        sk[:, 0, :T // 2] = sv[:, 0, :T // 2] = 0
+        pol = dict(state_k=sk, state_v=sv)
+    sh, kv, pk, pv, _ = compress_both(1, G * Hkv, Hkv, L, K, V, dtype=dtype, **pol)
+    O, LSE = hb.prefill_attn_planned(sh, _dev(Q, dtype), kv, 16 | 0x100, 1, causal=causal, q_start=q_start)
+    rows = [(0, h, i) for h in range(G * Hkv) for i in range(0, Lq, 3)]
+    idx = tuple(np.array(rows).T)
+    Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=causal, **({} if q_start is None else {"q_offset": q_start}))
+    assert_close(_f32(O)[idx], Or, "prefill by two teams")
+    assert_lse_close(LSE.cpu().numpy()[idx], Lr, "prefill by two teams lse")
+    for slab, n in ((32 | 0x100, 1), (16 | 0x100, 2)):
+        with pytest.raises(hb.HsError):
+            hb.prefill_attn_planned(sh, _dev(Q, dtype), kv, slab, n)
+
+
+@pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict(sparse_frac_k=0.0)), ("bf16", dict(dense_first_tiles=1, dense_last_tiles=4)),
+                                       ("fp16", dict(sparse_frac_k=0.5))])
+def test_prefill_nan_scores_come_out_of_two_teams(dtype, pol):
+    """A query that sees a NaN score, whichever team meets it, has O and LSE NaN; the others see nothing of it."""
+    T, Lq = 9, 128
+    Q, K, V, tok = _nan_case(T, Lq, dtype, 1310)
+    sh = hb.make_shape(1, 4, 2, 64 * T, dtype=Q.dtype)
+    kv = hb.compress_kv(sh, hb.make_policy(**pol), K.cuda(), V.cuda())
+    Ku, Vu = (x.cpu() for x in hb.unpack_kv(sh, kv))
+    Or, Lr = _nan_reference(Q[0], Ku[0], Vu[0], torch.arange(64 * T)[None, :] <= 64 * T - Lq + torch.arange(Lq)[:, None])
+    O, LSE = hb.prefill_attn_planned(sh, Q.cuda(), kv, 16 | 0x100, 1)
+    _check_nan_rows(O.cpu()[0], LSE.cpu()[0], Or, Lr, "two teams, NaN scores")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 @pytest.mark.parametrize("pol", [dict(), dict(sparse_frac_k=0.0), dict(sparse_frac_v=0.0), dict(sparse_frac_k=0.0, sparse_frac_v=0.0),
                                  dict(sparse_frac_k=0.5, sparse_frac_v=0.5), dict(sparse_frac_k=0.5), dict(dense_first_tiles=1, dense_last_tiles=1)])
