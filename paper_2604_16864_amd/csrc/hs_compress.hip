@@ -633,9 +633,10 @@ __device__ __forceinline__ void k_sparse_store(uint8_t* nnz, uint8_t* meta, int 
 // The words to store are built first.  v_f16 (bf16 cache): if every value the tile stores is
 // exact in fp16 (workgroup vote), the tile is written in fp16 encoding and *map_entry, which the
 // caller has set to mv, gets HS_MAP_F16, so that the attention kernels can feed the softmax
-// numerators as one fp16 term.  Every thread of the workgroup must call this.
+// numerators as one fp16 term.  256 threads call this, tid = 0 .. 255; vote(bad) tells each whether any of them is bad.
+template <class Vote>
 __device__ __forceinline__ void v_tile_store(const uint16_t* vl, int mv, int32_t* map_entry, const hs_kv_dev& kv,
-                                             int64_t row, int rule, int v_f16, int tid) {
+                                             int64_t row, int rule, int v_f16, int tid, Vote vote) {
   const int w = tid >> 6, l = tid & 63, a = l >> 4, r = l & 15;
   uint32_t words[4][4];
   const int n_chunks = mv > 0 ? 4 : 2;  // 16-byte chunks this lane stores
@@ -676,7 +677,7 @@ __device__ __forceinline__ void v_tile_store(const uint16_t* vl, int mv, int32_t
 #pragma unroll
       for (int p = 0; p < 4; p++)
         if (j < n_chunks) bad |= !pair_to_f16(words[j][p], conv[j][p]);
-    if (!__syncthreads_or(bad)) {
+    if (!vote(bad)) {
 #pragma unroll
       for (int j = 0; j < 4; j++)
 #pragma unroll
@@ -699,6 +700,11 @@ __device__ __forceinline__ void v_tile_store(const uint16_t* vl, int mv, int32_t
       st16<true>(nnz + ((2 * w + j) * 64 + l) * 16, make_uint4(words[j][0], words[j][1], words[j][2], words[j][3]));
     *reinterpret_cast<uint32_t*>(meta + (l * 4 + w) * 4) = idx;
   }
+}
+
+__device__ __forceinline__ void v_tile_store(const uint16_t* vl, int mv, int32_t* map_entry, const hs_kv_dev& kv,
+                                             int64_t row, int rule, int v_f16, int tid) {  // by the whole workgroup
+  v_tile_store(vl, mv, map_entry, kv, row, rule, v_f16, tid, [](int bad) { return __syncthreads_or(bad) != 0; });
 }
 
 // Dense V tile in pool order -> vl[token][channel], as bf16 patterns when the tile is held in fp16
@@ -822,6 +828,85 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
   if (mv == 0) return;
   __syncthreads();
   v_tile_store(vl, mv, const_cast<int32_t*>(kv.v_map) + row * T + t, kv, row, rule, v_f16, tid);
+}
+
+// Appends tile blockIdx.x of K, V to its row as tile t0 + blockIdx.x (t0_rows: one t0 per batch row, entries that are not a tile index
+// leave the row out), in states uni_k / uni_v: what pack_kernel does with APPEND, for few tiles.  There the call is one chain of
+// latencies (place, tile, maps, stores), so 4 waves take K and 4 take V: either half requests its tile and counts its map at once, and
+// both prune at the same time.  us, by 4 waves one after the other / by 8: 8 rows of 128 tiles, one tile 6.0 / 5.0, fp16 5.1 / 4.5; 128 rows
+// 6.2 / 5.3; 8 rows of 2048 6.6 / 5.5; 8 tiles in each of 8 rows 6.2 / 5.3.
+__global__ __launch_bounds__(512) void append_kernel(const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+                                                     int64_t sb, int64_t sh, int64_t st, int T, hs_kv_dev kv, int uni_k, int uni_v,
+                                                     int rule, int t0, int v_f16, const int32_t* __restrict__ t0_rows, int32_t* overflow) {
+  __shared__ uint16_t vl[HS_BT * kVStride];
+  __shared__ int part[2][4], bad_waves[4];
+  const int ts = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  if (t0_rows != nullptr) {
+    t0 = t0_rows[b];
+    if (t0 < 0 || t0 >= T) return;  // the whole workgroup
+  }
+  const int t = ts + t0;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool for_v = wave >= 4;  // wave-uniform
+  const int tid = threadIdx.x & 255, w = wave & 3, l = tid & 63, a = l >> 4, r = l & 15;
+  const int64_t row = (int64_t)b * gridDim.y + h;
+  const int64_t from = b * sb + h * sh + (int64_t)ts * HS_BT * st;
+  // K: what the thread stores (dense: channels 32 i + 8 a .. +7 of its token; 2:4: 64 (i / 2) + 16 a + 8 (i % 2) .. +7); V: its part of the rows
+  const uint16_t* src = for_v ? V + from + (tid >> 4) * st + 8 * (tid & 15) : K + from + (16 * w + r) * st + (uni_k == HS_DENSE ? 8 : 16) * a;
+  uint4 d[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int64_t step = for_v ? 16 * i * st : (uni_k == HS_DENSE ? 32 * i : 64 * (i >> 1) + 8 * (i & 1));
+    d[i] = ld16<false>(src + step);
+  }
+  int32_t* const map = const_cast<int32_t*>(for_v ? kv.v_map : kv.k_map) + row * T;
+  const bool dense = (for_v ? uni_v : uni_k) == HS_DENSE;
+  int n = 0;  // entries [t0, t0 + gridDim.x) are being written by this launch and do not count
+#pragma unroll 4
+  for (int i = tid; i < T; i += 256) {
+    const bool old = i < t0 || i >= t0 + (int)gridDim.x;
+    const int e = old ? map[i] : 0;
+    n += dense ? e > 0 : e < 0;
+  }
+  n = wave_scan_sum(n);
+  if (l == 63) part[for_v][w] = n;
+  if (for_v) {
+#pragma unroll
+    for (int i = 0; i < 4; i++) {  // as stage_v_tile
+      uint2* dst = reinterpret_cast<uint2*>(vl + ((tid >> 4) + 16 * i) * kVStride + 8 * (tid & 15));
+      dst[0] = make_uint2(d[i].x, d[i].y);
+      dst[1] = make_uint2(d[i].z, d[i].w);
+    }
+  }
+  __syncthreads();
+  const int sk = part[0][0] + part[0][1] + part[0][2] + part[0][3] + ts, sv = part[1][0] + part[1][1] + part[1][2] + part[1][3] + ts;
+  const bool fits = sk < (uni_k == HS_DENSE ? kv.cap_dense_k : kv.cap_sparse_k) && sv < (uni_v == HS_DENSE ? kv.cap_dense_v : kv.cap_sparse_v);
+  const int slot = for_v ? sv : sk, entry = !fits ? 0 : (dense ? slot + 1 : -(slot + 1));
+  if (tid == 0) {
+    map[t] = entry;
+    if (!fits && overflow != nullptr) *overflow = 1;
+  }
+  if (!fits) return;  // the whole workgroup
+  if (!for_v) {
+    if (dense) {
+      uint8_t* dst = const_cast<uint8_t*>(kv.k_dense) + (row * kv.cap_dense_k + slot) * (int64_t)HS_TILE_DENSE_BYTES;
+#pragma unroll
+      for (int i = 0; i < 4; i++) st16<false>(dst + ((w * 4 + i) * 64 + l) * 16, d[i]);
+    } else {
+      const int64_t at = row * kv.cap_sparse_k + slot;
+      k_sparse_store(const_cast<uint8_t*>(kv.k_nnz) + at * (int64_t)HS_TILE_NNZ_BYTES,
+                     const_cast<uint8_t*>(kv.k_meta) + at * (int64_t)HS_TILE_META_BYTES, w, l, rule,
+                     [&](int kb, int half) { return d[2 * kb + half]; });
+    }
+    if (v_f16) __syncthreads();  // the vote below
+  } else {
+    v_tile_store(vl, entry, map + t, kv, row, rule, v_f16, tid, [&](int bad) {
+      const bool any = __any(bad);
+      if (l == 0) bad_waves[w] = any;
+      __syncthreads();
+      return (bad_waves[0] | bad_waves[1] | bad_waves[2] | bad_waves[3]) != 0;
+    });
+  }
 }
 
 // ----------------------------------------------------------------------------------
@@ -1177,11 +1262,19 @@ hipError_t hs_launch_pack(const uint16_t* K, const uint16_t* V, int64_t sb, int6
 hipError_t hs_launch_append(const uint16_t* K, const uint16_t* V, int64_t sb, int64_t sh, int64_t st_, int B, int Hkv,
                             int T, int tile, int n_tiles, const int32_t* tile_rows, int state_k, int state_v,
                             hs_kv_dev kv, int rule, int v_f16, int32_t* overflow, hipStream_t st) {
+  // Few tiles: a workgroup of 8 waves each.  From 1024 on the chip is full and the smaller workgroups of pack_kernel are faster (us, 8 / 4
+  // waves: 512 tiles 8.8 / 8.9, 1024 13.2 / 12.9, 8192 80.4 / 73.0).
+  const bool one_launch = tile_rows != nullptr || (double)n_tiles * B * Hkv * T <= (double)(4 << 20);
+  if (one_launch && (int64_t)n_tiles * B * Hkv <= 512) {
+    hipLaunchKernelGGL(append_kernel, dim3(n_tiles, Hkv, B), dim3(512), 0, st, K, V, sb, sh, st_, T, kv, state_k, state_v, rule, tile, v_f16,
+                       tile_rows, overflow);
+    return hipGetLastError();
+  }
   const bool nt = 2.0 * B * Hkv * n_tiles * HS_BT * HS_D * 2.0 > 256e6;
   // One launch while the map entries that all workgroups read to count are few (32 MB): 1 x 8 rows of 512 tiles, one tile
   // 8.1 -> 6.1 us, 64 tiles 10.7 -> 8.1 us; 1 x 8 rows of 2048, 256 tiles 26.6 -> 23.3 us, 1024 tiles 76.5 us either way;
   // 16 x 8 rows of 512, 128 tiles 137 -> 140 us.  Per-row places come one tile at a time and always take it.
-  if (tile_rows != nullptr || (double)n_tiles * B * Hkv * T <= (double)(4 << 20)) {
+  if (one_launch) {
     if (nt)
       hipLaunchKernelGGL((pack_kernel<true, true>), dim3(n_tiles, Hkv, B), dim3(256), 0, st, K, V, sb, sh, st_, Hkv, T, kv, state_k,
                          state_v, 0, 0, rule, tile, v_f16, tile_rows, overflow);

@@ -1286,6 +1286,47 @@ def _pool_bytes_equal(a, b):
         assert (x is None) == (y is None) and (x is None or torch.equal(x, y)), name
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("state_k,state_v", [(2, 2), (1, 2), (2, 1), (1, 1)])
+@pytest.mark.parametrize("rule,places", [(0, "rows"), (1, "rows"), (0, 3), (1, 300)])
+def test_append_of_few_tiles_and_of_many_write_the_same_bytes(dtype, state_k, state_v, rule, places):
+    """520 rows in one call and in calls of fewer rows, which take a workgroup of 8 waves per tile: places per row (some rows left
+    out, some pools full) or one for all, tokens and heads in an order of their own, values that fp16 does not hold."""
+    B, Hkv, T = 65, 8, 310
+    g = torch.Generator(device="cuda").manual_seed(31)
+    K, V = (torch.randn((B, 64, Hkv, 136), device="cuda", generator=g).to(dtype)[..., :128].transpose(1, 2) for _ in range(2))
+    K, V = (torch.where(torch.rand(x.shape, device="cuda", generator=g) < 0.6, x, torch.zeros_like(x)) for x in (K, V)) if rule else (K, V)
+    K, V = (torch.empty((B, 64, Hkv, 136), device="cuda", dtype=dtype)[..., :128].transpose(1, 2).copy_(x) for x in (K, V))
+    if dtype == torch.bfloat16:
+        V[::5, :, 9, 3] = 1e-30
+    maps = torch.zeros((B, Hkv, T), dtype=torch.int32)
+    held = torch.randint(0, 5, (B,), generator=torch.Generator().manual_seed(32))
+    for b in range(B):
+        maps[b, :, 5:5 + held[b]] = -torch.arange(1, held[b] + 1, dtype=torch.int32)
+        maps[b, :, 290:290 + held[b]] = torch.arange(1, held[b] + 1, dtype=torch.int32)
+    at = torch.randint(-1, 5, (B,), generator=torch.Generator().manual_seed(33), dtype=torch.int32)
+    at[held == 1] = 309
+    results = []
+    for parts in ((slice(0, B),), (slice(0, 1), slice(1, 64), slice(64, B))):
+        out = []
+        for p in parts:
+            n = len(range(B)[p])
+            sh = hb.make_shape(n, Hkv, Hkv, 64 * T, dtype=dtype)
+            kv = hb.PackedKV(sh, [0, 4, 4, 4, 4])     # rows that hold four of a kind are full
+            kv.uniform = 0
+            for x in (kv.k_dense, kv.k_nnz, kv.k_meta, kv.v_dense, kv.v_nnz, kv.v_meta):
+                x.fill_(7)
+            kv.k_map.copy_(maps[p]), kv.v_map.copy_(maps[p])
+            over = torch.zeros(1, dtype=torch.int32, device="cuda")
+            hb.append_tile(sh, kv, at[p].cuda() if places == "rows" else places, K[p], V[p], state_k, state_v, element_rule=rule, overflow=over)
+            out.append([x.cpu().reshape(n, -1) for x in (kv.k_dense, kv.k_nnz, kv.k_meta, kv.v_dense, kv.v_nnz, kv.v_meta, kv.k_map, kv.v_map)] + [over.cpu()])
+        results.append([torch.cat([o[i] for o in out]) for i in range(8)] + [max(int(o[8]) for o in out)])
+    many, few = results
+    assert many[8] == few[8] == 1
+    for i in range(8):
+        assert torch.equal(many[i], few[i]), i
+
+
 @pytest.mark.parametrize("state_k,state_v", [(2, 2), (1, 2)])
 def test_append_beyond_the_last_level_cache_in_one_launch(state_k, state_v):
     """More than 256 MB of new K and V (read non-temporally) that one launch still counts: the bytes of shorter calls."""
