@@ -35,7 +35,7 @@ def native_command():
             "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
             "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
             "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "hs_torch.cpp"),
-            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", NATIVE]
+            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", NATIVE]
 
 
 def build_lib(verbose=True, extra=()):

@@ -1,7 +1,7 @@
 // Argument marshalling of the Python binding in native code: the per-call part of decode, prefill, append, compress and
 // re-compress.  What a call on a small cache costs is mostly this part: in Python with ctypes a decode call of 7 us of
 // kernels took 13.3 us (8 data_ptr() calls and a ctypes structure for the cache, three allocations, two library calls) and takes
-// 9 here, compressing 2K tokens 16.1 and 10.3.
+// 9 here, compressing 2K tokens 16.1 and 8.5.
 //
 // Every function repeats the binding's checks and returns None for a call that fails one or that it does not take as it is (other
 // types than exact tensors, a number that is neither int nor float); the binding's Python code then takes it, so which error a
@@ -10,8 +10,10 @@
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
+#include <ATen/Context.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/empty.h>
-#include <ATen/ops/empty_like.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -107,7 +109,30 @@ bool get_kv(PyObject* o, hs_kv* kv) {
 at::ScalarType element_type(const hs_shape& s) { return s.dtype == HS_FP16 ? at::kHalf : at::kBFloat16; }
 bool query_ok(const at::Tensor& q, const hs_shape& s) { return q.scalar_type() == element_type(s) && q.is_contiguous() && q.is_cuda(); }
 void* current_stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
-at::Tensor bytes_beside(const at::Tensor& t, size_t n) { return at::empty({(int64_t)n}, t.options().dtype(at::kByte)); }
+
+// New tensors on the device of `like`.  A call on a small cache is mostly its allocations (two to nine), and a third of one is the
+// dispatcher's two rounds, so where these have nothing to do the tensor is made by what they end in: not where anything listens
+// to the operators of this thread (dispatch modes, fake tensors, function transforms) or new memory is to be filled.
+// us a call through the dispatcher / at once, 1K tokens: decode with outputs and scratch of its own 9.9 / 9.3, prefill 6.1 / 5.7, compress
+// 10.2 / 8.4, re-compress 11.3 / 9.7.
+class NewTensors {
+ public:
+  explicit NewTensors(const at::Tensor& like) : like_(like) {
+    const auto usual = c10::DispatchKeySet({c10::DispatchKey::BackendSelect, c10::DispatchKey::ADInplaceOrView});
+    const auto& context = at::globalContext();
+    at_once_ = (c10::impl::tls_local_dispatch_key_set().included_ - usual).empty() && like.is_cuda() &&
+               !(context.deterministicAlgorithms() && context.deterministicFillUninitializedMemory());
+  }
+  at::Tensor operator()(at::IntArrayRef sizes, at::ScalarType type) const {
+    if (!at_once_) return at::empty(sizes, like_.options().dtype(type));
+    return at::Tensor(at::detail::empty_cuda(sizes, type, like_.device(), std::nullopt));
+  }
+  at::Tensor bytes(size_t n) const { return (*this)({(int64_t)n}, at::kByte); }
+
+ private:
+  const at::Tensor& like_;
+  bool at_once_;
+};
 
 // Other threads run while memory is allocated and the kernels are launched: the allocator may wait for the GPU (when it gives
 // cached blocks back) and a launch for room in the queue, and what they wait for may be up to another thread.
@@ -180,9 +205,10 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   int rc;
   {
     NoGil others_run;
-    if (own_ws) { ws = bytes_beside(q, need); ws_ptr = ws.data_ptr(); }
-    if (own_o) { o = at::empty_like(q); o_ptr = o.data_ptr(); }
-    if (own_lse) { lse = at::empty({q.size(0), q.size(1)}, q.options().dtype(at::kFloat)); lse_ptr = (float*)lse.data_ptr(); }
+    const NewTensors make(q);
+    if (own_ws) { ws = make.bytes(need); ws_ptr = ws.data_ptr(); }
+    if (own_o) { o = make(q.sizes(), q.scalar_type()); o_ptr = o.data_ptr(); }
+    if (own_lse) { lse = make({q.size(0), q.size(1)}, at::kFloat); lse_ptr = (float*)lse.data_ptr(); }
     void* st = current_stream();
     if (!has_tail) rc = g_hs.decode(&s, scale, n_splits, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, st);
     else if (rows != nullptr) rc = g_hs.decode_tail_rows(&s, scale, n_splits, q_ptr, &kv, tk, tv, lens, o_ptr, lse_ptr, ws_ptr, st);
@@ -248,8 +274,9 @@ PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   int rc = 0;
   {
     NoGil others_run;
-    if (own_o) { o = at::empty_like(q); o_ptr = o.data_ptr(); }
-    if (own_lse) { lse = at::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(at::kFloat)); lse_ptr = (float*)lse.data_ptr(); }
+    const NewTensors make(q);
+    if (own_o) { o = make(q.sizes(), q.scalar_type()); o_ptr = o.data_ptr(); }
+    if (own_lse) { lse = make({q.size(0), q.size(1), q.size(2)}, at::kFloat); lse_ptr = (float*)lse.data_ptr(); }
     if (!outputs_only)
       rc = g_hs.prefill(&s, Lq, at_pos, scale, causal, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, need, current_stream());
   }
@@ -306,12 +333,12 @@ struct Pools {
 
 // They are made beside the tensor `like`, from the bytes that hs_kv_bytes has given (without the GIL); kv: the cache as the library sees it.
 void make_pools(const hs_shape& s, const int32_t counts[5], const at::Tensor& like, int uniform, Pools* p, hs_kv* kv) {
-  const auto opt = like.options();
+  const NewTensors make(like);
   void** ptr[8] = {&kv->k_dense, &kv->k_nnz, &kv->k_meta, (void**)&kv->k_map, &kv->v_dense, &kv->v_nnz, &kv->v_meta, (void**)&kv->v_map};
   for (int i = 0; i < 8; i++) {
     const bool map = i == S_K_MAP || i == S_V_MAP;
     if (map || p->bytes[i] != 0)
-      p->t[i] = map ? at::empty({s.B, s.Hkv, s.L / 64}, opt.dtype(at::kInt)) : at::empty({(int64_t)p->bytes[i]}, opt.dtype(at::kByte));
+      p->t[i] = map ? make({s.B, s.Hkv, s.L / 64}, at::kInt) : make.bytes(p->bytes[i]);
     *ptr[i] = p->t[i].defined() ? p->t[i].data_ptr() : nullptr;
   }
   kv->cap_dense_k = counts[1]; kv->cap_sparse_k = counts[2]; kv->cap_dense_v = counts[3]; kv->cap_sparse_v = counts[4];
@@ -393,7 +420,7 @@ PyObject* compress(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   {
     NoGil others_run;
     make_pools(s, counts, k, uniform, &p, &kv);
-    const at::Tensor ws = bytes_beside(k, need < 16 ? 16 : need);
+    const at::Tensor ws = NewTensors(k).bytes(need < 16 ? 16 : need);
     rc = g_hs.compress(&s, &pol, kp, vp, strides, &kv, ws.data_ptr(), current_stream());
   }
   return new_cache(rc, counts, p, uniform);

@@ -259,3 +259,55 @@ def test_library_errors_are_raised_through_the_native_part():
     with pytest.raises(hb.HsError):                              # a uniform cache does not grow
         hb.append_tile(sh, kv, 3, torch.zeros(2, 2, 64, 128, dtype=torch.bfloat16, device="cuda"),
                        torch.zeros(2, 2, 64, 128, dtype=torch.bfloat16, device="cuda"))
+
+
+@pytest.mark.gpu
+def test_native_outputs_follow_the_modes_of_the_thread():
+    """New tensors are made past the dispatcher only where nothing listens: inference mode, a dispatch mode, memory that is to be
+    filled, and another stream give what the Python code gives."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Seen(TorchDispatchMode):
+        def __init__(self):
+            super().__init__()
+            self.names = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.names.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    sh = hb.make_shape(1, 4, 2, 256)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    K, V = (torch.randn((1, 2, 256, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
+    q = torch.randn((1, 4, 128), device="cuda", generator=g).bfloat16()
+    assert hb._native is not None
+    plain = hb.decode_attn(sh, q, hb.compress_kv(sh, hb.make_policy(), K, V))
+    assert not any(x.is_inference() or x.requires_grad for x in plain)
+    assert plain[0].dtype == q.dtype and plain[0].device == q.device and plain[0].stride() == q.stride() and plain[1].shape == (1, 4)
+
+    def same(pair):
+        return all(torch.equal(x, y) for x, y in zip(pair, plain))
+    with torch.inference_mode():
+        kv = hb.compress_kv(sh, hb.make_policy(), K, V)
+        out = hb.decode_attn(sh, q, kv)
+        assert all(x.is_inference() for x in (*out, kv.k_map, kv.v_nnz))
+    assert same(out)
+    with Seen() as seen:
+        out = hb.decode_attn(sh, q, hb.compress_kv(sh, hb.make_policy(), K, V))
+    assert same(out) and sum("empty" in n for n in seen.names) >= 8
+    torch.use_deterministic_algorithms(True)
+    try:
+        room = hb.PackedKV(sh, [0, 0, 6, 0, 6])                     # slots nobody writes
+        assert torch.utils.deterministic.fill_uninitialized_memory and int(room.k_nnz.reshape(2, 6, -1)[:, 4:].min()) == 255
+        kv = hb.compress_kv(sh, hb.make_policy(), K, V)
+        more = hb.recompress_kv(sh, kv, hb.make_policy(), counts=[0, 0, 6, 0, 6])
+        assert int(more.k_nnz.reshape(2, 6, -1)[:, 4:].min()) == 255
+        assert same(hb.decode_attn(sh, q, kv))
+    finally:
+        torch.use_deterministic_algorithms(False)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        out = hb.decode_attn(sh, q, hb.compress_kv(sh, hb.make_policy(), K, V))
+    side.synchronize()
+    assert same(out)
