@@ -298,26 +298,37 @@ __device__ __forceinline__ void tail_piece(const TailArgs& tail, int tail_len, i
   }
 }
 
-// Combines the N parts that the waves have left in LDS and writes the row's partial of split `slot`, or (DIRECT) its O and LSE.
-// Thread = (head tid / 32, 4 channels).  part_m, part_l, part_o: of N parts, 8 heads each.
-template <bool F16, bool DIRECT>
-__device__ __forceinline__ void combine_parts(int tid, int N, int G, int64_t hq0, const float (*part_m)[8], const float (*part_l)[8],
+// Combines the N parts that the waves have left in LDS (and, with_tail, the tail's four behind them) and writes the row's partial of split
+// `slot`, or (DIRECT) its O and LSE.  Thread = (head tid / 32, 4 channels).  part_m, part_l, part_o: 8 heads a part.
+template <bool F16, bool DIRECT, int N>
+__device__ __forceinline__ void combine_parts(int tid, bool with_tail, int G, int64_t hq0, const float (*part_m)[8], const float (*part_l)[8],
                                               const float (*part_o)[8][HS_D], int n_splits, int slot, float* __restrict__ ws_o,
                                               float* __restrict__ ws_l) {
   const int g = tid >> 5, ch = (tid & 31) * 4;
   if (g >= G) return;
   const int64_t hq = hq0 + g;
   float mstar = -INFINITY;
+#pragma unroll
   for (int k = 0; k < N; k++) mstar = fmaxf(mstar, part_m[k][g]);
+  if (DIRECT && with_tail) {
+#pragma unroll
+    for (int k = N; k < N + 4; k++) mstar = fmaxf(mstar, part_m[k][g]);
+  }
   // a part without a reference has seen nothing (l and O are 0) or only NaN scores (l is NaN): neither is left out,
   // and only l == 0 is an empty split, so that a NaN reaches O and LSE however the tiles are divided
   const float mref = mstar > -INFINITY ? mstar : 0.f;
   float lsum = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < N; k++) {
+  auto add = [&](int k) {
     const float f = __builtin_amdgcn_exp2f(part_m[k][g] - mref);
     lsum += f * part_l[k][g];
 #pragma unroll
     for (int i = 0; i < 4; i++) acc[i] += f * part_o[k][g][ch + i];
+  };
+#pragma unroll
+  for (int k = 0; k < N; k++) add(k);
+  if (DIRECT && with_tail) {
+#pragma unroll
+    for (int k = N; k < N + 4; k++) add(k);
   }
   const float inv = lsum == 0.f ? 0.f : 1.f / lsum;
   const float lse = lsum == 0.f ? -INFINITY : (mstar + __builtin_amdgcn_logf(lsum)) * kLn2;
@@ -394,7 +405,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HS_DEC_
   asm volatile("" : "+s"(to_o), "+s"(to_l));
   // the row, its group's first query head, and the partial slot that this workgroup writes
   int64_t row = (int64_t)b * Hkv + hkv, hq0 = (int64_t)b * Hq + hkv * G;
-  int slot = split, n_parts = NW;
+  int slot = split;
   if (!DIRECT && __builtin_expect(b >= B, 0)) {  // the whole workgroup: the dense tail of a row
     row = ((int64_t)(b - B) * Hkv + hkv) * n_work + split;
     if (row >= (int64_t)B * Hkv) return;
@@ -634,14 +645,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HS_DEC_
     }
     if constexpr (DIRECT) {
       if (tail.len >= 0) {  // by the waves that have no tile where the row has few
-        n_parts = NW + 4;
-        const int q = NW - 1 - w;
+          const int q = NW - 1 - w;
         if (q < 4) tail_piece<F16>(tail, tail_length(b), row, q, qb, scale_log2, l, sm_o[NW + q], sm_m[NW + q], sm_l[NW + q]);
       }
     }
   }
   __syncthreads();
-  combine_parts<F16, DIRECT>(tid, n_parts, G, hq0, sm_m, sm_l, sm_o, n_splits, slot, (float*)to_o, (float*)to_l);
+  combine_parts<F16, DIRECT, NW>(tid, tail.len >= 0, G, hq0, sm_m, sm_l, sm_o, n_splits, slot, (float*)to_o, (float*)to_l);
 }
 
 // Merge of the split partials (Sec. IV-C "lightweight post-processing kernel"):
