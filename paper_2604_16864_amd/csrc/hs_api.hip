@@ -284,6 +284,15 @@ int hs_compress_kv(const hs_shape* shape, const hs_policy* policy, const void* K
       e = hs_launch_score((const uint16_t*)K, (const uint16_t*)V, sb, sh, st, shape->B, shape->Hkv, T,
                           policy->element_rule, shape->dtype, what, (double*)workspace, s);
       if (e != hipSuccess) return hip_fail(e);
+      // Few short rows: ranked by the pack kernel itself, every tile's workgroup anew.  us, select + pack / in one, half skipped | half of the
+      // keys 2:4 | both with dense ends: 8 rows of 16 tiles 14.7 / 12.0 | 15.3 / 12.7 | 16.3 / 13.7; 8 of 64 16.9 / 14.8 | 16.7 / 16.6 | 20.8 / 19.4; 32 of 32
+      // 21.3 / 19.4 | 22.6 / 20.7 | 25.0 / 23.0; 128 of 16 31.3 / 30.5 | 37.0 / 34.3 | 35.8 / 33.4; 52 of 33 29.4 / 29.8 | 32.3 / 30.9 | 32.6 / 32.8; 32 of 64
+      // 32.2 / 37.4 | 37.0 / 40.0 | 36.4 / 46.1: the line is where the tiles looked at, rows x T x T, are as many as in 128 rows of 16.
+      if (T <= HS_RANK_TILES && (int64_t)rows * T * T <= 32768) {
+        e = hs_launch_rank_and_pack((const uint16_t*)K, (const uint16_t*)V, sb, sh, st, shape->B, shape->Hkv, T, hs_make_kv_dev(out),
+                                    (const double*)workspace, c[0], c[2], c[4], n_first, n_last, policy->element_rule, shape->dtype == HS_BF16, s);
+        return e != hipSuccess ? hip_fail(e) : HS_OK;
+      }
       e = hs_launch_select((const double*)workspace, rows, T, c[0], c[2], c[4], n_first, n_last, out->k_map,
                            out->v_map, s);
       if (e != hipSuccess) return hip_fail(e);

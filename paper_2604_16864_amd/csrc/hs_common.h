@@ -152,6 +152,11 @@ hipError_t hs_launch_select(const double* scores, int rows, int T, int n_skip, i
 hipError_t hs_launch_pack(const uint16_t* K, const uint16_t* V, int64_t sb, int64_t sh, int64_t st_,
                           int B, int Hkv, int T, hs_kv_dev kv, int uni_k, int uni_v, int n_first, int n_last, int rule,
                           int v_f16, hipStream_t st);
+// hs_launch_select and hs_launch_pack in one launch, rows of at most 64 tiles (HS_RANK_TILES)
+enum { HS_RANK_TILES = 64 };
+hipError_t hs_launch_rank_and_pack(const uint16_t* K, const uint16_t* V, int64_t sb, int64_t sh, int64_t st_, int B, int Hkv, int T,
+                                   hs_kv_dev kv, const double* scores, int n_skip, int n_sparse_k, int n_sparse_v, int n_first, int n_last,
+                                   int rule, int v_f16, hipStream_t st);
 // n_tiles tiles [B, Hkv, 64 n_tiles, D] into tile indices tile .. of a cache of T tiles per row
 hipError_t hs_launch_append(const uint16_t* K, const uint16_t* V, int64_t sb, int64_t sh, int64_t st_,
                             int B, int Hkv, int T, int tile, int n_tiles, const int32_t* tile_rows, int state_k, int state_v, hs_kv_dev kv, int rule,

@@ -1286,6 +1286,34 @@ def _pool_bytes_equal(a, b):
         assert (x is None) == (y is None) and (x is None or torch.equal(x, y)), name
 
 
+@pytest.mark.parametrize("T,B", [(17, 60), (33, 20), (64, 5)])
+@pytest.mark.parametrize("pol", [dict(skip_frac=0.5), dict(sparse_frac_k=0.5), dict(skip_frac=0.25, sparse_frac_k=0.3, sparse_frac_v=0.7), dict(sparse_frac_k=0.0, sparse_frac_v=0.6),
+                                 dict(skip_frac=0.9, sparse_frac_k=0.5, dense_first_tiles=1, dense_last_tiles=4), dict(skip_frac=0.4, dense_first_tiles=70),
+                                 dict(skip_frac=0.3, sparse_frac_v=0.2, element_rule=1)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_short_rows_ranked_by_the_pack_kernel_give_the_same_bytes(T, B, pol, dtype):
+    """Rows ranked by the selection kernel (a batch of them) and by the pack kernel itself (one sequence at a time), with
+    scores that tie inside a row and rows that hold nothing but zeros."""
+    Hkv, L = 2, 64 * T
+    g = torch.Generator(device="cuda").manual_seed(T)
+    K, V = (torch.randn((B, Hkv, L, 128), device="cuda", generator=g).to(dtype) for _ in range(2))
+    for x in (K, V):
+        y = x.view(B, Hkv, T, 64, 128)
+        y[:, :, 3::4] = y[:, :, 1:2]                  # equal tiles
+        y[1, 0] = 0
+        y[2, 1, ::2] = 0
+    names = ("k_dense", "k_nnz", "k_meta", "v_dense", "v_nnz", "v_meta", "k_map", "v_map")
+
+    def packed(k, v):
+        sh = hb.make_shape(len(k), Hkv, Hkv, L, dtype=dtype)
+        kv = hb.compress_kv(sh, hb.make_policy(**pol), k, v)
+        return [None if getattr(kv, n) is None else getattr(kv, n).reshape(len(k), -1) for n in names]
+    many = packed(K, V)
+    for b in range(0, B, 3):
+        for x, y, n in zip(many, packed(K[b:b + 1], V[b:b + 1]), names):
+            assert (x is None) == (y is None) and (x is None or torch.equal(x[b:b + 1], y)), (b, n)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("state_k,state_v", [(2, 2), (1, 2), (2, 1), (1, 1)])
 @pytest.mark.parametrize("rule,places", [(0, "rows"), (1, "rows"), (0, 3), (1, 300)])
