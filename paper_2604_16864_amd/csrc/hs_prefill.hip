@@ -60,14 +60,15 @@ int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, i
 // workgroups equally long); ranges add the merge launch and the partials.
 // Two teams of waves per workgroup (one workgroup per compute unit, which takes two tiles in little more than the time one team takes
 // for one) where slabs of 16 leave each compute unit one workgroup or none; one team / two, us: 64 workgroups of 16 tiles 15.5 / 13.4,
-// 128 of up to 32 26.7 / 21.7, half of the keys dense 31.3 / 24.3, dense ends 31.3 / 24.0, 128 of up to 8 10.8 / 10.3, 13.2 / 12.0; of up to 4
-// tiles 7.9 / 8.2.  Not with more workgroups than compute units, which fill the chip by themselves (prompt of 1024 tokens 18.4 / 20.1, 336
+// 128 of up to 32 26.7 / 21.7, half of the keys dense 31.3 / 24.3, dense ends 31.3 / 24.0, 64 of up to 4 tiles 7.9 / 8.2.
+//  The more workgroups, the more a tile takes them (per_wg; 16 of 64 tiles 0.43 us a tile, 128 of 32 0.46, 256 of 64 0.53: prompt of 4096
+// tokens x 4 heads 37.1 in slabs of 32, 40.5 by teams).  Not with more workgroups than compute units, which fill the chip by themselves (prompt of 1024 tokens 18.4 / 20.1, 336
 // workgroups of 40 tiles 35.4 / 36.7), and not in ranges: their tiles come from HBM, and both teams wait for the slower one's at every
 // barrier (3 x 128 queries x 8 heads on 33088 tokens, half of them skipped, 45 / 58; 64 queries x 32 heads on 4096 17.1 / 17.0).
 // The margins go by what the shape allows and not by `fit`, so a workspace of the size of the choice leads to the same choice.
 hs_prefill_choice hs_plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv, int fit) {
-  static const struct { int nb, teams, at_once; double start, alone, pair; } kWays[3] = {
-      {2, 1, 512, 7.2, 0.905, 1.13}, {1, 1, 512, 5.3, 0.70, 0.82}, {1, 2, 256, 6.9, 0.47, 0.47}};
+  static const struct { int nb, teams, at_once; double start, alone, pair, per_wg; } kWays[3] = {
+      {2, 1, 512, 7.2, 0.905, 1.13, 0}, {1, 1, 512, 5.3, 0.70, 0.82, 0}, {1, 2, 256, 6.3, 0.43, 0.53, 0.0004}};
   const int most = hs_prefill_auto_splits(B, Hq, Hkv, T, Lq, q_start, causal, kv);
   const int seen = causal ? (q_start + Lq + HS_BT - 1) / HS_BT : T;  // tiles of the last query
   const double share = (double)tiles_to_expect(T, seen, kv) / seen;
@@ -79,7 +80,7 @@ hs_prefill_choice hs_plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_s
     for (int n = 1; n <= most && n <= fit; n++) {
       const double wgs = n_wg * n, rounds = ceil(wgs / w.at_once);
       if (w.teams == 2 && (n > 1 || rounds > 1)) break;
-      double us = longest / n * (wgs <= 256 ? w.alone : w.pair) + w.start;
+      double us = longest / n * (wgs <= 256 ? w.alone + w.per_wg * wgs : w.pair) + w.start;
       us = fmax(us, (longest + shortest) / 2 / n * w.pair * wgs / w.at_once + rounds * w.start);
       if (rounds > 1) {  // (k + 1) (first - k fall), k = 1 .. rounds - 1: largest beside its vertex, or at an end
         const double first = longest / n * w.pair + w.start, fall = (longest - shortest) * w.at_once / wgs / n * w.pair;
@@ -89,7 +90,7 @@ hs_prefill_choice hs_plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_s
       if (n > 1) us += 3.0 + 0.014 * w.nb * wgs;
       // The wider slab in all the ranges allowed where things are even; ranges of the narrow one, two to a compute unit, are
       // where the sum is least sure (128 queries x 4 heads on 47104 tokens 25.8 / 28.0, 256 x 4 on 32768 29.6 / 27.0).
-      if (w.nb == 1) us *= n > 1 && wgs > 256 ? 1.12 : (w.teams == 2 ? 1.05 : 1.03);
+      if (w.nb == 1) us *= n > 1 && wgs > 256 ? 1.12 : (w.teams == 2 ? 1.08 : 1.03);
       else if (n != most) us *= 1.03;
       if (best_us == 0.0 || us < best_us) { best = {w.nb, n, w.teams}; best_us = us; }
     }
