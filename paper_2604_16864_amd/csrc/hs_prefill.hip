@@ -54,16 +54,16 @@ int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, i
 // mixed and dense ones; what matters is the difference of the two slabs, where most of that cancels.  Of those 500, all of which it
 // put in slabs of 16, the mean gain over slabs of 32 in all the ranges allowed is 1.20, and ten are 2 to 7.5 % slower (4 x 192 queries
 // of 40/8 heads on 3584 tokens with dense ends, fp16, 57.2 / 61.5; 4 x 64 of 7/1 on 13760, values dense, 32.6 / 35.2).
-// Its terms (us): a workgroup starts in kStart, a tile takes it kAlone with a compute unit
-// to itself and kPair beside a second one; 512 run at a time, the longest first, so the call ends with the longest, or when the
+// Its terms (us): a workgroup starts in `start`, a tile takes it `alone` with a compute unit
+// to itself and `pair` beside a second one; at_once run at a time, the longest first, so the call ends with the longest, or when the
 // whole is worked off, or with a pile of k + 1 where round k + 1 is just begun (queries at the end of a long context: all
 // workgroups equally long); ranges add the merge launch and the partials.
 // Two teams of waves per workgroup (one workgroup per compute unit, which takes two tiles in little more than the time one team takes
 // for one) where slabs of 16 leave each compute unit one workgroup or none; one team / two, us: 64 workgroups of 16 tiles 15.5 / 13.4,
 // 128 of up to 32 26.7 / 21.7, half of the keys dense 31.3 / 24.3, dense ends 31.3 / 24.0, 64 of up to 4 tiles 7.9 / 8.2.
-//  The more workgroups, the more a tile takes them (per_wg; 16 of 64 tiles 0.43 us a tile, 128 of 32 0.46, 256 of 64 0.53: prompt of 4096
-// tokens x 4 heads 37.1 in slabs of 32, 40.5 by teams).  Not with more workgroups than compute units, which fill the chip by themselves (prompt of 1024 tokens 18.4 / 20.1, 336
-// workgroups of 40 tiles 35.4 / 36.7), and not in ranges: their tiles come from HBM, and both teams wait for the slower one's at every
+// The more workgroups, the more a tile takes them (per_wg; 16 of 64 tiles 0.43 us a tile, 128 of 32 0.46, 256 of 64 0.53: prompt of 4096
+// tokens x 4 heads 37.1 in slabs of 32, 40.5 by teams).  Not with more workgroups than compute units, which fill the chip by
+// themselves (prompt of 1024 tokens 18.4 / 20.1, 336 workgroups of 40 tiles 35.4 / 36.7), and not in ranges: their tiles come from HBM, and both teams wait for the slower one's at every
 // barrier (3 x 128 queries x 8 heads on 33088 tokens, half of them skipped, 45 / 58; 64 queries x 32 heads on 4096 17.1 / 17.0).
 // The margins go by what the shape allows and not by `fit`, so a workspace of the size of the choice leads to the same choice.
 hs_prefill_choice hs_plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv, int fit) {
