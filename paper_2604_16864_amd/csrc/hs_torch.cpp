@@ -13,6 +13,7 @@
 #include <ATen/Context.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/empty.h>
+#include <ATen/record_function.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -112,7 +113,8 @@ void* current_stream() { return (void*)c10::hip::getCurrentHIPStream().stream();
 
 // New tensors on the device of `like`.  A call on a small cache is mostly its allocations (two to nine), and a third of one is the
 // dispatcher's two rounds, so where these have nothing to do the tensor is made by what they end in: not where anything listens
-// to the operators of this thread (dispatch modes, fake tensors, function transforms) or new memory is to be filled.
+// to the operators of this thread (dispatch modes, fake tensors, function transforms, profilers and other observers) or new memory is to be
+// filled.  Looking that up is for calls that make a tensor: those into kept buffers go without.
 // us a call through the dispatcher / at once, 1K tokens: decode with outputs and scratch of its own 9.9 / 9.3, prefill 6.1 / 5.7, compress
 // 10.2 / 8.4, re-compress 11.3 / 9.7.
 class NewTensors {
@@ -120,7 +122,7 @@ class NewTensors {
   explicit NewTensors(const at::Tensor& like) : like_(like) {
     const auto usual = c10::DispatchKeySet({c10::DispatchKey::BackendSelect, c10::DispatchKey::ADInplaceOrView});
     const auto& context = at::globalContext();
-    at_once_ = (c10::impl::tls_local_dispatch_key_set().included_ - usual).empty() && like.is_cuda() &&
+    at_once_ = (c10::impl::tls_local_dispatch_key_set().included_ - usual).empty() && like.is_cuda() && !at::hasCallbacks() &&
                !(context.deterministicAlgorithms() && context.deterministicFillUninitializedMemory());
   }
   at::Tensor operator()(at::IntArrayRef sizes, at::ScalarType type) const {
@@ -205,10 +207,12 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   int rc;
   {
     NoGil others_run;
-    const NewTensors make(q);
-    if (own_ws) { ws = make.bytes(need); ws_ptr = ws.data_ptr(); }
-    if (own_o) { o = make(q.sizes(), q.scalar_type()); o_ptr = o.data_ptr(); }
-    if (own_lse) { lse = make({q.size(0), q.size(1)}, at::kFloat); lse_ptr = (float*)lse.data_ptr(); }
+    if (own_ws || own_o || own_lse) {
+      const NewTensors make(q);
+      if (own_ws) { ws = make.bytes(need); ws_ptr = ws.data_ptr(); }
+      if (own_o) { o = make(q.sizes(), q.scalar_type()); o_ptr = o.data_ptr(); }
+      if (own_lse) { lse = make({q.size(0), q.size(1)}, at::kFloat); lse_ptr = (float*)lse.data_ptr(); }
+    }
     void* st = current_stream();
     if (!has_tail) rc = g_hs.decode(&s, scale, n_splits, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, st);
     else if (rows != nullptr) rc = g_hs.decode_tail_rows(&s, scale, n_splits, q_ptr, &kv, tk, tv, lens, o_ptr, lse_ptr, ws_ptr, st);
@@ -274,9 +278,11 @@ PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   int rc = 0;
   {
     NoGil others_run;
-    const NewTensors make(q);
-    if (own_o) { o = make(q.sizes(), q.scalar_type()); o_ptr = o.data_ptr(); }
-    if (own_lse) { lse = make({q.size(0), q.size(1), q.size(2)}, at::kFloat); lse_ptr = (float*)lse.data_ptr(); }
+    if (own_o || own_lse) {
+      const NewTensors make(q);
+      if (own_o) { o = make(q.sizes(), q.scalar_type()); o_ptr = o.data_ptr(); }
+      if (own_lse) { lse = make({q.size(0), q.size(1), q.size(2)}, at::kFloat); lse_ptr = (float*)lse.data_ptr(); }
+    }
     if (!outputs_only)
       rc = g_hs.prefill(&s, Lq, at_pos, scale, causal, q_ptr, &kv, o_ptr, lse_ptr, ws_ptr, need, current_stream());
   }

@@ -280,8 +280,8 @@ def test_native_outputs_follow_the_modes_of_the_thread():
     g = torch.Generator(device="cuda").manual_seed(8)
     K, V = (torch.randn((1, 2, 256, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
     q = torch.randn((1, 4, 128), device="cuda", generator=g).bfloat16()
-    assert hb._native is not None
     plain = hb.decode_attn(sh, q, hb.compress_kv(sh, hb.make_policy(), K, V))
+    assert hb._native is not None
     assert not any(x.is_inference() or x.requires_grad for x in plain)
     assert plain[0].dtype == q.dtype and plain[0].device == q.device and plain[0].stride() == q.stride() and plain[1].shape == (1, 4)
 
@@ -311,3 +311,24 @@ def test_native_outputs_follow_the_modes_of_the_thread():
         out = hb.decode_attn(sh, q, hb.compress_kv(sh, hb.make_policy(), K, V))
     side.synchronize()
     assert same(out)
+
+
+@pytest.mark.gpu
+def test_native_outputs_are_seen_by_observers():
+    """A profiler sees the tensors that a call makes, as it sees those of the Python code; a call into kept buffers makes none."""
+    sh = hb.make_shape(1, 4, 2, 256)
+    K, V = (torch.ones((1, 2, 256, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    q, q4 = (torch.ones(n, dtype=torch.bfloat16, device="cuda") for n in ((1, 4, 128), (1, 4, 64, 128)))
+    kv = hb.compress_kv(sh, hb.make_policy(), K, V)
+    assert hb._native is not None
+    room = torch.empty(hb.workspace_bytes(sh, 2, 0), dtype=torch.uint8, device="cuda")
+    o, lse = hb.decode_attn(sh, q, kv)
+
+    def made(call):
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as seen:
+            call()
+        return sum(e.name in ("aten::empty", "aten::empty_strided") for e in seen.events())
+    assert made(lambda: hb.decode_attn(sh, q, kv)) == 3                              # O, LSE, scratch
+    assert made(lambda: hb.prefill_attn(sh, q4, kv, want_lse=False)) == 1
+    assert made(lambda: hb.compress_kv(sh, hb.make_policy(skip_frac=0.5), K, V)) == 7  # K and V: values, positions, map; scratch
+    assert made(lambda: hb.decode_attn(sh, q, kv, out=o, lse=lse, workspace=room)) == 0
