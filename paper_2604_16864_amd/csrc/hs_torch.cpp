@@ -13,6 +13,7 @@
 #include <ATen/Context.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/empty.h>
+#include <ATen/ops/empty_like.h>
 #include <ATen/record_function.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPStream.h>
@@ -129,6 +130,10 @@ class NewTensors {
     if (!at_once_) return at::empty(sizes, like_.options().dtype(type));
     return at::Tensor(at::detail::empty_cuda(sizes, type, like_.device(), std::nullopt));
   }
+  at::Tensor beside() const {  // of the sizes, strides and type of `like`, which is contiguous
+    if (!at_once_) return at::empty_like(like_);
+    return at::Tensor(at::detail::empty_strided_cuda(like_.sizes(), like_.strides(), like_.scalar_type(), like_.device()));
+  }
   at::Tensor bytes(size_t n) const { return (*this)({(int64_t)n}, at::kByte); }
 
  private:
@@ -210,7 +215,7 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     if (own_ws || own_o || own_lse) {
       const NewTensors make(q);
       if (own_ws) { ws = make.bytes(need); ws_ptr = ws.data_ptr(); }
-      if (own_o) { o = make(q.sizes(), q.scalar_type()); o_ptr = o.data_ptr(); }
+      if (own_o) { o = make.beside(); o_ptr = o.data_ptr(); }
       if (own_lse) { lse = make({q.size(0), q.size(1)}, at::kFloat); lse_ptr = (float*)lse.data_ptr(); }
     }
     void* st = current_stream();
@@ -280,7 +285,7 @@ PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     NoGil others_run;
     if (own_o || own_lse) {
       const NewTensors make(q);
-      if (own_o) { o = make(q.sizes(), q.scalar_type()); o_ptr = o.data_ptr(); }
+      if (own_o) { o = make.beside(); o_ptr = o.data_ptr(); }
       if (own_lse) { lse = make({q.size(0), q.size(1), q.size(2)}, at::kFloat); lse_ptr = (float*)lse.data_ptr(); }
     }
     if (!outputs_only)

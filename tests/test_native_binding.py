@@ -332,3 +332,17 @@ def test_native_outputs_are_seen_by_observers():
     assert made(lambda: hb.prefill_attn(sh, q4, kv, want_lse=False)) == 1
     assert made(lambda: hb.compress_kv(sh, hb.make_policy(skip_frac=0.5), K, V)) == 7  # K and V: values, positions, map; scratch
     assert made(lambda: hb.decode_attn(sh, q, kv, out=o, lse=lse, workspace=room)) == 0
+
+
+@pytest.mark.gpu
+def test_native_outputs_have_the_strides_of_the_queries():
+    """O is laid out as torch.empty_like lays it out, also where a batch of one is cut from a tensor with more heads."""
+    sh = hb.make_shape(1, 4, 2, 256)
+    K, V = (torch.ones((1, 2, 256, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    kv = hb.compress_kv(sh, hb.make_policy(), K, V)
+    assert hb._native is not None
+    for call, q in ((hb.decode_attn, torch.ones((1, 6, 128), dtype=torch.bfloat16, device="cuda")[:, :4]),
+                    (hb.prefill_attn, torch.ones((1, 6, 64, 128), dtype=torch.bfloat16, device="cuda")[:, :4])):
+        assert q.is_contiguous() and q.stride(0) == 6 * q[0, 0].numel()
+        for kept in (dict(), dict(want_lse=False)):
+            assert call(sh, q, kv, **kept)[0].stride() == torch.empty_like(q).stride() == q.stride()
