@@ -302,7 +302,8 @@ HS_API int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t
 
 /* What hs_prefill_attn_ws does with a workspace of workspace_bytes (SIZE_MAX: as much as it can use): *slab = query positions
  * a wavefront works on (16 or 32), *ranges, *bytes = the workspace that these ranges take, 0 for one.  With a workspace of
- * *bytes it does the same.  Any of the three may be NULL.  Of kv only the capacities and `uniform` are read.  [host, pure] */
+ * *bytes it does the same.  Whether one or two teams of wavefronts share a workgroup's slabs is not told here (hs_prefill_plan_teams
+ * in hs_bench.h).  Any of the three may be NULL.  Of kv only the capacities and `uniform` are read.  [host, pure] */
 HS_API int hs_prefill_plan(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv, size_t workspace_bytes,
                     int32_t* slab, int32_t* ranges, size_t* bytes);
 

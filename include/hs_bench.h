@@ -20,10 +20,17 @@ HS_API int hs_decode_attn_phases(const hs_shape* shape, float scale, int32_t n_s
                           const void* Q, const hs_kv* kv, void* O, float* LSE,
                           void* workspace, void* stream, int phases);
 
+/* hs_prefill_plan as hs_prefill_attn_planned takes it: *slab also tells whether two teams of four waves share a workgroup
+ * (16 | HS_TWO_TEAMS), which hs_prefill_plan leaves out, so that handing *slab and *ranges to hs_prefill_attn_planned runs what
+ * hs_prefill_attn_ws runs.  Everything else as hs_prefill_plan.  [host, pure] */
 enum { HS_TWO_TEAMS = 0x100 };
-/* hs_prefill_attn_ws with the plan given instead of chosen (hs_prefill_plan), for tests and for measuring the plans against each
- * other: slab = 16 or 32 query positions per wavefront (16 | HS_TWO_TEAMS: two teams of four waves per workgroup, one range only), ranges = 1 .. 65535 ranges of the tiles (some may be empty).  More than one
- * range takes a workspace of ranges * B * Hq * Lq * 516 bytes; a smaller one is HS_EINVAL.  Everything else as hs_prefill_attn_ws. */
+HS_API int hs_prefill_plan_teams(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv, size_t workspace_bytes,
+                            int32_t* slab, int32_t* ranges, size_t* bytes);
+
+/* hs_prefill_attn_ws with the plan given instead of chosen (hs_prefill_plan_teams), for tests and for measuring the plans against
+ * each other: slab = 16 or 32 query positions per wavefront (16 | HS_TWO_TEAMS: two teams of four waves per workgroup, one range only),
+ * ranges = 1 .. 65535 ranges of the tiles (some may be empty).  More than one range takes a workspace of
+ * ranges * B * Hq * Lq * 516 bytes; a smaller one is HS_EINVAL.  Everything else as hs_prefill_attn_ws. */
 HS_API int hs_prefill_attn_planned(const hs_shape* shape, int32_t Lq, int32_t q_start, float scale, int causal,
                             const void* Q, const hs_kv* kv, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                             int32_t slab, int32_t ranges, void* stream);

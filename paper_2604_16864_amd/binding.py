@@ -77,6 +77,8 @@ EXPORTS = {
                                              C.POINTER(C.c_size_t)]),
     "hs_prefill_plan": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_int, C.POINTER(HsKV), C.c_size_t,
                                   C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_size_t)]),
+    "hs_prefill_plan_teams": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_int, C.POINTER(HsKV), C.c_size_t,
+                                        C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_size_t)]),
     "hs_prefill_attn_planned": (C.c_int, [C.POINTER(HsShape), C.c_int32, C.c_int32, C.c_float, C.c_int, C.c_void_p, C.POINTER(HsKV),
                                           C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_int32, C.c_int32, C.c_void_p]),
     "hs_decode_attn": (C.c_int, [C.POINTER(HsShape), C.c_float, C.c_int32, C.c_void_p, C.POINTER(HsKV), C.c_void_p,
@@ -433,12 +435,26 @@ def unpack_kv(shape, kv):
     return K, V
 
 
-def prefill_plan(shape, Lq, q_start, kv, causal=True, workspace_bytes=C.c_size_t(-1).value):
-    """(slab, ranges, bytes) of hs_prefill_plan: how a prefill call with that much scratch runs.  kv: PackedKV."""
+def _plan(entry, shape, Lq, q_start, kv, causal, workspace_bytes):
     slab, ranges, need = C.c_int32(0), C.c_int32(0), C.c_size_t(0)
-    _check(lib().hs_prefill_plan(C.byref(shape), Lq, q_start, int(bool(causal)), C.byref(kv.struct()), workspace_bytes, C.byref(slab),
-                                 C.byref(ranges), C.byref(need)))
+    _check(entry(C.byref(shape), Lq, q_start, int(bool(causal)), C.byref(kv.struct()), workspace_bytes, C.byref(slab), C.byref(ranges),
+                 C.byref(need)))
     return slab.value, ranges.value, need.value
+
+
+def prefill_plan(shape, Lq, q_start, kv, causal=True, workspace_bytes=C.c_size_t(-1).value):
+    """(slab, ranges, bytes) of hs_prefill_plan: how a prefill call with that much scratch runs, without the teams of a slab
+    (prefill_plan_teams).  kv: PackedKV."""
+    return _plan(lib().hs_prefill_plan, shape, Lq, q_start, kv, causal, workspace_bytes)
+
+
+TWO_TEAMS = 0x100
+
+
+def prefill_plan_teams(shape, Lq, q_start, kv, causal=True, workspace_bytes=C.c_size_t(-1).value):
+    """prefill_plan as prefill_attn_planned takes it: slab is 16 | TWO_TEAMS where two teams of waves share a workgroup.  For tests
+    and measurements."""
+    return _plan(lib().hs_prefill_plan_teams, shape, Lq, q_start, kv, causal, workspace_bytes)
 
 
 def prefill_workspace_bytes(shape, Lq, q_start, kv, causal=True):
@@ -480,8 +496,9 @@ def prefill_attn(shape, Q, kv, causal=True, scale=0.0, want_lse=True, out=None, 
 
 
 def prefill_attn_planned(shape, Q, kv, slab, ranges, causal=True, scale=0.0, q_start=None, workspace=None):
-    """prefill_attn by a given plan (hs_prefill_attn_planned): slab = 16 or 32 query positions per wavefront, ranges of the tiles.
-    For tests and measurements.  Returns (O, LSE)."""
+    """prefill_attn by a given plan (hs_prefill_attn_planned): slab = 16 or 32 query positions per wavefront or 16 | TWO_TEAMS (one range
+    only), ranges of the tiles; prefill_plan_teams gives the one that prefill_attn takes.  For tests and measurements.
+    Returns (O, LSE)."""
     assert Q.dtype == torch_dtype(shape) and Q.is_contiguous() and Q.is_cuda
     Lq = Q.shape[2]
     O, lse = torch.empty_like(Q), Q.new_empty(Q.shape[:3], dtype=torch.float32)

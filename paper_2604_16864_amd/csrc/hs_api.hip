@@ -459,18 +459,25 @@ int hs_prefill_workspace_bytes(const hs_shape* shape, int32_t Lq, int32_t q_star
   return HS_OK;
 }
 
-int hs_prefill_plan(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv, size_t workspace_bytes,
-                    int32_t* slab, int32_t* ranges, size_t* bytes) {
+int hs_prefill_plan_teams(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv, size_t workspace_bytes,
+                          int32_t* slab, int32_t* ranges, size_t* bytes) {
   const int rc = check_shape(shape);
   if (rc != HS_OK) return rc;
   if (kv == nullptr) return HS_EINVAL;
   const int bad = prefill_args(shape, Lq, q_start);
   if (bad != HS_OK) return bad;
   const hs_prefill_choice how = prefill_plan(shape, Lq, q_start, causal, kv, workspace_bytes);
-  if (slab != nullptr) *slab = 16 * how.nb;
+  if (slab != nullptr) *slab = 16 * how.nb | (how.teams == 2 ? HS_TWO_TEAMS : 0);
   if (ranges != nullptr) *ranges = how.n_splits;
   if (bytes != nullptr) *bytes = how.n_splits > 1 ? (size_t)how.n_splits * prefill_split_bytes(shape, Lq) : 0;
   return HS_OK;
+}
+
+int hs_prefill_plan(const hs_shape* shape, int32_t Lq, int32_t q_start, int causal, const hs_kv* kv, size_t workspace_bytes,
+                    int32_t* slab, int32_t* ranges, size_t* bytes) {
+  const int rc = hs_prefill_plan_teams(shape, Lq, q_start, causal, kv, workspace_bytes, slab, ranges, bytes);
+  if (rc == HS_OK && slab != nullptr) *slab &= ~HS_TWO_TEAMS;
+  return rc;
 }
 
 int hs_prefill_attn_ws(const hs_shape* shape, int32_t Lq, int32_t q_start, float scale, int causal, const void* Q,

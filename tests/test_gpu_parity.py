@@ -540,6 +540,22 @@ def test_prefill_two_teams_of_waves(T, Lq, q_start, causal, G, dtype, pol):
             hb.prefill_attn_planned(sh, _dev(Q, dtype), kv, slab, n)
 
 
+@pytest.mark.parametrize("B,Hkv,L,Lq,plan", [(1, 8, 2048, 512, (16 | hb.TWO_TEAMS, 1)), (1, 8, 2048, 576, (16, 1)), (2, 2, 1024, 256, (16 | hb.TWO_TEAMS, 1)),
+                                             (1, 8, 256, 128, (16, 1)), (1, 1, 4096, 4096, (16, 3)), (1, 8, 8192, 64, (16, 8))])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+def test_prefill_by_the_plan_that_is_told_is_the_call(B, Hkv, L, Lq, plan, dtype):
+    """prefill_attn and the plan of prefill_plan_teams handed to prefill_attn_planned: the same bits."""
+    sh = hb.make_shape(B, 4 * Hkv, Hkv, L, dtype=hb.FP16 if dtype == "fp16" else hb.BF16)
+    g = torch.Generator(device="cuda").manual_seed(1320)
+    K, V, Q = (torch.randn((B, h, n, 128), device="cuda", generator=g).to(hb.torch_dtype(sh)) for h, n in ((Hkv, L), (Hkv, L), (4 * Hkv, Lq)))
+    kv = hb.compress_kv(sh, hb.make_policy(), K, V)
+    slab, ranges, need = hb.prefill_plan_teams(sh, Lq, L - Lq, kv)
+    assert (slab, ranges) == plan
+    O, LSE = hb.prefill_attn(sh, Q, kv)
+    O2, LSE2 = hb.prefill_attn_planned(sh, Q, kv, slab, ranges)
+    assert torch.equal(O.view(torch.int16), O2.view(torch.int16)) and torch.equal(LSE, LSE2)
+
+
 @pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict(sparse_frac_k=0.0)), ("bf16", dict(dense_first_tiles=1, dense_last_tiles=4)),
                                        ("fp16", dict(sparse_frac_k=0.5))])
 def test_prefill_nan_scores_come_out_of_two_teams(dtype, pol):

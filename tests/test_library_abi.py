@@ -192,6 +192,35 @@ def test_prefill_scratch_is_what_the_call_uses(L):
     assert L.hs_prefill_plan(C.byref(sh), 64, 0, 1, C.byref(kv.struct()), 0, None, None, None) == 0
 
 
+def test_prefill_plan_with_its_teams(L):
+    """The whole plan of a call, on both sides of the line for two teams of waves: one workgroup per compute unit and more, rows of
+    few tiles, ranges, and a cache of mixed tiles."""
+    def plan(L_, Lq, Hq=32, Hkv=8, B=1, caps=None, room=C.c_size_t(-1).value):
+        sh = hb.make_shape(B, Hq, Hkv, L_)
+        kv = hb.PackedKV(sh, caps or [0, 0, L_ // 64, 0, L_ // 64], "cpu")
+        slab, ranges, need = hb.prefill_plan_teams(sh, Lq, L_ - Lq, kv, True, room)
+        assert hb.prefill_plan(sh, Lq, L_ - Lq, kv, True, room) == (slab & ~hb.TWO_TEAMS, ranges, need)
+        assert slab in (16, 32, 16 | hb.TWO_TEAMS) and (slab < 64 or ranges == 1)
+        return slab, ranges
+    two = 16 | hb.TWO_TEAMS
+    assert plan(2048, 512) == (two, 1)                       # 256 workgroups, one per compute unit
+    assert plan(2048, 576) == (16, 1)                        # 288
+    assert plan(1024, 128) == (two, 1)                       # 64 workgroups of 16 tiles
+    assert plan(256, 128) == (16, 1)                         # 64 of 4
+    assert plan(1024, 1024) == (16, 1)                       # 512, a whole prompt
+    assert plan(4096, 4096, Hq=4, Hkv=1) == (16, 3)          # 256 of up to 64 tiles
+    assert plan(32768, 64) == (32, 32)                       # in ranges
+    assert plan(32768, 64, room=0) == (two, 1)               # the same call without scratch
+    assert plan(2048, 512, caps=[0, 16, 16, 0, 32]) == (two, 1)
+    sh = hb.make_shape(1, 32, 8, 1024)
+    kv = hb.PackedKV(sh, [0, 0, 16, 0, 16], "cpu")
+    for bad in ((64, 1024), (0, 0), (100, 0), (64, -1)):
+        with pytest.raises(hb.HsError):
+            hb.prefill_plan_teams(sh, *bad, kv)
+    assert L.hs_prefill_plan_teams(C.byref(sh), 64, 0, 1, None, 0, None, None, None) == -1
+    assert L.hs_prefill_plan_teams(C.byref(sh), 64, 0, 1, C.byref(kv.struct()), 0, None, None, None) == 0
+
+
 def test_current_stream_without_the_raw_handle(monkeypatch):
     """A torch without the two non-public functions gets the stream from the public object."""
     import torch
