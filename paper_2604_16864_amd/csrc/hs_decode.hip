@@ -241,7 +241,8 @@ __device__ __forceinline__ void load_q(const uint16_t* __restrict__ Q, int64_t h
 // the LDS once more per head and was the last to end: us a call, then / now, 8 rows of 256 tiles with a tail, 4 heads a row
 // 14.1 / 12.5, 8 heads 16.1 / 12.8; 128 rows of 16 tiles 13.7 / 12.4, 15.9 / 12.8; 8 rows of 32 tiles 8.3 / 7.6, 10.1 / 7.6; with one
 // head a row the same.
-template <bool F16>
+// AHEAD: the caller has raised the wave's priority, until its loads are requested.
+template <bool F16, bool AHEAD>
 __device__ __forceinline__ void tail_piece(const TailArgs& tail, int tail_len, int64_t row, int q, const uint4 (&qb)[4], float scale_log2,
                                            int l, float (&sm_o)[8][HS_D], float (&sm_m)[8], float (&sm_l)[8]) {
   typedef hs_elem<F16> E;
@@ -258,6 +259,7 @@ __device__ __forceinline__ void tail_piece(const TailArgs& tail, int tail_len, i
     for (int s = 0; s < 4; s++) kk[s] = c < left ? *reinterpret_cast<const uint4*>(tk + 32 * s) : make_uint4(0, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 4; i++) vv[i] = 4 * a + i < left ? *reinterpret_cast<const uint4*>(tv + i * HS_D) : make_uint4(0, 0, 0, 0);
+    if constexpr (AHEAD) { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_setprio(0); }
     f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int st = 0; st < 4; st++) s = E::mma(kk[st], qb[st], s);
@@ -409,15 +411,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HS_DEC_
   if (!DIRECT && __builtin_expect(b >= B, 0)) {  // the whole workgroup: the dense tail of a row
     row = ((int64_t)(b - B) * Hkv + hkv) * n_work + split;
     if (row >= (int64_t)B * Hkv) return;
-    __builtin_amdgcn_s_setprio(3);  // one short chain beside waves that stream: last, it would be what the launch ends with (16 x 2K tokens, one head a row, 17.6 / 16.8)
+    // One short chain beside waves that stream: last, it would be what the launch ends with, so its loads are requested ahead of theirs.  Its
+    // arithmetic is not put first: it takes issue slots from splits of few tiles.  us, no priority / all the way / until the loads are
+    // requested: 128 rows of 2K tokens, one head a row, 17.5 / 16.8 / 16.8, 4 heads 17.5 / 17.2 / 17.1; 128 rows that keep 9 tiles of 36 11.04 / 11.33 / 11.05.
+    __builtin_amdgcn_s_setprio(3);
     const int tb = (int)(row / Hkv);
     hq0 = (int64_t)tb * Hq + (row - (int64_t)tb * Hkv) * G;
     slot = n_work;
     uint4 qt[4];
     load_q(Q, hq0, G, a, c, qt);
-    tail_piece<F16>(tail, tail_length(tb), row, w, qt, scale_log2, l, sm_o[w], sm_m[w], sm_l[w]);
+    tail_piece<F16, true>(tail, tail_length(tb), row, w, qt, scale_log2, l, sm_o[w], sm_m[w], sm_l[w]);
   } else {
-      const int t_begin = split * per, t_end = min(T, t_begin + per);
+    const int t_begin = split * per, t_end = min(T, t_begin + per);
 
     uint4 qb[4];  // dense k-steps s = 0..3 (channels 32s + 8a + e); sparse kb uses steps 2kb, 2kb+1
     load_q(Q, hq0, G, a, c, qb);
@@ -646,7 +651,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HS_DEC_
     if constexpr (DIRECT) {
       if (tail.len >= 0) {  // by the waves that have no tile where the row has few
           const int q = NW - 1 - w;
-        if (q < 4) tail_piece<F16>(tail, tail_length(b), row, q, qb, scale_log2, l, sm_o[NW + q], sm_m[NW + q], sm_l[NW + q]);
+        if (q < 4) tail_piece<F16, false>(tail, tail_length(b), row, q, qb, scale_log2, l, sm_o[NW + q], sm_m[NW + q], sm_l[NW + q]);
       }
     }
   }
