@@ -419,9 +419,10 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void prefill_kernel(int Hq, int Hkv
   // mid_tag: MID mode; only16_tag: every V tile ahead is known to be in fp16 encoding
   auto main_loop = [&](auto mid_tag, auto only16_tag) {
     constexpr bool MID = decltype(mid_tag)::value, ONLY16 = F16 || decltype(only16_tag)::value;
-    // 2:4 V operands are fetched from LDS before the softmax, unless the K prefetch of MID mode
-    // already holds the registers (both together spill; measured no gain there)
-    constexpr bool V_EARLY = F16 && VM == 0 && !MID && NB > 1;
+    // 2:4 V operands are fetched from LDS before the softmax, unless the K prefetch of MID mode already holds the registers (both
+    // together spill; measured no gain there), which leaves fp16 caches with mixed keys.  us without / with it, half of the keys dense, slabs
+    // of 16: one team 512 tokens 11.49 / 11.07, two teams 512 queries on 2048 23.6 / 22.8, in ranges 128 on 4096 24.5 / 23.7.
+    constexpr bool V_EARLY = F16 && VM == 0 && !MID;
     // Whole rows of 2:4 tiles, slabs of 16: the score accumulators of the next tile are cleared among the products of GEMM2,
     // where the vector ALU is idle, instead of in front of GEMM1 (the sparse instruction accumulates in place): 512 tokens
     // 10.94 -> 10.70 us, 1024 tokens 18.9 -> 18.4.  Elsewhere the registers or the scheduling it costs are worth more (slabs of
