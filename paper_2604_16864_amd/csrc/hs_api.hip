@@ -288,7 +288,11 @@ int hs_compress_kv(const hs_shape* shape, const hs_policy* policy, const void* K
       // keys 2:4 | both with dense ends: 8 rows of 16 tiles 14.7 / 12.0 | 15.3 / 12.7 | 16.3 / 13.7; 8 of 64 16.9 / 14.8 | 16.7 / 16.6 | 20.8 / 19.4; 32 of 32
       // 21.3 / 19.4 | 22.6 / 20.7 | 25.0 / 23.0; 128 of 16 31.3 / 30.5 | 37.0 / 34.3 | 35.8 / 33.4; 52 of 33 29.4 / 29.8 | 32.3 / 30.9 | 32.6 / 32.8; 32 of 64
       // 32.2 / 37.4 | 37.0 / 40.0 | 36.4 / 46.1: the line is where the tiles looked at, rows x T x T, are as many as in 128 rows of 16.
-      if (T <= HS_RANK_TILES && (int64_t)rows * T * T <= 32768) {
+      // Nor with more tiles than those rows have: the pack kernel then reads V of tiles it skips, and past the last-level cache K and V
+      // without the streaming hint (half skipped | three quarters | nine tenths and half of the keys: 512 rows of 8 49.8 / 51.3 | 43.0 / 46.0 | 37.9 /
+      // 41.1; 2048 of 4 90.7 / 92.9 | 75.6 / 81.9 | 72.0 / 80.4; but 128 of 16 31.4 / 30.4 | 28.5 / 28.4 | 28.0 / 27.5; 256 of 8 31.0 / 29.5 | 28.4 / 27.6 |
+      // 23.9 / 23.3; 1024 of 2 31.3 / 28.9 | 31.3 / 28.8 | 28.3 / 26.6).
+      if (T <= HS_RANK_TILES && (int64_t)rows * T * T <= 32768 && (int64_t)rows * T <= 2048) {
         e = hs_launch_rank_and_pack((const uint16_t*)K, (const uint16_t*)V, sb, sh, st, shape->B, shape->Hkv, T, hs_make_kv_dev(out),
                                     (const double*)workspace, c[0], c[2], c[4], n_first, n_last, policy->element_rule, shape->dtype == HS_BF16, s);
         return e != hipSuccess ? hip_fail(e) : HS_OK;

@@ -1302,7 +1302,7 @@ def _pool_bytes_equal(a, b):
         assert (x is None) == (y is None) and (x is None or torch.equal(x, y)), name
 
 
-@pytest.mark.parametrize("T,B", [(17, 60), (33, 20), (64, 5)])
+@pytest.mark.parametrize("T,B", [(4, 260), (17, 60), (33, 20), (64, 5)])
 @pytest.mark.parametrize("pol", [dict(skip_frac=0.5), dict(sparse_frac_k=0.5), dict(skip_frac=0.25, sparse_frac_k=0.3, sparse_frac_v=0.7), dict(sparse_frac_k=0.0, sparse_frac_v=0.6),
                                  dict(skip_frac=0.9, sparse_frac_k=0.5, dense_first_tiles=1, dense_last_tiles=4), dict(skip_frac=0.4, dense_first_tiles=70),
                                  dict(skip_frac=0.3, sparse_frac_v=0.2, element_rule=1)])
