@@ -44,18 +44,17 @@ def assert_lse_close(lse, ref, what):
 
 def _prefill(sh, Q, kv, causal=True, scale=0.0, q_start=None):
     """hb.prefill_attn, whose result the test holds against the oracle, after the kernels that the library did not choose for so
-    small a call (slabs of 16 and of 32 queries, in one range and in two) have been held against it: as close to it as each has to be
-    to the oracle, head by head."""
+    small a call (slabs of 16 and of 32 queries, in one range and in two, and two teams of waves) have been held against it: as close
+    to it as each has to be to the oracle, head by head."""
     O, LSE = hb.prefill_attn(sh, Q, kv, causal=causal, scale=scale, q_start=q_start)
     ref, lref = _f32(O), LSE.cpu().numpy()
     assert np.isfinite(ref).all()
-    for slab in (16, 32):
-        for n in (1, 2):
-            Os, Ls = hb.prefill_attn_planned(sh, Q, kv, slab, n, causal=causal, scale=scale, q_start=q_start)
-            err = np.abs(_f32(Os) - ref)
-            assert (err.max((2, 3)) <= MAX_TOL * np.abs(ref).max((2, 3))).all(), (slab, n)
-            assert (err.mean((2, 3)) <= MEAN_TOL * np.abs(ref).mean((2, 3))).all(), (slab, n)
-            assert_lse_close(Ls.cpu().numpy(), lref, (slab, n))
+    for slab, n in ((16, 1), (16, 2), (32, 1), (32, 2), (16 | hb.TWO_TEAMS, 1)):
+        Os, Ls = hb.prefill_attn_planned(sh, Q, kv, slab, n, causal=causal, scale=scale, q_start=q_start)
+        err = np.abs(_f32(Os) - ref)
+        assert (err.max((2, 3)) <= MAX_TOL * np.abs(ref).max((2, 3))).all(), (slab, n)
+        assert (err.mean((2, 3)) <= MEAN_TOL * np.abs(ref).mean((2, 3))).all(), (slab, n)
+        assert_lse_close(Ls.cpu().numpy(), lref, (slab, n))
     return O, LSE
 
 
@@ -513,29 +512,29 @@ def test_prefill_tiles_cut_into_ranges(slab, n_ranges, B, G, T, Lq, q_start, cau
         assert torch.equal(O2.view(torch.int16), O.view(torch.int16)) and torch.equal(LSE2, LSE)
 
 
-@pytest.mark.parametrize("T,Lq,q_start,causal,G", [(1, 64, None, True, 4), (2, 128, None, True, 3), (7, 64, 64 * 3 + 17, True, 1),
-                                                    (66, 128, None, True, 2), (67, 64, 5, False, 5)])
+@pytest.mark.parametrize("B,T,Lq,q_start,causal,G", [(1, 1, 64, None, True, 4), (1, 2, 128, None, True, 3), (1, 7, 64, 64 * 3 + 17, True, 1),
+                                                      (1, 66, 128, None, True, 2), (1, 67, 64, 5, False, 5), (3, 8, 192, None, True, 2), (2, 5, 320, None, True, 7)])
 @pytest.mark.parametrize("dtype,pol", [("bf16", dict()), ("fp16", dict()), ("bf16", "states"), ("fp16", "states"), ("fp16", dict(sparse_frac_k=0.0)),
                                        ("bf16", dict(sparse_frac_v=0.0)), ("bf16", dict(sparse_frac_k=0.0, sparse_frac_v=0.0)),
                                        ("bf16", dict(sparse_frac_k=0.5)), ("bf16", dict(sparse_frac_v=0.5, skip_frac=0.3))])
-def test_prefill_two_teams_of_waves(T, Lq, q_start, causal, G, dtype, pol):
+def test_prefill_two_teams_of_waves(B, T, Lq, q_start, causal, G, dtype, pol):
     """Two teams that take a workgroup's tiles in turn: no tile, one, an odd number, more than a window of the maps; every kind
-    and both encodings of V; groups with idle waves; queries that see nothing."""
+    and both encodings of V; groups with idle waves; queries that see nothing; batches."""
     Hkv, L = 2, 64 * T
-    Q, K, V = wl.make_qkv(1, G * Hkv, Hkv, L, 128, Lq, seed=1300 + T, dtype=dtype)
+    Q, K, V = wl.make_qkv(B, G * Hkv, Hkv, L, 128, Lq, seed=1300 + T, dtype=dtype)
     V[:, 1, ::67, 5] = 0x0001                         # in bf16: values that fp16 does not hold
     if pol == "states":
-        sk, sv = _mixed_states(1, Hkv, T, seed=1301)
+        sk, sv = _mixed_states(B, Hkv, T, seed=1301)
         sk[:, 0, :T // 2] = sv[:, 0, :T // 2] = 0
         pol = dict(state_k=sk, state_v=sv)
-    sh, kv, pk, pv, _ = compress_both(1, G * Hkv, Hkv, L, K, V, dtype=dtype, **pol)
-    O, LSE = hb.prefill_attn_planned(sh, _dev(Q, dtype), kv, 16 | 0x100, 1, causal=causal, q_start=q_start)
-    rows = [(0, h, i) for h in range(G * Hkv) for i in range(0, Lq, 3)]
+    sh, kv, pk, pv, _ = compress_both(B, G * Hkv, Hkv, L, K, V, dtype=dtype, **pol)
+    O, LSE = hb.prefill_attn_planned(sh, _dev(Q, dtype), kv, 16 | hb.TWO_TEAMS, 1, causal=causal, q_start=q_start)
+    rows = [(b, h, i) for b in range(B) for h in range(G * Hkv) for i in range(0, Lq, 3)]
     idx = tuple(np.array(rows).T)
     Or, Lr = orc.attention_rows(Q, pk, pv, rows, causal=causal, **({} if q_start is None else {"q_offset": q_start}))
     assert_close(_f32(O)[idx], Or, "prefill by two teams")
     assert_lse_close(LSE.cpu().numpy()[idx], Lr, "prefill by two teams lse")
-    for slab, n in ((32 | 0x100, 1), (16 | 0x100, 2)):
+    for slab, n in ((32 | hb.TWO_TEAMS, 1), (16 | hb.TWO_TEAMS, 2)):
         with pytest.raises(hb.HsError):
             hb.prefill_attn_planned(sh, _dev(Q, dtype), kv, slab, n)
 
@@ -566,7 +565,7 @@ def test_prefill_nan_scores_come_out_of_two_teams(dtype, pol):
     kv = hb.compress_kv(sh, hb.make_policy(**pol), K.cuda(), V.cuda())
     Ku, Vu = (x.cpu() for x in hb.unpack_kv(sh, kv))
     Or, Lr = _nan_reference(Q[0], Ku[0], Vu[0], torch.arange(64 * T)[None, :] <= 64 * T - Lq + torch.arange(Lq)[:, None])
-    O, LSE = hb.prefill_attn_planned(sh, Q.cuda(), kv, 16 | 0x100, 1)
+    O, LSE = hb.prefill_attn_planned(sh, Q.cuda(), kv, 16 | hb.TWO_TEAMS, 1)
     _check_nan_rows(O.cpu()[0], LSE.cpu()[0], Or, Lr, "two teams, NaN scores")
 
 
