@@ -633,7 +633,8 @@ __device__ __forceinline__ void k_sparse_store(uint8_t* nnz, uint8_t* meta, int 
 // The words to store are built first.  v_f16 (bf16 cache): if every value the tile stores is
 // exact in fp16 (workgroup vote), the tile is written in fp16 encoding and *map_entry, which the
 // caller has set to mv, gets HS_MAP_F16, so that the attention kernels can feed the softmax
-// numerators as one fp16 term.  256 threads call this, tid = 0 .. 255; vote(bad) tells each whether any of them is bad.
+// numerators as one fp16 term.  256 threads call this, tid = 0 .. 255; vote(bad) tells each whether any of them is bad.  It is called
+// exactly once if v_f16 is set and not at all otherwise, and there is no other barrier here: append_kernel's other waves count on it.
 template <class Vote>
 __device__ __forceinline__ void v_tile_store(const uint16_t* vl, int mv, int32_t* map_entry, const hs_kv_dev& kv,
                                              int64_t row, int rule, int v_f16, int tid, Vote vote) {
@@ -949,7 +950,9 @@ __global__ __launch_bounds__(512) void append_kernel(const uint16_t* __restrict_
                      const_cast<uint8_t*>(kv.k_meta) + at * (int64_t)HS_TILE_META_BYTES, w, l, rule,
                      [&](int kb, int half) { return d[2 * kb + half]; });
     }
-    if (v_f16) __syncthreads();  // the vote below
+    // The vote that v_tile_store calls once if v_f16 is set.  (One barrier that both halves reach, between building V's words and storing
+    // them, is slower: fp16 4.33 -> 4.45 us, bf16 of one head 4.49 -> 4.55.)
+    if (v_f16) __syncthreads();
   } else {
     v_tile_store(vl, entry, map + t, kv, row, rule, v_f16, tid, [&](int bad) {
       const bool any = __any(bad);

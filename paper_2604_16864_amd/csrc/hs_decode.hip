@@ -373,12 +373,9 @@ constexpr int kScanBatch = 2048;  // tiles of the row looked at per scan step: 8
 // waves_per_eu: what the registers allow, as the most too: the scheduler otherwise goes by what the LDS would allow, and orders the loads
 // of a mixed tensor's tiles worse (4 sequences of 32K tokens, half of the keys dense, 58.7 / 58.3 us).
 template <int KM, int VM, int MODE, bool F16, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HS_DEC_OCC, HS_DEC_OCC))) void decode_split_kernel(int B, int z0, int turn, int Hq, int Hkv, int T, float scale_log2,
-                                                                             int n_splits, int per,
-                                                                             const uint16_t* __restrict__ Q,
-                                                                             hs_kv_dev kv, TailArgs tail,
-                                                                             float* __restrict__ ws_o,
-                                                                             float* __restrict__ ws_l) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HS_DEC_OCC, HS_DEC_OCC)))
+void decode_split_kernel(int B, int z0, int turn, int Hq, int Hkv, int T, float scale_log2, int n_splits, int per,
+                         const uint16_t* __restrict__ Q, hs_kv_dev kv, TailArgs tail, float* __restrict__ ws_o, float* __restrict__ ws_l) {
   const int hkv = blockIdx.y, b = blockIdx.z + z0;
   // Workgroups go round-robin over the 8 XCDs by their index: with an even number of splits the same splits of every row
   // meet on an XCD (with 8 of them, split s on XCD s), and where rows differ in length the XCDs of the late splits have little to
@@ -400,7 +397,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HS_DEC_
     return __builtin_amdgcn_readfirstlane(tail.lens != nullptr ? min(max(tail.lens[of], 0), HS_BT) : tail.len);
   };
   // Where the results go, in registers from the start: left to itself the compiler reads the two pointers from the kernel's arguments
-  // in front of the last stores, and the launch ends 0.2 to 0.4 us later (16 sequences of 4K to 16K tokens with tails 66.0 / 66.5 us,
+  // in front of the last stores, and the launch ends 0.3 to 0.5 us later (16 sequences of 4K to 16K tokens with tails 66.0 / 66.5 us,
   // 128 rows of 49 tiles 17.3 / 17.6).
   typedef __attribute__((address_space(1))) float* global_t;
   global_t to_o = (global_t)ws_o, to_l = (global_t)ws_l;
@@ -462,8 +459,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HS_DEC_
       constexpr int DEPTH = kMixed || NW == 8 ? ((KK == 0 && VK == 0) ? 2 : 1) : HS_DEC_DEPTH;
       TileRegs<KK, VK> ring[DEPTH];
       unsigned seen = 0;
-  // what the two copies of a round below share: the form ballots, and the loop that consumes the tiles in
-  // flight and refills their ring slots from `act`
+      // what the two copies of a round below share: the form ballots, and the loop that consumes the tiles in
+      // flight and refills their ring slots from `act`
 #define HS_ROUND_BALLOTS                                                                                              \
     const int form_v = form_of(mk_v, mv_v);                                                                             \
     unsigned long long act = __ballot(mk_v != 0 && form_v == kForm);                                                    \

@@ -59,12 +59,13 @@ int hs_prefill_auto_splits(int B, int Hq, int Hkv, int T, int Lq, int q_start, i
 // whole is worked off, or with a pile of k + 1 where round k + 1 is just begun (queries at the end of a long context: all
 // workgroups equally long); ranges add the merge launch and the partials.
 // Two teams of waves per workgroup (one workgroup per compute unit, which takes two tiles in little more than the time one team takes
-// for one) where slabs of 16 leave each compute unit one workgroup or none; one team / two, us: 64 workgroups of 16 tiles 15.5 / 13.4,
-// 128 of up to 32 26.7 / 21.7, half of the keys dense 31.3 / 24.3, dense ends 31.3 / 24.0, 64 of up to 4 tiles 7.9 / 8.2.
-// The more workgroups, the more a tile takes them (per_wg; 16 of 64 tiles 0.43 us a tile, 128 of 32 0.46, 256 of 64 0.53: prompt of 4096
-// tokens x 4 heads 37.1 in slabs of 32, 40.5 by teams).  Not with more workgroups than compute units, which fill the chip by
-// themselves (prompt of 1024 tokens 18.4 / 20.1, 336 workgroups of 40 tiles 35.4 / 36.7), and not in ranges: their tiles come from HBM, and both teams wait for the slower one's at every
-// barrier (3 x 128 queries x 8 heads on 33088 tokens, half of them skipped, 45 / 58; 64 queries x 32 heads on 4096 17.1 / 17.0).
+// for one) where slabs of 16 leave each compute unit one workgroup or none; one team / two, us: 64 workgroups of 16 tiles 15.7 / 13.3,
+// 256 of up to 32 26.5 / 21.2, half of the keys dense 31.2 / 23.9, dense ends 31.2 / 23.6, 64 of up to 4 tiles 7.8 / 8.0.
+// The more workgroups, the more a tile takes them (per_wg; 16 of 64 tiles 0.44 us a tile, 128 of 32 0.45, 256 of 32 0.47, and of 64, one to 64
+// of them causal, 0.54 in bf16 and 0.44 in fp16: a prompt of 4096 tokens x 4 heads takes 36.9 and 35.4 in three ranges by one team, 40.8
+// and 34.7 by two).  Not with more workgroups than compute units, which fill the chip by themselves (prompt of 1024 tokens
+// 18.3 / 20.8, 352 workgroups of 40 tiles 35.5 / 43.8), and not in ranges: their tiles come from HBM, and both teams wait for the slower
+// one's at every barrier (3 x 128 queries x 8 heads on 33088 tokens, half of them skipped, 45 / 58; 64 queries x 32 heads on 4096 17.1 / 17.0).
 // The margins go by what the shape allows and not by `fit`, so a workspace of the size of the choice leads to the same choice.
 hs_prefill_choice hs_plan_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_start, int causal, const hs_kv_dev& kv, int fit) {
   static const struct { int nb, teams, at_once; double start, alone, pair, per_wg; } kWays[3] = {

@@ -868,3 +868,8 @@ static hipError_t launch_prefill(int B, int Hq, int Hkv, int T, int Lq, int q_st
 #undef HS_LAUNCH
   return hipGetLastError();
 }
+// slabs of 16 queries, by one team of waves or by two
+template <int KM, int VM, class... Args>
+static hipError_t launch_prefill_narrow(int teams, Args... args) {
+  return teams == 2 ? launch_prefill<KM, VM, 1, 2>(args...) : launch_prefill<KM, VM, 1, 1>(args...);
+}

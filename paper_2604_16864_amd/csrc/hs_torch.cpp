@@ -117,7 +117,7 @@ void* current_stream() { return (void*)c10::hip::getCurrentHIPStream().stream();
 // to the operators of this thread (dispatch modes, fake tensors, function transforms, profilers and other observers) or new memory is to be
 // filled.  Looking that up is for calls that make a tensor: those into kept buffers go without.
 // us a call through the dispatcher / at once, 1K tokens: decode with outputs and scratch of its own 9.9 / 9.3, prefill 6.1 / 5.7, compress
-// 10.2 / 8.4, re-compress 11.3 / 9.7.
+// 10.2 / 8.4, re-compress 11.3 / 9.7; of that, asking for observers is 0.01 to 0.04.
 class NewTensors {
  public:
   explicit NewTensors(const at::Tensor& like) : like_(like) {
