@@ -647,7 +647,7 @@ void decode_split_kernel(int B, int z0, int turn, int Hq, int Hkv, int T, float 
     }
     if constexpr (DIRECT) {
       if (tail.len >= 0) {  // by the waves that have no tile where the row has few
-          const int q = NW - 1 - w;
+        const int q = NW - 1 - w;
         if (q < 4) tail_piece<F16, false>(tail, tail_length(b), row, q, qb, scale_log2, l, sm_o[NW + q], sm_m[NW + q], sm_l[NW + q]);
       }
     }
